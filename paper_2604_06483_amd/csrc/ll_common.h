@@ -43,6 +43,12 @@ __device__ __forceinline__ float wave_sum(float x) {
   return x;
 }
 
+__device__ __forceinline__ float wave_max(float x) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) x = fmaxf(x, __shfl_xor(x, off, kWave));
+  return x;
+}
+
 // Adds the squares of the 8 bf16 values in q: low halves into acc0, high halves into acc1.  The
 // RMS statistic of every kernel goes through this (and wave_sum) so that all of them get the
 // same bits for the same row.

@@ -6,13 +6,13 @@
 // Eq. 1 live only in MFMA accumulators.
 #include "ll_epilogue.h"
 #include "ll_epilogue_sweep.h"
+#include "ll_few_rows.h"
 #include "ll_gemm_lds.h"
 #include "ll_gemm_staged.h"
 
 #include <atomic>
 #include <climits>
 #include <mutex>
-#include <type_traits>
 #include <utility>
 #include <vector>
 
@@ -46,7 +46,7 @@ __global__ __launch_bounds__(256) void ll_norm_panel_kernel(const uint16_t* __re
                                                             const uint16_t* __restrict__ gamma, uint16_t* __restrict__ panel,
                                                             int rows, int d, int64_t lda, float eps) {
   const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (row >= rows) return;
   const uint4* src = reinterpret_cast<const uint4*>(hidden + (int64_t)row * d);
   uint4* dst = reinterpret_cast<uint4*>(panel + (int64_t)row * lda);
@@ -54,26 +54,7 @@ __global__ __launch_bounds__(256) void ll_norm_panel_kernel(const uint16_t* __re
   const int n16 = d >> 3;
   const int n16_pad = (int)(lda >> 3);
   float acc0 = 0.f, acc1 = 0.f;
-  uint4 cache[NITER > 0 ? NITER : 1];
-  if (NITER > 0) {
-#pragma unroll
-    for (int it = 0; it < NITER; ++it) {
-      const int c = lane + 64 * it;
-      if (c < n16) {
-        cache[it] = src[c];
-        accum_sq(cache[it], acc0, acc1);
-      }
-    }
-  } else {
-    for (int c = lane; c < n16; c += 64) accum_sq(src[c], acc0, acc1);
-  }
-  const float inv = inv_rms_from_sumsq(wave_sum(acc0 + acc1), d, eps);
-  auto emit = [&](int c, const uint4 q) {
-    if (gamma == nullptr) {
-      dst[c] = q;
-      return;
-    }
-    const uint4 g = g4[c];
+  auto emit = [&](int c, const uint4 q, const uint4 g, float inv) {
     const uint32_t hw[4] = {q.x, q.y, q.z, q.w};
     const uint32_t gw[4] = {g.x, g.y, g.z, g.w};
     uint32_t ow[4];
@@ -82,14 +63,26 @@ __global__ __launch_bounds__(256) void ll_norm_panel_kernel(const uint16_t* __re
       ow[i] = pack_bf16(bf16_lo(hw[i]) * inv * bf16_lo(gw[i]), bf16_hi(hw[i]) * inv * bf16_hi(gw[i]));
     dst[c] = make_uint4(ow[0], ow[1], ow[2], ow[3]);
   };
-  if (NITER > 0) {
+  if (gamma == nullptr) {
+    for (int c = lane; c < n16; c += 64) dst[c] = src[c];
+  } else if (NITER > 0) {
+    // all loads of the row and of gamma before the first use, chunks past the end at the last one (their squares count as zero)
+    uint4 cache[NITER > 0 ? NITER : 1], g[NITER > 0 ? NITER : 1];
 #pragma unroll
-    for (int it = 0; it < NITER; ++it) {
-      const int c = lane + 64 * it;
-      if (c < n16) emit(c, cache[it]);
-    }
+    for (int it = 0; it < NITER; ++it) cache[it] = src[min(lane + 64 * it, n16 - 1)];
+#pragma unroll
+    for (int it = 0; it < NITER; ++it) g[it] = g4[min(lane + 64 * it, n16 - 1)];
+#pragma unroll
+    for (int it = 0; it < NITER; ++it)
+      if (lane + 64 * it < n16) accum_sq(cache[it], acc0, acc1);
+    const float inv = inv_rms_from_sumsq(wave_sum(acc0 + acc1), d, eps);
+#pragma unroll
+    for (int it = 0; it < NITER; ++it)
+      if (lane + 64 * it < n16) emit(lane + 64 * it, cache[it], g[it], inv);
   } else {
-    for (int c = lane; c < n16; c += 64) emit(c, src[c]);
+    for (int c = lane; c < n16; c += 64) accum_sq(src[c], acc0, acc1);
+    const float inv = inv_rms_from_sumsq(wave_sum(acc0 + acc1), d, eps);
+    for (int c = lane; c < n16; c += 64) emit(c, src[c], g4[c], inv);
   }
   for (int c = n16 + lane; c < n16_pad; c += 64) dst[c] = make_uint4(0, 0, 0, 0);
 }
@@ -183,11 +176,6 @@ __global__ __launch_bounds__(256) void ll_sweep_merge_kernel(const float4* __res
 // ---------------------------------------------------------------------------------------
 // a8: merge the splits of each row and finalise.  One wavefront per row, one lane per split.
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x = fmaxf(x, __shfl_xor(x, off, kWave));
-  return x;
-}
 __device__ __forceinline__ int wave_min_int(int x) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) x = min(x, __shfl_xor(x, off, kWave));
@@ -442,9 +430,38 @@ __global__ __launch_bounds__(256) void ll_sweep_topk_merge_kernel(const float4* 
 // ---------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------
+// The few-rows kernel: how the vocabulary is dealt.  One part, of one workgroup, per compute unit, or fewer when there
+// are not eight groups of 16 vocabulary rows (one per wavefront) for each.  A wavefront holds the accumulators of MU
+// groups against all the rows, so the register file bounds MU by the number of 16-row blocks; a larger share of the
+// vocabulary goes in two or more rounds of workgroups.
+struct FewPlan {
+  bool ok;
+  int nj, mu, units, splits;   // nj: 16-row blocks of the kernel instance; mu: groups per wavefront; units: groups in all
+};
+
+FewPlan make_few_plan(const ll_shape* s) {
+  FewPlan f = {};
+  if (s->N < 1 || s->N > FEW_ROWS) return f;
+  const int blocks = (int)((s->N + 15) / 16);
+  f.nj = blocks <= 4 ? blocks : (blocks <= 6 ? 6 : 8);
+  const int mu_max = f.nj <= 4 ? 5 : (f.nj == 6 ? 4 : 3);
+  f.units = (int)(((int64_t)s->V + 15) / 16);
+  int parts = (f.units + FEW_WAVES - 1) / FEW_WAVES;
+  if (parts > NUM_CU) parts = NUM_CU;
+  const int share = (f.units + parts - 1) / parts;
+  const int rounds = (share + FEW_WAVES * mu_max - 1) / (FEW_WAVES * mu_max);
+  f.splits = parts * rounds;
+  if (f.splits > FEW_MAX_SPLITS) return f;   // V beyond some 200 000 to 330 000
+  f.mu = ((f.units + f.splits - 1) / f.splits + FEW_WAVES - 1) / FEW_WAVES;
+  f.ok = true;
+  return f;
+}
+
 struct Plan {
   size_t off_inv_rms, off_bound, off_bias, off_stats, off_top, off_panel, total;
   int64_t lda;
+  FewPlan few;
+  size_t few_off_stats, few_off_cand, few_off_count, few_off_panel;
 };
 
 bool shape_ok(const ll_shape* s, int k) {
@@ -475,7 +492,37 @@ Plan make_plan(const ll_shape* s, int k, int chunk_rows = CHUNK_ROWS) {
   p.off_panel = off;
   off = align_up(off + rows * (size_t)p.lda * sizeof(uint16_t), 256);
   p.total = off;
+  // The few-rows kernel's own layout of the same workspace.  It is taken only where it also fits the library's static
+  // buffer, so that ll_project and ll_project_static run the same kernels.
+  p.few = make_few_plan(s);
+  if (p.few.ok) {
+    const size_t lists = (size_t)s->N * p.few.splits;
+    off = 0;
+    p.few_off_stats = off;
+    off = align_up(off + lists * sizeof(float4), 256);
+    p.few_off_cand = off;
+    off = align_up(off + lists * FEW_CAP * sizeof(uint2), 256);
+    p.few_off_count = off;
+    off = align_up(off + lists * sizeof(int), 256);
+    p.few_off_panel = off;
+    off = align_up(off + rows * (size_t)p.lda * sizeof(uint16_t), 256);
+    p.few.ok = off <= (size_t)LL_STATIC_SCRATCH_BYTES;
+    if (p.few.ok && off > p.total) p.total = off;
+  }
   return p;
+}
+
+void (*few_kernel(int nj, int mu))(const FewArgs) {
+#define LL_FEW(NJ, MU) \
+  if (nj == NJ && mu <= MU) return ll_lens_few_kernel<NJ, MU>
+  LL_FEW(1, 1); LL_FEW(1, 3); LL_FEW(1, 5);
+  LL_FEW(2, 1); LL_FEW(2, 3); LL_FEW(2, 5);
+  LL_FEW(3, 1); LL_FEW(3, 3); LL_FEW(3, 5);
+  LL_FEW(4, 1); LL_FEW(4, 3); LL_FEW(4, 5);
+  LL_FEW(6, 2); LL_FEW(6, 4);
+  LL_FEW(8, 1); LL_FEW(8, 3);
+#undef LL_FEW
+  return nullptr;
 }
 
 // A kernel that uses more than 64 KB of dynamic LDS has to be told so once per device; remembered
@@ -491,6 +538,21 @@ int allow_dynamic_lds(const void* kern, size_t lds) {
   LL_HIP_CHECK(hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));
   done.emplace_back(dev, kern);
   return LL_OK;
+}
+
+// (few rows: one wavefront per block, so that they spread over the compute units)
+void launch_norm_panel(const uint16_t* hidden, const uint16_t* gamma, uint16_t* panel, int rows, int d, int64_t lda, float eps,
+                       hipStream_t stream) {
+  const int per_block = rows <= 1024 ? 1 : 4;
+  const dim3 grid((unsigned)((rows + per_block - 1) / per_block)), block(64 * per_block);
+  if (d <= 64 * 8 * 4)
+    hipLaunchKernelGGL(ll_norm_panel_kernel<4>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps);
+  else if (d <= 64 * 8 * 8)
+    hipLaunchKernelGGL(ll_norm_panel_kernel<8>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps);
+  else if (d <= 64 * 8 * 16)
+    hipLaunchKernelGGL(ll_norm_panel_kernel<16>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps);
+  else
+    hipLaunchKernelGGL(ll_norm_panel_kernel<0>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps);
 }
 
 int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, const void* hidden, const void* gamma,
@@ -563,11 +625,63 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
   };
   auto finish = [&](int rc) { return rc; };
   const std::vector<hipEvent_t>& ev = ev_pool;
+  auto read_phases = [&]() -> int {   // ll_project_timed: four marks per row pass
+    if (!phase_ms) return LL_OK;
+    LL_HIP_CHECK(hipStreamSynchronize(stream));
+    phase_ms[0] = phase_ms[1] = phase_ms[2] = 0.f;
+    for (size_t i = 0; i + 3 < n_ev; i += 4)
+      for (int j = 0; j < 3; ++j) {
+        float ms = 0.f;
+        LL_HIP_CHECK(hipEventElapsedTime(&ms, ev[i + j], ev[i + j + 1]));
+        phase_ms[j] += ms;
+      }
+    return LL_OK;
+  };
 #define LL_CHECK_F(expr)                                   \
   do {                                                     \
     hipError_t e__ = (expr);                               \
     if (e__ != hipSuccess) return finish(hip_failed(e__)); \
   } while (0)
+
+  // Few rows: one read of W_U.  Whole call, us, here / on the 256-row tiles: d = 8192, V = 128256, k = 20: 1 row 331 / 480, 81 rows
+  // 348 / 490, 97 to 128 rows (two rounds of workgroups) 460 / 495; d = 2560, V = 151936, k = 10: 37 rows 145 / 245, 128 rows 228 /
+  // 275; 64 rows of d = 256, V = 4096: 19 / 49.  Past 128 rows the accumulators do not fit and the 256-row tiles are the better split.
+  if (plan.few.ok && !(flags & LL_FLAG_REGISTER_STAGED)) {
+    const FewPlan& few = plan.few;
+    uint16_t* few_panel = reinterpret_cast<uint16_t*>(ws + plan.few_off_panel);
+    const bool copy = has_gamma || plan.lda != d;
+    LL_CHECK_F(mark());
+    if (copy) {
+      launch_norm_panel(static_cast<const uint16_t*>(hidden), static_cast<const uint16_t*>(gamma), few_panel, (int)N, d, plan.lda, eps,
+                        stream);
+      LL_CHECK_F(hipGetLastError());
+    }
+    FewArgs a;
+    a.A = copy ? few_panel : static_cast<const uint16_t*>(hidden);
+    a.W = static_cast<const uint16_t*>(W_U);
+    a.target = target_ids;
+    a.bias = bias;
+    a.stats = reinterpret_cast<float4*>(ws + plan.few_off_stats);
+    a.cand = reinterpret_cast<uint2*>(ws + plan.few_off_cand);
+    a.count = reinterpret_cast<int*>(ws + plan.few_off_count);
+    a.lda = plan.lda;
+    a.rows = (int)N;
+    a.d = d;
+    a.V = V;
+    a.k = k;
+    a.splits = few.splits;
+    a.units = few.units;
+    LL_CHECK_F(mark());
+    hipLaunchKernelGGL(few_kernel(few.nj, few.mu), dim3(few.splits), dim3(FEW_THREADS), 0, stream, a);
+    LL_CHECK_F(hipGetLastError());
+    LL_CHECK_F(mark());
+    hipLaunchKernelGGL(ll_few_merge_kernel, dim3((unsigned)N), dim3(FEW_MERGE_THREADS), 0, stream, (const float4*)a.stats, (const uint2*)a.cand,
+                       (const int*)a.count, a.splits, k, V, (flags & LL_FLAG_TOPK_SOFTMAX) ? 1 : 0, target_ids, out_topk_ids,
+                       out_topk_p, out_target_logp, out_entropy);
+    LL_CHECK_F(hipGetLastError());
+    LL_CHECK_F(mark());
+    return finish(read_phases());
+  }
 
   const int tiles = (V + BM - 1) / BM;
   // Top-k bounds shared between the vocabulary splits of a row (direct-to-LDS kernel): zero at the start of a
@@ -591,14 +705,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     // a2 (+ a3 when the panel is used)
     LL_CHECK_F(mark());
     if (need_panel) {
-      const dim3 grid((unsigned)((rows + 3) / 4));
-      const uint16_t* g = static_cast<const uint16_t*>(gamma);
-      if (d <= 64 * 8 * 4)
-        hipLaunchKernelGGL(ll_norm_panel_kernel<4>, grid, dim3(256), 0, stream, h_rows, g, panel, rows, d, plan.lda, eps);
-      else if (d <= 64 * 8 * 16)
-        hipLaunchKernelGGL(ll_norm_panel_kernel<16>, grid, dim3(256), 0, stream, h_rows, g, panel, rows, d, plan.lda, eps);
-      else
-        hipLaunchKernelGGL(ll_norm_panel_kernel<0>, grid, dim3(256), 0, stream, h_rows, g, panel, rows, d, plan.lda, eps);
+      launch_norm_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, d, plan.lda, eps, stream);
       LL_CHECK_F(hipGetLastError());
     } else if (!dma && has_gamma) {
       hipLaunchKernelGGL(ll_rms_stats_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, h_rows, (int64_t)rows, d,
@@ -650,21 +757,8 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     LL_CHECK_F(hipGetLastError());
     LL_CHECK_F(mark());
   }
-  if (phase_ms) {
-    LL_CHECK_F(hipStreamSynchronize(stream));
-    phase_ms[0] = phase_ms[1] = phase_ms[2] = 0.f;
-    for (size_t i = 0; i + 3 < n_ev; i += 4) {
-      float ms = 0.f;
-      LL_CHECK_F(hipEventElapsedTime(&ms, ev[i], ev[i + 1]));
-      phase_ms[0] += ms;
-      LL_CHECK_F(hipEventElapsedTime(&ms, ev[i + 1], ev[i + 2]));
-      phase_ms[1] += ms;
-      LL_CHECK_F(hipEventElapsedTime(&ms, ev[i + 2], ev[i + 3]));
-      phase_ms[2] += ms;
-    }
-  }
 #undef LL_CHECK_F
-  return finish(LL_OK);
+  return finish(read_phases());
 }
 
 struct SweepPlan {
@@ -769,14 +863,7 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     const int rows = (int)((N - r0 < CHUNK_ROWS) ? (N - r0) : CHUNK_ROWS);
     const uint16_t* h_rows = static_cast<const uint16_t*>(hidden) + r0 * d;
     if (gamma != nullptr && dma) {
-      const dim3 grid((unsigned)((rows + 3) / 4));
-      const uint16_t* g = static_cast<const uint16_t*>(gamma);
-      if (d <= 64 * 8 * 4)
-        hipLaunchKernelGGL(ll_norm_panel_kernel<4>, grid, dim3(256), 0, stream, h_rows, g, panel, rows, d, plan.lda, eps);
-      else if (d <= 64 * 8 * 16)
-        hipLaunchKernelGGL(ll_norm_panel_kernel<16>, grid, dim3(256), 0, stream, h_rows, g, panel, rows, d, plan.lda, eps);
-      else
-        hipLaunchKernelGGL(ll_norm_panel_kernel<0>, grid, dim3(256), 0, stream, h_rows, g, panel, rows, d, plan.lda, eps);
+      launch_norm_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, d, plan.lda, eps, stream);
       LL_CHECK_S(hipGetLastError());
     } else if (gamma != nullptr) {
       hipLaunchKernelGGL(ll_rms_stats_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, h_rows, (int64_t)rows, d,

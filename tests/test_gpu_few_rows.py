@@ -1,0 +1,89 @@
+"""The projection of few lens rows (at most 128: its own kernel, vocabulary dealt in groups of 16 rows, unordered
+candidate lists merged by counting), at the sizes where it can go wrong, against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle.lens_oracle as O
+from paper_2604_06483_amd import binding as LL
+from paper_2604_06483_amd import workloads as WL
+from tests import parity as P
+from tests.conftest import say
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+CASES = [
+    # N,   d,    V,   k, bias
+    (1,    64,   33,  1, False),     # one stage (filled up to two), three groups of 16, the last with one row
+    (16,   192,  300, 32, False),    # three stages; longest list
+    (17,   72,   129, 5, True),      # d not a whole number of stages: one chunk in the last
+    (33,   120,  2000, 20, False),   # seven chunks in the last stage
+    (48,   8,    4096, 7, False),    # one chunk in all
+    (64,   1096, 5001, 3, True),     # odd number of stages and a ragged last one
+    (65,   320,  40000, 20, False),  # 16-row blocks rounded up to six
+    (96,   128,  70000, 10, False),  # parts of 17 and 18 groups
+    (97,   256,  33000, 32, True),   # eight 16-row blocks
+    (128,  64,   140000, 20, False),  # two rounds of workgroups
+    (37,   64,   151936, 10, False),  # five groups per wavefront
+    (20,   64,   300000, 12, False),  # two rounds of five
+    (5,    64,   400000, 4, False),  # a vocabulary past the kernel's parts: the 256-row kernel
+]
+
+
+def inputs(N, d, V, seed=21):
+    cfg = WL.LensConfig("few", L=1, T=N, d=d, V=V, k=1, n_outliers=2 if d > 100 else 0, outlier_scale=20.0)
+    return WL.make_workload(cfg, DEV, seed=seed)
+
+
+def reference(w, k, bias=None):
+    return P.oracle_rows(WL.bf16_bits(w.hidden.reshape(-1, w.cfg.d)), WL.bf16_bits(w.gamma), WL.bf16_bits(w.W_U), w.cfg.eps, k,
+                         w.target_ids.cpu().numpy(), bias=None if bias is None else bias.cpu().numpy())
+
+
+@pytest.mark.parametrize("N,d,V,k,with_bias", CASES)
+def test_few_rows(N, d, V, k, with_bias):
+    say(f"few rows N={N} d={d} V={V} k={k} bias={with_bias}")
+    w = inputs(N, d, V)
+    bias = 0.5 * torch.randn((V,), generator=torch.Generator(device=DEV).manual_seed(3), device=DEV) if with_bias else None
+    ws = torch.full((LL.ll_workspace_bytes(N, d, V, k),), 0xFF, dtype=torch.uint8, device=DEV)
+    res = LL.ll_project(w.hidden, w.gamma, w.W_U, w.cfg.eps, k, w.target_ids, workspace=ws, bias=bias)
+    torch.cuda.synchronize()
+    got = P.to_numpy(res)
+    P.compare(got, reference(w, k, bias), k, label="few")
+    P.check_invariants(got, V, k, label="few")
+    if bias is None:
+        static = LL.ll_project_static(w.hidden, w.gamma, w.W_U, w.cfg.eps, k, w.target_ids)
+        for a, b in zip(res, static):
+            assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("N,d,V,k", [(100, 256, 9000, 20), (128, 320, 3000, 32)])
+def test_same_logits_as_the_256_row_kernel(N, d, V, k):
+    """K order and matrix instruction are the same, so ids and their order are; the softmax sums run over other
+    parts: a relative 2^-24 for each of the at most log2(V) + 16 additions in sequence, under 1e-5."""
+    say(f"few rows against many N={N} d={d} V={V} k={k}")
+    w = inputs(N + 200, d, V)
+    few = LL.ll_project(w.hidden[:, :N].contiguous(), w.gamma, w.W_U, w.cfg.eps, k, w.target_ids[:N].contiguous())
+    many = LL.ll_project(w.hidden, w.gamma, w.W_U, w.cfg.eps, k, w.target_ids)
+    assert torch.equal(few[0], many[0][:N])
+    for a, b in zip(few[1:], many[1:]):
+        torch.testing.assert_close(a, b[:N], rtol=1e-5, atol=1e-5)
+
+
+@pytest.mark.parametrize("N,V,k", [(70, 9000, 20), (128, 70000, 32), (11, 40000, 5)])
+def test_lists_that_overflow(N, V, k):
+    """Many equal logits (all-zero rows, one repeated vocabulary row) and best entries that sit in one lane: more entries
+    reach a part's threshold than its list holds."""
+    say(f"few rows, overflowing lists N={N} V={V} k={k}")
+    w = inputs(N, 128, V)
+    w.hidden[0, 1] = 0
+    w.W_U[V // 3:V // 3 + 2000] = 8.0 * w.W_U[V // 3]       # the best 2000 of about half the rows
+    w.W_U[V // 2:V // 2 + 4] *= 3.0
+    got = P.to_numpy(LL.ll_project(w.hidden, w.gamma, w.W_U, w.cfg.eps, k, w.target_ids))
+    ref = reference(w, k)
+    P.compare(got, ref, k, label="overflow")
+    assert list(got["topk_ids"][1]) == list(range(k))
+    ids = got["topk_ids"].astype(np.int64)                  # equal logits in ascending id
+    tie = ref["topk_logits"][:, 1:] == ref["topk_logits"][:, :-1]
+    assert tie.sum() > k and np.all(ids[:, 1:][tie] > ids[:, :-1][tie])

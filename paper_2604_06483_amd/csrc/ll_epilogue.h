@@ -10,6 +10,40 @@
 #include <limits.h>
 #include <math.h>
 
+#include <type_traits>
+
+namespace ll {
+
+struct GemmArgs {
+  const uint16_t* A;        // [rows, lda] bf16 (this pass's rows)
+  const float* inv_rms;     // [rows] or nullptr (rows already normalised)
+  const uint16_t* gamma;    // [d] or nullptr
+  const uint16_t* W;        // [V, d] bf16
+  const int32_t* target;    // [rows] or nullptr
+  const float* bias;        // [tiles * BM] fp32 (zero padded beyond V) or nullptr: the b of Eq. 1
+  float4* stats;            // [rows, splits]     (m, S, T, z_target)
+  uint2* top;               // [rows, splits, k]  (logit bits, id), sorted
+  int64_t lda;              // row stride of A in elements
+  int rows, d, V, k, splits, tiles, row_blocks;
+  // steering sweep only (Sec. 3.4, Eq. 3 for several alpha in one pass):
+  const float* au;          // [n_alpha, au_stride] fp32: alpha_a * (W_U v)[id], zero padded to whole tiles
+  float4* sweep_stats;      // [rows, splits, n_alpha]  (m, S, T, bits of the arg max id)
+  float* sweep_ztgt;        // [rows, splits]           logit of the target id at alpha = 0
+  uint2* sweep_top;         // [rows, splits, n_alpha, SWEEP_KS] (logit bits, id), sorted: the sweep with top-k lists
+  int au_stride, n_alpha;
+  // sharing top-k thresholds between the vocabulary splits of a row (nullptr: off)
+  unsigned* bound;          // [rows] lower bounds on each row's k-th best logit, as ordered keys; zero at launch
+};
+
+using GemmKernel = void (*)(const GemmArgs);
+
+// The direct-to-LDS kernels for a d that is not a multiple of 64 (ll_project_tail.hip); nullptr where there is none (the longest
+// list with a bias).
+GemmKernel tail_topk_kernel(int k, bool bias);
+GemmKernel tail_sweep_kernel(bool lists);
+
+}  // namespace ll
+
 namespace {
 
 using namespace ll;
@@ -45,27 +79,6 @@ constexpr float LOG2E = 1.4426950408889634f;
 #define LL_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 
 typedef const float __attribute__((address_space(4)))* const_f32_ptr;   // read through scalar loads when the address is wave-uniform
-
-struct GemmArgs {
-  const uint16_t* A;        // [rows, lda] bf16 (this pass's rows)
-  const float* inv_rms;     // [rows] or nullptr (rows already normalised)
-  const uint16_t* gamma;    // [d] or nullptr
-  const uint16_t* W;        // [V, d] bf16
-  const int32_t* target;    // [rows] or nullptr
-  const float* bias;        // [tiles * BM] fp32 (zero padded beyond V) or nullptr: the b of Eq. 1
-  float4* stats;            // [rows, splits]     (m, S, T, z_target)
-  uint2* top;               // [rows, splits, k]  (logit bits, id), sorted
-  int64_t lda;              // row stride of A in elements
-  int rows, d, V, k, splits, tiles, row_blocks;
-  // steering sweep only (Sec. 3.4, Eq. 3 for several alpha in one pass):
-  const float* au;          // [n_alpha, au_stride] fp32: alpha_a * (W_U v)[id], zero padded to whole tiles
-  float4* sweep_stats;      // [rows, splits, n_alpha]  (m, S, T, bits of the arg max id)
-  float* sweep_ztgt;        // [rows, splits]           logit of the target id at alpha = 0
-  uint2* sweep_top;         // [rows, splits, n_alpha, SWEEP_KS] (logit bits, id), sorted: the sweep with top-k lists
-  int au_stride, n_alpha;
-  // sharing top-k thresholds between the vocabulary splits of a row (nullptr: off)
-  unsigned* bound;          // [rows] lower bounds on each row's k-th best logit, as ordered keys; zero at launch
-};
 
 // ---------------------------------------------------------------------------------------
 // Epilogue shared by both GEMM kernels.  State of one lens row, private to the lane that owns it.
@@ -399,6 +412,15 @@ struct TopKEpilogue {   // a5..a7: softmax statistics, k best logits, target log
     epilogue_store(p, st, my_row, split);
   }
 };
+
+// The top-k lists live in registers: the kernels are built for a few list lengths KR >= k.  pick(KR as a constant)
+template <class F>
+auto with_list_length(int k, F pick) {
+  if (k <= 4) return pick(std::integral_constant<int, 4>{});
+  if (k <= 12) return pick(std::integral_constant<int, 12>{});
+  if (k <= 20) return pick(std::integral_constant<int, 20>{});
+  return pick(std::integral_constant<int, 32>{});
+}
 
 // Workgroup ids are dealt round-robin over the 8 XCDs; remap so that one XCD (one L2) gets a
 // compact rectangle of (row blocks) x (all splits) and its CUs share A panels and W tiles.

@@ -4,8 +4,6 @@
 
 #include "ll_epilogue.h"
 
-#include <type_traits>
-
 namespace {
 
 // ---------------------------------------------------------------------------------------

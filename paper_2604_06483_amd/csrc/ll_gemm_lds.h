@@ -1,5 +1,5 @@
-// Direct-to-LDS projection kernel (d a multiple of 64; operands by global_load_lds into LDS rings,
-// v_mfma_f32_16x16x32_bf16): the kernel the benchmark times.
+// Direct-to-LDS projection kernel (operands by global_load_lds into LDS rings, v_mfma_f32_16x16x32_bf16):
+// the kernel the benchmark times.
 #pragma once
 
 #include "ll_epilogue.h"
@@ -11,7 +11,7 @@ namespace {
 // 16 bytes per lane) in stages of K = 64, so that every load instruction takes whole 128-byte
 // lines (8 rows x 128 B).  A must be a panel of already normalised bf16 rows with row stride
 // lda, a multiple of 64, zero padded beyond d (ll_norm_panel_kernel writes it); W rows are read
-// in place.
+// in place, whatever d.
 //
 // LDS holds five 32 KB slots, each one operand tile [256 rows][128 B]: a ring of three for the
 // W tiles (stage g in slot g % 3) and a ring of two for the A tiles (stage g in slot 3 + g % 2).
@@ -49,6 +49,12 @@ namespace {
 // across vocabulary tiles (the next tile's first stages load under the epilogue); past the last
 // real stage they re-fetch the last tile, never consumed, which keeps the count of loads in
 // flight, and with it the s_waitcnt, constant.
+//
+// TAIL (an instantiation of its own): d is not a multiple of 64.  In a row's last stage the lanes whose
+// chunk lies past the row's end fetch its last chunk instead, and once the tile has landed each
+// wavefront overwrites those chunks of its own 64 rows with zeros, before the barrier that hands the
+// tile to the others.  (A's padding is zero as well, but zero times an infinity of W would not be.)
+// Once per vocabulary tile: not measurable beside the padded share of the stage itself.
 // ---------------------------------------------------------------------------------------
 constexpr int DK = 64;
 constexpr int W_SLOTS = 3, A_SLOTS = 2, SLOTS = W_SLOTS + A_SLOTS;
@@ -97,10 +103,8 @@ __device__ __forceinline__ f32x4 mfma16_from_zero(bf16x8 a, bf16x8 b) {
   return c;
 }
 
-template <class EPI>
-__global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(1, 1)))
-void ll_lens_gemm_dma_kernel(const GemmArgs p) {
-  extern __shared__ __align__(16) unsigned char smem[];
+template <class EPI, bool TAIL>
+__device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* const smem) {
 
   const int logical = xcd_logical_block();
   if (logical >= p.row_blocks * p.splits) return;
@@ -135,11 +139,29 @@ void ll_lens_gemm_dma_kernel(const GemmArgs p) {
 #pragma unroll
   for (int s = 0; s < 8; ++s)
     a_off[s] = (unsigned)(min(seg_row + 8 * s, a_last) * lda + ((s & 1) ? seg_koff1 : seg_koff0)) * 2u + (7168u - 1024u * s);
+  // TAIL: whole chunks of the last stage; lanes past them step back to the last one (made from the lane number each time, once
+  // per vocabulary tile: the long lists leave no registers to keep the two distances in)
+  const int tail_chunks = TAIL ? (d - (KT - 1) * DK) >> 3 : 8;
+  auto step_back = [&]() {
+    int l = lane;
+    asm volatile("" : "+v"(l));
+    const int c = (l & 7) ^ (l >> 4);
+    const unsigned even = (unsigned)max(c - (tail_chunks - 1), 0) * 16u, odd = (unsigned)max((c ^ 4) - (tail_chunks - 1), 0) * 16u;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) w_off[s] -= (s & 1) ? odd : even;
+  };
   auto set_w_rows = [&](int tile) {
     const int w_last = V - 1 - tile * BM;
 #pragma unroll
     for (int s = 0; s < 8; ++s)
       w_off[s] = (unsigned)(min(seg_row + 8 * s, w_last) * d + ((s & 1) ? seg_koff1 : seg_koff0)) * 2u + (7168u - 1024u * s);
+    if (TAIL && KT == 1) step_back();
+  };
+  // TAIL: zeros into the chunks past the row's end of this wavefront's rows of the W tile at LDS offset `tile_off`
+  auto zero_tail = [&](int tile_off) {
+    const int row = 64 * wave + lane;
+    for (int c = tail_chunks; c < 8; ++c)
+      *reinterpret_cast<uint4*>(smem + tile_off + row * (DK * 2) + ((c ^ (row >> 1)) & 7) * 16) = make_uint4(0, 0, 0, 0);
   };
 
   // Producer state of the two operand streams, all wave-uniform and moved on by a few scalar
@@ -169,6 +191,8 @@ void ll_lens_gemm_dma_kernel(const GemmArgs p) {
       const int t = w_tile < tile1 ? w_tile : tile1 - 1;
       set_w_rows(t);
       w_base = w_tile_base(t);
+    } else if (TAIL && w_kt == KT - 1) {
+      step_back();
     }
     LL_PIN_S(w_lds);
     LL_PIN_S(w_base);
@@ -216,6 +240,7 @@ void ll_lens_gemm_dma_kernel(const GemmArgs p) {
   set_lds_dma_base(w_lds);
   LL_DMA_W(0); LL_DMA_W(1); LL_DMA_W(2); LL_DMA_W(3);
   __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * LOADS_PER_TILE + 4, 15));   // W0 and A0 landed
+  if (TAIL && KT == 1) zero_tail(0);
   __syncthreads();
   // A: the four row tiles of both K halves of the stage.  W: two sets of eight fragments, each the
   // four vocabulary tiles of a slice in both K halves (fragment 2 t + hk).
@@ -352,17 +377,18 @@ void ll_lens_gemm_dma_kernel(const GemmArgs p) {
   for (int tile = tile0; tile < tile1; ++tile) {
     f32x4 acc[16][4];   // first written by the K half 0 MFMAs of stage 0, with C = 0
     // One stage; MF0 is the MFMA form of K half 0: from zero in a tile's first stage, accumulating after.
-#define LL_STAGE(MF0)                                                                                  \
+#define LL_STAGE(MF0, KTILE)                                                                           \
     LL_SLICE(MF0, 0, 1, fw0, fw1, cW, 1, LL_A_NONE, LL_A_NONE, LL_HOOK_S0, LL_RD_SPREAD)               \
     LL_SLICE(MF0, 1, 0, fw1, fw0, cW, 2, LL_A_NONE, LL_A_NONE, LL_HOOK_S1, LL_RD_SPREAD)               \
     LL_SLICE(MF0, 2, 0, fw0, fw1, cW, 3, LL_A_NONE, LL_A_NONE, LL_HOOK_S2, LL_RD_AHEAD)                \
     /* stage g+1 landed (W(g+2) and A(g+2) may still be out); all my reads of W(g) are done */         \
     __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * LOADS_PER_TILE, 0));                                    \
+    if (TAIL && (KT == 1 || (KTILE) == KT - 2)) zero_tail(nW);   /* stage g+1 is a row's last */        \
     __syncthreads();                                                                                   \
     LL_SLICE(MF0, 3, 1, fw1, fw0, nW, 0, LL_AIN_S3, LL_AOUT_S3, LL_HOOK_S3, LL_RD_SPREAD)
-    LL_STAGE(LL_MFMA16_Z)
+    LL_STAGE(LL_MFMA16_Z, 0)
     for (int kt = 1; kt < KT; ++kt) {
-      LL_STAGE(LL_MFMA16)
+      LL_STAGE(LL_MFMA16, kt)
     }
 #undef LL_STAGE
     EPI::tile(acc, st, tile * BM, p, my_row);
@@ -390,6 +416,20 @@ void ll_lens_gemm_dma_kernel(const GemmArgs p) {
 #undef LL_DMA_W
   __builtin_amdgcn_s_waitcnt(waitcnt_imm(0, 15));   // drain the ring before the LDS is given back
   EPI::store(p, st, my_row, split);
+}
+
+template <class EPI>
+__global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void ll_lens_gemm_dma_kernel(const GemmArgs p) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  lens_gemm_dma<EPI, false>(p, smem);
+}
+
+template <class EPI>
+__global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void ll_lens_gemm_dma_tail_kernel(const GemmArgs p) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  lens_gemm_dma<EPI, true>(p, smem);
 }
 
 }  // namespace

@@ -540,6 +540,15 @@ int allow_dynamic_lds(const void* kern, size_t lds) {
   return LL_OK;
 }
 
+// The fewest vocabulary splits that give no workgroup more tiles than `most` splits would: the call takes as long as its
+// busiest workgroup, and the others' lists cost the merge (197 tiles over 64 splits are four each at most; so they are over 50).
+int even_splits(int tiles, int most) {
+  if (most > tiles) most = tiles;
+  if (most < 1) most = 1;
+  const int each = (tiles + most - 1) / most;
+  return (tiles + each - 1) / each;
+}
+
 // (few rows: one wavefront per block, so that they spread over the compute units)
 void launch_norm_panel(const uint16_t* hidden, const uint16_t* gamma, uint16_t* panel, int rows, int d, int64_t lda, float eps,
                        hipStream_t stream) {
@@ -584,26 +593,20 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
   const int64_t N = shape->N;
   const int d = shape->d, V = shape->V;
   const bool has_gamma = gamma != nullptr;
-  // The direct-to-LDS kernel addresses rows with 32-bit byte offsets from a per-tile base.
-  const bool dma_ok = d % DK == 0 && (int64_t)BM * d * 2 < (int64_t)1 << 31 && (int64_t)CHUNK_ROWS * plan.lda * 2 < (int64_t)1 << 31;
+  // The direct-to-LDS kernel addresses rows with 32-bit byte offsets from a per-tile base.  It takes every other shape, a d
+  // that is not a multiple of 64 in an instantiation of its own, which the longest list with a bias does not have.
+  // 777 rows, d = 1608, V = 50257, k = 3 with a bias: TAIL_MEASURED.
+  const GemmKernel tail_kern = d % DK != 0 ? tail_topk_kernel(k, bias != nullptr) : nullptr;
+  const bool dma = !(flags & LL_FLAG_REGISTER_STAGED) && (d % DK == 0 || tail_kern != nullptr) &&
+                   (int64_t)BM * plan.lda * 2 < (int64_t)1 << 31 && (int64_t)CHUNK_ROWS * plan.lda * 2 < (int64_t)1 << 31;
+  const size_t lds = dma ? (size_t)SLOTS * SLOT_BYTES : (size_t)(BM + BN) * BK * 2;
   // A bias (rare: the paper's model families have none) selects a separate instantiation of the
   // kernel, so that calls without one carry no code or registers for it.
-  const bool dma = dma_ok && !(flags & LL_FLAG_REGISTER_STAGED);
-  const size_t lds = dma ? (size_t)SLOTS * SLOT_BYTES : (size_t)(BM + BN) * BK * 2;
-  // The top-k lists live in registers: the kernels are built for a few list lengths KR >= k.
-  void (*kern)(const GemmArgs);
-#define LL_PICK(KR) \
-  (dma ? (bias ? ll_lens_gemm_dma_kernel<TopKEpilogue<KR, true>> : ll_lens_gemm_dma_kernel<TopKEpilogue<KR, false>>) \
-       : (bias ? ll_lens_gemm_kernel<TopKEpilogue<KR, true>> : ll_lens_gemm_kernel<TopKEpilogue<KR, false>>))
-  if (k <= 4)
-    kern = LL_PICK(4);
-  else if (k <= 12)
-    kern = LL_PICK(12);
-  else if (k <= 20)
-    kern = LL_PICK(20);
-  else
-    kern = LL_PICK(32);
-#undef LL_PICK
+  const GemmKernel kern = dma && tail_kern != nullptr ? tail_kern : with_list_length(k, [&](auto kr) -> GemmKernel {
+    constexpr int KR = decltype(kr)::value;
+    if (dma) return bias ? ll_lens_gemm_dma_kernel<TopKEpilogue<KR, true>> : ll_lens_gemm_dma_kernel<TopKEpilogue<KR, false>>;
+    return bias ? ll_lens_gemm_kernel<TopKEpilogue<KR, true>> : ll_lens_gemm_kernel<TopKEpilogue<KR, false>>;
+  });
   if (const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds); rc != LL_OK) return rc;
   // The direct-to-LDS kernel reads hidden in place when the rows need neither scaling nor padding.
   const bool need_panel = dma && (has_gamma || plan.lda != d);
@@ -717,8 +720,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     // of W_U, spread over every compute unit's share of the memory system).
     int splits = NUM_CU / row_blocks;
     if (splits > MAX_PROJECT_SPLITS) splits = MAX_PROJECT_SPLITS;
-    if (splits > tiles) splits = tiles;
-    if (splits < 1) splits = 1;
+    splits = even_splits(tiles, splits);
     GemmArgs a;
     a.A = need_panel ? panel : h_rows;
     a.lda = need_panel ? plan.lda : d;
@@ -762,7 +764,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
 }
 
 struct SweepPlan {
-  size_t off_au, off_stats, off_ztgt, off_top, off_inv_rms, off_panel, total;
+  size_t off_au, off_stats, off_ztgt, off_top, off_panel, total;
   int64_t lda;
   int au_stride;
 };
@@ -782,10 +784,8 @@ SweepPlan make_sweep_plan(const ll_shape* s, int n_alpha, int k = 1) {
   off = align_up(off + partials * sizeof(float), 256);
   p.off_top = off;
   if (k > 1) off = align_up(off + partials * (size_t)SWEEP_TOPK_ALPHAS * SWEEP_KS * sizeof(uint2), 256);
-  p.off_inv_rms = off;   // d not a multiple of 64: the register-staged kernel normalises inside its A-tile load
-  off = align_up(off + rows * sizeof(float), 256);
-  p.lda = s->d;
-  p.off_panel = off;     // d a multiple of 64: normalised rows for the direct-to-LDS kernel
+  p.lda = ((int64_t)s->d + DK - 1) / DK * DK;
+  p.off_panel = off;
   off = align_up(off + rows * (size_t)p.lda * sizeof(uint16_t), 256);
   p.total = off;
   return p;
@@ -822,7 +822,6 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
   float4* stats = reinterpret_cast<float4*>(ws + plan.off_stats);
   float* ztgt = reinterpret_cast<float*>(ws + plan.off_ztgt);
   uint2* top = reinterpret_cast<uint2*>(ws + plan.off_top);
-  float* inv_rms = reinterpret_cast<float*>(ws + plan.off_inv_rms);
   uint16_t* panel = reinterpret_cast<uint16_t*>(ws + plan.off_panel);
   const int64_t N = shape->N;
   const int d = shape->d, V = shape->V;
@@ -848,38 +847,28 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
   hipLaunchKernelGGL(ll_unembed_direction_kernel, dim3(NUM_CU * 4), dim3(256), (size_t)d * sizeof(float), stream,
                      static_cast<const uint16_t*>(W_U), v, V, d, al, n_alpha, au, plan.au_stride);
   LL_CHECK_S(hipGetLastError());
-  // The direct-to-LDS kernel needs whole K stages of 64 and 32-bit row offsets; otherwise the register-staged
-  // kernel, which normalises inside its A-tile load.
-  const bool dma = d % DK == 0 && (int64_t)BM * d * 2 < (int64_t)1 << 31 && (int64_t)CHUNK_ROWS * d * 2 < (int64_t)1 << 31;
-  void (*kern)(const GemmArgs);
-  if (k == 1)
-    kern = dma ? ll_lens_gemm_dma_kernel<SweepEpilogue> : ll_lens_gemm_kernel<SweepEpilogue>;
-  else
-    kern = dma ? ll_lens_gemm_dma_kernel<SweepTopKEpilogue> : ll_lens_gemm_kernel<SweepTopKEpilogue>;
-  const size_t lds = dma ? (size_t)SLOTS * SLOT_BYTES : (size_t)(BM + BN) * BK * 2;
+  // (d is at most SWEEP_MAX_D: the direct-to-LDS kernel's 32-bit row offsets always suffice)
+  const GemmKernel kern = d % DK != 0 ? tail_sweep_kernel(k > 1)
+                          : k > 1     ? ll_lens_gemm_dma_kernel<SweepTopKEpilogue>
+                                      : ll_lens_gemm_dma_kernel<SweepEpilogue>;
+  const size_t lds = (size_t)SLOTS * SLOT_BYTES;
   if (const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds); rc != LL_OK) return rc;
 
   for (int64_t r0 = 0; r0 < N; r0 += CHUNK_ROWS) {
     const int rows = (int)((N - r0 < CHUNK_ROWS) ? (N - r0) : CHUNK_ROWS);
     const uint16_t* h_rows = static_cast<const uint16_t*>(hidden) + r0 * d;
-    if (gamma != nullptr && dma) {
+    const bool need_panel = gamma != nullptr || plan.lda != d;
+    if (need_panel) {
       launch_norm_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, d, plan.lda, eps, stream);
-      LL_CHECK_S(hipGetLastError());
-    } else if (gamma != nullptr) {
-      hipLaunchKernelGGL(ll_rms_stats_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, h_rows, (int64_t)rows, d,
-                         eps, inv_rms);
       LL_CHECK_S(hipGetLastError());
     }
     const int row_blocks = (rows + BN - 1) / BN;
     int splits = NUM_CU / row_blocks;
     if (splits > MAX_SPLITS) splits = MAX_SPLITS;
-    if (splits > tiles) splits = tiles;
-    if (splits < 1) splits = 1;
+    splits = even_splits(tiles, splits);
     GemmArgs a = {};
-    a.A = (gamma != nullptr && dma) ? panel : h_rows;
+    a.A = need_panel ? panel : h_rows;
     a.lda = plan.lda;
-    a.inv_rms = (gamma != nullptr && !dma) ? inv_rms : nullptr;
-    a.gamma = static_cast<const uint16_t*>(gamma);
     a.sweep_top = top;
     a.W = static_cast<const uint16_t*>(W_U);
     a.target = target_ids ? target_ids + r0 : nullptr;

@@ -26,13 +26,17 @@ struct GemmArgs {
   int64_t lda;              // row stride of A in elements
   int rows, d, V, k, splits, tiles, row_blocks;
   // steering sweep only (Sec. 3.4, Eq. 3 for several alpha in one pass):
-  const float* au;          // [n_alpha, au_stride] fp32: alpha_a * (W_U v)[id], zero padded to whole tiles
-  float4* sweep_stats;      // [rows, splits, n_alpha]  (m, S, T, bits of the arg max id)
-  float* sweep_ztgt;        // [rows, splits]           logit of the target id at alpha = 0
-  uint2* sweep_top;         // [rows, splits, n_alpha, SWEEP_KS] (logit bits, id), sorted: the sweep with top-k lists
-  int au_stride, n_alpha;
+  const float* u;           // [tiles * BM] fp32: W_U v, zero padded
+  const float* eu;          // [tiles * BM / 16, n_alpha, 32] fp32: of 16 ids e^(alpha u), then u e^(alpha u)
+  const float* shift_max;   // [tiles * BM / 16, n_alpha] fp32: largest alpha u of 16 ids
+  const int* sweep_general; // nonzero: some |alpha u| is too large for the factored form
+  float4* sweep_stats;      // [rows, n_alpha, splits]      (reference, S, T)
+  float* sweep_ztgt;        // [rows, splits]               logit of the target id at alpha = 0
+  uint2* sweep_top;         // [rows, n_alpha, splits, KS]  (logit bits, id), sorted
+  int n_alpha;
+  float alphas[LL_SWEEP_MAX];
   // sharing top-k thresholds between the vocabulary splits of a row (nullptr: off)
-  unsigned* bound;          // [rows] lower bounds on each row's k-th best logit, as ordered keys; zero at launch
+  unsigned* bound;          // [rows] (sweep: [n_alpha, rows]) lower bounds on each row's k-th best logit, as ordered keys; zero at launch
 };
 
 using GemmKernel = void (*)(const GemmArgs);
@@ -41,6 +45,8 @@ using GemmKernel = void (*)(const GemmArgs);
 // list with a bias).
 GemmKernel tail_topk_kernel(int k, bool bias);
 GemmKernel tail_sweep_kernel(bool lists);
+// The general form of the steering sweep, for any d (see ll_epilogue_sweep.h).
+GemmKernel general_sweep_kernel(bool lists);
 
 }  // namespace ll
 
@@ -398,6 +404,8 @@ __device__ __forceinline__ void epilogue_store(const GemmArgs& p, const RowState
 template <int KR, bool BIAS = false>
 struct TopKEpilogue {   // a5..a7: softmax statistics, k best logits, target logit (BIAS: Eq. 1's b added to every logit first)
   using State = RowState<KR>;
+  static constexpr bool RELOAD_FRAGMENTS = false;
+  static __device__ __forceinline__ bool skip(const GemmArgs&) { return false; }
   static __device__ __forceinline__ void init(State& st, const GemmArgs& p, int my_row) {
     st.init();
     st.tgt = (p.target != nullptr && my_row < p.rows) ? p.target[my_row] : -1;

@@ -107,7 +107,7 @@ template <class EPI, bool TAIL>
 __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* const smem) {
 
   const int logical = xcd_logical_block();
-  if (logical >= p.row_blocks * p.splits) return;
+  if (__builtin_expect(logical >= p.row_blocks * p.splits || EPI::skip(p), 0)) return;
   const int split = logical % p.splits;
   const int rb = logical / p.splits;
   const int tile0 = (int)((int64_t)split * p.tiles / p.splits);
@@ -152,9 +152,12 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
   };
   auto set_w_rows = [&](int tile) {
     const int w_last = V - 1 - tile * BM;
+    int l = lane;
+    if (EPI::RELOAD_FRAGMENTS) asm volatile("" : "+v"(l));   // (made anew for every tile: 18 registers less to keep)
+    const int row = 64 * wave + (l >> 3), koff0 = ((l & 7) ^ (l >> 4)) * 8;
 #pragma unroll
     for (int s = 0; s < 8; ++s)
-      w_off[s] = (unsigned)(min(seg_row + 8 * s, w_last) * d + ((s & 1) ? seg_koff1 : seg_koff0)) * 2u + (7168u - 1024u * s);
+      w_off[s] = (unsigned)(min(row + 8 * s, w_last) * d + ((s & 1) ? koff0 ^ 32 : koff0)) * 2u + (7168u - 1024u * s);
     if (TAIL && KT == 1) step_back();
   };
   // TAIL: zeros into the chunks past the row's end of this wavefront's rows of the W tile at LDS offset `tile_off`
@@ -245,13 +248,15 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
   // A: the four row tiles of both K halves of the stage.  W: two sets of eight fragments, each the
   // four vocabulary tiles of a slice in both K halves (fragment 2 t + hk).
   bf16x8 fa[2][4], fw0[8], fw1[8];
+  auto read_fragments = [&](int w_tile_off, int a_tile_off) {   // those that slice 0 of a stage starts from
 #pragma unroll
-  for (int hk = 0; hk < 2; ++hk)
+    for (int hk = 0; hk < 2; ++hk)
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-      fa[hk][j] = *reinterpret_cast<const bf16x8*>(smem + W_SLOTS * SLOT_BYTES + a_wave_off + j * 16 * (DK * 2) + f_off[hk]);
+      for (int j = 0; j < 4; ++j) fa[hk][j] = *reinterpret_cast<const bf16x8*>(smem + a_tile_off + j * 16 * (DK * 2) + f_off[hk]);
 #pragma unroll
-  for (int q = 0; q < 8; ++q) fw0[q] = *reinterpret_cast<const bf16x8*>(smem + (q >> 1) * 16 * (DK * 2) + f_off[q & 1]);
+    for (int q = 0; q < 8; ++q) fw0[q] = *reinterpret_cast<const bf16x8*>(smem + w_tile_off + (q >> 1) * 16 * (DK * 2) + f_off[q & 1]);
+  };
+  read_fragments(0, W_SLOTS * SLOT_BYTES + a_wave_off);
 
   // A stage is four slices of 32 MFMAs; slice S is vocabulary tiles 4 S .. 4 S + 3 against the
   // four row tiles, BOTH K halves: the two MFMAs of an accumulator tile are issued back to back,
@@ -392,6 +397,9 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
     }
 #undef LL_STAGE
     EPI::tile(acc, st, tile * BM, p, my_row);
+    // An epilogue that needs the 64 registers reads the next stage's first fragments again: both tiles stay in LDS until that
+    // stage's own slices send the loads that replace them.
+    if (EPI::RELOAD_FRAGMENTS) read_fragments(cW, a_flip - nA);
   }
 #undef LL_PAIR
 #undef LL_RD_SPREAD

@@ -104,38 +104,49 @@ __global__ __launch_bounds__(256) void ll_fill_f32_kernel(float* __restrict__ p,
 }
 
 // ---------------------------------------------------------------------------------------
-// Steering sweep, step 1: u = W_U v (one pass over W_U, HBM-bound: 2 V d bytes), written as the
-// table au[a, id] = alpha_a * u[id] that the sweep epilogue adds to the logits.  One wavefront
-// takes eight vocabulary rows at a time: a chunk of v read from LDS serves eight products, and
-// eight 16-byte loads per lane are in flight.
+// Steering sweep, step 1: u = W_U v (one pass over W_U, HBM-bound: 2 V d bytes) and, per workgroup, the
+// largest |u|.  One wavefront takes eight vocabulary rows at a time: a chunk of v read from LDS serves
+// eight products, and eight 16-byte loads per lane are in flight.  STREAM: the loads carry the
+// non-temporal hint, for a W_U that the Infinity Cache (256 MiB) would not keep for step 3 anyway.
+// DIRECTION_MEASURED
 // ---------------------------------------------------------------------------------------
 struct AlphaList {
   float a[SWEEP_MAX];
 };
 
 constexpr int UD_ROWS = 8;   // vocabulary rows a wavefront takes at a time
+constexpr int UD_BLOCKS = NUM_CU * 4;
+constexpr int64_t INFINITY_CACHE_BYTES = 256ll << 20;
 
+typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+
+// The larger of two numbers, NaN once one of them is.
+__device__ __forceinline__ float sticky_max(float a, float b) { return (a != a || a >= b) ? a : b; }
+
+template <bool STREAM>
 __global__ __launch_bounds__(256) void ll_unembed_direction_kernel(const uint16_t* __restrict__ W, const float* __restrict__ v,
-                                                                   int V, int d, AlphaList alphas, int n_alpha,
-                                                                   float* __restrict__ au, int au_stride) {
+                                                                   int V, int d, float* __restrict__ u,
+                                                                   float* __restrict__ block_max) {
   extern __shared__ __align__(16) float sv[];
   for (int j = threadIdx.x; j < d; j += blockDim.x) sv[j] = v[j];
   __syncthreads();
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int n16 = d >> 3;
+  float largest = 0.f;   // (NaN once any u is)
   for (int r0 = (blockIdx.x * 4 + wave) * UD_ROWS; r0 < V; r0 += gridDim.x * 4 * UD_ROWS) {
     float acc[UD_ROWS];
-    const uint4* rows[UD_ROWS];
+    const u32x4* rows[UD_ROWS];
 #pragma unroll
     for (int i = 0; i < UD_ROWS; ++i) {
       acc[i] = 0.f;
-      rows[i] = reinterpret_cast<const uint4*>(W + (int64_t)min(r0 + i, V - 1) * d);
+      rows[i] = reinterpret_cast<const u32x4*>(W + (int64_t)min(r0 + i, V - 1) * d);
     }
     for (int c = lane; c < n16; c += 64) {
-      uint4 q[UD_ROWS];
+      u32x4 q[UD_ROWS];
 #pragma unroll
-      for (int i = 0; i < UD_ROWS; ++i) q[i] = rows[i][c];   // all loads of the step in flight before the first use
+      for (int i = 0; i < UD_ROWS; ++i)   // all loads of the step in flight before the first use
+        q[i] = STREAM ? __builtin_nontemporal_load(rows[i] + c) : rows[i][c];
       const float4 v0 = *reinterpret_cast<const float4*>(sv + 8 * c);
       const float4 v1 = *reinterpret_cast<const float4*>(sv + 8 * c + 4);
 #pragma unroll
@@ -154,24 +165,53 @@ __global__ __launch_bounds__(256) void ll_unembed_direction_kernel(const uint16_
     }
 #pragma unroll
     for (int i = 0; i < UD_ROWS; ++i) {
-      const float u = wave_sum(acc[i]);
-      if (lane == 0 && r0 + i < V) {
-#pragma unroll
-        for (int a = 0; a < SWEEP_MAX; ++a)
-          if (a < n_alpha) au[(int64_t)a * au_stride + r0 + i] = alphas.a[a] * u;
+      const float x = wave_sum(acc[i]);
+      if (r0 + i < V) {
+        if (lane == 0) u[r0 + i] = x;
+        largest = sticky_max(largest, fabsf(x));
       }
     }
   }
+  __syncthreads();   // v is done with: its LDS (all of it, at the largest d) takes the wavefronts' maxima
+  if (lane == 0) sv[wave] = largest;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 4; ++w) largest = sticky_max(largest, sv[w]);
+    block_max[blockIdx.x] = largest;
+  }
 }
 
-// Steering sweep, step 3: merge the splits of each (row, alpha) and finalise.  One wavefront per
-// row, lane s = split s.
-__global__ __launch_bounds__(256) void ll_sweep_merge_kernel(const float4* __restrict__ stats, const float* __restrict__ ztgt,
-                                                             const float* __restrict__ au, int au_stride, int rows, int splits,
-                                                             int n_alpha, int V, const int32_t* __restrict__ target,
-                                                             int64_t out_stride, int32_t* __restrict__ out_ids,
-                                                             float* __restrict__ out_p, float* __restrict__ out_logp,
-                                                             float* __restrict__ out_entropy);
+// Step 2: what the sweep epilogue reads per group of 16 ids (see GemmArgs), the padding of u, the flag that says which form
+// of the epilogue runs, and the zeroed bounds.
+__global__ __launch_bounds__(256) void ll_sweep_table_kernel(const float* __restrict__ block_max, int n_blocks, int V, int n_padded,
+                                                             AlphaList alphas, int n_alpha, float* __restrict__ u,
+                                                             float* __restrict__ eu, float* __restrict__ shift_max,
+                                                             int* __restrict__ general, unsigned* __restrict__ bound, int n_bound) {
+  for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_bound; i += gridDim.x * blockDim.x) bound[i] = 0u;
+  for (int id = blockIdx.x * blockDim.x + threadIdx.x; id < n_padded; id += gridDim.x * blockDim.x) {   // (whole groups: n_padded is a multiple of 256)
+    const float x = id < V ? u[id] : 0.f;
+    if (id >= V) u[id] = 0.f;
+    const int64_t row = (int64_t)(id >> 4) * n_alpha;
+    for (int a = 0; a < n_alpha; ++a) {
+      const float shift = alphas.a[a] * x;
+      const float e = expf(shift);
+      eu[(row + a) * SWEEP_ROW + (id & 15)] = e;
+      eu[(row + a) * SWEEP_ROW + 16 + (id & 15)] = e * x;
+      float most = shift;
+#pragma unroll
+      for (int off = 8; off > 0; off >>= 1) most = fmaxf(most, __shfl_xor(most, off, kWave));
+      if ((id & 15) == 0) shift_max[row + a] = most;
+    }
+  }
+  if (blockIdx.x != 0 || threadIdx.x >= 64) return;
+  float largest = 0.f, alpha = 0.f;
+  for (int i = threadIdx.x; i < n_blocks; i += 64) largest = sticky_max(largest, block_max[i]);
+#pragma unroll
+  for (int a = 0; a < SWEEP_MAX; ++a) alpha = fmaxf(alpha, fabsf(alphas.a[a]));
+  const bool fine = alpha * largest <= SWEEP_SHIFT;
+  const bool all_fine = __builtin_amdgcn_ballot_w64(!fine) == 0;
+  if (threadIdx.x == 0) *general = all_fine ? 0 : 1;
+}
 
 // ---------------------------------------------------------------------------------------
 // a8: merge the splits of each row and finalise.  One wavefront per row, one lane per split.
@@ -321,108 +361,85 @@ __global__ __launch_bounds__(256) void ll_merge_kernel(const float4* __restrict_
   }
 }
 
-__global__ __launch_bounds__(256) void ll_sweep_merge_kernel(const float4* __restrict__ stats, const float* __restrict__ ztgt,
-                                                             const float* __restrict__ au, int au_stride, int rows, int splits,
-                                                             int n_alpha, int V, const int32_t* __restrict__ target,
-                                                             int64_t out_stride, int32_t* __restrict__ out_ids,
-                                                             float* __restrict__ out_p, float* __restrict__ out_logp,
-                                                             float* __restrict__ out_entropy) {
-  const int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (row >= rows) return;
+// Steering sweep, step 4: merge the splits of each (row, alpha) and finalise.  One wavefront each; lane l takes splits l,
+// l + 64, ... (increasing ids), keeps their KS best, and the wavefront takes the best of its lanes' heads k times.
+template <int KS>
+__global__ __launch_bounds__(256) void ll_sweep_merge_kernel(const float4* __restrict__ stats, const uint2* __restrict__ top,
+                                                             const float* __restrict__ ztgt, const float* __restrict__ u,
+                                                             AlphaList alphas, int rows, int splits, int n_alpha, int k, int V,
+                                                             const int32_t* __restrict__ target, int64_t out_stride,
+                                                             int32_t* __restrict__ out_ids, float* __restrict__ out_p,
+                                                             float* __restrict__ out_logp, float* __restrict__ out_entropy,
+                                                             unsigned* __restrict__ bound) {
+  const int item = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (item >= rows * n_alpha) return;
   const int lane = threadIdx.x & 63;
-  const bool live = lane < splits;
-  int t = -1;
-  float zt0 = -INFINITY;
-  if (target != nullptr) {
-    t = target[row];
-    zt0 = wave_max(live ? ztgt[(int64_t)row * splits + lane] : -INFINITY);
+  const int row = item / n_alpha, a = item - row * n_alpha;
+  const float4* const q = stats + (int64_t)item * splits;
+  const uint2* const lists = top + (int64_t)item * splits * KS;
+  float m = -INFINITY, zt = -INFINITY;
+  float z[KS];
+  int id[KS];
+#pragma unroll
+  for (int j = 0; j < KS; ++j) {
+    z[j] = -INFINITY;
+    id[j] = INT_MAX;
   }
-  const bool t_ok = t >= 0 && t < V;
-  for (int a = 0; a < n_alpha; ++a) {
-    float4 q = make_float4(-INFINITY, 0.f, 0.f, __int_as_float(INT_MAX));
-    if (live) q = stats[((int64_t)row * splits + lane) * n_alpha + a];
-    const float M = wave_max(q.x);
-    // splits hold increasing id ranges, and within one the smallest id of its maximum is kept
-    const int best = wave_min_int(q.x == M ? __float_as_int(q.w) : INT_MAX);
-    const float sc = live ? __builtin_amdgcn_exp2f((q.x - M) * LOG2E) : 0.f;
-    const float S = wave_sum(sc * q.y);
-    const float T = wave_sum(sc * q.z);
-    if (lane == 0) {
-      const float logS = logf(S);
-      const int64_t o = (int64_t)a * out_stride + row;
-      out_ids[o] = best;
-      out_p[o] = 1.0f / S;                      // exp(M - (M + log S))
-      out_entropy[o] = (M - T / S) + logS;
-      if (target != nullptr)
-        out_logp[o] = t_ok ? ((zt0 + au[(int64_t)a * au_stride + t]) - M) - logS : __builtin_nanf("");
-    }
-  }
-}
-
-// The sweep with top-k lists: per (row, alpha) the splits' statistics and sorted lists of SWEEP_KS
-// entries are merged as in ll_merge_kernel (one wavefront per row, lane s = split s; the lists
-// are short, so their heads are read from the workspace directly).  Outputs are [n_alpha, N, k].
-__global__ __launch_bounds__(256) void ll_sweep_topk_merge_kernel(const float4* __restrict__ stats, const uint2* __restrict__ top,
-                                                                  const float* __restrict__ ztgt, const float* __restrict__ au,
-                                                                  int au_stride, int rows, int splits, int n_alpha, int k, int V,
-                                                                  const int32_t* __restrict__ target, int64_t out_stride,
-                                                                  int32_t* __restrict__ out_ids, float* __restrict__ out_p,
-                                                                  float* __restrict__ out_logp, float* __restrict__ out_entropy) {
-  const int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (row >= rows) return;
-  const int lane = threadIdx.x & 63;
-  const bool live = lane < splits;
-  int t = -1;
-  float zt0 = -INFINITY;
-  if (target != nullptr) {
-    t = target[row];
-    zt0 = wave_max(live ? ztgt[(int64_t)row * splits + lane] : -INFINITY);
-  }
-  const bool t_ok = t >= 0 && t < V;
-  int width = 1;
-  while (width < splits) width <<= 1;
-  for (int a = 0; a < n_alpha; ++a) {
-    const int64_t part = ((int64_t)row * splits + (live ? lane : 0)) * n_alpha + a;
-    float4 q = make_float4(-INFINITY, 0.f, 0.f, 0.f);
-    if (live) q = stats[part];
-    const float M = wave_max(q.x);
-    const float sc = live ? __builtin_amdgcn_exp2f((q.x - M) * LOG2E) : 0.f;
-    const float S = wave_sum(sc * q.y);
-    const float T = wave_sum(sc * q.z);
-    const float logS = logf(S);
-    const int64_t o = (int64_t)a * out_stride + row;
-    if (lane == 0) {
-      out_entropy[o] = (M - T / S) + logS;
-      if (target != nullptr)
-        out_logp[o] = t_ok ? ((zt0 + au[(int64_t)a * au_stride + t]) - M) - logS : __builtin_nanf("");
-    }
-    const uint2* tl = top + part * SWEEP_KS;
-    int head = 0;
-    float z = -INFINITY;
-    int id = INT_MAX;
-    if (live) {
-      const uint2 e = tl[0];
-      z = __uint_as_float(e.x);
-      id = (int)e.y;
-    }
-    for (int j = 0; j < k; ++j) {
-      const float bz = group_max(z, width);
-      const int bi = group_min_int(z == bz ? id : INT_MAX, width);
-      if (live && z == bz && id == bi) {
-        ++head;
-        if (head < SWEEP_KS) {
-          const uint2 e = tl[head];
-          z = __uint_as_float(e.x);
-          id = (int)e.y;
-        } else {
-          z = -INFINITY;
-          id = INT_MAX;
-        }
+  for (int s = lane; s < splits; s += 64) {
+    m = fmaxf(m, q[s].x);
+    if (target != nullptr) zt = fmaxf(zt, ztgt[(int64_t)row * splits + s]);
+#pragma unroll
+    for (int i = 0; i < KS; ++i) {
+      const uint2 e = lists[(int64_t)s * KS + i];
+      float ze = __uint_as_float(e.x);
+      int ie = (int)e.y;
+#pragma unroll
+      for (int j = 0; j < KS; ++j) {   // an entry that ranks above slot j takes it and pushes the slot's down (ids only grow: strictly greater)
+        const bool above = ze > z[j];
+        const float zo = z[j];
+        const int io = id[j];
+        z[j] = above ? ze : zo;
+        id[j] = above ? ie : io;
+        ze = above ? zo : ze;
+        ie = above ? io : ie;
       }
-      if (lane == 0) {
-        out_ids[o * k + j] = bi;
-        out_p[o * k + j] = __builtin_amdgcn_exp2f(((bz - M) - logS) * LOG2E);
+    }
+  }
+  const float M = wave_max(m);
+  float s_lane = 0.f, t_lane = 0.f;
+  for (int s = lane; s < splits; s += 64) {
+    const float4 x = q[s];
+    const float sc = __builtin_amdgcn_exp2f((x.x - M) * LOG2E);
+    s_lane = fmaf(sc, x.y, s_lane);
+    t_lane = fmaf(sc, x.z, t_lane);
+  }
+  const float S = wave_sum(s_lane), T = wave_sum(t_lane);
+  const float logS = logf(S);
+  zt = wave_max(zt);
+  const int64_t o = (int64_t)a * out_stride + row;
+  if (lane == 0) {
+    bound[a * rows + row] = 0u;   // the projection kernel of this pass is done with it: clear it for the next pass
+    out_entropy[o] = (M - T / S) + logS;
+    if (target != nullptr) {
+      const int t = target[row];
+      out_logp[o] = t >= 0 && t < V ? ((zt + alphas.a[a] * u[t]) - M) - logS : __builtin_nanf("");
+    }
+  }
+  for (int j = 0; j < k; ++j) {
+    const float bz = wave_max(z[0]);
+    const int bi = wave_min_int(z[0] == bz ? id[0] : INT_MAX);
+    if (z[0] == bz && id[0] == bi) {   // ids are distinct: one lane
+#pragma unroll
+      for (int i = 0; i + 1 < KS; ++i) {
+        z[i] = z[i + 1];
+        id[i] = id[i + 1];
       }
+      z[KS - 1] = -INFINITY;
+      id[KS - 1] = INT_MAX;
+    }
+    if (lane == 0) {
+      out_ids[o * k + j] = bi;
+      out_p[o * k + j] = __builtin_amdgcn_exp2f(((bz - M) - logS) * LOG2E);
     }
   }
 }
@@ -595,7 +612,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
   const bool has_gamma = gamma != nullptr;
   // The direct-to-LDS kernel addresses rows with 32-bit byte offsets from a per-tile base.  It takes every other shape, a d
   // that is not a multiple of 64 in an instantiation of its own, which the longest list with a bias does not have.
-  // 777 rows, d = 1608, V = 50257, k = 3 with a bias: TAIL_MEASURED.
+  // 777 rows, d = 1608, V = 50257, k = 3 with a bias: 201 us, on the register-staged kernel 369
   const GemmKernel tail_kern = d % DK != 0 ? tail_topk_kernel(k, bias != nullptr) : nullptr;
   const bool dma = !(flags & LL_FLAG_REGISTER_STAGED) && (d % DK == 0 || tail_kern != nullptr) &&
                    (int64_t)BM * plan.lda * 2 < (int64_t)1 << 31 && (int64_t)CHUNK_ROWS * plan.lda * 2 < (int64_t)1 << 31;
@@ -764,29 +781,46 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
 }
 
 struct SweepPlan {
-  size_t off_au, off_stats, off_ztgt, off_top, off_panel, total;
+  size_t off_u, off_eu, off_shift, off_block_max, off_general, off_bound, off_stats, off_ztgt, off_top, off_panel, total;
   int64_t lda;
-  int au_stride;
+  int n_padded;   // V in whole tiles
 };
 
-// k == 1: the arg max travels inside the statistics; k > 1: room for the sorted lists as well.
+// Vocabulary splits of a pass: one workgroup per compute unit, and ids within a split in 16 bits.
+int sweep_splits(int rows, int tiles) {
+  const int row_blocks = (rows + BN - 1) / BN;
+  const int splits = even_splits(tiles, NUM_CU / row_blocks);
+  const int least = (tiles + SWEEP_MAX_TILES - 1) / SWEEP_MAX_TILES;
+  return splits > least ? splits : least;
+}
+
 SweepPlan make_sweep_plan(const ll_shape* s, int n_alpha, int k = 1) {
   SweepPlan p;
   size_t off = 0;
-  p.au_stride = (s->V + BM - 1) / BM * BM;
-  p.off_au = off;
-  off = align_up(off + (size_t)n_alpha * p.au_stride * sizeof(float), 256);
+  auto take = [&](size_t bytes) {
+    const size_t at = off;
+    off = align_up(off + bytes, 256);
+    return at;
+  };
+  const int tiles = (s->V + BM - 1) / BM;
+  p.n_padded = tiles * BM;
+  const size_t groups = (size_t)p.n_padded / SWEEP_GROUP;
   const size_t rows = (size_t)(s->N < CHUNK_ROWS ? s->N : CHUNK_ROWS);
-  p.off_stats = off;
-  const size_t partials = rows * MAX_SPLITS < (size_t)MAX_PARTIALS ? rows * MAX_SPLITS : (size_t)MAX_PARTIALS;
-  off = align_up(off + partials * (size_t)n_alpha * sizeof(float4), 256);
-  p.off_ztgt = off;
-  off = align_up(off + partials * sizeof(float), 256);
-  p.off_top = off;
-  if (k > 1) off = align_up(off + partials * (size_t)SWEEP_TOPK_ALPHAS * SWEEP_KS * sizeof(uint2), 256);
+  // rows x splits of a full pass and of a shorter last one
+  size_t partials = rows * NUM_CU < (size_t)MAX_PARTIALS ? rows * NUM_CU : (size_t)MAX_PARTIALS;
+  const size_t least = rows * ((tiles + SWEEP_MAX_TILES - 1) / SWEEP_MAX_TILES);
+  if (partials < least) partials = least;
+  p.off_u = take((size_t)p.n_padded * sizeof(float));
+  p.off_eu = take((groups + 1) * n_alpha * SWEEP_ROW * sizeof(float));   // (the epilogue sends its reads one row ahead)
+  p.off_shift = take(groups * n_alpha * sizeof(float));
+  p.off_block_max = take(UD_BLOCKS * sizeof(float));
+  p.off_general = take(sizeof(int));
+  p.off_bound = take(rows * n_alpha * sizeof(unsigned));
+  p.off_stats = take(partials * n_alpha * sizeof(float4));
+  p.off_ztgt = take(partials * sizeof(float));
+  p.off_top = take(partials * n_alpha * (k > 1 ? SWEEP_KS : 1) * sizeof(uint2));
   p.lda = ((int64_t)s->d + DK - 1) / DK * DK;
-  p.off_panel = off;
-  off = align_up(off + rows * (size_t)p.lda * sizeof(uint16_t), 256);
+  p.off_panel = take(rows * (size_t)p.lda * sizeof(uint16_t));
   p.total = off;
   return p;
 }
@@ -818,7 +852,12 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
   if (workspace == nullptr || workspace_bytes < plan.total || ((uintptr_t)workspace & 255)) return LL_EWORKSPACE;
 
   unsigned char* ws = static_cast<unsigned char*>(workspace);
-  float* au = reinterpret_cast<float*>(ws + plan.off_au);
+  float* u = reinterpret_cast<float*>(ws + plan.off_u);
+  float* eu = reinterpret_cast<float*>(ws + plan.off_eu);
+  float* shift_max = reinterpret_cast<float*>(ws + plan.off_shift);
+  float* block_max = reinterpret_cast<float*>(ws + plan.off_block_max);
+  int* general = reinterpret_cast<int*>(ws + plan.off_general);
+  unsigned* bound = reinterpret_cast<unsigned*>(ws + plan.off_bound);
   float4* stats = reinterpret_cast<float4*>(ws + plan.off_stats);
   float* ztgt = reinterpret_cast<float*>(ws + plan.off_ztgt);
   uint2* top = reinterpret_cast<uint2*>(ws + plan.off_top);
@@ -832,27 +871,25 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     if (e__ != hipSuccess) return hip_failed(e__); \
   } while (0)
 
-  // the padding of the table (ids V .. au_stride) is read by the last tile and masked afterwards:
-  // any finite value will do, zero it once
-  if (plan.au_stride > V) {
-    for (int a = 0; a < n_alpha; ++a)
-      hipLaunchKernelGGL(ll_fill_f32_kernel, dim3(1), dim3(256), 0, stream, au + (size_t)a * plan.au_stride + V,
-                         plan.au_stride - V, 0.f);
-    LL_CHECK_S(hipGetLastError());
-  }
-  if ((size_t)d * sizeof(float) > 64 * 1024)
-    if (const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(ll_unembed_direction_kernel), (size_t)d * sizeof(float));
-        rc != LL_OK)
-      return rc;
-  hipLaunchKernelGGL(ll_unembed_direction_kernel, dim3(NUM_CU * 4), dim3(256), (size_t)d * sizeof(float), stream,
-                     static_cast<const uint16_t*>(W_U), v, V, d, al, n_alpha, au, plan.au_stride);
+  const auto direction = (int64_t)V * d * 2 >= INFINITY_CACHE_BYTES ? ll_unembed_direction_kernel<true> : ll_unembed_direction_kernel<false>;
+  const size_t v_bytes = (size_t)d * sizeof(float);
+  if (v_bytes > 64 * 1024)
+    if (const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(direction), (size_t)SWEEP_MAX_D * sizeof(float)); rc != LL_OK) return rc;
+  hipLaunchKernelGGL(direction, dim3(UD_BLOCKS), dim3(256), v_bytes, stream, static_cast<const uint16_t*>(W_U), v, V, d, u, block_max);
+  LL_CHECK_S(hipGetLastError());
+  const int n_bound = (int)(N < CHUNK_ROWS ? N : CHUNK_ROWS) * n_alpha;
+  hipLaunchKernelGGL(ll_sweep_table_kernel, dim3(plan.n_padded / 256 < 2048 ? plan.n_padded / 256 : 2048), dim3(256), 0, stream,
+                     (const float*)block_max, UD_BLOCKS, V, plan.n_padded, al, n_alpha, u, eu, shift_max, general, bound, n_bound);
   LL_CHECK_S(hipGetLastError());
   // (d is at most SWEEP_MAX_D: the direct-to-LDS kernel's 32-bit row offsets always suffice)
-  const GemmKernel kern = d % DK != 0 ? tail_sweep_kernel(k > 1)
-                          : k > 1     ? ll_lens_gemm_dma_kernel<SweepTopKEpilogue>
-                                      : ll_lens_gemm_dma_kernel<SweepEpilogue>;
+  const bool lists = k > 1;
+  const GemmKernel kern[2] = {d % DK != 0 ? tail_sweep_kernel(lists)
+                              : lists     ? ll_lens_gemm_dma_kernel<SweepEpilogue<SWEEP_KS, false>>
+                                          : ll_lens_gemm_dma_kernel<SweepEpilogue<1, false>>,
+                              general_sweep_kernel(lists)};   // (one of the two returns at once)
   const size_t lds = (size_t)SLOTS * SLOT_BYTES;
-  if (const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds); rc != LL_OK) return rc;
+  for (const GemmKernel g : kern)
+    if (const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(g), lds); rc != LL_OK) return rc;
 
   for (int64_t r0 = 0; r0 < N; r0 += CHUNK_ROWS) {
     const int rows = (int)((N - r0 < CHUNK_ROWS) ? (N - r0) : CHUNK_ROWS);
@@ -862,47 +899,38 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
       launch_norm_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, d, plan.lda, eps, stream);
       LL_CHECK_S(hipGetLastError());
     }
-    const int row_blocks = (rows + BN - 1) / BN;
-    int splits = NUM_CU / row_blocks;
-    if (splits > MAX_SPLITS) splits = MAX_SPLITS;
-    splits = even_splits(tiles, splits);
     GemmArgs a = {};
     a.A = need_panel ? panel : h_rows;
     a.lda = plan.lda;
-    a.sweep_top = top;
     a.W = static_cast<const uint16_t*>(W_U);
     a.target = target_ids ? target_ids + r0 : nullptr;
     a.rows = rows;
     a.d = d;
     a.V = V;
-    a.k = 1;
-    a.splits = splits;
+    a.k = k;
     a.tiles = tiles;
-    a.row_blocks = row_blocks;
-    a.au_stride = plan.au_stride;
+    a.row_blocks = (rows + BN - 1) / BN;
+    a.splits = sweep_splits(rows, tiles);
+    a.u = u;
+    a.eu = eu;
+    a.shift_max = shift_max;
+    a.sweep_general = general;
     a.sweep_stats = stats;
     a.sweep_ztgt = ztgt;
-    const int grid = (row_blocks * splits + NUM_XCD - 1) / NUM_XCD * NUM_XCD;
-    // k == 1: all alphas in one pass over W_U; with lists: SWEEP_TOPK_ALPHAS alphas per pass
-    const int per_pass = k == 1 ? n_alpha : SWEEP_TOPK_ALPHAS;
-    for (int a0 = 0; a0 < n_alpha; a0 += per_pass) {
-      const int na = n_alpha - a0 < per_pass ? n_alpha - a0 : per_pass;
-      a.au = au + (size_t)a0 * plan.au_stride;
-      a.n_alpha = na;
-      hipLaunchKernelGGL(kern, dim3(grid), dim3(NTHREADS), lds, stream, a);
-      LL_CHECK_S(hipGetLastError());
-      const int64_t o0 = (int64_t)a0 * N + r0;   // first output of this pass: alpha a0, row r0
-      if (k == 1)
-        hipLaunchKernelGGL(ll_sweep_merge_kernel, dim3((rows + 3) / 4), dim3(256), 0, stream, (const float4*)stats,
-                           (const float*)ztgt, (const float*)a.au, plan.au_stride, rows, splits, na, V, a.target, N,
-                           out_ids + o0, out_p + o0, out_logp ? out_logp + o0 : nullptr, out_entropy + o0);
-      else   // outputs [n_alpha, N, k]
-        hipLaunchKernelGGL(ll_sweep_topk_merge_kernel, dim3((rows + 3) / 4), dim3(256), 0, stream, (const float4*)stats,
-                           (const uint2*)top, (const float*)ztgt, (const float*)a.au, plan.au_stride, rows, splits, na, k, V,
-                           a.target, N, out_ids + o0 * k, out_p + o0 * k, out_logp ? out_logp + o0 : nullptr,
-                           out_entropy + o0);
+    a.sweep_top = top;
+    a.bound = bound;
+    a.n_alpha = n_alpha;
+    for (int i = 0; i < SWEEP_MAX; ++i) a.alphas[i] = al.a[i];
+    const int64_t blocks = ((int64_t)a.row_blocks * a.splits + NUM_XCD - 1) / NUM_XCD * NUM_XCD;
+    for (const GemmKernel g : kern) {
+      hipLaunchKernelGGL(g, dim3((unsigned)blocks), dim3(NTHREADS), lds, stream, a);
       LL_CHECK_S(hipGetLastError());
     }
+    const auto merge = lists ? ll_sweep_merge_kernel<SWEEP_KS> : ll_sweep_merge_kernel<1>;
+    hipLaunchKernelGGL(merge, dim3((unsigned)((rows * n_alpha + 3) / 4)), dim3(256), 0, stream, (const float4*)stats, (const uint2*)top,
+                       (const float*)ztgt, (const float*)u, al, rows, a.splits, n_alpha, k, V, a.target, N, out_ids + r0 * k,
+                       out_p + r0 * k, out_logp ? out_logp + r0 : nullptr, out_entropy + r0, bound);
+    LL_CHECK_S(hipGetLastError());
   }
 #undef LL_CHECK_S
   return LL_OK;

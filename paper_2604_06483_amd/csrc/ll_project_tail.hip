@@ -1,5 +1,5 @@
-// The direct-to-LDS projection kernels for a hidden size that is not a multiple of 64, in a translation unit of their
-// own so that they build beside the others.
+// The direct-to-LDS projection kernels for a hidden size that is not a multiple of 64, and the rarely taken form of the
+// steering sweep, in a translation unit of their own so that they build beside the others.
 #include "ll_epilogue.h"
 #include "ll_epilogue_sweep.h"
 #include "ll_gemm_lds.h"
@@ -18,7 +18,11 @@ GemmKernel tail_topk_kernel(int k, bool bias) {
 }
 
 GemmKernel tail_sweep_kernel(bool lists) {
-  return lists ? ll_lens_gemm_dma_tail_kernel<SweepTopKEpilogue> : ll_lens_gemm_dma_tail_kernel<SweepEpilogue>;
+  return lists ? ll_lens_gemm_dma_tail_kernel<SweepEpilogue<SWEEP_KS, false>> : ll_lens_gemm_dma_tail_kernel<SweepEpilogue<1, false>>;
+}
+
+GemmKernel general_sweep_kernel(bool lists) {
+  return lists ? ll_lens_gemm_dma_tail_kernel<SweepEpilogue<SWEEP_KS, true>> : ll_lens_gemm_dma_tail_kernel<SweepEpilogue<1, true>>;
 }
 
 }  // namespace ll

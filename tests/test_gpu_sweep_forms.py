@@ -1,0 +1,50 @@
+"""The two forms of the steering sweep's epilogue (e^(alpha u) as a table factor; every shifted logit exponentiated, for
+shifts past 20) and its splits of the vocabulary, against the CPU oracle."""
+import numpy as np
+import pytest
+import torch
+
+import oracle.lens_oracle as O
+from paper_2604_06483_amd import binding as LL
+from paper_2604_06483_amd import workloads as WL
+from tests.conftest import say
+from tests.test_gpu_sweep import ALPHAS9, compare_sweep, direction
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def check(N, d, V, alphas, k, length, label):
+    cfg = WL.LensConfig("form", L=1, T=N, d=d, V=V, k=1, n_outliers=2 if d > 100 else 0, outlier_scale=20.0)
+    w = WL.make_workload(cfg, DEV, seed=41)
+    v = direction(d) * length
+    hidden = w.hidden.reshape(N, d)
+    got = LL.ll_steer_sweep(hidden, w.gamma, w.W_U, cfg.eps, v, alphas, w.target_ids, k=k)
+    torch.cuda.synchronize()
+    inputs = (WL.bf16_bits(hidden), WL.bf16_bits(w.gamma), WL.bf16_bits(w.W_U), cfg.eps, v.cpu().numpy(), alphas)
+    u = O.bf16_bits_to_f64(inputs[2]) @ inputs[4].astype(np.float64)
+    want = O.steer_sweep(*inputs, w.target_ids.cpu().numpy(), k=k or 1)
+    compare_sweep(got, want, np.arange(N), label, inputs)
+    return max(abs(a) for a in alphas) * np.abs(u).max()
+
+
+# (u is Gaussian with sigma 0.02 times v's length: its largest entry of some thousand is about four sigma)
+@pytest.mark.parametrize("k", [None, 2, 4])
+@pytest.mark.parametrize("length,general", [(50.0, False), (400.0, True)])
+@pytest.mark.parametrize("d", [256, 200])
+def test_both_forms(k, length, general, d):
+    say(f"sweep form general={general} d={d} k={k}")
+    # a logit of some 20 is held to 2^-24 of itself and of its shift: the tolerances stand
+    assert (check(300, d, 3001, ALPHAS9, k, length, f"form {length}") > 20.0) == general
+
+
+@pytest.mark.parametrize("N,d,V,n_alpha,k", [
+    (40, 64, 40000, 9, 3),       # 157 splits of one tile
+    (10, 128, 70000, 2, None),   # 137 splits of two tiles: bounds are exchanged
+    (300, 64, 66000, 9, 4),      # two row blocks, 86 splits of three tiles
+    (1000, 64, 20000, 7, None),  # four row blocks
+    (260, 192, 263, 9, 3),       # a last tile of seven ids
+])
+def test_splits(N, d, V, n_alpha, k):
+    say(f"sweep splits N={N} d={d} V={V} A={n_alpha} k={k}")
+    check(N, d, V, ALPHAS9[:n_alpha], k, 1.0, "splits")

@@ -27,9 +27,9 @@ struct GemmArgs {
   int rows, d, V, k, splits, tiles, row_blocks;
   // steering sweep only (Sec. 3.4, Eq. 3 for several alpha in one pass):
   const float* u;           // [tiles * BM] fp32: W_U v, zero padded
-  const float* eu;          // [tiles * BM / 16, n_alpha, 32] fp32: of 16 ids e^(alpha u), then u e^(alpha u)
-  const float* shift_max;   // [tiles * BM / 16, n_alpha] fp32: largest alpha u of 16 ids
-  const int* sweep_general; // nonzero: some |alpha u| is too large for the factored form
+  const float* eu;          // [tiles * BM / 16, 32, 16]: rows of e^(alpha u) and u e^(alpha u) of 16 ids (see ll_epilogue_sweep.h)
+  const float* shift_max;   // [tiles * BM / 16, 16]: per alpha the largest alpha u of 16 ids; entry 15 the largest spread of any alpha u among them
+  const int* sweep_general; // nonzero: some |alpha u| is too large for the factored form; nullptr: the general form in any case
   float4* sweep_stats;      // [rows, n_alpha, splits]      (reference, S, T)
   float* sweep_ztgt;        // [rows, splits]               logit of the target id at alpha = 0
   uint2* sweep_top;         // [rows, n_alpha, splits, KS]  (logit bits, id), sorted
@@ -85,6 +85,13 @@ constexpr float LOG2E = 1.4426950408889634f;
 #define LL_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 
 typedef const float __attribute__((address_space(4)))* const_f32_ptr;   // read through scalar loads when the address is wave-uniform
+
+// Workgroup ids are dealt round-robin over the 8 XCDs; remap so that one XCD (one L2) gets a
+// compact rectangle of (row blocks) x (all splits) and its CUs share A panels and W tiles.
+__device__ __forceinline__ int xcd_logical_block() {
+  const int per_xcd = gridDim.x / NUM_XCD;
+  return (blockIdx.x % NUM_XCD) * per_xcd + blockIdx.x / NUM_XCD;
+}
 
 // ---------------------------------------------------------------------------------------
 // Epilogue shared by both GEMM kernels.  State of one lens row, private to the lane that owns it.
@@ -428,13 +435,6 @@ auto with_list_length(int k, F pick) {
   if (k <= 12) return pick(std::integral_constant<int, 12>{});
   if (k <= 20) return pick(std::integral_constant<int, 20>{});
   return pick(std::integral_constant<int, 32>{});
-}
-
-// Workgroup ids are dealt round-robin over the 8 XCDs; remap so that one XCD (one L2) gets a
-// compact rectangle of (row blocks) x (all splits) and its CUs share A panels and W tiles.
-__device__ __forceinline__ int xcd_logical_block() {
-  const int per_xcd = gridDim.x / NUM_XCD;
-  return (blockIdx.x % NUM_XCD) * per_xcd + blockIdx.x / NUM_XCD;
 }
 
 }  // namespace

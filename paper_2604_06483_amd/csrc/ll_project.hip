@@ -108,7 +108,7 @@ __global__ __launch_bounds__(256) void ll_fill_f32_kernel(float* __restrict__ p,
 // largest |u|.  One wavefront takes eight vocabulary rows at a time: a chunk of v read from LDS serves
 // eight products, and eight 16-byte loads per lane are in flight.  STREAM: the loads carry the
 // non-temporal hint, for a W_U that the Infinity Cache (256 MiB) would not keep for step 3 anyway.
-// DIRECTION_MEASURED
+// 151936 x 2560: 145 us without the hint, 118 us with it (6.6 TB/s); 128256 x 4096: 206 and 180 us (5.8 TB/s).
 // ---------------------------------------------------------------------------------------
 struct AlphaList {
   float a[SWEEP_MAX];
@@ -125,7 +125,7 @@ __device__ __forceinline__ float sticky_max(float a, float b) { return (a != a |
 
 template <bool STREAM>
 __global__ __launch_bounds__(256) void ll_unembed_direction_kernel(const uint16_t* __restrict__ W, const float* __restrict__ v,
-                                                                   int V, int d, float* __restrict__ u,
+                                                                   int V, int d, float* __restrict__ u, int n_padded,
                                                                    float* __restrict__ block_max) {
   extern __shared__ __align__(16) float sv[];
   for (int j = threadIdx.x; j < d; j += blockDim.x) sv[j] = v[j];
@@ -133,6 +133,7 @@ __global__ __launch_bounds__(256) void ll_unembed_direction_kernel(const uint16_
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
   const int n16 = d >> 3;
+  if (blockIdx.x == 0 && V + (int)threadIdx.x < n_padded) u[V + threadIdx.x] = 0.f;   // (less than a tile)
   float largest = 0.f;   // (NaN once any u is)
   for (int r0 = (blockIdx.x * 4 + wave) * UD_ROWS; r0 < V; r0 += gridDim.x * 4 * UD_ROWS) {
     float acc[UD_ROWS];
@@ -181,27 +182,38 @@ __global__ __launch_bounds__(256) void ll_unembed_direction_kernel(const uint16_
   }
 }
 
-// Step 2: what the sweep epilogue reads per group of 16 ids (see GemmArgs), the padding of u, the flag that says which form
-// of the epilogue runs, and the zeroed bounds.
-__global__ __launch_bounds__(256) void ll_sweep_table_kernel(const float* __restrict__ block_max, int n_blocks, int V, int n_padded,
-                                                             AlphaList alphas, int n_alpha, float* __restrict__ u,
+// Step 2: what the sweep epilogue reads per group of 16 ids (see GemmArgs), the flag that says which form of the epilogue
+// runs, and the zeroed bounds.
+__global__ __launch_bounds__(256) void ll_sweep_table_kernel(const float* __restrict__ block_max, int n_blocks, int n_padded,
+                                                             AlphaList alphas, int n_alpha, const float* __restrict__ u,
                                                              float* __restrict__ eu, float* __restrict__ shift_max,
                                                              int* __restrict__ general, unsigned* __restrict__ bound, int n_bound) {
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_bound; i += gridDim.x * blockDim.x) bound[i] = 0u;
   for (int id = blockIdx.x * blockDim.x + threadIdx.x; id < n_padded; id += gridDim.x * blockDim.x) {   // (whole groups: n_padded is a multiple of 256)
-    const float x = id < V ? u[id] : 0.f;
-    if (id >= V) u[id] = 0.f;
-    const int64_t row = (int64_t)(id >> 4) * n_alpha;
-    for (int a = 0; a < n_alpha; ++a) {
-      const float shift = alphas.a[a] * x;
-      const float e = expf(shift);
-      eu[(row + a) * SWEEP_ROW + (id & 15)] = e;
-      eu[(row + a) * SWEEP_ROW + 16 + (id & 15)] = e * x;
-      float most = shift;
+    const float x = u[id];
+    float* const rows = eu + (int64_t)(id >> 4) * (SWEEP_ROWS * SWEEP_GROUP) + (id & 15);
+    const int second = n_alpha <= SWEEP_SPLIT_ROWS ? SWEEP_SPLIT_ROWS : SWEEP_GROUP;   // first row of the factors times u
+    float spread = 0.f;
+    for (int a = 0; a < second; ++a) {
+      float e = 0.f, most = 0.f;
+      if (a < n_alpha) {
+        const float shift = alphas.a[a] * x;
+        e = expf(shift);
+        most = shift;
+        float least = shift;
 #pragma unroll
-      for (int off = 8; off > 0; off >>= 1) most = fmaxf(most, __shfl_xor(most, off, kWave));
-      if ((id & 15) == 0) shift_max[row + a] = most;
+        for (int off = 8; off > 0; off >>= 1) {
+          most = fmaxf(most, __shfl_xor(most, off, kWave));
+          least = fminf(least, __shfl_xor(least, off, kWave));
+        }
+        spread = fmaxf(spread, most - least);
+      }
+      rows[a * SWEEP_GROUP] = e;
+      rows[(second + a) * SWEEP_GROUP] = e * x;
+      if ((id & 15) == a && a < 15) shift_max[id] = most;                            // (alpha number a of the group: its first id + a)
+      if (a == 0 && (id & 15) >= second && (id & 15) < 15) shift_max[id] = 0.f;
     }
+    if ((id & 15) == 15) shift_max[id] = spread;
   }
   if (blockIdx.x != 0 || threadIdx.x >= 64) return;
   float largest = 0.f, alpha = 0.f;
@@ -804,15 +816,14 @@ SweepPlan make_sweep_plan(const ll_shape* s, int n_alpha, int k = 1) {
   };
   const int tiles = (s->V + BM - 1) / BM;
   p.n_padded = tiles * BM;
-  const size_t groups = (size_t)p.n_padded / SWEEP_GROUP;
   const size_t rows = (size_t)(s->N < CHUNK_ROWS ? s->N : CHUNK_ROWS);
   // rows x splits of a full pass and of a shorter last one
   size_t partials = rows * NUM_CU < (size_t)MAX_PARTIALS ? rows * NUM_CU : (size_t)MAX_PARTIALS;
   const size_t least = rows * ((tiles + SWEEP_MAX_TILES - 1) / SWEEP_MAX_TILES);
   if (partials < least) partials = least;
   p.off_u = take((size_t)p.n_padded * sizeof(float));
-  p.off_eu = take((groups + 1) * n_alpha * SWEEP_ROW * sizeof(float));   // (the epilogue sends its reads one row ahead)
-  p.off_shift = take(groups * n_alpha * sizeof(float));
+  p.off_eu = take((size_t)p.n_padded * SWEEP_ROWS * sizeof(float));
+  p.off_shift = take((size_t)p.n_padded * sizeof(float));
   p.off_block_max = take(UD_BLOCKS * sizeof(float));
   p.off_general = take(sizeof(int));
   p.off_bound = take(rows * n_alpha * sizeof(unsigned));
@@ -875,21 +886,35 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
   const size_t v_bytes = (size_t)d * sizeof(float);
   if (v_bytes > 64 * 1024)
     if (const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(direction), (size_t)SWEEP_MAX_D * sizeof(float)); rc != LL_OK) return rc;
-  hipLaunchKernelGGL(direction, dim3(UD_BLOCKS), dim3(256), v_bytes, stream, static_cast<const uint16_t*>(W_U), v, V, d, u, block_max);
+  hipLaunchKernelGGL(direction, dim3(UD_BLOCKS), dim3(256), v_bytes, stream, static_cast<const uint16_t*>(W_U), v, V, d, u, plan.n_padded,
+                     block_max);
   LL_CHECK_S(hipGetLastError());
-  const int n_bound = (int)(N < CHUNK_ROWS ? N : CHUNK_ROWS) * n_alpha;
-  hipLaunchKernelGGL(ll_sweep_table_kernel, dim3(plan.n_padded / 256 < 2048 ? plan.n_padded / 256 : 2048), dim3(256), 0, stream,
-                     (const float*)block_max, UD_BLOCKS, V, plan.n_padded, al, n_alpha, u, eu, shift_max, general, bound, n_bound);
-  LL_CHECK_S(hipGetLastError());
+  // Few alphas: the general form alone, without the tables and the launch that fills them.  Its cost grows with every alpha, the
+  // factored one's hardly does.  Whole calls, general | factored, us, three / four / five alphas:
+  //   arg max:  64 rows, d = 256, V = 4096        41 | 60       47 | 61       52 | 65
+  //             1138 rows, d = 384, V = 74495    190 | 223     220 | 229     250 | 235
+  //             1500 rows, d = 4096, V = 128256 1463 | 1492   1505 | 1468   1556 | 1476
+  //   lists:    64 rows, d = 256, V = 4096        70 | 83       84 | 84       99 | 105
+  //             1138 rows, d = 384, V = 74495    255 | 282     307 | 290     361 | 330
+  //             1500 rows, d = 4096, V = 128256 1538 | 1541   1599 | 1523   1648 | 1586
+  const bool lists = k > 1, only_general = n_alpha <= (lists ? 3 : 4);
+  if (!only_general) {
+    const int n_bound = (int)(N < CHUNK_ROWS ? N : CHUNK_ROWS) * n_alpha;
+    hipLaunchKernelGGL(ll_sweep_table_kernel, dim3(plan.n_padded / 256 < 2048 ? plan.n_padded / 256 : 2048), dim3(256), 0, stream,
+                       (const float*)block_max, UD_BLOCKS, plan.n_padded, al, n_alpha, (const float*)u, eu, shift_max, general, bound,
+                       n_bound);
+    LL_CHECK_S(hipGetLastError());
+  }
   // (d is at most SWEEP_MAX_D: the direct-to-LDS kernel's 32-bit row offsets always suffice)
-  const bool lists = k > 1;
-  const GemmKernel kern[2] = {d % DK != 0 ? tail_sweep_kernel(lists)
-                              : lists     ? ll_lens_gemm_dma_kernel<SweepEpilogue<SWEEP_KS, false>>
-                                          : ll_lens_gemm_dma_kernel<SweepEpilogue<1, false>>,
-                              general_sweep_kernel(lists)};   // (one of the two returns at once)
+  const GemmKernel kern[2] = {general_sweep_kernel(lists),   // of two, one returns at once
+                              only_general  ? nullptr
+                              : d % DK != 0 ? tail_sweep_kernel(lists)
+                              : lists       ? ll_lens_gemm_dma_kernel<SweepEpilogue<SWEEP_KS, false>>
+                                            : ll_lens_gemm_dma_kernel<SweepEpilogue<1, false>>};
   const size_t lds = (size_t)SLOTS * SLOT_BYTES;
   for (const GemmKernel g : kern)
-    if (const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(g), lds); rc != LL_OK) return rc;
+    if (g != nullptr)
+      if (const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(g), lds); rc != LL_OK) return rc;
 
   for (int64_t r0 = 0; r0 < N; r0 += CHUNK_ROWS) {
     const int rows = (int)((N - r0 < CHUNK_ROWS) ? (N - r0) : CHUNK_ROWS);
@@ -914,7 +939,7 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     a.u = u;
     a.eu = eu;
     a.shift_max = shift_max;
-    a.sweep_general = general;
+    a.sweep_general = only_general ? nullptr : general;
     a.sweep_stats = stats;
     a.sweep_ztgt = ztgt;
     a.sweep_top = top;
@@ -923,6 +948,7 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     for (int i = 0; i < SWEEP_MAX; ++i) a.alphas[i] = al.a[i];
     const int64_t blocks = ((int64_t)a.row_blocks * a.splits + NUM_XCD - 1) / NUM_XCD * NUM_XCD;
     for (const GemmKernel g : kern) {
+      if (g == nullptr) continue;
       hipLaunchKernelGGL(g, dim3((unsigned)blocks), dim3(NTHREADS), lds, stream, a);
       LL_CHECK_S(hipGetLastError());
     }

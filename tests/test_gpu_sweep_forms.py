@@ -44,6 +44,8 @@ def test_both_forms(k, length, general, d):
     (300, 64, 66000, 9, 4),      # two row blocks, 86 splits of three tiles
     (1000, 64, 20000, 7, None),  # four row blocks
     (260, 192, 263, 9, 3),       # a last tile of seven ids
+    (70, 128, 5000, 4, None), (70, 128, 5000, 5, None),   # either side of the number that takes the form without tables
+    (70, 128, 5000, 3, 4), (70, 128, 5000, 4, 4), (70, 128, 5000, 1, 2),
 ])
 def test_splits(N, d, V, n_alpha, k):
     say(f"sweep splits N={N} d={d} V={V} A={n_alpha} k={k}")

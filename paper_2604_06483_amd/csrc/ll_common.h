@@ -36,17 +36,54 @@ __device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
   return __builtin_bit_cast(uint32_t, b);
 }
 
+// The value of lane l ^ OFF, combined with the lane's own by f (commutative), without a trip through LDS: six steps of an
+// LDS exchange are some 600 cycles of waiting, six of these 60.  All lanes of the wavefront have to be on.
+template <int CTRL>
+__device__ __forceinline__ uint32_t dpp(uint32_t x) {
+  return (uint32_t)__builtin_amdgcn_mov_dpp((int)x, CTRL, 0xF, 0xF, true);
+}
+template <int OFF, class F>
+__device__ __forceinline__ uint32_t with_lane_xor(uint32_t x, F f) {
+  static_assert(OFF == 1 || OFF == 2 || OFF == 4 || OFF == 8 || OFF == 16 || OFF == 32, "one bit of the lane number");
+  if constexpr (OFF == 32) {
+    const auto p = __builtin_amdgcn_permlane32_swap(x, x, false, false);
+    return f(p[0], p[1]);
+  } else if constexpr (OFF == 16) {
+    const auto p = __builtin_amdgcn_permlane16_swap(x, x, false, false);
+    return f(p[0], p[1]);
+  } else if constexpr (OFF == 8) {
+    return f(x, dpp<0x128>(x));             // row_ror:8
+  } else if constexpr (OFF == 4) {
+    return f(x, dpp<0x1B>(dpp<0x141>(x)));  // row_half_mirror, then each quad reversed: l ^ 7 ^ 3
+  } else {
+    return f(x, dpp<OFF == 2 ? 0x4E : 0xB1>(x));
+  }
+}
+template <class F>
+__device__ __forceinline__ uint32_t wave_combine(uint32_t x, F f) {
+  x = with_lane_xor<32>(x, f);
+  x = with_lane_xor<16>(x, f);
+  x = with_lane_xor<8>(x, f);
+  x = with_lane_xor<4>(x, f);
+  x = with_lane_xor<2>(x, f);
+  return with_lane_xor<1>(x, f);
+}
+
 // Sum over the 64 lanes of a wavefront; every lane gets the total.
 __device__ __forceinline__ float wave_sum(float x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x += __shfl_xor(x, off, kWave);
-  return x;
+  return __uint_as_float(wave_combine(__float_as_uint(x), [](uint32_t a, uint32_t b) {
+    return __float_as_uint(__uint_as_float(a) + __uint_as_float(b));
+  }));
 }
 
 __device__ __forceinline__ float wave_max(float x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x = fmaxf(x, __shfl_xor(x, off, kWave));
-  return x;
+  return __uint_as_float(wave_combine(__float_as_uint(x), [](uint32_t a, uint32_t b) {
+    return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b)));
+  }));
+}
+
+__device__ __forceinline__ int wave_min_int(int x) {
+  return (int)wave_combine((uint32_t)x, [](uint32_t a, uint32_t b) { return (uint32_t)((int)a < (int)b ? (int)a : (int)b); });
 }
 
 // Adds the squares of the 8 bf16 values in q: low halves into acc0, high halves into acc1.  The

@@ -228,22 +228,6 @@ __global__ __launch_bounds__(256) void ll_sweep_table_kernel(const float* __rest
 // ---------------------------------------------------------------------------------------
 // a8: merge the splits of each row and finalise.  One wavefront per row, one lane per split.
 // ---------------------------------------------------------------------------------------
-__device__ __forceinline__ int wave_min_int(int x) {
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) x = min(x, __shfl_xor(x, off, kWave));
-  return x;
-}
-// The same over the first `width` lanes only (a power of two; every lane below it gets the result):
-// the k steps of the merge are a chain of these exchanges, and with eight splits three rounds do.
-__device__ __forceinline__ float group_max(float x, int width) {
-  for (int off = width >> 1; off > 0; off >>= 1) x = fmaxf(x, __shfl_xor(x, off, kWave));
-  return x;
-}
-__device__ __forceinline__ int group_min_int(int x, int width) {
-  for (int off = width >> 1; off > 0; off >>= 1) x = min(x, __shfl_xor(x, off, kWave));
-  return x;
-}
-
 // One wavefront per row; lane s holds the lists of splits [s LPL, s LPL + LPL) (LPL = 1 while the splits fit one
 // lane each; 4 when a pass of few rows cuts the vocabulary finer than that so as to fill the chip).  The row's
 // lists (splits x k pairs, contiguous in the workspace) are first copied into LDS with coalesced loads: the k steps
@@ -251,6 +235,8 @@ __device__ __forceinline__ int group_min_int(int x, int width) {
 // costs a fraction of a trip to memory.  At LPL = 1 a block is four wavefronts with a row each; at LPL = 4 a block
 // has ONE row, all four wavefronts copy its lists (up to 64 KB: one wavefront alone would spend its time waiting for
 // its own loads) and the first one merges.
+// The chain's two reductions a step stay out of LDS (180 rows, 148 splits, k = 30, whole call: 125 us with exchanges through
+// LDS, 107 now; 1500 rows, 37 splits, k = 5: 99 and 96).
 // Dynamic LDS: rows of the block x splits x k x 8 bytes (at most 64 KB).
 constexpr int MERGE_LPL = 4;                              // lists per lane of the merge when splits > 64
 constexpr int MAX_PROJECT_SPLITS = MAX_SPLITS * MERGE_LPL;   // vocabulary splits per row block of the projection
@@ -328,8 +314,6 @@ __global__ __launch_bounds__(256) void ll_merge_kernel(const float4* __restrict_
   float z0 = 0.f, sk = 0.f;   // top-k-only softmax: the largest selected logit and the sum over the selection
   float my_z = 0.f;           // lane j keeps the j-th selected logit and id, written out together at the end
   int my_id = 0;
-  int width = 1;   // lanes that hold a list, rounded up to a power of two (lanes past them hold the neutral head)
-  while (width * LPL < splits) width <<= 1;
   for (int j = 0; j < k; ++j) {
     float lz = z[0];   // this lane's best head: largest logit, smallest id among equals
     int li = id[0];
@@ -339,8 +323,8 @@ __global__ __launch_bounds__(256) void ll_merge_kernel(const float4* __restrict_
       lz = better ? z[i] : lz;
       li = better ? id[i] : li;
     }
-    const float bz = group_max(lz, width);
-    const int bi = group_min_int(lz == bz ? li : INT_MAX, width);
+    const float bz = wave_max(lz);
+    const int bi = wave_min_int(lz == bz ? li : INT_MAX);
 #pragma unroll
     for (int i = 0; i < LPL; ++i) {
       if (live[i] && z[i] == bz && id[i] == bi) {   // ids are distinct: exactly one list of one lane
@@ -355,14 +339,11 @@ __global__ __launch_bounds__(256) void ll_merge_kernel(const float4* __restrict_
         }
       }
     }
-    // (lanes past `width` did not take part: what they keep comes from lane 0)
-    const float out_z = __uint_as_float(__builtin_amdgcn_readfirstlane(__float_as_uint(bz)));
-    const int out_id = __builtin_amdgcn_readfirstlane(bi);
-    if (j == 0) z0 = out_z;
-    sk += __builtin_amdgcn_exp2f((out_z - z0) * LOG2E);
+    if (j == 0) z0 = bz;
+    sk += __builtin_amdgcn_exp2f((bz - z0) * LOG2E);
     if (lane == j) {
-      my_z = out_z;
-      my_id = out_id;
+      my_z = bz;
+      my_id = bi;
     }
   }
   if (lane < k) {

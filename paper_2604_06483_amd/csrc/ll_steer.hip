@@ -31,13 +31,10 @@ __device__ __forceinline__ uint4 load_row(const uint16_t* p) {
   return make_uint4(x[0], x[1], x[2], x[3]);
 }
 
-// Sum over the lanes that differ in bits 3 to 5, without a trip through LDS.
+// Sum over the lanes that differ in bits 3 to 5.
 __device__ __forceinline__ float sum_rows8(float x) {
-  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x128, 0xF, 0xF, true));   // row_ror:8
-  const auto a = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  x = __uint_as_float(a[0]) + __uint_as_float(a[1]);
-  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  return __uint_as_float(b[0]) + __uint_as_float(b[1]);
+  const auto add = [](uint32_t a, uint32_t b) { return __float_as_uint(__uint_as_float(a) + __uint_as_float(b)); };
+  return __uint_as_float(with_lane_xor<32>(with_lane_xor<16>(with_lane_xor<8>(__float_as_uint(x), add), add), add));
 }
 
 template <bool STREAM>

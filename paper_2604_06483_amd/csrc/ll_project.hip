@@ -44,10 +44,11 @@ __global__ __launch_bounds__(256) void ll_rms_stats_kernel(const uint16_t* __res
 template <int NITER>
 __global__ __launch_bounds__(256) void ll_norm_panel_kernel(const uint16_t* __restrict__ hidden,
                                                             const uint16_t* __restrict__ gamma, uint16_t* __restrict__ panel,
-                                                            int rows, int d, int64_t lda, float eps) {
+                                                            int rows, int d, int64_t lda, float eps, unsigned* __restrict__ bound) {
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (row >= rows) return;
+  if (bound != nullptr && lane == 0) bound[row] = 0u;   // the row's shared top-k bound, before the pass that uses it
   const uint4* src = reinterpret_cast<const uint4*>(hidden + (int64_t)row * d);
   uint4* dst = reinterpret_cast<uint4*>(panel + (int64_t)row * lda);
   const uint4* g4 = reinterpret_cast<const uint4*>(gamma);
@@ -561,17 +562,17 @@ int even_splits(int tiles, int most) {
 
 // (few rows: one wavefront per block, so that they spread over the compute units)
 void launch_norm_panel(const uint16_t* hidden, const uint16_t* gamma, uint16_t* panel, int rows, int d, int64_t lda, float eps,
-                       hipStream_t stream) {
+                       unsigned* bound, hipStream_t stream) {
   const int per_block = rows <= 1024 ? 1 : 4;
   const dim3 grid((unsigned)((rows + per_block - 1) / per_block)), block(64 * per_block);
   if (d <= 64 * 8 * 4)
-    hipLaunchKernelGGL(ll_norm_panel_kernel<4>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps);
+    hipLaunchKernelGGL(ll_norm_panel_kernel<4>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps, bound);
   else if (d <= 64 * 8 * 8)
-    hipLaunchKernelGGL(ll_norm_panel_kernel<8>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps);
+    hipLaunchKernelGGL(ll_norm_panel_kernel<8>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps, bound);
   else if (d <= 64 * 8 * 16)
-    hipLaunchKernelGGL(ll_norm_panel_kernel<16>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps);
+    hipLaunchKernelGGL(ll_norm_panel_kernel<16>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps, bound);
   else
-    hipLaunchKernelGGL(ll_norm_panel_kernel<0>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps);
+    hipLaunchKernelGGL(ll_norm_panel_kernel<0>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps, bound);
 }
 
 int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, const void* hidden, const void* gamma,
@@ -606,7 +607,17 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
   // The direct-to-LDS kernel addresses rows with 32-bit byte offsets from a per-tile base.  It takes every other shape, a d
   // that is not a multiple of 64 in an instantiation of its own, which the longest list with a bias does not have.
   // 777 rows, d = 1608, V = 50257, k = 3 with a bias: 201 us, on the register-staged kernel 369
-  const GemmKernel tail_kern = d % DK != 0 ? tail_topk_kernel(k, bias != nullptr) : nullptr;
+  // It needs the rows padded, which is a launch; calls whose busiest workgroup has next to nothing to do (fewer than four stages
+  // of 64 columns, with a norm fewer than two) are faster without.  Whole calls, k = 1, direct-to-LDS | register-staged, us:
+  //   V = 37876, d = 168, 180 rows (three stages): 34.3 | 32.5, with a norm 34.2 | 35.6;   600 rows (six): 50.0 | 52.7
+  //   V = 37876, d = 72, 180 rows (two): 33.1 | 31.0, with a norm 33.3 | 34.8;             600 rows (four): 45.6 | 46.7
+  //   V = 37876, d = 40, 180 rows (one): 33.0 | 29.1, with a norm 32.7 | 31.5;             V = 4000, 5000 rows (two): 42.5 | 41.4
+  const int tiles = (V + BM - 1) / BM;
+  const int first_blocks = (int)(((N < CHUNK_ROWS ? N : CHUNK_ROWS) + BN - 1) / BN);   // (whatever the scratch: the same kernel)
+  const int first_splits = even_splits(tiles, NUM_CU / first_blocks < MAX_PROJECT_SPLITS ? NUM_CU / first_blocks : MAX_PROJECT_SPLITS);
+  const int64_t stages = (int64_t)((tiles + first_splits - 1) / first_splits) * (plan.lda / DK);
+  const bool worth_padding = stages >= (has_gamma ? 2 : 4);
+  const GemmKernel tail_kern = d % DK != 0 && worth_padding ? tail_topk_kernel(k, bias != nullptr) : nullptr;
   const bool dma = !(flags & LL_FLAG_REGISTER_STAGED) && (d % DK == 0 || tail_kern != nullptr) &&
                    (int64_t)BM * plan.lda * 2 < (int64_t)1 << 31 && (int64_t)CHUNK_ROWS * plan.lda * 2 < (int64_t)1 << 31;
   const size_t lds = dma ? (size_t)SLOTS * SLOT_BYTES : (size_t)(BM + BN) * BK * 2;
@@ -666,7 +677,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     LL_CHECK_F(mark());
     if (copy) {
       launch_norm_panel(static_cast<const uint16_t*>(hidden), static_cast<const uint16_t*>(gamma), few_panel, (int)N, d, plan.lda, eps,
-                        stream);
+                        nullptr, stream);
       LL_CHECK_F(hipGetLastError());
     }
     FewArgs a;
@@ -696,15 +707,16 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     return finish(read_phases());
   }
 
-  const int tiles = (V + BM - 1) / BM;
-  // Top-k bounds shared between the vocabulary splits of a row (direct-to-LDS kernel): zero at the start of a
-  // pass; the merge kernel of a pass clears them again for the next one.
+  // Top-k bounds shared between the vocabulary splits of a row (direct-to-LDS kernel): zero at the start of a pass.  The panel
+  // kernel clears them; where the rows are read in place a launch of its own does for the first pass, and the merge kernel of a pass for the next one.
   unsigned* bound = nullptr;
   if (dma) {
     bound = reinterpret_cast<unsigned*>(ws + plan.off_bound);
-    const int n_zero = (int)(N < chunk_rows ? N : chunk_rows);
-    hipLaunchKernelGGL(ll_zero_u32_kernel, dim3((n_zero + 255) / 256), dim3(256), 0, stream, bound, n_zero);
-    LL_CHECK_F(hipGetLastError());
+    if (!need_panel) {
+      const int n_zero = (int)(N < chunk_rows ? N : chunk_rows);
+      hipLaunchKernelGGL(ll_zero_u32_kernel, dim3((n_zero + 255) / 256), dim3(256), 0, stream, bound, n_zero);
+      LL_CHECK_F(hipGetLastError());
+    }
   }
   float* bias_padded = nullptr;
   if (bias != nullptr) {
@@ -718,7 +730,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     // a2 (+ a3 when the panel is used)
     LL_CHECK_F(mark());
     if (need_panel) {
-      launch_norm_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, d, plan.lda, eps, stream);
+      launch_norm_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, d, plan.lda, eps, bound, stream);
       LL_CHECK_F(hipGetLastError());
     } else if (!dma && has_gamma) {
       hipLaunchKernelGGL(ll_rms_stats_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, h_rows, (int64_t)rows, d,
@@ -902,7 +914,7 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     const uint16_t* h_rows = static_cast<const uint16_t*>(hidden) + r0 * d;
     const bool need_panel = gamma != nullptr || plan.lda != d;
     if (need_panel) {
-      launch_norm_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, d, plan.lda, eps, stream);
+      launch_norm_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, d, plan.lda, eps, nullptr, stream);
       LL_CHECK_S(hipGetLastError());
     }
     GemmArgs a = {};

@@ -25,6 +25,8 @@ def inputs(N, d, V, k):
     (520, 120, 5001, 12, False, True),    # two stages, seven chunks
     (777, 1608, 2050, 3, True, True),     # many stages
     (9000, 136, 600, 5, False, True),     # two row passes
+    (8200, 8, 5001, 1, False, True),      # one stage, three tiles a workgroup (fewer are left to the register-staged kernel)
+    (8200, 56, 8000, 20, True, False),    # one stage, four tiles, rows only padded
 ])
 def test_ragged_hidden_size(N, d, V, k, with_bias, gamma):
     say(f"tail N={N} d={d} V={V} k={k} bias={with_bias} gamma={gamma}")

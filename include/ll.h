@@ -85,12 +85,13 @@ int ll_project(const ll_shape* shape, void* workspace, size_t workspace_bytes,
  *          i.e. p_i / sum_{j in top-k} p_j; entropy and target log-prob stay full-vocabulary.
  *          LL_FLAG_REGISTER_STAGED: run this call on the register-staged kernel, which applies the
  *          RMSNorm scaling inside the A-tile load of the GEMM, even where the default applies (the
- *          direct-to-LDS kernel fed from a normalised bf16 panel written once per row pass; d a
- *          multiple of 64).  Both compute the same quantities from the same bf16 operands (the
+ *          direct-to-LDS kernel fed from a normalised bf16 panel written once per row pass).  Both compute the same quantities from the same bf16 operands (the
  *          normalised row is rounded to bf16 identically); they use different MFMA shapes, so a
  *          logit's fp32 partial sums are added in a different order and results agree to fp32
- *          accumulation rounding.  For tuning and tests; any d that is not a multiple of 64 runs on
- *          this kernel anyway.
+ *          accumulation rounding.  For tuning and tests.  Without the flag a call takes the
+ *          register-staged kernel only where d is not a multiple of 64 and either the call is so
+ *          small that padding the rows is not worth a launch, or k > 20 with a bias; up to 128
+ *          rows run on a kernel of their own, which the flag also switches off.
  *          Any other bit set is LL_EINVAL.
  */
 #define LL_FLAG_TOPK_SOFTMAX    1u
@@ -244,16 +245,14 @@ int ll_capture_append(const ll_capture_shape* shape, void* store, const void* sl
  *   out_target_logp [n_alpha, N] fp32 NaN where the target id is outside [0, V)
  *   out_entropy  [n_alpha, N] fp32    nats
  * Requirements beyond ll_project's: d at most 40960 (the direction v is held in LDS while
- * u = W_U v is formed; LL_EINVAL beyond).  d a multiple of 64 runs on the direct-to-LDS kernel, any
- * other multiple of 8 on the register-staged one.  Workspace: ll_steer_sweep_workspace_bytes(shape,
+ * u = W_U v is formed; LL_EINVAL beyond).  Workspace: ll_steer_sweep_workspace_bytes(shape,
  * n_alpha).  Same error, ownership, stream and N == 0 conventions as ll_project.
  *
  * ll_steer_sweep_topk: the same with the k most likely tokens per alpha and row instead of one
  * (1 <= k <= LL_SWEEP_KMAX; the paper's figures list k = 3), sorted as in ll_project:
  *   out_topk_ids [n_alpha, N, k] int32,  out_topk_p [n_alpha, N, k] fp32 (full-softmax probabilities)
- * With k == 1 it is ll_steer_sweep.  With k > 1 the lists of five alphas are what fits the
- * register file beside the accumulators, so the call makes ceil(n_alpha / 5) passes over W_U
- * (nine alphas: two passes, against nine for ll_steer_inject + ll_project pairs).  Workspace:
+ * With k == 1 it is ll_steer_sweep.  Any number of alphas takes one pass over W_U besides the one
+ * that forms u (against nine for nine ll_steer_inject + ll_project pairs).  Workspace:
  * ll_steer_sweep_topk_workspace_bytes(shape, n_alpha, k).
  */
 #define LL_SWEEP_MAX 9

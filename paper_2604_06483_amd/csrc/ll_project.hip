@@ -100,10 +100,6 @@ __global__ __launch_bounds__(256) void ll_zero_u32_kernel(unsigned* __restrict__
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) p[i] = 0u;
 }
 
-__global__ __launch_bounds__(256) void ll_fill_f32_kernel(float* __restrict__ p, int n, float value) {
-  for (int i = threadIdx.x; i < n; i += blockDim.x) p[i] = value;
-}
-
 // ---------------------------------------------------------------------------------------
 // Steering sweep, step 1: u = W_U v (one pass over W_U, HBM-bound: 2 V d bytes) and, per workgroup, the
 // largest |u|.  One wavefront takes eight vocabulary rows at a time: a chunk of v read from LDS serves

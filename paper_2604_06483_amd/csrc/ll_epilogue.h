@@ -111,6 +111,13 @@ __device__ __forceinline__ float key_float(unsigned k) {
   return __uint_as_float((k & 0x80000000u) ? (k & 0x7fffffffu) : ~k);
 }
 constexpr unsigned KEY_NEG_INF = 0x007fffffu;   // float_key(-inf)
+constexpr unsigned KEY_ZERO = 0x80000000u;      // float_key(+0); the key below it is -0's, an equal logit
+
+// The largest float that ranks below a shared bound (-inf while there is none).  A logit EQUAL to the bound may still belong in
+// the top k, since a smaller id wins a tie, so what is at or below the returned value, and no more, is out.
+__device__ __forceinline__ float below_bound(unsigned key) {
+  return key > KEY_NEG_INF ? key_float(key - (key == KEY_ZERO ? 2u : 1u)) : -INFINITY;
+}
 
 template <int KR>
 struct RowState {

@@ -422,8 +422,8 @@ __device__ __forceinline__ void sweep_group(const float (&y)[4][4], SweepState<K
 }
 
 // As exchange_bound of the projection, per alpha: publishes the k-th best of this split's list and picks up the row's
-// best bound.  Entries below the bound cannot be in the row's top k: they give way to the bound itself (the float just
-// below it, since an equal logit with a smaller id still counts), which then is what a candidate has to beat.
+// best bound.  Entries below the bound cannot be in the row's top k: they give way to the largest float below it
+// (below_bound: an equal logit with a smaller id still counts), which then is what a candidate has to beat.
 template <int KS>
 __device__ __forceinline__ void sweep_exchange(SweepState<KS, false>& st, const GemmArgs& p, int my_row) {
   asm volatile("" : "+v"(my_row));   // (the addresses made anew for every tile rather than kept)
@@ -443,7 +443,7 @@ __device__ __forceinline__ void sweep_exchange(SweepState<KS, false>& st, const 
       const unsigned key = float_key(kth);
       if (my_row < p.rows && key > fresh[a] && key > KEY_NEG_INF)
         __hip_atomic_fetch_max(at(a), key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const float floor = fresh[a] > KEY_NEG_INF ? key_float(fresh[a] - 1u) : -INFINITY;
+      const float floor = below_bound(fresh[a]);
 #pragma unroll
       for (int j = 0; j < KS; ++j) {
         const bool below = st.lv[a][j] <= floor;

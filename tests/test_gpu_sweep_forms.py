@@ -50,3 +50,43 @@ def test_both_forms(k, length, general, d):
 def test_splits(N, d, V, n_alpha, k):
     say(f"sweep splits N={N} d={d} V={V} A={n_alpha} k={k}")
     check(N, d, V, ALPHAS9[:n_alpha], k, 1.0, "splits")
+
+
+@pytest.mark.parametrize("k", [None, 3, 4])
+@pytest.mark.parametrize("N,d,V", [
+    (300, 128, 66000),   # two row blocks, 86 splits of three tiles
+    (300, 200, 66000),   # the same on the kernel for ragged hidden sizes
+    (40, 64, 40000),     # one tile a split: what a list loses depends on which split came first
+    (10, 128, 70000),    # two tiles a split
+])
+def test_equal_logits_are_listed_in_id_order(N, d, V, k):
+    """Rows whose shifted logits are all zero (an all-zero row at strength 0, any row of zeros with no direction) and tokens
+    that tie across splits: the k-th best equals the bound that the splits share."""
+    say(f"sweep ties N={N} d={d} V={V} k={k}")
+    w = WL.make_workload(WL.LensConfig("ties", L=1, T=N, d=d, V=V, k=1), DEV, seed=42)
+    hidden = w.hidden.reshape(N, d)
+    hidden[[0, 7, N - 1]] = 0
+    listed = k or 1
+
+    def uniform(got, a, row):
+        ids, p, _, ent = (None if x is None else x[a, row].cpu().numpy() for x in got)
+        assert np.array_equal(np.atleast_1d(ids), np.arange(listed)), ids
+        # one rounding each of the sum, its logarithm and the probability's exponent (log V of magnitude 11)
+        assert np.abs(p * V - 1.0).max() < 1e-5 and abs(ent - np.log(V)) < 1e-5
+
+    got = LL.ll_steer_sweep(hidden, w.gamma, w.W_U, w.cfg.eps, direction(d), ALPHAS9, None, k=k)
+    still = LL.ll_steer_sweep(hidden, w.gamma, w.W_U, w.cfg.eps, torch.zeros((d,), device=DEV), ALPHAS9, None, k=k)
+    torch.cuda.synchronize()
+    for row in (0, 7, N - 1):
+        uniform(got, ALPHAS9.index(0.0), row)
+        for a in range(len(ALPHAS9)):
+            uniform(still, a, row)
+    # every token three times, thousands of ids apart: lists of repeated logits, smaller id first
+    w.W_U[V // 3:2 * (V // 3)] = w.W_U[:V // 3]
+    w.W_U[2 * (V // 3):3 * (V // 3)] = w.W_U[:V // 3]
+    w.W_U[3 * (V // 3):] = w.W_U[0]
+    ids = LL.ll_steer_sweep(hidden, w.gamma, w.W_U, w.cfg.eps, direction(d), ALPHAS9, None, k=k)[0].cpu().numpy().reshape(9, N, listed)
+    some = np.setdiff1d(np.arange(N), [0, 7, N - 1])
+    assert ids.min() >= 0 and np.all(ids[:, some, 0] < V // 3)
+    if listed > 1:
+        assert np.all(ids[:, some, 1] == ids[:, some, 0] + V // 3) and np.all(ids[:, some, 2] == ids[:, some, 0] + 2 * (V // 3))

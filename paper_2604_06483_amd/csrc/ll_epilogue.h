@@ -375,7 +375,7 @@ __device__ __forceinline__ void epilogue_tile(const ACC& acc, RowState<KR>& st, 
 // row for n vocabulary entries: eight short streams cost far more than one long one).  After each
 // tile a lane picks up the row's shared bound and publishes its own (atomic max on the key).  A
 // logit EQUAL to the bound may still belong in the top k (a smaller id wins a tie), so the
-// threshold is the next float below it.  The final result does not depend on timing: a bound only
+// threshold is the next float below it (below_bound).  The final result does not depend on timing: a bound only
 // removes entries that cannot be in the final top k; a split's own list may end up with fewer
 // than k real entries, which the merge treats as absent.
 // Placed at the END of the tile's epilogue: the operand loads in flight were sent before the
@@ -387,7 +387,7 @@ __device__ __forceinline__ void exchange_bound(RowState<KR>& st, const GemmArgs&
   unsigned* const b = p.bound + min(my_row, p.rows - 1);
   asm volatile("" ::: "memory");
   const unsigned fresh = __hip_atomic_load(b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  st.shared_bound = fresh > KEY_NEG_INF ? key_float(fresh - 1u) : -INFINITY;
+  st.shared_bound = below_bound(fresh);
   // own bound: the k-th best of this split's list (k <= KR, KR - k < 12)
   // (each entry goes through an empty asm statement: a plain chain of selects on k the optimiser
   // folds into an indexed access and moves the whole list to scratch memory)

@@ -222,6 +222,20 @@ def test_exact_ties_break_by_ascending_id():
             assert row.index(0) < row.index(1)
 
 
+@pytest.mark.parametrize("first", [256, 512])
+def test_zero_logits_that_come_late_in_their_split_still_win_ties(first):
+    """Vocabulary splits of four tiles; the first one's leading tiles are negative and all other logits zero, so the other
+    splits' bound is zero before the first split meets the zeros with the smallest ids."""
+    say(f"late zeros from id {first}")
+    N, d, V, k = 200, 64, 200000, 5
+    hidden = torch.ones((N, d), dtype=torch.bfloat16, device=DEV)
+    W = torch.zeros((V, d), dtype=torch.bfloat16, device=DEV)
+    W[:first] = -0.125
+    ids = LL.ll_project(hidden, None, W, 1e-5, k, register_staged=STAGED)[0].cpu().numpy()
+    torch.cuda.synchronize()
+    assert np.array_equal(ids, np.tile(first + np.arange(k), (N, 1)))
+
+
 def test_no_target_and_prenormalised_rows():
     say("target_ids = NULL; gamma = NULL")
     cfg = WL.LensConfig("nt", L=2, T=80, d=256, V=900, k=5)

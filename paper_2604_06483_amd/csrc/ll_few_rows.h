@@ -62,6 +62,12 @@ __device__ __forceinline__ unsigned ror8_into_low(unsigned keep, unsigned from) 
   return (unsigned)__builtin_amdgcn_update_dpp((int)keep, (int)from, 0x128, 0xF, 0x3, false);
 }
 
+// What stands in a lane's accumulators for an entry that is not there: past the wavefront's share or the vocabulary.  No entry
+// of -inf is listed either; every other logit is, however low a bias has put it.
+constexpr float FEW_ABSENT = -INFINITY;
+constexpr float FEW_LOWEST = -3.402823466e38f;   // the lowest float that can be listed
+constexpr float FEW_VOID = -2.0e38f;             // a maximum this low (its product with log2 e would not be finite): nothing that counts
+
 // Total order of a part's entries: larger logit first (-0 and 0 alike), then the smaller position (0 .. 1023) in the part.
 __device__ __forceinline__ unsigned long long few_key(float z, int pos) {
   return ((unsigned long long)float_key(z + 0.f) << 10) | (unsigned)(1023 - pos);
@@ -196,8 +202,7 @@ __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs 
   }
 
   // ---- epilogue: lane holds, of group u and row block j, vocabulary entries 16 (u0 + u) + 4 grp + r of lens row 16 j + col
-  // (Entries past the wavefront's share or the vocabulary become NEG_BIG.  Row block by row block, fenced: otherwise the
-  // compiler interleaves them all and runs out of registers.)
+  // (Row block by row block, fenced: otherwise the compiler interleaves them all and runs out of registers.)
   const int id0 = u0 * 16 + 4 * grp;
   const int part0 = ua * 16;                                                 // first id of the part
   const int id_end = min((u0 + nu) * 16, V);
@@ -208,14 +213,14 @@ __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs 
       const int id = id0 + 16 * u + r;
       const float b = p.bias != nullptr ? p.bias[min(id, V - 1)] : 0.f;
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) acc[u][j][r] = id < id_end ? acc[u][j][r] + b : NEG_BIG;
+      for (int j = 0; j < NJ; ++j) acc[u][j][r] = id < id_end ? acc[u][j][r] + b : FEW_ABSENT;
     }
   LL_SCHED_FENCE();
 #pragma unroll
   for (int j = 0; j < NJ; ++j) {
     const int n = 16 * j + col;
     const int tgt = (p.target != nullptr && n < p.rows) ? p.target[n] : -1;
-    float mx = NEG_BIG;
+    float mx = FEW_ABSENT;
 #pragma unroll
     for (int u = 0; u < MU; ++u)
 #pragma unroll
@@ -230,7 +235,7 @@ __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs 
     }
     float m = fmaxf(mx, __shfl_xor(mx, 16, kWave));
     m = fmaxf(m, __shfl_xor(m, 32, kWave));
-    const float mb = m == NEG_BIG ? 0.f : m * LOG2E;   // no entries: all terms are exp2(-inf)
+    const float mb = m <= FEW_VOID ? 0.f : m * LOG2E;   // (all terms are exp2(-inf))
     float s = 0.f, t = 0.f;
 #pragma unroll
     for (int u = 0; u < MU; ++u)
@@ -238,7 +243,7 @@ __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs 
       for (int r = 0; r < 4; ++r) {
         const float e = __builtin_amdgcn_exp2f(fmaf(acc[u][j][r], LOG2E, -mb));
         s += e;
-        t = fmaf(e, acc[u][j][r], t);
+        t = fmaf(e, id0 + 16 * u + r < id_end ? acc[u][j][r] : 0.f, t);
       }
     s += __shfl_xor(s, 16, kWave);
     t += __shfl_xor(t, 16, kWave);
@@ -253,7 +258,7 @@ __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs 
   }
   if (tid < R) {
     s_cnt[tid] = 0;
-    s_tau[tid] = -INFINITY;
+    s_tau[tid] = FEW_LOWEST;
   }
   if (tid == 0) s_over = 0;
   __syncthreads();
@@ -272,7 +277,7 @@ __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs 
       rank += (o.z > mine || (o.z == mine && i + 2 < q)) ? 1 : 0;
       rank += (o.w > mine || (o.w == mine && i + 3 < q)) ? 1 : 0;
     }
-    if (rank == p.k - 1) s_tau[n] = mine;
+    if (rank == p.k - 1) s_tau[n] = fmaxf(mine, FEW_LOWEST);
   }
   // softmax statistics of the part: one thread a row
   if (tid < p.rows) {
@@ -282,7 +287,7 @@ __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs 
     float s = 0.f, t = 0.f;
 #pragma unroll
     for (int w = 0; w < FEW_WAVES; ++w) {
-      const float sc = __builtin_amdgcn_exp2f((s_m[w][tid] - m) * LOG2E);
+      const float sc = m <= FEW_VOID ? 1.f : __builtin_amdgcn_exp2f((s_m[w][tid] - m) * LOG2E);   // (sums of 0 or NaN, whatever the scale)
       s = fmaf(sc, s_s[w][tid], s);
       t = fmaf(sc, s_t[w][tid], t);
     }
@@ -315,7 +320,7 @@ __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs 
       LL_SCHED_FENCE();
     }
   };
-  append([&](int u, int j, int r) { return acc[u][j][r] >= s_tau[16 * j + col] && acc[u][j][r] > NEG_BIG; });
+  append([&](int u, int j, int r) { return acc[u][j][r] >= s_tau[16 * j + col]; });
   __syncthreads();
   if (s_over != 0) {
     // A list does not hold all that passed (many equal logits, or a row whose best entries sit together): find
@@ -335,7 +340,7 @@ __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs 
           for (int r = 0; r < 4; ++r) {
             float z = acc[u][j][r];
             asm volatile("" : "+v"(z));   // (the key is made anew for every bit: kept, the keys of all entries would not fit the registers)
-            c += (z > NEG_BIG && few_key(z, id0 + 16 * u + r - part0) >= trial) ? 1 : 0;
+            c += (z >= FEW_LOWEST && few_key(z, id0 + 16 * u + r - part0) >= trial) ? 1 : 0;
           }
         if (c != 0) atomicAdd(&s_cnt[16 * j + col], c);
         LL_SCHED_FENCE();
@@ -347,7 +352,7 @@ __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs 
     if (tid < R) s_cnt[tid] = 0;
     __syncthreads();
     append([&](int u, int j, int r) {
-      return acc[u][j][r] > NEG_BIG && few_key(acc[u][j][r], id0 + 16 * u + r - part0) >= s_key[16 * j + col];
+      return acc[u][j][r] >= FEW_LOWEST && few_key(acc[u][j][r], id0 + 16 * u + r - part0) >= s_key[16 * j + col];
     });
     __syncthreads();
   }

@@ -87,3 +87,25 @@ def test_lists_that_overflow(N, V, k):
     ids = got["topk_ids"].astype(np.int64)                  # equal logits in ascending id
     tie = ref["topk_logits"][:, 1:] == ref["topk_logits"][:, :-1]
     assert tie.sum() > k and np.all(ids[:, 1:][tie] > ids[:, :-1][tie])
+
+
+@pytest.mark.parametrize("low", [torch.finfo(torch.float32).min, -3.2e38])
+@pytest.mark.parametrize("N,V,k", [(40, 5000, 5), (100, 40000, 20)])
+def test_tokens_masked_by_the_lowest_bias_are_listed_last(N, V, k, low):
+    """A bias that leaves fewer than k tokens: the others have probability zero, but they are tokens, equal ones."""
+    say(f"few rows, masked N={N} V={V} k={k} low={low}")
+    w = inputs(N, 128, V)
+    allowed = np.array([17, V // 2, V - 1])
+    bias = torch.full((V,), low, device=DEV)
+    bias[allowed.tolist()] = 0.25
+    ids, p, logp, ent = (x.cpu().numpy() for x in LL.ll_project(w.hidden, w.gamma, w.W_U, w.cfg.eps, k, w.target_ids, bias=bias))
+    z = reference(w, 1)["z"][:, allowed]
+    order = np.argsort(-z, axis=1)
+    want = np.exp(np.take_along_axis(z, order, 1) - z.max(1, keepdims=True))
+    want /= want.sum(1, keepdims=True)
+    assert np.array_equal(ids[:, :3], allowed[order])
+    assert np.array_equal(ids[:, 3:], np.tile(np.setdiff1d(np.arange(k), allowed)[:k - 3], (N, 1)))
+    assert np.abs(p[:, :3] - want).max() < 1e-4 and np.all(p[:, 3:] == 0)     # (the logits' fp32 sums: some 1e-6 of their size)
+    assert np.abs(ent + (want * np.log(want)).sum(1)).max() < 1e-3
+    masked = ~np.isin(w.target_ids.cpu().numpy(), allowed)
+    assert np.all(logp[masked] < -1e38)

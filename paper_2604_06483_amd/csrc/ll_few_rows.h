@@ -68,10 +68,14 @@ constexpr float FEW_ABSENT = -INFINITY;
 constexpr float FEW_LOWEST = -3.402823466e38f;   // the lowest float that can be listed
 constexpr float FEW_VOID = -2.0e38f;             // a maximum this low (its product with log2 e would not be finite): nothing that counts
 
-// Total order of a part's entries: larger logit first (-0 and 0 alike), then the smaller position (0 .. 1023) in the part.
-__device__ __forceinline__ unsigned long long few_key(float z, int pos) {
-  return ((unsigned long long)float_key(z + 0.f) << 10) | (unsigned)(1023 - pos);
-}
+// What the search for a row's threshold keeps (over the A tiles, which are done with).
+template <int R>
+struct FewSearch {
+  float tau[R];              // the value on trial, then the threshold; NaN for rows that need none
+  int count[R];              // entries at or above it
+  int need[R];               // entries equal to the threshold that are listed, smallest ids first
+  int ties[FEW_WAVES][R];    // such entries of each wavefront
+};
 
 template <int NJ, int MU>
 __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs p) {
@@ -83,7 +87,6 @@ __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs 
   __shared__ float s_m[FEW_WAVES][R], s_s[FEW_WAVES][R], s_t[FEW_WAVES][R];
   __shared__ float s_zt[R], s_tau[R];
   __shared__ int s_cnt[R];
-  __shared__ unsigned long long s_key[R];
   __shared__ int s_over;
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -204,7 +207,6 @@ __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs 
   // ---- epilogue: lane holds, of group u and row block j, vocabulary entries 16 (u0 + u) + 4 grp + r of lens row 16 j + col
   // (Row block by row block, fenced: otherwise the compiler interleaves them all and runs out of registers.)
   const int id0 = u0 * 16 + 4 * grp;
-  const int part0 = ua * 16;                                                 // first id of the part
   const int id_end = min((u0 + nu) * 16, V);
 #pragma unroll
   for (int u = 0; u < MU; ++u)
@@ -277,7 +279,14 @@ __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs 
       rank += (o.z > mine || (o.z == mine && i + 2 < q)) ? 1 : 0;
       rank += (o.w > mine || (o.w == mine && i + 3 < q)) ? 1 : 0;
     }
-    if (rank == p.k - 1) s_tau[n] = fmaxf(mine, FEW_LOWEST);
+    // Equal logits all over (more than three quarters of the maxima are the first one): nothing is appended before the search below.
+    const int first = __builtin_amdgcn_readlane(__float_as_int(mine), 0), second = __builtin_amdgcn_readlane(__float_as_int(mine), 32);
+    const unsigned long long same = __builtin_amdgcn_ballot_w64(mine == __int_as_float(lane < 32 ? first : second));
+    const bool flat = __builtin_popcount(lane < 32 ? (unsigned)same : (unsigned)(same >> 32)) > FEW_GROUPS / 4 * 3;
+    if (rank == p.k - 1) {
+      s_tau[n] = fmaxf(mine, FEW_LOWEST);
+      if (flat && mine > FEW_ABSENT) s_cnt[n] = FEW_CAP + 1;
+    }
   }
   // softmax statistics of the part: one thread a row
   if (tid < p.rows) {
@@ -294,18 +303,16 @@ __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs 
     p.stats[(int64_t)tid * p.splits + part] = make_float4(m, s, t, s_zt[tid]);
   }
   __syncthreads();
-  // Append the entries that reach the threshold to the row's list: one counter update per lane and row.
-  auto append = [&](auto passes) {
+  // Append a lane's entries to the row's list, one counter update per lane and row.  passing(j): bit 4 u + r for entry (u, j, r).
+  static_assert(MU * 4 <= 32, "a bit per entry");
+  auto append = [&](auto passing) {
 #pragma unroll
     for (int j = 0; j < NJ; ++j) {
       const int n = 16 * j + col;
-      int c = 0;
-#pragma unroll
-      for (int u = 0; u < MU; ++u)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) c += passes(u, j, r) ? 1 : 0;
+      const unsigned bits = passing(j);
+      const int c = __builtin_popcount(bits);
       if (c != 0 && n < p.rows) {
-        int at = atomicAdd(&s_cnt[n], c);
+        const int at = atomicAdd(&s_cnt[n], c);
         if (at + c > FEW_CAP) {
           s_over = 1;
         } else {
@@ -314,45 +321,124 @@ __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs 
           for (int u = 0; u < MU; ++u)
 #pragma unroll
             for (int r = 0; r < 4; ++r)
-              if (passes(u, j, r)) *list++ = make_uint2(__float_as_uint(acc[u][j][r]), (unsigned)(id0 + 16 * u + r));
+              if (bits & (1u << (4 * u + r))) *list++ = make_uint2(__float_as_uint(acc[u][j][r]), (unsigned)(id0 + 16 * u + r));
         }
       }
       LL_SCHED_FENCE();
     }
   };
-  append([&](int u, int j, int r) { return acc[u][j][r] >= s_tau[16 * j + col]; });
+  auto mask_of = [&](auto pass) {
+    unsigned bits = 0;
+#pragma unroll
+    for (int u = 0; u < MU; ++u)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) bits |= pass(u, r) ? 1u << (4 * u + r) : 0u;
+    return bits;
+  };
+  append([&](int j) {
+    const float tau = s_tau[16 * j + col];
+    return mask_of([&](int u, int r) { return acc[u][j][r] >= tau; });
+  });
   __syncthreads();
   if (s_over != 0) {
-    // A list does not hold all that passed (many equal logits, or a row whose best entries sit together): find
-    // every row's exact k-th best by bisection on the entries' order, bit by bit, and append again.
-    for (int n = tid; n < R; n += FEW_THREADS) s_key[n] = 0;
-    for (int bit = 41; bit >= 0; --bit) {
-      __syncthreads();                              // s_key settled, s_cnt read by everyone
-      if (tid < R) s_cnt[tid] = 0;
+    // Some lists do not hold all that passed: k is close to the number of partial maxima, the best entries sit together (like
+    // tokens have neighbouring ids), or many are equal.  Those rows get a threshold that k to FEW_CAP entries reach, found by
+    // bisection between the first one and the part's maximum; where that ends at a value which too many entries share, the
+    // ones with the smallest ids make up the k.  The first trial is the next value up, so that equal logits (rows of zeros, masked
+    // tokens) take one step; else a list ends after three to six, 32 at the most.
+    // Whole calls, with the exact k-th best found bit by bit over all 42 bits of (value, position) | now, us: d = 256, k = 32,
+    // 96 rows: V = 50257 157 | 54, V = 128256 277 | 67; k = 10, every 16th row zero: 96 rows, V = 50257 153 | 38.
+    FewSearch<R>& f = *reinterpret_cast<FewSearch<R>*>(&sA[0][0]);
+    static_assert(sizeof(FewSearch<R>) <= sizeof(sA), "over the A tiles");
+    const bool mine = tid < R && s_cnt[min(tid, R - 1)] > FEW_CAP;   // thread n looks after row n
+    unsigned lo = 0, hi = 0, trial = 0;   // keys: at least k entries reach lo, `above` < k of them hi
+    int above = 0;
+    if (mine) {
+      float m = s_m[0][tid];
+#pragma unroll
+      for (int w = 1; w < FEW_WAVES; ++w) m = fmaxf(m, s_m[w][tid]);
+      lo = float_key(s_tau[tid] + 0.f);
+      hi = float_key(m + 0.f) + 1;
+      trial = lo + 1;
+      s_cnt[tid] = 0;
+    }
+    bool searching = mine;
+    for (;;) {
+      if (tid < R) {
+        f.tau[tid] = searching ? key_float(trial) : __builtin_nanf("");
+        f.count[tid] = 0;
+      }
       __syncthreads();
+      if (tid == 0) s_over = 0;   // (everyone has read it)
 #pragma unroll
       for (int j = 0; j < NJ; ++j) {
-        const unsigned long long trial = s_key[16 * j + col] | (1ull << bit);
-        int c = 0;
+        const float tau = f.tau[16 * j + col];
+        if (__builtin_amdgcn_ballot_w64(tau == tau) != 0) {
+          int c = 0;
 #pragma unroll
-        for (int u = 0; u < MU; ++u)
+          for (int u = 0; u < MU; ++u)
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            float z = acc[u][j][r];
-            asm volatile("" : "+v"(z));   // (the key is made anew for every bit: kept, the keys of all entries would not fit the registers)
-            c += (z >= FEW_LOWEST && few_key(z, id0 + 16 * u + r - part0) >= trial) ? 1 : 0;
-          }
-        if (c != 0) atomicAdd(&s_cnt[16 * j + col], c);
+            for (int r = 0; r < 4; ++r) c += acc[u][j][r] >= tau ? 1 : 0;
+          if (c != 0) atomicAdd(&f.count[16 * j + col], c);
+        }
         LL_SCHED_FENCE();
       }
       __syncthreads();
-      if (tid < R && s_cnt[tid] >= p.k) s_key[tid] |= 1ull << bit;
+      if (searching) {
+        const int c = f.count[tid];
+        if (c >= p.k) {
+          lo = trial;
+        } else {
+          hi = trial;
+          above = c;
+        }
+        searching = !(c >= p.k && c <= FEW_CAP) && hi - lo > 1;
+        trial = lo + (hi - lo) / 2;
+        if (searching) s_over = 1;
+      }
+      __syncthreads();
+      if (s_over == 0) break;
+    }
+    if (tid < R) {
+      f.tau[tid] = mine ? key_float(lo) : __builtin_nanf("");
+      f.need[tid] = hi - lo == 1 ? p.k - above : FEW_CAP;
     }
     __syncthreads();
-    if (tid < R) s_cnt[tid] = 0;
+#pragma unroll
+    for (int j = 0; j < NJ; ++j) {
+      const float tau = f.tau[16 * j + col];
+      int c = 0;
+#pragma unroll
+      for (int u = 0; u < MU; ++u)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) c += acc[u][j][r] == tau ? 1 : 0;
+      c += __shfl_xor(c, 16, kWave);
+      c += __shfl_xor(c, 32, kWave);
+      if (grp == 0) f.ties[wave][16 * j + col] = c;
+      LL_SCHED_FENCE();
+    }
     __syncthreads();
-    append([&](int u, int j, int r) {
-      return acc[u][j][r] >= FEW_LOWEST && few_key(acc[u][j][r], id0 + 16 * u + r - part0) >= s_key[16 * j + col];
+    append([&](int j) {
+      const int n = 16 * j + col;
+      const float tau = f.tau[n];
+      unsigned bits = mask_of([&](int u, int r) { return acc[u][j][r] > tau; });
+      int left = f.need[n];   // ties still to list, in the order of the ids: wavefront, group, lane block, entry
+      for (int w = 0; w < wave; ++w) left -= f.ties[w][n];
+#pragma unroll
+      for (int u = 0; u < MU; ++u) {
+        unsigned tie = 0;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) tie |= acc[u][j][r] == tau ? 1u << r : 0u;
+        const int c = __builtin_popcount(tie);
+        const int beside = __shfl_xor(c, 16, kWave), pair = c + beside, other = __shfl_xor(pair, 32, kWave);
+        int here = left - ((grp & 1) ? beside : 0) - ((grp & 2) ? other : 0);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          if ((tie & (1u << r)) != 0 && here-- > 0) bits |= 1u << (4 * u + r);
+        }
+        left -= pair + other;
+      }
+      return bits;
     });
     __syncthreads();
   }
@@ -365,10 +451,13 @@ __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs 
 // entry below the k-th best maximum: what is left of the k lists that matter, some tens of entries, is
 // ranked by counting.  Bound by latency, so it has no chain of k dependent steps (k rounds of cross-lane
 // exchanges over 256 sorted lists took 34 us for 81 rows at k = 20) and two trips to memory.
+// Where many are left (few parts and a long k, many equal logits) they are bisected down to FEW_MERGE_RANKED
+// first: counting takes the square of their number, 2048 entries 100 us.
 // Order of entries as 64-bit keys: the logit's ordered bits, then the smaller part or id.
 // ---------------------------------------------------------------------------------------
 constexpr int FEW_MERGE_THREADS = 512;
 constexpr int FEW_MERGE_MAX = LL_KMAX * FEW_CAP;   // entries of k lists
+constexpr int FEW_MERGE_RANKED = 256;              // most entries ranked by counting (>= LL_KMAX)
 
 __device__ __forceinline__ unsigned long long few_order(float z, unsigned id) {
   return ((unsigned long long)float_key(z + 0.f) << 32) | (unsigned)~id;
@@ -395,7 +484,7 @@ __global__ __launch_bounds__(FEW_MERGE_THREADS) void ll_few_merge_kernel(
   __shared__ float s_red[4][WAVES];
   __shared__ int2 s_list[LL_KMAX];   // (part, entries)
   __shared__ float s_tau;
-  __shared__ int s_n;
+  __shared__ int s_n, s_count[2][WAVES];
   __shared__ float s_z[LL_KMAX];
   __shared__ int s_id[LL_KMAX];
   const int row = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -453,7 +542,42 @@ __global__ __launch_bounds__(FEW_MERGE_THREADS) void ll_few_merge_kernel(
     if (pass) s_c[at + __builtin_popcountll(passing & ((1ull << lane) - 1))] = few_order(__uint_as_float(e.x), e.y);
   }
   __syncthreads();
-  const int n = s_n, n4 = (n + 3) & ~3;
+  int n = s_n;
+  if (n > FEW_MERGE_RANKED) {   // (the same for all threads)
+    constexpr int PER = FEW_MERGE_MAX / FEW_MERGE_THREADS;
+    unsigned long long own[PER];
+#pragma unroll
+    for (int i = 0; i < PER; ++i) own[i] = tid + FEW_MERGE_THREADS * i < n ? s_c[tid + FEW_MERGE_THREADS * i] : 0ull;
+    // keys differ: all n reach lo, none hi; each step halves the distance, and some step leaves k to FEW_MERGE_RANKED
+    unsigned long long lo = few_order(tau, 0xffffffffu), hi = few_order(M, 0u) + 1;
+    for (int step = 0;; ++step) {
+      const unsigned long long trial = lo + (hi - lo) / 2;
+      int c = 0;
+#pragma unroll
+      for (int i = 0; i < PER; ++i) c += __builtin_popcountll(__builtin_amdgcn_ballot_w64(own[i] >= trial));
+      if (lane == 0) s_count[step & 1][wave] = c;
+      __syncthreads();
+      c = 0;
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w) c += s_count[step & 1][w];
+      if (c >= k) lo = trial; else hi = trial;
+      if ((c >= k && c <= FEW_MERGE_RANKED) || hi - lo <= 1) break;
+    }
+    if (tid == 0) s_n = 0;
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < PER; ++i) {
+      const bool pass = own[i] >= lo;
+      const unsigned long long passing = __builtin_amdgcn_ballot_w64(pass);
+      int at = 0;
+      if (lane == 0 && passing != 0) at = atomicAdd(&s_n, __builtin_popcountll(passing));
+      at = __builtin_amdgcn_readfirstlane(at);
+      if (pass) s_c[at + __builtin_popcountll(passing & ((1ull << lane) - 1))] = own[i];
+    }
+    __syncthreads();
+    n = s_n;
+  }
+  const int n4 = (n + 3) & ~3;
   if (tid < n4 - n) s_c[n + tid] = 0ull;
   __syncthreads();
   for (int i = tid; i < n; i += FEW_MERGE_THREADS) {

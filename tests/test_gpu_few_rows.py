@@ -109,3 +109,57 @@ def test_tokens_masked_by_the_lowest_bias_are_listed_last(N, V, k, low):
     assert np.abs(ent + (want * np.log(want)).sum(1)).max() < 1e-3
     masked = ~np.isin(w.target_ids.cpu().numpy(), allowed)
     assert np.all(logp[masked] < -1e38)
+
+
+def like_tokens(w, n):
+    """The last n tokens are near copies of one with long logits: every row's best (or worst) entries sit together."""
+    V = w.cfg.V
+    w.W_U[V - n:] = (4.0 * w.W_U[V - n].float() + 0.25 * w.W_U[V - n:].float()).to(torch.bfloat16)
+
+
+@pytest.mark.parametrize("N,d,V,k", [
+    (3, 128, 1000, 32),        # eight parts of 128 ids
+    (16, 192, 50257, 32),      # longest list: the threshold is the least of the partial maxima
+    (81, 128, 128256, 32),
+    (128, 64, 40000, 21),
+    (37, 128, 151936, 10),     # five groups a wavefront
+])
+def test_best_entries_that_sit_together(N, d, V, k):
+    say(f"few rows, like tokens N={N} d={d} V={V} k={k}")
+    w = inputs(N, d, V, seed=23)
+    w.hidden[0, N // 2] = 0
+    like_tokens(w, 300)
+    got = P.to_numpy(LL.ll_project(w.hidden, w.gamma, w.W_U, w.cfg.eps, k, w.target_ids))
+    P.compare(got, reference(w, k), k, label="together")
+    assert list(got["topk_ids"][N // 2]) == list(range(k))
+
+
+def call_time(w, rows, k):
+    hidden, target = w.hidden[:, :rows].contiguous(), w.target_ids[:rows].contiguous()
+    ws = torch.empty(LL.ll_workspace_bytes(rows, w.cfg.d, w.cfg.V, k), dtype=torch.uint8, device=DEV)
+    out = LL.ll_project(hidden, w.gamma, w.W_U, w.cfg.eps, k, target, workspace=ws)
+    times = []
+    for _ in range(9):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(10):
+            LL.ll_project(hidden, w.gamma, w.W_U, w.cfg.eps, k, target, workspace=ws, out=out)
+        b.record()
+        b.synchronize()
+        times.append(a.elapsed_time(b) / 10)
+    return sorted(times)[4]
+
+
+@pytest.mark.parametrize("rows,V,k,what", [(96, 50257, 32, "longest list"), (96, 128256, 32, "longest list"), (96, 50257, 10, "zero rows"),
+                                           (96, 50257, 10, "like tokens")])
+def test_full_lists_cost_no_more_than_the_256_row_kernel(rows, V, k, what):
+    """(One row more than this kernel takes.  Half as much again is allowed for the clock's moods.)"""
+    say(f"few rows, time of {what}, {rows} rows, V={V} k={k}")
+    w = inputs(129, 256, V)
+    if what == "zero rows":
+        w.hidden[0, ::16] = 0
+    if what == "like tokens":
+        like_tokens(w, 256)
+    few, many = call_time(w, rows, k), call_time(w, 129, k)
+    say(f"few rows, time of {what}: {1e3 * few:.1f} us, 129 rows {1e3 * many:.1f} us")
+    assert few < 1.5 * many

@@ -446,7 +446,7 @@ struct FewPlan {
   int nj, mu, units, splits;   // nj: 16-row blocks of the kernel instance; mu: groups per wavefront; units: groups in all
 };
 
-FewPlan make_few_plan(const ll_shape* s) {
+FewPlan make_few_plan(const ll_shape* s, int k) {
   FewPlan f = {};
   if (s->N < 1 || s->N > FEW_ROWS) return f;
   const int blocks = (int)((s->N + 15) / 16);
@@ -459,6 +459,11 @@ FewPlan make_few_plan(const ll_shape* s) {
   const int rounds = (share + FEW_WAVES * mu_max - 1) / (FEW_WAVES * mu_max);
   f.splits = parts * rounds;
   if (f.splits > FEW_MAX_SPLITS) return f;   // V beyond some 200 000 to 330 000
+  // More than 96 rows over more than one round (V past 98 000): a round's contraction and epilogue are no longer small beside
+  // its share of W_U, and what is saved is the 256-row kernel's insertions, few with its shortest list.  128 rows, here | 256-row
+  // kernel, us: V = 128256: d = 64: k = 1 54 | 45, k = 4 55 | 51, k = 5 55 | 66; d = 2560: k = 1 190 | 162, k = 4 185 | 167,
+  // k = 5 182 | 182, k = 10 184 | 188; d = 8192: k = 1 441 | 442, k = 4 441 | 437; V = 100000, d = 2560: k = 1 167 | 147, k = 5 167 | 166.
+  if (rounds > 1 && f.nj == 8 && k <= 4) return f;
   f.mu = ((f.units + f.splits - 1) / f.splits + FEW_WAVES - 1) / FEW_WAVES;
   f.ok = true;
   return f;
@@ -501,7 +506,7 @@ Plan make_plan(const ll_shape* s, int k, int chunk_rows = CHUNK_ROWS) {
   p.total = off;
   // The few-rows kernel's own layout of the same workspace.  It is taken only where it also fits the library's static
   // buffer, so that ll_project and ll_project_static run the same kernels.
-  p.few = make_few_plan(s);
+  p.few = make_few_plan(s, k);
   if (p.few.ok) {
     const size_t lists = (size_t)s->N * p.few.splits;
     off = 0;
@@ -526,8 +531,8 @@ void (*few_kernel(int nj, int mu))(const FewArgs) {
   LL_FEW(2, 1); LL_FEW(2, 3); LL_FEW(2, 5);
   LL_FEW(3, 1); LL_FEW(3, 3); LL_FEW(3, 5);
   LL_FEW(4, 1); LL_FEW(4, 3); LL_FEW(4, 5);
-  LL_FEW(6, 2); LL_FEW(6, 4);
-  LL_FEW(8, 1); LL_FEW(8, 3);
+  LL_FEW(6, 2); LL_FEW(6, 3); LL_FEW(6, 4);
+  LL_FEW(8, 1); LL_FEW(8, 2); LL_FEW(8, 3);
 #undef LL_FEW
   return nullptr;
 }

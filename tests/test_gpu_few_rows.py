@@ -25,6 +25,8 @@ CASES = [
     (96,   128,  70000, 10, False),  # parts of 17 and 18 groups
     (97,   256,  33000, 32, True),   # eight 16-row blocks
     (128,  64,   140000, 20, False),  # two rounds of workgroups
+    (128,  64,   100000, 5, False),  # the same, two groups a wavefront
+    (113,  64,   100000, 4, False),  # the same with a short list: the 256-row kernel
     (37,   64,   151936, 10, False),  # five groups per wavefront
     (20,   64,   300000, 12, False),  # two rounds of five
     (5,    64,   400000, 4, False),  # a vocabulary past the kernel's parts: the 256-row kernel

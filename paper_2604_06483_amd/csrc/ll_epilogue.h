@@ -398,7 +398,9 @@ __device__ __forceinline__ void exchange_bound(RowState<KR>& st, const GemmArgs&
     asm volatile("" : "+v"(entry));
     mine = (p.k - 1 == j) ? entry : mine;
   }
-  if (my_row < p.rows && mine > st.shared_bound) __hip_atomic_fetch_max(b, float_key(mine), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  // (only what is news: the split whose bound it is, or any while all logits are equal, would send it after every tile)
+  const unsigned key = float_key(mine);
+  if (my_row < p.rows && key > fresh && key > KEY_NEG_INF) __hip_atomic_fetch_max(b, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   asm volatile("" ::: "memory");
 }
 

@@ -60,7 +60,10 @@ size_t ll_workspace_bytes(const ll_shape* shape, int k);
  *               ll_steer_inject) and are used as they are
  *   W_U         bf16 [V, d]
  *   target_ids  int32 [N], or NULL: out_target_logp is not written (and may be NULL)
- *   workspace   device scratch of at least ll_workspace_bytes(shape, k) bytes, 256-byte aligned
+ *   workspace   device scratch of at least ll_workspace_bytes(shape, k) bytes, 256-byte aligned.  One sized for
+ *               more rows (same d, V and k) serves as well, though ll_workspace_bytes may ask for more: it reserves
+ *               what the kernel for up to 128 rows needs, and in a smaller workspace such a call runs on the
+ *               kernel for more rows, which takes longer.
  *
  * Requirements: d a positive multiple of 8, V at most 2^31 - 257, 1 <= k <= min(LL_KMAX, V), all
  * tensors 16-byte aligned.  N == 0 is a successful no-op.  Rows are processed in passes of at most 8192 rows
@@ -127,7 +130,8 @@ int ll_project_timed(const ll_shape* shape, void* workspace, size_t workspace_by
  * process ends.  The call allocates and frees nothing.
  *
  * Rows are processed in passes of ll_project_static_pass_rows(shape, k) rows: 8192 as in
- * ll_project when that plan fits the buffer (then the results are bit-identical to ll_project's),
+ * ll_project when that plan fits the buffer (then the results are bit-identical to ll_project's in a
+ * workspace of ll_workspace_bytes),
  * otherwise the largest multiple of 256 that fits (same quantities; the fp32 partial sums of a row
  * are then merged from a different number of vocabulary splits).  LL_ESCRATCH if not even 256 rows
  * fit (d above roughly 100 000).

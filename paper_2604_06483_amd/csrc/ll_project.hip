@@ -470,10 +470,10 @@ FewPlan make_few_plan(const ll_shape* s, int k) {
 }
 
 struct Plan {
-  size_t off_inv_rms, off_bound, off_bias, off_stats, off_top, off_panel, total;
+  size_t off_inv_rms, off_bound, off_bias, off_stats, off_top, off_panel, total;   // total: never less for more rows
   int64_t lda;
   FewPlan few;
-  size_t few_off_stats, few_off_cand, few_off_count, few_off_panel;
+  size_t few_total, few_off_stats, few_off_cand, few_off_count, few_off_panel;
 };
 
 bool shape_ok(const ll_shape* s, int k) {
@@ -486,7 +486,7 @@ bool shape_ok(const ll_shape* s, int k) {
 }
 
 Plan make_plan(const ll_shape* s, int k, int chunk_rows = CHUNK_ROWS) {
-  Plan p;
+  Plan p = {};
   size_t off = 0;
   p.off_inv_rms = off;
   off = align_up(off + (size_t)s->N * sizeof(float), 256);
@@ -504,8 +504,9 @@ Plan make_plan(const ll_shape* s, int k, int chunk_rows = CHUNK_ROWS) {
   p.off_panel = off;
   off = align_up(off + rows * (size_t)p.lda * sizeof(uint16_t), 256);
   p.total = off;
-  // The few-rows kernel's own layout of the same workspace.  It is taken only where it also fits the library's static
-  // buffer, so that ll_project and ll_project_static run the same kernels.
+  // The few-rows kernel's own layout of the same workspace, larger than what many more rows need above: 64 entries a row and part.
+  // It is taken only where it fits the workspace that the caller handed over (one sized for a longer call need not hold it), and
+  // where it also fits the library's static buffer, so that ll_project and ll_project_static run the same kernels.
   p.few = make_few_plan(s, k);
   if (p.few.ok) {
     const size_t lists = (size_t)s->N * p.few.splits;
@@ -518,8 +519,8 @@ Plan make_plan(const ll_shape* s, int k, int chunk_rows = CHUNK_ROWS) {
     off = align_up(off + lists * sizeof(int), 256);
     p.few_off_panel = off;
     off = align_up(off + rows * (size_t)p.lda * sizeof(uint16_t), 256);
+    p.few_total = off;
     p.few.ok = off <= (size_t)LL_STATIC_SCRATCH_BYTES;
-    if (p.few.ok && off > p.total) p.total = off;
   }
   return p;
 }
@@ -595,6 +596,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
   if (align_or & 15) return LL_EINVAL;
   const Plan plan = make_plan(shape, k, chunk_rows);
   if (workspace == nullptr || workspace_bytes < plan.total || ((uintptr_t)workspace & 255)) return LL_EWORKSPACE;
+  const bool few_rows = plan.few.ok && workspace_bytes >= plan.few_total && !(flags & LL_FLAG_REGISTER_STAGED);
 
   unsigned char* ws = static_cast<unsigned char*>(workspace);
   float* inv_rms = reinterpret_cast<float*>(ws + plan.off_inv_rms);
@@ -671,7 +673,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
   // Few rows: one read of W_U.  Whole call, us, here / on the 256-row tiles: d = 8192, V = 128256, k = 20: 1 row 331 / 480, 81 rows
   // 348 / 490, 97 to 128 rows (two rounds of workgroups) 460 / 495; d = 2560, V = 151936, k = 10: 37 rows 145 / 245, 128 rows 228 /
   // 275; 64 rows of d = 256, V = 4096: 19 / 49.  Past 128 rows the accumulators do not fit and the 256-row tiles are the better split.
-  if (plan.few.ok && !(flags & LL_FLAG_REGISTER_STAGED)) {
+  if (few_rows) {
     const FewPlan& few = plan.few;
     uint16_t* few_panel = reinterpret_cast<uint16_t*>(ws + plan.few_off_panel);
     const bool copy = has_gamma || plan.lda != d;
@@ -1041,7 +1043,8 @@ int ll_steer_sweep(const ll_shape* shape, void* workspace, size_t workspace_byte
 size_t ll_workspace_bytes(const ll_shape* shape, int k) {
   if (!shape_ok(shape, k)) return 0;
   if (shape->N == 0) return 256;
-  return make_plan(shape, k).total;
+  const Plan plan = make_plan(shape, k);
+  return plan.few.ok && plan.few_total > plan.total ? plan.few_total : plan.total;
 }
 
 int ll_project(const ll_shape* shape, void* workspace, size_t workspace_bytes, const void* hidden, const void* gamma,

@@ -107,6 +107,23 @@ def test_project_rejects_bad_arguments_without_touching_the_gpu():
                               a["ids"], a["p"], a["lp"], a["e"], a["st"], None) == LL.LL_EINVAL
 
 
+@pytest.mark.parametrize("d,V,k", [(2560, 151936, 10), (256, 4096, 5), (8192, 128256, 20), (72, 300, 1)])
+def test_a_workspace_for_more_rows_is_accepted_for_fewer(d, V, k):
+    """Up to 128 rows ll_workspace_bytes reserves more than some longer calls need; a caller who sized one workspace for the
+    longest prompt still may hand it over."""
+    import torch
+    if torch.cuda.is_available():
+        pytest.skip("fake addresses: only where no device would follow them")
+    L = LL.lib()
+    f = _fake()
+    for longest in (129, 200, 1500, 9000):
+        size = LL.ll_workspace_bytes(longest, d, V, k)
+        for N in (1, 16, 64, 81, 96, 97, 128, 129, longest):
+            rc = L.ll_project(LL.ll_shape(N, d, V), _fake(4096 * 256), size, f, f, f, 1e-5, k, f, f, f, f, f, None)
+            assert rc == LL.LL_EHIP, (longest, N, rc)          # past the checks of its arguments, no device to run on
+    assert L.ll_project(LL.ll_shape(128, d, V), _fake(4096 * 256), 1024, f, f, f, 1e-5, k, f, f, f, f, f, None) == LL.LL_EWORKSPACE
+
+
 def test_static_variant_sizes_its_passes_and_rejects_what_does_not_fit():
     """ll_project_static: pass size from host arithmetic; bad arguments and oversized shapes are refused before
     anything touches the device (fake pointers, no GPU)."""

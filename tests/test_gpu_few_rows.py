@@ -60,6 +60,16 @@ def test_few_rows(N, d, V, k, with_bias):
             assert torch.equal(a, b)
 
 
+def test_a_workspace_sized_for_more_rows():
+    N, d, V, k = 81, 128, 128256, 10
+    say(f"few rows in the workspace of a longer call N={N} d={d} V={V} k={k}")
+    assert LL.ll_workspace_bytes(1500, d, V, k) < LL.ll_workspace_bytes(N, d, V, k)
+    w = inputs(N, d, V)
+    ws = torch.full((LL.ll_workspace_bytes(1500, d, V, k),), 0xFF, dtype=torch.uint8, device=DEV)
+    got = P.to_numpy(LL.ll_project(w.hidden, w.gamma, w.W_U, w.cfg.eps, k, w.target_ids, workspace=ws))
+    P.compare(got, reference(w, k), k, label="longer call's workspace")
+
+
 @pytest.mark.parametrize("N,d,V,k", [(100, 256, 9000, 20), (128, 320, 3000, 32)])
 def test_same_logits_as_the_256_row_kernel(N, d, V, k):
     """K order and matrix instruction are the same, so ids and their order are; the softmax sums run over other

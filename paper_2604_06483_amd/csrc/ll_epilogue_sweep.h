@@ -18,7 +18,7 @@ namespace {
 // The exponential is therefore taken out of the per-alpha work: with m a reference of the row,
 //     e^(w - m) = e^(z - m) e^(alpha u),
 // one exponential per logit and a factor E = e^(alpha u) that is the same for every row, and the sums
-//     S = sum e E,   T1 = sum (e z) E,   T2 = sum e (E u),        T = T1 + alpha T2 = sum e^(w - m) w
+//     S = sum e E,   T1 = sum (e z) E,   T2 = sum e (alpha E u),        T = T1 + T2 = sum e^(w - m) w
 // become products of small matrices, [alphas, ids] times [ids, rows], which the matrix pipe does in fp32
 // (v_mfma_f32_16x16x4_f32: full precision, fp32 accumulation).  The accumulator layout of the contraction is the
 // operand layout of that instruction: register r of a 16 x 16 tile is, for lane l, id 4 (l / 16) + r of lens row
@@ -51,7 +51,7 @@ constexpr unsigned SWEEP_NO_ID = 0xffffu;         // list entry that stands for 
 constexpr int SWEEP_MAX_TILES = 255;              // tiles per split: ids relative to the split's first fit 16 bits
 
 // Table rows of a group of 16 ids, 16 floats each: rows 0 .. 15 are the first A operand, rows 16 .. 31 the second.
-// Up to eight alphas: E of alpha a in row a, E u in row 8 + a, and no second operand.  Nine: E in row a, E u in row 16 + a.
+// Up to eight alphas: E of alpha a in row a, alpha E u in row 8 + a, and no second operand.  Nine: E in row a, alpha E u in row 16 + a.
 constexpr int SWEEP_ROWS = 32;
 constexpr int SWEEP_FEW = 4;          // code for all alphas is branched over past these
 constexpr int SWEEP_SPLIT_ROWS = 8;   // most alphas with both factors in one operand
@@ -107,9 +107,10 @@ struct SweepState {
   // registers are short.
   static constexpr int PER = GENERAL ? 1 : 2, IDS = (KS + PER - 1) / PER;
   __device__ __forceinline__ unsigned id(int a, int j) const { return (li[a][j / PER] >> (16 * (j % PER))) & 0xffffu; }
-  // Factored form, per row block j of the wavefront (rows 16 j + l % 16): reference, and S, T1, T2 as D operands (alphas 4 (l / 16) + r).
+  // Factored form, per row block j of the wavefront (rows 16 j + l % 16): reference, and as D operands (alphas 4 (l / 16) + r) S, with
+  // up to eight alphas T2 in the rows 8 + a of it, and T1, with nine alphas T.
   float ref[4];
-  f32x4 s[4], t1[4], t2[4];
+  f32x4 s[4], t[4];
   // General form, of the lane's own row.
   float gs[SWEEP_MAX], gt[SWEEP_MAX];
   // Of the lane's own row (64 w + l):
@@ -298,20 +299,34 @@ __device__ __forceinline__ void sweep_group_general(const float (&x)[16], SweepS
 // acc[alpha, row] += sum over lane blocks of a[alpha, id] b[id, row].  Written as an instruction: given the builtin the compiler
 // wants the results in AGPRs, which the contraction fills.  So the waits are ours: two states between a vector instruction
 // that writes an operand and the product that reads it, two more between products on one accumulator (there is always another
-// one in between, or the s_nop here), and sweep_settle before a vector instruction reads or writes a result.
+// one in between, or the s_nop here), and 18 before a vector instruction reads a result.
 __device__ __forceinline__ void sweep_product(f32x4& acc, float a, float b) {
   asm volatile("s_nop 1\n\tv_mfma_f32_16x16x4_f32 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
 }
-template <int KS>
-__device__ __forceinline__ void sweep_settle(SweepState<KS, false>& st) {
-#pragma unroll
-  for (int j = 0; j < 4; ++j) asm volatile("s_nop 15\n\ts_nop 3" : "+v"(st.s[j]), "+v"(st.t1[j]), "+v"(st.t2[j]));
+__device__ __forceinline__ void sweep_first_product(f32x4& acc, float a, float b) {   // acc = 0 + ...
+  asm volatile("s_nop 1\n\tv_mfma_f32_16x16x4_f32 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
 }
 
+// The products of one group and row block, which start from zero and are added to the row's sums while the next block's
+// products run: the instruction does not round to nearest, and a chain of them over a split of 51 tiles left S too small by
+// 1.1e-5 of itself and the entropy by 1e-4 (6000 rows, V = 128256).  Four products of a group and one addition a group have
+// the error that a sum of exponentials in vector instructions has.
+struct SweepPending {
+  f32x4 s[2], t[2];   // of row blocks of this parity
+};
+template <int KS>
+__device__ __forceinline__ void sweep_fold(SweepState<KS, false>& st, SweepPending& pend, int block) {
+  const int c = block & 1;
+  asm volatile("" : "+v"(pend.s[c]), "+v"(pend.t[c]));   // (here, not earlier)
+  st.s[block] += pend.s[c];
+  st.t[block] += pend.t[c];
+  asm volatile("" : "+v"(st.s[block]), "+v"(st.t[block]));
+}
 // The factored form (y as in sweep_group).
 template <int KS>
 __device__ __forceinline__ void sweep_group_factored(const float (&y)[4][4], SweepState<KS, false>& st, const SweepTable& tab,
                                                      unsigned first, const GemmArgs& p) {
+  SweepPending pend;
   // references
   float most[4];
 #pragma unroll
@@ -320,7 +335,6 @@ __device__ __forceinline__ void sweep_group_factored(const float (&y)[4][4], Swe
 #pragma unroll
   for (int j = 0; j < 4; ++j) move = move || most[j] > st.ref[j] + SWEEP_SHIFT;
   if (__builtin_amdgcn_ballot_w64(move) != 0) {
-    sweep_settle(st);
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       float full = fmaxf(most[j], __shfl_xor(most[j], 16, kWave));
@@ -329,10 +343,8 @@ __device__ __forceinline__ void sweep_group_factored(const float (&y)[4][4], Swe
       const float sc = ref == st.ref[j] ? 1.0f : __builtin_amdgcn_exp2f((st.ref[j] - ref) * LOG2E);   // first group: exp2(-inf) = 0
       st.ref[j] = ref;
       st.s[j] *= sc;
-      st.t1[j] *= sc;
-      st.t2[j] *= sc;
+      st.t[j] *= sc;
     }
-    // (the vector instructions above are done two states before the products: sweep_products waits)
   }
   const float a0[4] = {tab.a0.x, tab.a0.y, tab.a0.z, tab.a0.w}, a1[4] = {tab.a1.x, tab.a1.y, tab.a1.z, tab.a1.w};
   // Sums, row block by row block: the exponentials of the next one are made between the products of this one (a product
@@ -351,21 +363,24 @@ __device__ __forceinline__ void sweep_group_factored(const float (&y)[4][4], Swe
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
       LL_SCHED_FENCE();
-      sweep_product(st.s[j], a0[r], e[c][r]);
+      if (r == 0) sweep_first_product(pend.s[c], a0[r], e[c][r]); else sweep_product(pend.s[c], a0[r], e[c][r]);
       if (j < 3) {
         e[n][r] = __builtin_amdgcn_exp2f(fmaf(y[jn][r], LOG2E, -st.ref[jn] * LOG2E));
         asm volatile("" : "+v"(e[n][r]));   // (here, not where it is used)
       }
       LL_SCHED_FENCE();
-      sweep_product(st.t1[j], a0[r], ez[c][r]);
+      if (r == 0) sweep_first_product(pend.t[c], a0[r], ez[c][r]); else sweep_product(pend.t[c], a0[r], ez[c][r]);
       if (j < 3) {
         ez[n][r] = e[n][r] * y[jn][r];
         asm volatile("" : "+v"(ez[n][r]));
       }
     }
+    LL_SCHED_FENCE();
+    if (j > 0) sweep_fold(st, pend, j - 1);   // eight products since
+    LL_SCHED_FENCE();
     if (second) {
 #pragma unroll
-      for (int r = 0; r < 4; ++r) sweep_product(st.t2[j], a1[r], e[c][r]);
+      for (int r = 0; r < 4; ++r) sweep_product(pend.t[c], a1[r], e[c][r]);
     }
     if (j < 3) asm volatile("s_nop 1" : "+v"(e[n][3]), "+v"(ez[n][3]));   // (the last of them was written just now)
   }
@@ -386,6 +401,8 @@ __device__ __forceinline__ void sweep_group_factored(const float (&y)[4][4], Swe
       if (a >= SWEEP_FEW) lim = fminf(lim, minus_bcast16<a>(st.lv[a][KS - 1], tab.shift));
     });
   lim = fmaxf(lim - (fabsf(lim) + 2.0f * SWEEP_SHIFT) * 0x1p-22f, NEG_BIG);   // (entries past the vocabulary are NEG_BIG)
+  asm volatile("s_nop 15\n\ts_nop 3" : "+v"(lim), "+v"(pend.s[1]), "+v"(pend.t[1]));   // (behind the limit's dozen instructions)
+  sweep_fold(st, pend, 3);
   if (__builtin_amdgcn_ballot_w64(gmax > lim) != 0) {
     float x[16];
     own_row(y, x);
@@ -469,7 +486,7 @@ struct SweepEpilogue {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       st.ref[j] = -INFINITY;
-      st.s[j] = st.t1[j] = st.t2[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      st.s[j] = st.t[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 #pragma unroll
     for (int a = 0; a < SWEEP_MAX; ++a) {
@@ -525,10 +542,7 @@ struct SweepEpilogue {
       }
       sweep_group<KS, GENERAL>(y, st, tab, g0, p);
     }
-    if constexpr (!GENERAL) {
-      sweep_exchange<KS>(st, p, my_row);
-      sweep_settle(st);   // (once per tile, so that nothing after the tile has to think of it)
-    }
+    if constexpr (!GENERAL) sweep_exchange<KS>(st, p, my_row);
   }
   static __device__ __forceinline__ void store(const GemmArgs& p, const State& st, int my_row, int split) {
     if constexpr (!GENERAL) {   // statistics in accumulator layout: rows 16 j + l % 16 of the wavefront, alphas 4 (l / 16) + r
@@ -539,12 +553,11 @@ struct SweepEpilogue {
         const int row = my_row - lane + 16 * j + (lane & 15);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const float s = st.s[j][r], t1 = st.t1[j][r];
-          const float upper = __shfl_xor(s, 32, kWave);   // row 8 + a of the one operand, where T2 is with up to eight alphas
-          const float t2 = second ? st.t2[j][r] : upper;
+          const float s = st.s[j][r], t = st.t[j][r];
+          const float t2 = __shfl_xor(s, 32, kWave);   // row 8 + a
           const int a = 4 * (lane >> 4) + r;
           if (row < p.rows && a < p.n_alpha)
-            p.sweep_stats[((int64_t)row * p.n_alpha + a) * p.splits + split] = make_float4(st.ref[j], s, fmaf(p.alphas[a], t2, t1), 0.f);
+            p.sweep_stats[((int64_t)row * p.n_alpha + a) * p.splits + split] = make_float4(st.ref[j], s, second ? t : t + t2, 0.f);
         }
       }
     }

@@ -192,10 +192,11 @@ __global__ __launch_bounds__(256) void ll_sweep_table_kernel(const float* __rest
     const int second = n_alpha <= SWEEP_SPLIT_ROWS ? SWEEP_SPLIT_ROWS : SWEEP_GROUP;   // first row of the factors times u
     float spread = 0.f;
     for (int a = 0; a < second; ++a) {
-      float e = 0.f, most = 0.f;
+      float e = 0.f, es = 0.f, most = 0.f;
       if (a < n_alpha) {
         const float shift = alphas.a[a] * x;
         e = expf(shift);
+        es = e * shift;
         most = shift;
         float least = shift;
 #pragma unroll
@@ -206,7 +207,7 @@ __global__ __launch_bounds__(256) void ll_sweep_table_kernel(const float* __rest
         spread = fmaxf(spread, most - least);
       }
       rows[a * SWEEP_GROUP] = e;
-      rows[(second + a) * SWEEP_GROUP] = e * x;
+      rows[(second + a) * SWEEP_GROUP] = es;
       if ((id & 15) == a && a < 15) shift_max[id] = most;                            // (alpha number a of the group: its first id + a)
       if (a == 0 && (id & 15) >= second && (id & 15) < 15) shift_max[id] = 0.f;
     }
@@ -351,8 +352,22 @@ __global__ __launch_bounds__(256) void ll_merge_kernel(const float4* __restrict_
   }
 }
 
+// e^(a - b), a and b of any distance that counts: what the rounding of a - b and of its product with log2 e leaves out is applied
+// to the result.  (exp2f(rounded) alone is off by 2^-25 of the exponent: 1e-6 where two references are 20 apart.)
+__device__ __forceinline__ float exp_difference(float a, float b) {
+  constexpr float LOG2E_LOW = 1.92596299e-8f;   // log2 e - LOG2E
+  const float d = a - b;
+  if (!(fabsf(d) < 100.f)) return __builtin_amdgcn_exp2f(d * LOG2E);   // (0, infinity or NaN)
+  const float back = d + b, lost = (a - back) + ((back - d) - b);      // a - b = d + lost
+  const float x = d * LOG2E;
+  const float rest = fmaf(d, LOG2E, -x) + (d * LOG2E_LOW + lost * LOG2E);
+  return __builtin_amdgcn_exp2f(x) * fmaf(rest, 0.693147181f, 1.0f);
+}
+
 // Steering sweep, step 4: merge the splits of each (row, alpha) and finalise.  One wavefront each; lane l takes splits l,
 // l + 64, ... (increasing ids), keeps their KS best, and the wavefront takes the best of its lanes' heads k times.
+// The splits' references are any logits of the row, some of them far below its largest, so that M and log S are no small
+// numbers that nearly cancel: the last steps are in 64 bits.
 template <int KS>
 __global__ __launch_bounds__(256) void ll_sweep_merge_kernel(const float4* __restrict__ stats, const uint2* __restrict__ top,
                                                              const float* __restrict__ ztgt, const float* __restrict__ u,
@@ -399,22 +414,24 @@ __global__ __launch_bounds__(256) void ll_sweep_merge_kernel(const float4* __res
   float s_lane = 0.f, t_lane = 0.f;
   for (int s = lane; s < splits; s += 64) {
     const float4 x = q[s];
-    const float sc = __builtin_amdgcn_exp2f((x.x - M) * LOG2E);
+    const float sc = exp_difference(x.x, M);
     s_lane = fmaf(sc, x.y, s_lane);
     t_lane = fmaf(sc, x.z, t_lane);
   }
   const float S = wave_sum(s_lane), T = wave_sum(t_lane);
-  const float logS = logf(S);
+  const double lse = (double)M + log((double)S);
   zt = wave_max(zt);
   const int64_t o = (int64_t)a * out_stride + row;
   if (lane == 0) {
     bound[a * rows + row] = 0u;   // the projection kernel of this pass is done with it: clear it for the next pass
-    out_entropy[o] = (M - T / S) + logS;
+    out_entropy[o] = (float)(lse - (double)T / (double)S);
     if (target != nullptr) {
       const int t = target[row];
-      out_logp[o] = t >= 0 && t < V ? ((zt + alphas.a[a] * u[t]) - M) - logS : __builtin_nanf("");
+      out_logp[o] = t >= 0 && t < V ? (float)(((double)zt + (double)alphas.a[a] * u[t]) - lse) : __builtin_nanf("");
     }
   }
+  float my_z = 0.f;   // lane j keeps the j-th
+  int my_id = 0;
   for (int j = 0; j < k; ++j) {
     const float bz = wave_max(z[0]);
     const int bi = wave_min_int(z[0] == bz ? id[0] : INT_MAX);
@@ -427,10 +444,14 @@ __global__ __launch_bounds__(256) void ll_sweep_merge_kernel(const float4* __res
       z[KS - 1] = -INFINITY;
       id[KS - 1] = INT_MAX;
     }
-    if (lane == 0) {
-      out_ids[o * k + j] = bi;
-      out_p[o * k + j] = __builtin_amdgcn_exp2f(((bz - M) - logS) * LOG2E);
+    if (lane == j) {
+      my_z = bz;
+      my_id = bi;
     }
+  }
+  if (lane < k) {
+    out_ids[o * k + lane] = my_id;
+    out_p[o * k + lane] = expf((float)((double)my_z - lse));
   }
 }
 

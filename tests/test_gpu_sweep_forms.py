@@ -52,6 +52,42 @@ def test_splits(N, d, V, n_alpha, k):
     check(N, d, V, ALPHAS9[:n_alpha], k, 1.0, "splits")
 
 
+@pytest.mark.parametrize("N,d,V,n_alpha,k", [
+    (4200, 64, 100000, 9, 3),     # 17 row blocks, 15 splits of 27 tiles: 432 groups of 16 ids a sum
+    (1500, 128, 50257, 8, None),  # 40 splits of five tiles
+    (300, 200, 3001, 9, 4),       # one tile a split
+])
+def test_sums_have_the_error_of_single_roundings(N, d, V, n_alpha, k):
+    """The softmax sums against 64 bits, rows given as bf16 so that only the logits and the sums round.  A sum of the G groups of
+    a split rounds G times, to nearest: a relative sqrt(G) 2^-24 at most in the root mean square, and no bias to speak of.  The
+    entropy is that of the sums' quotient, weighed logits of up to 30 or so, and a logit's own sum rounds d times."""
+    say(f"sweep sums N={N} d={d} V={V} A={n_alpha} k={k}")
+    g = torch.Generator(device=DEV).manual_seed(51)
+    hidden = torch.randn((N, d), generator=g, device=DEV).to(torch.bfloat16)
+    W = (torch.randn((V, d), generator=g, device=DEV) * (5.0 / d ** 0.5)).to(torch.bfloat16)
+    v, alphas = direction(d), ALPHAS9[:n_alpha]
+    target = torch.randint(0, V, (N,), generator=g, device=DEV, dtype=torch.int32)
+    _, _, logp, ent = LL.ll_steer_sweep(hidden, None, W, 1e-5, v, alphas, target, k=k)
+    rows = torch.randint(0, N, (256,), generator=g, device=DEV)
+    Wt = W.double().t().contiguous()
+    z = hidden[rows].double() @ Wt
+    u = v.double() @ Wt
+    splits = max(1, 256 // ((N + 255) // 256))
+    groups = -(-(-(-V // 256)) // splits) * 16
+    for a, alpha in enumerate(alphas):
+        w = z + alpha * u
+        lse = torch.logsumexp(w, -1)
+        lp = w - lse[:, None]
+        p = lp.exp()
+        of_logits = 2.0 ** -24 * d ** 0.5 * 5.0 + 2.0 ** -23 * float(w.abs().max())   # of a logit and of its shift
+        of_sums = 2.0 ** -24 * groups ** 0.5
+        err = logp[a, rows].double() - lp.gather(1, target[rows].long()[:, None])[:, 0]
+        assert float(err.square().mean().sqrt()) <= of_logits + of_sums
+        weighed = float((p * w).sum(-1).abs().max())
+        err = ent[a, rows].double() + (p * lp).sum(-1)
+        assert float(err.square().mean().sqrt()) <= of_logits + of_sums * weighed, (alpha, float(err.mean()))
+
+
 @pytest.mark.parametrize("k", [None, 3, 4])
 @pytest.mark.parametrize("N,d,V", [
     (300, 128, 66000),   # two row blocks, 86 splits of three tiles

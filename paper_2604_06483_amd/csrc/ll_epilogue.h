@@ -28,7 +28,7 @@ struct GemmArgs {
   // steering sweep only (Sec. 3.4, Eq. 3 for several alpha in one pass):
   const float* u;           // [tiles * BM] fp32: W_U v, zero padded
   const float* eu;          // [tiles * BM / 16, 32, 16]: rows of e^(alpha u) and alpha u e^(alpha u) of 16 ids (see ll_epilogue_sweep.h)
-  const float* shift_max;   // [tiles * BM / 16, 16]: per alpha the largest alpha u of 16 ids; entry 15 the largest spread of any alpha u among them
+  const float* shift_max;   // [tiles * BM / 16, 16]: per alpha the largest alpha u of 16 ids, with a margin; entry 15 the largest spread of any alpha u among them
   const int* sweep_general; // nonzero: some |alpha u| is too large for the factored form; nullptr: the general form in any case
   float4* sweep_stats;      // [rows, n_alpha, splits]      (reference, S, T)
   float* sweep_ztgt;        // [rows, splits]               logit of the target id at alpha = 0

@@ -192,13 +192,12 @@ __global__ __launch_bounds__(256) void ll_sweep_table_kernel(const float* __rest
     const int second = n_alpha <= SWEEP_SPLIT_ROWS ? SWEEP_SPLIT_ROWS : SWEEP_GROUP;   // first row of the factors times u
     float spread = 0.f;
     for (int a = 0; a < second; ++a) {
-      float e = 0.f, es = 0.f, most = 0.f;
+      float e = 0.f, es = 0.f, most = 0.f, least = 0.f;
       if (a < n_alpha) {
         const float shift = alphas.a[a] * x;
         e = expf(shift);
         es = e * shift;
-        most = shift;
-        float least = shift;
+        most = least = shift;
 #pragma unroll
         for (int off = 8; off > 0; off >>= 1) {
           most = fmaxf(most, __shfl_xor(most, off, kWave));
@@ -208,7 +207,8 @@ __global__ __launch_bounds__(256) void ll_sweep_table_kernel(const float* __rest
       }
       rows[a * SWEEP_GROUP] = e;
       rows[(second + a) * SWEEP_GROUP] = es;
-      if ((id & 15) == a && a < 15) shift_max[id] = most;                            // (alpha number a of the group: its first id + a)
+      // (alpha number a of the group: its first id + a; with the margin for its rounding, SWEEP_MARGIN, unless no logit is shifted at all)
+      if ((id & 15) == a && a < 15) shift_max[id] = most == 0.f && least == 0.f ? 0.f : most + SWEEP_MARGIN;
       if (a == 0 && (id & 15) >= second && (id & 15) < 15) shift_max[id] = 0.f;
     }
     if ((id & 15) == 15) shift_max[id] = spread;

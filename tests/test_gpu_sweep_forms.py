@@ -126,3 +126,33 @@ def test_equal_logits_are_listed_in_id_order(N, d, V, k):
     assert ids.min() >= 0 and np.all(ids[:, some, 0] < V // 3)
     if listed > 1:
         assert np.all(ids[:, some, 1] == ids[:, some, 0] + V // 3) and np.all(ids[:, some, 2] == ids[:, some, 0] + 2 * (V // 3))
+
+
+@pytest.mark.parametrize("k,limit", [(None, 1.33), (3, 1.67)])
+def test_rows_of_zeros_cost_little_more_than_others(k, limit):
+    """Equal logits are no candidates for a full list.  (Lists meet more groups that do hold one, whose sixteen equal logits then
+    are looked at together.  The rest is for the clock's moods.)"""
+    say(f"sweep, time with zero rows k={k}")
+    N, d, V = 500, 256, 50257
+    w = WL.make_workload(WL.LensConfig("zeros", L=1, T=N, d=d, V=V, k=1), DEV, seed=43)
+    hidden, v = w.hidden.reshape(N, d), direction(d)
+    ws = torch.empty(LL.ll_steer_sweep_workspace_bytes(N, d, V, 9, k or 1), dtype=torch.uint8, device=DEV)
+
+    def call_time():
+        times = []
+        for _ in range(9):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            LL.ll_steer_sweep(hidden, w.gamma, w.W_U, w.cfg.eps, v, ALPHAS9, None, k=k, workspace=ws)
+            a.record()
+            for _ in range(5):
+                LL.ll_steer_sweep(hidden, w.gamma, w.W_U, w.cfg.eps, v, ALPHAS9, None, k=k, workspace=ws)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b) / 5)
+        return sorted(times)[4]
+
+    without = call_time()
+    hidden[::64] = 0
+    some = call_time()
+    say(f"sweep k={k}: {1e3 * without:.1f} us, with zero rows {1e3 * some:.1f} us")
+    assert some < limit * without

@@ -907,14 +907,21 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
                      block_max);
   LL_CHECK_S(hipGetLastError());
   // Few alphas: the general form alone, without the tables and the launch that fills them.  Its cost grows with every alpha, the
-  // factored one's hardly does.  Whole calls, general | factored, us, three / four / five alphas:
-  //   arg max:  64 rows, d = 256, V = 4096        41 | 60       47 | 61       52 | 65
-  //             1138 rows, d = 384, V = 74495    190 | 223     220 | 229     250 | 235
-  //             1500 rows, d = 4096, V = 128256 1463 | 1492   1505 | 1468   1556 | 1476
-  //   lists:    64 rows, d = 256, V = 4096        70 | 83       84 | 84       99 | 105
-  //             1138 rows, d = 384, V = 74495    255 | 282     307 | 290     361 | 330
-  //             1500 rows, d = 4096, V = 128256 1538 | 1541   1599 | 1523   1648 | 1586
-  const bool lists = k > 1, only_general = n_alpha <= (lists ? 3 : 4);
+  // factored one's hardly does after a split's first tile, where it looks at more candidates: the line moves up with fewer tiles a
+  // split.  Whole calls, general | factored, us, d = 512 (N x V: tiles a split), arg max:
+  //   100 x 50257 (1)      A = 5  69 | 93       A = 6  75 | 95       A = 7  81 | 95
+  //   300 x 50257 (2)      A = 4  99 | 121      A = 5  110 | 127     A = 6  122 | 130    A = 7  134 | 133
+  //   700 x 50257 (3)      A = 4  133 | 150     A = 5  149 | 159     A = 6  167 | 162
+  //   1500 x 50257 (5)     A = 4  204 | 221     A = 5  231 | 231     A = 6  257 | 234
+  //   4000 x 128256 (32)   A = 4  1047 | 1081   A = 5  1181 | 1102
+  // and lists:
+  //   100 x 50257 (1)      A = 4  103 | 113     A = 5  117 | 134     A = 6  133 | 135    A = 7  147 | 137
+  //   700 x 50257 (3)      A = 3  161 | 190     A = 4  192 | 193     A = 5  222 | 228    A = 6  253 | 231
+  //   1500 x 50257 (5)     A = 3  236 | 275     A = 4  279 | 280     A = 5  324 | 319
+  //   4000 x 128256 (32)   A = 3  1089 | 1230   A = 4  1281 | 1245
+  const int first_rows = (int)(N < CHUNK_ROWS ? N : CHUNK_ROWS), first_splits = sweep_splits(first_rows, tiles);
+  const int each = (tiles + first_splits - 1) / first_splits;
+  const bool lists = k > 1, only_general = n_alpha <= (lists ? 3 : 4) + (each == 1 ? 2 : each <= 4 ? 1 : 0);
   if (!only_general) {
     const int n_bound = (int)(N < CHUNK_ROWS ? N : CHUNK_ROWS) * n_alpha;
     hipLaunchKernelGGL(ll_sweep_table_kernel, dim3(plan.n_padded / 256 < 2048 ? plan.n_padded / 256 : 2048), dim3(256), 0, stream,

@@ -44,8 +44,11 @@ def test_both_forms(k, length, general, d):
     (300, 64, 66000, 9, 4),      # two row blocks, 86 splits of three tiles
     (1000, 64, 20000, 7, None),  # four row blocks
     (260, 192, 263, 9, 3),       # a last tile of seven ids
-    (70, 128, 5000, 4, None), (70, 128, 5000, 5, None),   # either side of the number that takes the form without tables
+    (70, 128, 5000, 4, None), (70, 128, 5000, 5, None),   # one tile a split: few enough for the form without tables
     (70, 128, 5000, 3, 4), (70, 128, 5000, 4, 4), (70, 128, 5000, 1, 2),
+    (70, 128, 5000, 6, None), (70, 128, 5000, 7, None), (70, 128, 5000, 5, 4), (70, 128, 5000, 6, 4),   # either side of that number
+    (10, 128, 70000, 5, None), (10, 128, 70000, 6, None), (10, 128, 70000, 4, 3), (10, 128, 70000, 5, 3),   # the same, two tiles
+    (260, 64, 140000, 3, 3), (260, 64, 140000, 4, 3),   # the same, five tiles
 ])
 def test_splits(N, d, V, n_alpha, k):
     say(f"sweep splits N={N} d={d} V={V} A={n_alpha} k={k}")

@@ -122,7 +122,7 @@ __device__ __forceinline__ float sticky_max(float a, float b) { return (a != a |
 
 template <bool STREAM>
 __global__ __launch_bounds__(256) void ll_unembed_direction_kernel(const uint16_t* __restrict__ W, const float* __restrict__ v,
-                                                                   int V, int d, float* __restrict__ u, int n_padded,
+                                                                   int V, int d, float scale, float* __restrict__ u, int n_padded,
                                                                    float* __restrict__ block_max) {
   extern __shared__ __align__(16) float sv[];
   for (int j = threadIdx.x; j < d; j += blockDim.x) sv[j] = v[j];
@@ -165,7 +165,7 @@ __global__ __launch_bounds__(256) void ll_unembed_direction_kernel(const uint16_
     for (int i = 0; i < UD_ROWS; ++i) {
       const float x = wave_sum(acc[i]);
       if (r0 + i < V) {
-        if (lane == 0) u[r0 + i] = x;
+        if (lane == 0) u[r0 + i] = scale * x;
         largest = sticky_max(largest, fabsf(x));
       }
     }
@@ -546,6 +546,9 @@ Plan make_plan(const ll_shape* s, int k, int chunk_rows = CHUNK_ROWS) {
   return p;
 }
 
+// What a call is fastest with: room for the few-rows kernel's layout where that applies.
+size_t wanted_bytes(const Plan& plan) { return plan.few.ok && plan.few_total > plan.total ? plan.few_total : plan.total; }
+
 void (*few_kernel(int nj, int mu))(const FewArgs) {
 #define LL_FEW(NJ, MU) \
   if (nj == NJ && mu <= MU) return ll_lens_few_kernel<NJ, MU>
@@ -810,7 +813,8 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
 }
 
 struct SweepPlan {
-  size_t off_u, off_eu, off_shift, off_block_max, off_general, off_bound, off_stats, off_ztgt, off_top, off_panel, total;
+  size_t off_u, off_block_max, off_eu, off_shift, off_general, off_bound, off_stats, off_ztgt, off_top, off_panel, total;
+  size_t off_project, wanted;   // the projection's workspace where one alpha is left to it; wanted: what the call is fastest with
   int64_t lda;
   int n_padded;   // V in whole tiles
 };
@@ -824,7 +828,7 @@ int sweep_splits(int rows, int tiles) {
 }
 
 SweepPlan make_sweep_plan(const ll_shape* s, int n_alpha, int k = 1) {
-  SweepPlan p;
+  SweepPlan p = {};
   size_t off = 0;
   auto take = [&](size_t bytes) {
     const size_t at = off;
@@ -839,9 +843,10 @@ SweepPlan make_sweep_plan(const ll_shape* s, int n_alpha, int k = 1) {
   const size_t least = rows * ((tiles + SWEEP_MAX_TILES - 1) / SWEEP_MAX_TILES);
   if (partials < least) partials = least;
   p.off_u = take((size_t)p.n_padded * sizeof(float));
+  p.off_block_max = take(UD_BLOCKS * sizeof(float));
+  p.off_project = off;
   p.off_eu = take((size_t)p.n_padded * SWEEP_ROWS * sizeof(float));
   p.off_shift = take((size_t)p.n_padded * sizeof(float));
-  p.off_block_max = take(UD_BLOCKS * sizeof(float));
   p.off_general = take(sizeof(int));
   p.off_bound = take(rows * n_alpha * sizeof(unsigned));
   p.off_stats = take(partials * n_alpha * sizeof(float4));
@@ -849,7 +854,13 @@ SweepPlan make_sweep_plan(const ll_shape* s, int n_alpha, int k = 1) {
   p.off_top = take(partials * n_alpha * (k > 1 ? SWEEP_KS : 1) * sizeof(uint2));
   p.lda = ((int64_t)s->d + DK - 1) / DK * DK;
   p.off_panel = take(rows * (size_t)p.lda * sizeof(uint16_t));
-  p.total = off;
+  p.total = p.wanted = off;
+  if (n_alpha == 1) {
+    const Plan project = make_plan(s, k);
+    if (p.off_project + project.total > p.total) p.total = p.off_project + project.total;
+    p.wanted = p.off_project + wanted_bytes(project);
+    if (p.wanted < p.total) p.wanted = p.total;
+  }
   return p;
 }
 
@@ -880,7 +891,7 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
   if (workspace == nullptr || workspace_bytes < plan.total || ((uintptr_t)workspace & 255)) return LL_EWORKSPACE;
 
   unsigned char* ws = static_cast<unsigned char*>(workspace);
-  float* u = reinterpret_cast<float*>(ws + plan.off_u);
+  float* const u = reinterpret_cast<float*>(ws + plan.off_u);
   float* eu = reinterpret_cast<float*>(ws + plan.off_eu);
   float* shift_max = reinterpret_cast<float*>(ws + plan.off_shift);
   float* block_max = reinterpret_cast<float*>(ws + plan.off_block_max);
@@ -903,9 +914,19 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
   const size_t v_bytes = (size_t)d * sizeof(float);
   if (v_bytes > 64 * 1024)
     if (const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(direction), (size_t)SWEEP_MAX_D * sizeof(float)); rc != LL_OK) return rc;
-  hipLaunchKernelGGL(direction, dim3(UD_BLOCKS), dim3(256), v_bytes, stream, static_cast<const uint16_t*>(W_U), v, V, d, u, plan.n_padded,
-                     block_max);
+  const int first_rows = (int)(N < CHUNK_ROWS ? N : CHUNK_ROWS), first_splits = sweep_splits(first_rows, tiles);
+  const int each = (tiles + first_splits - 1) / first_splits;
+  // One strength is a projection whose bias is alpha u, which is the faster call for few rows and for many tiles a split (else
+  // its longer list and the copy of the bias cost more).  Whole calls, projection | the sweep's own kernel, us, d = 256 (N x V: tiles
+  // a split), arg max: 1500 x 4096 (1) 42 | 34, 4000 x 50257 (13) 193 | 218, 4000 x 128256 (32) 405 | 494; lists of two:
+  // 1500 x 128256 (12) 201 | 244, 4000 x 128256 (32) 417 | 545.
+  const bool as_projection = n_alpha == 1 && (N <= FEW_ROWS || each > 4);
+  hipLaunchKernelGGL(direction, dim3(UD_BLOCKS), dim3(256), v_bytes, stream, static_cast<const uint16_t*>(W_U), v, V, d,
+                     as_projection ? al.a[0] : 1.0f, u, plan.n_padded, block_max);
   LL_CHECK_S(hipGetLastError());
+  if (as_projection)
+    return project_impl(shape, ws + plan.off_project, workspace_bytes - plan.off_project, hidden, gamma, W_U, u, 0u, eps, k, target_ids, out_ids,
+                        out_p, out_logp, out_entropy, stream, nullptr);
   // Few alphas: the general form alone, without the tables and the launch that fills them.  Its cost grows with every alpha, the
   // factored one's hardly does after a split's first tile, where it looks at more candidates: the line moves up with fewer tiles a
   // split.  Whole calls, general | factored, us, d = 512 (N x V: tiles a split), arg max:
@@ -919,8 +940,6 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
   //   700 x 50257 (3)      A = 3  161 | 190     A = 4  192 | 193     A = 5  222 | 228    A = 6  253 | 231
   //   1500 x 50257 (5)     A = 3  236 | 275     A = 4  279 | 280     A = 5  324 | 319
   //   4000 x 128256 (32)   A = 3  1089 | 1230   A = 4  1281 | 1245
-  const int first_rows = (int)(N < CHUNK_ROWS ? N : CHUNK_ROWS), first_splits = sweep_splits(first_rows, tiles);
-  const int each = (tiles + first_splits - 1) / first_splits;
   const bool lists = k > 1, only_general = n_alpha <= (lists ? 3 : 4) + (each == 1 ? 2 : each <= 4 ? 1 : 0);
   if (!only_general) {
     const int n_bound = (int)(N < CHUNK_ROWS ? N : CHUNK_ROWS) * n_alpha;
@@ -1045,12 +1064,12 @@ int64_t ll_project_static_pass_rows(const ll_shape* shape, int k) {
 
 size_t ll_steer_sweep_workspace_bytes(const ll_shape* shape, int n_alpha) {
   if (!sweep_shape_ok(shape, n_alpha)) return 0;
-  return make_sweep_plan(shape, n_alpha).total;
+  return make_sweep_plan(shape, n_alpha).wanted;
 }
 
 size_t ll_steer_sweep_topk_workspace_bytes(const ll_shape* shape, int n_alpha, int k) {
   if (!sweep_shape_ok(shape, n_alpha, k)) return 0;
-  return make_sweep_plan(shape, n_alpha, k).total;
+  return make_sweep_plan(shape, n_alpha, k).wanted;
 }
 
 int ll_steer_sweep_topk(const ll_shape* shape, void* workspace, size_t workspace_bytes, const void* hidden, const void* gamma,
@@ -1071,8 +1090,7 @@ int ll_steer_sweep(const ll_shape* shape, void* workspace, size_t workspace_byte
 size_t ll_workspace_bytes(const ll_shape* shape, int k) {
   if (!shape_ok(shape, k)) return 0;
   if (shape->N == 0) return 256;
-  const Plan plan = make_plan(shape, k);
-  return plan.few.ok && plan.few_total > plan.total ? plan.few_total : plan.total;
+  return wanted_bytes(make_plan(shape, k));
 }
 
 int ll_project(const ll_shape* shape, void* workspace, size_t workspace_bytes, const void* hidden, const void* gamma,

@@ -46,6 +46,7 @@ def test_both_forms(k, length, general, d):
     (260, 192, 263, 9, 3),       # a last tile of seven ids
     (70, 128, 5000, 4, None), (70, 128, 5000, 5, None),   # one tile a split: few enough for the form without tables
     (70, 128, 5000, 3, 4), (70, 128, 5000, 4, 4), (70, 128, 5000, 1, 2),
+    (129, 72, 5000, 1, None), (300, 64, 140000, 1, 3), (300, 72, 140000, 1, None),   # one strength: the sweep's own kernel; a projection
     (70, 128, 5000, 6, None), (70, 128, 5000, 7, None), (70, 128, 5000, 5, 4), (70, 128, 5000, 6, 4),   # either side of that number
     (10, 128, 70000, 5, None), (10, 128, 70000, 6, None), (10, 128, 70000, 4, 3), (10, 128, 70000, 5, 3),   # the same, two tiles
     (260, 64, 140000, 3, 3), (260, 64, 140000, 4, 3),   # the same, five tiles

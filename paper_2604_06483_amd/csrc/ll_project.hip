@@ -634,16 +634,18 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
   // The direct-to-LDS kernel addresses rows with 32-bit byte offsets from a per-tile base.  It takes every other shape, a d
   // that is not a multiple of 64 in an instantiation of its own, which the longest list with a bias does not have.
   // 777 rows, d = 1608, V = 50257, k = 3 with a bias: 201 us, on the register-staged kernel 369
-  // It needs the rows padded, which is a launch; calls whose busiest workgroup has next to nothing to do (fewer than four stages
-  // of 64 columns, with a norm fewer than two) are faster without.  Whole calls, k = 1, direct-to-LDS | register-staged, us:
-  //   V = 37876, d = 168, 180 rows (three stages): 34.3 | 32.5, with a norm 34.2 | 35.6;   600 rows (six): 50.0 | 52.7
-  //   V = 37876, d = 72, 180 rows (two): 33.1 | 31.0, with a norm 33.3 | 34.8;             600 rows (four): 45.6 | 46.7
-  //   V = 37876, d = 40, 180 rows (one): 33.0 | 29.1, with a norm 32.7 | 31.5;             V = 4000, 5000 rows (two): 42.5 | 41.4
+  // It needs the rows padded, which is a launch; calls whose busiest workgroup has little to do (fewer than ten stages of 64
+  // columns, with a norm fewer than six) are as fast or faster without.  Whole calls, direct-to-LDS over register-staged, 129 to
+  // 1500 rows, V = 5000 to 128256, by the stages and the tiles they are of; k = 1 and k = 10:
+  //   no norm:  4 of 1 tile 1.00-1.08, 0.97-1.03;  4 of 2 1.03-1.16, 1.05-1.13;  6 of 2 0.99-1.10, 1.03-1.11;  8 of 2 0.94-1.06,
+  //             0.99-1.07;  8 of 4 0.89-0.92, 0.98-1.05;  10 of 1 0.84-0.89, 0.87-0.93;  12 of 2 0.88-0.99, 0.95-1.01
+  //   a norm:   2 of 1 0.97-1.04, 0.95-1.01;  2 of 2 1.02-1.10, 1.03-1.12;  4 of 2 0.94-1.06, 1.00-1.08;  4 of 4 0.89-0.93, 0.98-1.05;
+  //             6 of 2 0.90-1.01, 0.96-1.05;  8 of 1 0.80-0.85, 0.82-0.86
   const int tiles = (V + BM - 1) / BM;
   const int first_blocks = (int)(((N < CHUNK_ROWS ? N : CHUNK_ROWS) + BN - 1) / BN);   // (whatever the scratch: the same kernel)
   const int first_splits = even_splits(tiles, NUM_CU / first_blocks < MAX_PROJECT_SPLITS ? NUM_CU / first_blocks : MAX_PROJECT_SPLITS);
   const int64_t stages = (int64_t)((tiles + first_splits - 1) / first_splits) * (plan.lda / DK);
-  const bool worth_padding = stages >= (has_gamma ? 2 : 4);
+  const bool worth_padding = stages >= (has_gamma ? 6 : 10);
   const GemmKernel tail_kern = d % DK != 0 && worth_padding ? tail_topk_kernel(k, bias != nullptr) : nullptr;
   const bool dma = !(flags & LL_FLAG_REGISTER_STAGED) && (d % DK == 0 || tail_kern != nullptr) &&
                    (int64_t)BM * plan.lda * 2 < (int64_t)1 << 31 && (int64_t)CHUNK_ROWS * plan.lda * 2 < (int64_t)1 << 31;

@@ -25,8 +25,13 @@ def inputs(N, d, V, k):
     (520, 120, 5001, 12, False, True),    # two stages, seven chunks
     (777, 1608, 2050, 3, True, True),     # many stages
     (9000, 136, 600, 5, False, True),     # two row passes
-    (8200, 8, 5001, 1, False, True),      # one stage, three tiles a workgroup (fewer are left to the register-staged kernel)
+    (8200, 8, 5001, 1, False, True),      # one stage, three tiles a workgroup
     (8200, 56, 8000, 20, True, False),    # one stage, four tiles, rows only padded
+    (8200, 8, 12801, 1, False, True),     # one stage, seven tiles a workgroup (five and fewer are left to the register-staged kernel)
+    (8200, 56, 12801, 20, True, True),    # the same, seven chunks of the stage real
+    (1000, 72, 41000, 12, False, True),   # two stages, three tiles, the second stage with one chunk
+    (300, 328, 700, 32, False, True),     # six stages, one tile
+    (300, 648, 700, 3, True, False),      # eleven stages, rows only padded
 ])
 def test_ragged_hidden_size(N, d, V, k, with_bias, gamma):
     say(f"tail N={N} d={d} V={V} k={k} bias={with_bias} gamma={gamma}")
@@ -38,10 +43,10 @@ def test_ragged_hidden_size(N, d, V, k, with_bias, gamma):
     P.compare(got, ref, k, label="tail")
 
 
-@pytest.mark.parametrize("N", [200, 100])     # this kernel; the few-rows kernel
-def test_infinite_weights_stay_in_their_own_logit(N):
-    say(f"tail, infinite weights N={N}")
-    w = inputs(N, 200, 1000, 6)
+@pytest.mark.parametrize("N,d", [(200, 200), (100, 200), (200, 392)])     # register-staged; the few-rows kernel; this kernel
+def test_infinite_weights_stay_in_their_own_logit(N, d):
+    say(f"tail, infinite weights N={N} d={d}")
+    w = inputs(N, d, 1000, 6)
     w.W_U[3, -1] = float("-inf")     # the last chunk of a row, which lanes past the end fetch
     w.W_U[700, 0] = float("inf")     # the first chunk of a row, which is what follows the end of the row before
     a = LL.ll_project(w.hidden, w.gamma, w.W_U, w.cfg.eps, 6, w.target_ids)

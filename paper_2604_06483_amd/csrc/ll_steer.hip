@@ -40,11 +40,15 @@ __device__ __forceinline__ float sum_rows8(float x) {
 template <bool STREAM>
 __global__ __launch_bounds__(256) void ll_steer_colsum_kernel(const uint16_t* __restrict__ base, int64_t n_base,
                                                               const uint16_t* __restrict__ target, int64_t n_target,
-                                                              int d, int slices, float* __restrict__ out, float* __restrict__ sq) {
+                                                              int d, int slices, int col_blocks, int neighbours,
+                                                              float* __restrict__ out, float* __restrict__ sq) {
   __shared__ float red[2][4][SUM_COLS];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  const int col0 = blockIdx.x * SUM_COLS + (lane & 7) * 8;
+  // (workgroups are dealt round-robin over the 8 XCDs: `neighbours` column blocks in a row on one of them, or 0: as they come)
+  const int block = neighbours != 0 ? (int)(blockIdx.x % 8) * neighbours + (int)(blockIdx.x / 8) : (int)blockIdx.x;
+  if (block >= col_blocks) return;
+  const int col0 = block * SUM_COLS + (lane & 7) * 8;
   const int64_t step = (int64_t)slices * SUM_ROWS;
   const int64_t n_max = n_base > n_target ? n_base : n_target;
 
@@ -90,7 +94,7 @@ __global__ __launch_bounds__(256) void ll_steer_colsum_kernel(const uint16_t* __
     }
   __syncthreads();
   if (wave != 0) return;
-  const int col = blockIdx.x * SUM_COLS + lane;
+  const int col = block * SUM_COLS + lane;
   const float sb = (red[0][0][lane] + red[0][1][lane]) + (red[0][2][lane] + red[0][3][lane]);
   const float st = (red[1][0][lane] + red[1][1][lane]) + (red[1][2][lane] + red[1][3][lane]);
   if (slices > 1) {
@@ -104,7 +108,7 @@ __global__ __launch_bounds__(256) void ll_steer_colsum_kernel(const uint16_t* __
   if (col < d) out[col] = diff;
   if (sq != nullptr) {
     const float ss = wave_sum(diff * diff);
-    if (lane == 0) sq[blockIdx.x] = ss;
+    if (lane == 0) sq[block] = ss;
   }
 }
 
@@ -445,9 +449,15 @@ int ll_steer_vector(const void* base, int64_t n_base, const void* target, int64_
   // a slice for what the workgroup has in flight at once
   int64_t slices = workspace == nullptr ? 1 : (n_max + SUM_ROWS * SUM_LOADS - 1) / (SUM_ROWS * SUM_LOADS);
   if (slices > STEER_SLICES) slices = STEER_SLICES;
-  const bool stream_rows = (double)(n_base + n_target) * d * 2 > STREAM_BYTES;
-  hipLaunchKernelGGL(stream_rows ? ll_steer_colsum_kernel<true> : ll_steer_colsum_kernel<false>, dim3(col_blocks, (unsigned)slices), dim3(256), 0, stream, b, n_base, t, n_target, d,
-                     (int)slices, slices > 1 ? part : out_v, sq);
+  // Rows that are not whole 128-byte lines: two column blocks share lines, so they go past no cache and next to each other on one
+  // XCD, whose L2 then has the line for both.  20000 + 20000 rows of d = 8200, with the hint | without | neighbours, us: 190 | 175 | 130
+  // (d = 1000, 40000 + 40000: 51 without, 42; d = 264, whose five blocks would leave three XCDs idle: 22, 30).
+  const bool whole_lines = ((uintptr_t)base | (uintptr_t)target | (uintptr_t)d * 2) % 128 == 0;
+  const bool stream_rows = whole_lines && (double)(n_base + n_target) * d * 2 > STREAM_BYTES;
+  const unsigned neighbours = whole_lines || col_blocks < 16 ? 0 : (col_blocks + 7) / 8;
+  hipLaunchKernelGGL(stream_rows ? ll_steer_colsum_kernel<true> : ll_steer_colsum_kernel<false>,
+                     dim3(neighbours == 0 ? col_blocks : 8 * neighbours, (unsigned)slices), dim3(256), 0, stream, b, n_base, t, n_target, d, (int)slices,
+                     (int)col_blocks, (int)neighbours, slices > 1 ? part : out_v, sq);
   LL_HIP_CHECK(hipGetLastError());
   if (slices > 1) {
     hipLaunchKernelGGL(ll_steer_reduce_kernel, dim3(col_blocks), dim3(256), 0, stream, (const float*)part, (int)slices, n_base,

@@ -20,7 +20,7 @@ def rows(n, d, seed, offset=0.0):
 
 @pytest.mark.parametrize("use_ws", [False, True])
 @pytest.mark.parametrize("nb,nt,d", [(1, 16, 8192), (16, 2, 8), (17, 1, 72), (16, 16, 8200), (128, 3, 1032), (3, 129, 1032),
-                                     (2000, 7689, 200)])
+                                     (2000, 7689, 200), (300, 40, 1000), (130, 700, 1096)])
 def test_direction(nb, nt, d, use_ws):
     say(f"steer direction nb={nb} nt={nt} d={d} ws={use_ws}")
     base, target = rows(nb, d, nb), rows(nt, d, nt + 1, 0.5)

@@ -13,21 +13,26 @@ import subprocess
 import pytest
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-SRC = os.path.join(ROOT, "paper_2604_06483_amd", "csrc", "ll_project.hip")
+CSRC = os.path.join(ROOT, "paper_2604_06483_amd", "csrc")
+# source, its direct-to-LDS kernels, and how many there are
+SOURCES = {
+    "ll_project": ("ll_lens_gemm_dma_kernel", 10),             # four top-k list lengths, each with and without a bias, and the two steering sweeps
+    "ll_project_tail": ("ll_lens_gemm_dma_tail_kernel", 11),   # ragged hidden sizes: the same but the longest list with a bias; the two general sweeps
+}
 
 pytestmark = pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not on PATH")
 
 
-@pytest.fixture(scope="module")
-def asm(tmp_path_factory):
-    out = tmp_path_factory.mktemp("isa") / "ll_project.s"
+@pytest.fixture(scope="module", params=sorted(SOURCES))
+def source(request, tmp_path_factory):
+    """(assembly, name of the direct-to-LDS kernels in it, their number)"""
+    out = tmp_path_factory.mktemp("isa") / (request.param + ".s")
     cmd = ["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-S", "--cuda-device-only",
            "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument",
-           "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2604_06483_amd", "csrc"),
-           SRC, "-o", str(out)]
+           "-I", os.path.join(ROOT, "include"), "-I", CSRC, os.path.join(CSRC, request.param + ".hip"), "-o", str(out)]
     res = subprocess.run(cmd, capture_output=True, text=True)
     assert res.returncode == 0, res.stderr[-2000:]
-    return out.read_text()
+    return (out.read_text(), *SOURCES[request.param])
 
 
 def kernel_bodies(asm_text, needle):
@@ -39,9 +44,10 @@ def kernel_bodies(asm_text, needle):
     return bodies
 
 
-def test_m0_is_only_written_by_the_lds_base_setter(asm):
-    bodies = kernel_bodies(asm, "ll_lens_gemm_dma_kernel")
-    assert len(bodies) == 10, sorted(bodies)         # four top-k list lengths, each with and without a bias, and the two steering sweeps
+def test_m0_is_only_written_by_the_lds_base_setter(source):
+    asm, kernel, count = source
+    bodies = kernel_bodies(asm, kernel)
+    assert len(bodies) == count, sorted(bodies)
     for name, ins in bodies.items():
         loads = [i for i, l in enumerate(ins) if l.startswith("global_load_lds_dwordx4")]
         assert len(loads) >= 16 + 36, (name, len(loads))          # main loop + prologue
@@ -57,25 +63,27 @@ def test_m0_is_only_written_by_the_lds_base_setter(asm):
             assert not op.startswith(("v_movrel", "s_movrel", "s_sendmsg", "ds_gws", "s_set_gpr_idx")), (name, l)
 
 
-def test_projection_kernels_fit_one_wave_per_simd_without_scratch(asm):
+def test_projection_kernels_fit_one_wave_per_simd_without_scratch(source):
+    asm, kernel, count = source
     meta = {}
     for m in re.finditer(r"\.name:\s+(\S+)\n(.*?)\.wavefront_size", asm, re.S):
         block = m.group(2)
         get = lambda key: int(re.search(r"\." + key + r":\s+(\d+)", block).group(1))
         meta[m.group(1)] = dict(vgpr=get("vgpr_count"), scratch=get("private_segment_fixed_size"),
                                 vspill=get("vgpr_spill_count"))
-    dma = {k: v for k, v in meta.items() if "ll_lens_gemm_dma_kernel" in k}
-    assert len(dma) == 10
+    dma = {k: v for k, v in meta.items() if kernel in k}
+    assert len(dma) == count
     for name, v in dma.items():
         assert v["vgpr"] <= 512 and v["scratch"] == 0 and v["vspill"] == 0, (name, v)
 
 
-def test_no_valu_reads_an_sgpr_a_valu_wrote_within_two_instructions(asm):
+def test_no_valu_reads_an_sgpr_a_valu_wrote_within_two_instructions(source):
     """gfx950 needs two wait states between a VALU instruction that writes an SGPR (a comparison,
     a carry-out) and a VALU instruction that reads it.  The compiler keeps that distance for its
     own instructions but does not look inside inline asm: check the hand-written selects and
     add-with-carry of the top-k epilogue."""
-    bodies = {**kernel_bodies(asm, "ll_lens_gemm_dma_kernel"), **kernel_bodies(asm, "ll_lens_gemm_kernel")}
+    asm, kernel, _ = source
+    bodies = {**kernel_bodies(asm, kernel), **kernel_bodies(asm, "ll_lens_gemm_kernel")}
     assert bodies
     checked = 0
     for name, ins in bodies.items():
@@ -94,3 +102,57 @@ def test_no_valu_reads_an_sgpr_a_valu_wrote_within_two_instructions(asm):
                     dests = ops[1].split(",")[:2]            # destination, and carry-out where there is one
                     assert all(sreg != dd.strip() for dd in dests), (name, prev, l)
     assert checked > 1000
+
+
+def registers(operand):
+    """The vector registers that an operand names."""
+    m = re.fullmatch(r"v\[(\d+):(\d+)\]|v(\d+)", operand.strip())
+    if not m:
+        return set()
+    return {int(m.group(3))} if m.group(3) else set(range(int(m.group(1)), int(m.group(2)) + 1))
+
+
+def written(instruction):
+    return registers(instruction.split(None, 1)[1].split(",")[0]) if instruction.startswith("v_") and " " in instruction else set()
+
+
+def wait_states(instruction):
+    nop = re.fullmatch(r"s_nop (\d+)", instruction)
+    if instruction.startswith("v_mfma_f32_16x16x4"):
+        return 8                                          # passes of four cycles
+    return 1 + int(nop.group(1)) if nop else 1
+
+
+def test_the_sweeps_products_and_broadcasts_keep_their_distances(source):
+    """The steering sweep writes its fp32 matrix products and its DPP broadcasts as instructions, whose hazards the compiler does not
+    see: two wait states between a vector instruction that writes an operand and the product or the DPP instruction that reads it,
+    and 18 between a product and a vector or memory instruction that touches its result."""
+    asm, kernel, _ = source
+    products = broadcasts = 0
+    for name, ins in kernel_bodies(asm, kernel + r"\w*SweepEpilogue").items():
+        ins = [l.split(";")[0].strip() for l in ins]
+        ins = [l for l in ins if l]
+        for i, l in enumerate(ins):
+            product = l.startswith("v_mfma_f32_16x16x4_f32")
+            if not product and not l.startswith("v_subrev_f32_dpp"):
+                continue
+            operands = l.split(None, 1)[1].split(",")
+            reads = set().union(*(registers(o) for o in operands[1:])) if product else registers(operands[1])
+            states, j = 0, i - 1
+            while j >= 0 and states < 2:
+                assert ins[j].startswith("v_mfma") or not written(ins[j]) & reads, (name, ins[j], l)
+                states += wait_states(ins[j])
+                j -= 1
+            if not product:
+                broadcasts += 1
+                continue
+            products += 1
+            result = registers(operands[0])
+            states, j = 0, i + 1
+            while j < len(ins) and states < 18:
+                if ins[j].startswith(("v_", "global_", "ds_")) and not ins[j].startswith("v_mfma") and " " in ins[j]:
+                    touched = set().union(*(registers(o) for o in ins[j].split(None, 1)[1].split(",")))
+                    assert not touched & result, (name, l, ins[j])
+                states += wait_states(ins[j])
+                j += 1
+    assert products == 96 and broadcasts == 20            # two kernels of 48 products; nine limits and a spread, in each

@@ -88,13 +88,14 @@ int ll_project(const ll_shape* shape, void* workspace, size_t workspace_bytes,
  *          i.e. p_i / sum_{j in top-k} p_j; entropy and target log-prob stay full-vocabulary.
  *          LL_FLAG_REGISTER_STAGED: run this call on the register-staged kernel, which applies the
  *          RMSNorm scaling inside the A-tile load of the GEMM, even where the default applies (the
- *          direct-to-LDS kernel fed from a normalised bf16 panel written once per row pass).  Both compute the same quantities from the same bf16 operands (the
- *          normalised row is rounded to bf16 identically); they use different MFMA shapes, so a
+ *          direct-to-LDS kernel fed from a normalised bf16 panel written once per row pass).  Both
+ *          compute the same quantities from the same bf16 operands (the normalised row is rounded
+ *          to bf16 identically); they use different MFMA shapes, so a
  *          logit's fp32 partial sums are added in a different order and results agree to fp32
  *          accumulation rounding.  For tuning and tests.  Without the flag a call takes the
  *          register-staged kernel only where d is not a multiple of 64 and either the call is so
  *          small that padding the rows is not worth a launch, or k > 20 with a bias; up to 128
- *          rows run on a kernel of their own, which the flag also switches off.
+ *          rows run on a kernel of their own where it is the faster one, which the flag also switches off.
  *          Any other bit set is LL_EINVAL.
  */
 #define LL_FLAG_TOPK_SOFTMAX    1u
@@ -139,8 +140,8 @@ int ll_project_timed(const ll_shape* shape, void* workspace, size_t workspace_by
  * All calls on one GPU share that GPU's buffer: two calls whose kernels may overlap on the same
  * GPU (different streams, different threads) race; calls queued on one stream are safe.  The
  * buffer keeps the last call's contents; the one part that has to start at zero (the top-k bounds
- * the vocabulary splits share) is cleared by a small fill kernel at the start of every call, as
- * in ll_project, never by a memset (the call stays capturable).  The first call on a
+ * the vocabulary splits share, where there are any) is cleared by the call's own kernels, as in
+ * ll_project, never by a memset (the call stays capturable).  The first call on a
  * device looks up the buffer's address (no allocation) and sets a kernel attribute: make it
  * outside stream capture.
  */

@@ -29,7 +29,11 @@ namespace {
 // Bound by the read of W_U.  Kernel alone, W_U of 128256 x 8192 (2.1 GB), 81 rows, k = 20: 333 us =
 // 6.3 TB/s, against 473 us on the 256-row tiles of the direct-to-LDS kernel; 151936 x 2560, 37 rows: 129 us
 // = 6.0 TB/s against 212 us.  A loop that only loads W this way reaches 6.6 TB/s (without the
-// non-temporal hint 5.9); loads of 16 rows x 64 B, which need no exchange of halves, 6.1.
+// non-temporal hint 5.9; W_U of 2.1 GB); loads of 16 rows x 64 B, which need no exchange of halves, 6.1.
+// The hint is not chosen by size.  Whole calls repeated on one W_U, with it | without, us: 24 rows, d = 4096: 60 MB 50 | 46,
+// 240 MB 65 | 51, 400 MB 101 | 109; d = 1024: 60 MB 27 | 26, 240 MB 56 | 58, 400 MB 83 | 91; 16 rows, d = 4096, 1.05 GB:
+// 172 | 192.  It costs where the Infinity Cache could keep W_U, and where rows are not whole lines of 128 bytes and a
+// line serves two stages (16 rows, d = 4104, 1.05 GB: 286 | 215).  The 256-row tiles need 68 to 445 us for these.
 // ---------------------------------------------------------------------------------------
 constexpr int FEW_WAVES = 8;
 constexpr int FEW_THREADS = 64 * FEW_WAVES;
@@ -265,8 +269,8 @@ __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs 
   if (tid == 0) s_over = 0;
   __syncthreads();
   // Threshold of a row: the k-th largest of its 32 partial maxima (the k entries that are those
-  // maxima reach it, so nothing below it can be in the part's top k).  About 1.5 k of the part's 512
-  // entries pass, whatever their distribution, as long as few are equal.  32 lanes a row, rank by counting.
+  // maxima reach it, so nothing below it can be in the part's top k).  Up to k = 20 or so about 1.5 k of the part's
+  // 512 entries pass, as long as they lie anywhere and few are equal.  32 lanes a row, rank by counting.
   for (int n = tid >> 5; n < p.rows; n += FEW_THREADS / 32) {
     const int q = tid & 31;
     const float mine = s_max[n][q];

@@ -192,7 +192,7 @@ def test_steer_sweep_rejects_bad_arguments_before_any_device_work():
     s = LL.ll_shape(16, 64, 300)
     need = LL.ll_steer_sweep_workspace_bytes(16, 64, 300, 9)
     assert need > 0 and need % 256 == 0
-    assert LL.ll_steer_sweep_workspace_bytes(16, 72, 300, 9) > 0         # any multiple of 8 (the register-staged kernel)
+    assert LL.ll_steer_sweep_workspace_bytes(16, 72, 300, 9) > 0         # any multiple of 8
     assert LL.ll_steer_sweep_workspace_bytes(16, 76, 300, 9) == 0        # d not a multiple of 8
     assert LL.ll_steer_sweep_workspace_bytes(16, 40960, 300, 9) > 0      # the largest hidden size: v is held in LDS
     assert LL.ll_steer_sweep_workspace_bytes(16, 40968, 300, 9) == 0
@@ -202,7 +202,7 @@ def test_steer_sweep_rejects_bad_arguments_before_any_device_work():
     assert LL.ll_steer_sweep_workspace_bytes(16, 64, 2, 9, 3) == 0       # k > V
     assert LL.ll_steer_sweep_workspace_bytes(16, 64, 300, 0) == 0
     assert LL.ll_steer_sweep_workspace_bytes(16, 64, 300, LL.LL_SWEEP_MAX + 1) == 0
-    # the table of alpha * (W_U v) is part of the workspace: more alphas, more bytes
+    # every alpha has its partial results: more alphas, more bytes
     assert LL.ll_steer_sweep_workspace_bytes(16, 64, 300, 9) > LL.ll_steer_sweep_workspace_bytes(16, 64, 300, 1)
     call = lambda **kw: L.ll_steer_sweep(*[{**dict(shape=s, ws=_fake(4096 * 256), wsb=1 << 30, h=f, g=f, w=f, eps=1e-5, v=f,
                                                    al=al, n=9, t=f, ids=f, p=f, lp=f, e=f, st=None), **kw}[k]

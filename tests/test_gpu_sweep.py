@@ -67,7 +67,7 @@ def compare_sweep(got, want, rows, label, inputs):
     (520, 1024, 33000, 5, False),    # rows already normalised, many tiles per split
     (40, 64, 300, 1, True),          # a single alpha, one K step
     (9000, 128, 1000, 2, True),      # two row passes: the second starts at row 8192 of every output
-    (200, 328, 1000, 9, True),       # d not a multiple of 64: the register-staged kernel, norm inside its A-tile load
+    (200, 328, 1000, 9, True),       # d not a multiple of 64: the kernel that clears the last stage's padding
     (130, 72, 600, 4, False),        # the same with rows that are already normalised
     (40, 40960, 300, 2, True),       # the largest hidden size admitted (the direction fills the LDS)
 ])
@@ -98,10 +98,10 @@ def test_sweep_matches_oracle(N, d, V, n_alpha, gamma):
 
 
 @pytest.mark.parametrize("N,d,V,n_alpha,k,gamma", [
-    (300, 512, 5000, 9, 3, True),     # nine alphas, two passes of the kernel (5 + 4), two row blocks
+    (300, 512, 5000, 9, 3, True),     # nine alphas, two row blocks
     (257, 128, 777, 5, 4, True),      # the longest list, ragged vocabulary
-    (64, 256, 4096, 4, 2, False),     # one pass; rows already normalised
-    (200, 328, 1000, 9, 3, True),     # d not a multiple of 64: the register-staged kernel
+    (64, 256, 4096, 4, 2, False),     # rows already normalised
+    (200, 328, 1000, 9, 3, True),     # d not a multiple of 64
     (9000, 128, 1000, 6, 2, True),    # two row passes
     (33, 64, 3, 2, 3, True),          # k = V: every token listed
 ])
@@ -182,7 +182,7 @@ def test_sweep_full_size_layer(name):
     want = O.steer_sweep(*inputs, tgt.cpu().numpy()[rows], k=3)
     mism, total = compare_sweep(got, want, rows, name, inputs)
     say(f"sweep {name}: {mism} of {total} arg max ids differ from the oracle's, each a near-tie")
-    # the same rows with the three most likely tokens per alpha (the paper's figures list k = 3): three passes over W_U
+    # the same rows with the three most likely tokens per alpha (the paper's figures list k = 3)
     got3 = LL.ll_steer_sweep(rows_h, w.gamma, w.W_U, cfg.eps, v, ALPHAS9, tgt, k=3)
     torch.cuda.synchronize()
     mism, total = compare_sweep(got3, want, rows, name + " k=3", inputs)

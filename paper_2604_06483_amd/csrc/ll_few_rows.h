@@ -270,7 +270,7 @@ __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs 
   __syncthreads();
   // Threshold of a row: the k-th largest of its 32 partial maxima (the k entries that are those
   // maxima reach it, so nothing below it can be in the part's top k).  Up to k = 20 or so about 1.5 k of the part's
-  // 512 entries pass, as long as they lie anywhere and few are equal.  32 lanes a row, rank by counting.
+  // entries pass, as long as they lie anywhere and few are equal.  32 lanes a row, rank by counting.
   for (int n = tid >> 5; n < p.rows; n += FEW_THREADS / 32) {
     const int q = tid & 31;
     const float mine = s_max[n][q];

@@ -27,16 +27,18 @@ struct GemmArgs {
   int rows, d, V, k, splits, tiles, row_blocks;
   // steering sweep only (Sec. 3.4, Eq. 3 for several alpha in one pass):
   const float* u;           // [tiles * BM] fp32: W_U v, zero padded
-  const float* eu;          // [tiles * BM / 16, 32, 16]: rows of e^(alpha u) and alpha u e^(alpha u) of 16 ids (see ll_epilogue_sweep.h)
+  const float* eu;          // [2, tiles * BM / 16, 16, 16]: rows of e^(alpha u) and alpha u e^(alpha u) of 16 ids (see ll_epilogue_sweep.h)
   const float* shift_max;   // [tiles * BM / 16, 16]: per alpha the largest alpha u of 16 ids, with a margin; entry 15 the largest spread of any alpha u among them
+  const float* shift_min;   // [tiles * BM / 16, 16]: per alpha the least
+  const float* shift_tile;  // [tiles, 16]: per alpha the largest of a tile, with the margin
   const int* sweep_general; // nonzero: some |alpha u| is too large for the factored form; nullptr: the general form in any case
   float4* sweep_stats;      // [rows, n_alpha, splits]      (reference, S, T)
   float* sweep_ztgt;        // [rows, splits]               logit of the target id at alpha = 0
   uint2* sweep_top;         // [rows, n_alpha, splits, KS]  (logit bits, id), sorted
-  int n_alpha;
+  int n_alpha, zero_alpha;  // zero_alpha: of nine, one that is zero, or -1
   float alphas[LL_SWEEP_MAX];
   // sharing top-k thresholds between the vocabulary splits of a row (nullptr: off)
-  unsigned* bound;          // [rows] (sweep: [n_alpha, rows]) lower bounds on each row's k-th best logit, as ordered keys; zero at launch
+  unsigned* bound;          // [rows] (sweep: [k, n_alpha, rows]) lower bounds on each row's k-th best logit, as ordered keys; zero at launch
 };
 
 using GemmKernel = void (*)(const GemmArgs);
@@ -422,7 +424,7 @@ struct TopKEpilogue {   // a5..a7: softmax statistics, k best logits, target log
   using State = RowState<KR>;
   static constexpr bool RELOAD_FRAGMENTS = false;
   static __device__ __forceinline__ bool skip(const GemmArgs&) { return false; }
-  static __device__ __forceinline__ void init(State& st, const GemmArgs& p, int my_row) {
+  static __device__ __forceinline__ void init(State& st, const GemmArgs& p, int my_row, int) {
     st.init();
     st.tgt = (p.target != nullptr && my_row < p.rows) ? p.target[my_row] : -1;
   }

@@ -31,17 +31,20 @@ namespace {
 // rarely.  A sweep with larger shifts anywhere takes the general form, which exponentiates every shifted logit
 // against the list's head, and so does one of few alphas: the products cost the same for any number up to eight.
 //
-// The shifted logits themselves are formed only where a group might hold a listed token: when its largest
-// logit plus its largest shift (a table entry) beats the list's last entry for some lane.  The lists know the other
-// splits' thresholds (sweep_exchange), so past a split's first tile that is rare.
+// A tile goes in three passes over its accumulators, groups of 16 ids (one row of 16 x 16 accumulator tiles) each:
+//   1. the largest logit of every group and of the tile (sweep_scan): which groups may hold a listed token, and whether the
+//      references have to move, decided once a tile instead of beside every group's products;
+//   2. the sums (sweep_sums): nothing but products and, between them, the exponentials of the next sixteen rows;
+//   3. the shifted logits themselves (sweep_lists), only of the groups that pass 1 has marked.
+// The lists know the other splits' logits (sweep_take_bounds), so past a split's first tile that is rare; and in a split's first
+// tile, where every group would be marked, the splits tell each other their best logits between the passes (sweep_announce).
+// The loops over groups are not unrolled where they are long, so that the code stays in the instruction cache.
 //
-// Groups of 16 ids (one row of 16 x 16 accumulator tiles) in a loop that is not unrolled, so that the code stays in the
-// instruction cache.
-//
-// Measured, whole call, nine alphas: 1500 rows, d = 4096, V = 128256, arg max: 2.14 ms with nine exponentials a logit, 1.54 ms
-// now (a plain projection of the rows takes 1.36 ms and u = W_U v 0.16 ms); 500 rows, d = 2560, V = 151936, lists of
-// three: 2.09 ms (two passes of five and four alphas, over 64 splits), 0.65 ms now.  What is left above the projection is
-// the unembedded direction, a read of W_U, and vector work beside the matrix pipe: an exponential a logit and its products.
+// Bound by the vector ALU, on which the fp32 products run too: 32 of 32 cycles a group (48 with nine alphas none of which is zero)
+// and some 120 other instructions.  Cycles of a tile's epilogue, with all of it in one pass | now: arg max, 1500 rows, d = 4096,
+// V = 128256, nine alphas: first tile 89 900 | 74 600, the others 62 000 | 50 100 falling to 44 000 (sums 33 800, scan 3500; the
+// contraction 145 000); lists of three, 500 rows, d = 2560, V = 151936: 184 700 | 96 400, then 103 000 falling to 78 900 | 69 700
+// falling to 55 600 (contraction 100 000).  Whole calls: 1505 | 1444 us and 647 | 557 us.
 // ---------------------------------------------------------------------------------------
 constexpr int SWEEP_MAX = LL_SWEEP_MAX;
 constexpr int SWEEP_KS = LL_SWEEP_KMAX;
@@ -51,29 +54,15 @@ constexpr int SWEEP_GROUP = 16;
 constexpr unsigned SWEEP_NO_ID = 0xffffu;         // list entry that stands for "below the row's shared bound"
 constexpr int SWEEP_MAX_TILES = 255;              // tiles per split: ids relative to the split's first fit 16 bits
 
-// Table rows of a group of 16 ids, 16 floats each: rows 0 .. 15 are the first A operand, rows 16 .. 31 the second.
-// Up to eight alphas: E of alpha a in row a, alpha E u in row 8 + a, and no second operand.  Nine: E in row a, alpha E u in row 16 + a.
-constexpr int SWEEP_ROWS = 32;
+// Table rows of a group of 16 ids, 16 floats each.  Up to eight alphas: E of alpha a in row a, alpha E u in row 8 + a.  Nine alphas
+// one of which is zero: the same of the other eight; with E = 1 and alpha E u = 0 the zero one's sums are plain sums of e and e z.
+// Nine others: alpha E u in row a, and E in row a of a second table behind the first.
+constexpr int SWEEP_ROWS = 16;
 constexpr int SWEEP_FEW = 4;          // code for all alphas is branched over past these
 constexpr int SWEEP_SPLIT_ROWS = 8;   // most alphas with both factors in one operand
 
-// What a lane reads for one group.
-struct SweepTable {
-  float4 a0, a1;   // its elements of the A operands: row l % 16, ids 4 (l / 16) ..
-  float u;         // u of id l % 16
-  float shift;     // largest alpha u of the group with a margin, of alpha number l % 16
-};
-
-template <bool GENERAL>
-__device__ __forceinline__ void sweep_load_table(SweepTable& t, int g0, const GemmArgs& p) {
-  const int lane = threadIdx.x & 63, l = lane & 15;
-  t.u = p.u[g0 + l];
-  if (GENERAL) return;
-  t.shift = p.shift_max[g0 + l];
-  const float4* const eu = reinterpret_cast<const float4*>(p.eu + (int64_t)(g0 / SWEEP_GROUP) * SWEEP_ROWS * SWEEP_GROUP) + (lane >> 4);
-  t.a0 = eu[4 * l];
-  t.a1 = eu[4 * l + SWEEP_ROWS * SWEEP_GROUP / 8];   // (unused with up to eight alphas; no branch around a load: the waits stay counted)
-}
+// u of id g0 + l % 16 (the general form reads no more of the tables).
+__device__ __forceinline__ float sweep_load_u(int g0, const GemmArgs& p) { return p.u[g0 + (threadIdx.x & 15)]; }
 
 // Entry I of the lane's block of 16, as a DPP operand of the instruction that uses it.
 template <int I>
@@ -108,17 +97,19 @@ struct SweepState {
   // registers are short.
   static constexpr int PER = GENERAL ? 1 : 2, IDS = (KS + PER - 1) / PER;
   __device__ __forceinline__ unsigned id(int a, int j) const { return (li[a][j / PER] >> (16 * (j % PER))) & 0xffffu; }
-  // Factored form, per row block j of the wavefront (rows 16 j + l % 16): reference, and as D operands (alphas 4 (l / 16) + r) S, with
-  // up to eight alphas T2 in the rows 8 + a of it, and T1, with nine alphas T.
+  // Factored form, per row block j of the wavefront (rows 16 j + l % 16): reference, and as D operands (rows 4 (l / 16) + r) S of alpha
+  // a in row a and T in row 8 + a; of nine alphas that have a second table T in row a, and S in `more`.  Of nine of which one is
+  // zero, more[j][0] and more[j][1] are the lane's share (ids 4 (l / 16) + r) of its S and T, the plain sums.
   float ref[4];
-  f32x4 s[4], t[4];
+  f32x4 st[4], more[4];
+  float next_shift;                          // of the tile that comes next, largest alpha u of alpha number l % 16
   // General form, of the lane's own row.
   float gs[SWEEP_MAX], gt[SWEEP_MAX];
   // Of the lane's own row (64 w + l):
   float lv[SWEEP_MAX][KS];                   // best shifted logits, sorted
   unsigned li[SWEEP_MAX][IDS];
   float z_tgt;
-  int tgt, id0;                              // id0: first id of the split
+  int tgt, id0, split;                       // id0: first id of the split
 };
 
 // Register j of lane block g <-> register g of lane block j (see load_group).
@@ -241,38 +232,15 @@ __device__ __forceinline__ const_f32_ptr sweep_alphas() {
   return (const_f32_ptr)(args + offsetof(GemmArgs, alphas));
 }
 
-// Lists, for every alpha, those of the group's logits above lim that beat its list's last entry, in id order.  All alphas
-// share one walk over the logits (their shifts are small: mostly the same ids), and all lanes stay on (a lane without a
-// candidate left takes part with one that ranks nowhere).
-template <int KS>
-__device__ __forceinline__ void sweep_collect_all(const float (&x)[16], float lim, SweepState<KS, false>& st, float u, unsigned first,
-                                                  const GemmArgs& p) {
-  const_f32_ptr alphas = sweep_alphas();
-  unsigned mask = above_mask16(x, lim);
-  while (__builtin_amdgcn_ballot_w64(mask != 0) != 0) {
-    const int o = mask != 0 ? __builtin_ctz(mask) : 0;
-    const float z = mask != 0 ? pick16(x, o) : -INFINITY;
-    const float uo = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * o, __float_as_int(u)));   // (lanes 0 .. 15 hold the group's u)
-    const unsigned id = first + (unsigned)o;
-    mask &= mask - 1;
-#pragma unroll
-    for (int a = 0; a < SWEEP_MAX; ++a) {
-      if (a == SWEEP_FEW && p.n_alpha <= SWEEP_FEW) break;
-      sweep_insert<KS, false>(st, a, fmaf(alphas[a], uo, z), id);
-      LL_SCHED_FENCE();
-    }
-  }
-}
-
 // The general form: every shifted logit exponentiated against the list's head (which is at least every shifted logit seen).
 template <int KS>
-__device__ __forceinline__ void sweep_group_general(const float (&x)[16], SweepState<KS, true>& st, unsigned first, const SweepTable& tab,
+__device__ __forceinline__ void sweep_group_general(const float (&x)[16], SweepState<KS, true>& st, unsigned first, float u,
                                                     const GemmArgs& p) {
 #pragma unroll
   for (int a = 0; a < SWEEP_MAX; ++a) {
     if (a < p.n_alpha) {
       float w[16];
-      const float shift = p.alphas[a] * tab.u;
+      const float shift = p.alphas[a] * u;
       each16([&](auto o) { w[o] = x[o] + bcast16<o>(shift); });
       const float most = max16(w);
       if (most > st.lv[a][KS - 1]) {
@@ -297,173 +265,335 @@ __device__ __forceinline__ void sweep_group_general(const float (&x)[16], SweepS
   }
 }
 
-// acc[alpha, row] += sum over lane blocks of a[alpha, id] b[id, row].  Written as an instruction: given the builtin the compiler
-// wants the results in AGPRs, which the contraction fills.  So the waits are ours: two states between a vector instruction
-// that writes an operand and the product that reads it, two more between products on one accumulator (there is always another
-// one in between, or the s_nop here), and 18 before a vector instruction reads a result.
-__device__ __forceinline__ void sweep_product(f32x4& acc, float a, float b) {
-  asm volatile("s_nop 1\n\tv_mfma_f32_16x16x4_f32 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+// The largest and the least of three, as one instruction (the compiler's fmaxf first makes every operand that it can't trace a
+// quiet number).
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
 }
-__device__ __forceinline__ void sweep_first_product(f32x4& acc, float a, float b) {   // acc = 0 + ...
-  asm volatile("s_nop 1\n\tv_mfma_f32_16x16x4_f32 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
+__device__ __forceinline__ float min3(float a, float b, float c) {
+  float r;
+  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
 }
 
-// The products of one group and row block, which start from zero and are added to the row's sums while the next block's
-// products run: the instruction does not round to nearest, and a chain of them over a split of 51 tiles left S too small by
-// 1.1e-5 of itself and the entropy by 1e-4 (6000 rows, V = 128256).  Four products of a group and one addition a group have
-// the error that a sum of exponentials in vector instructions has.
-struct SweepPending {
-  f32x4 s[2], t[2];   // of row blocks of this parity
-};
-template <int KS>
-__device__ __forceinline__ void sweep_fold(SweepState<KS, false>& st, SweepPending& pend, int block) {
-  const int c = block & 1;
-  asm volatile("" : "+v"(pend.s[c]), "+v"(pend.t[c]));   // (here, not earlier)
-  st.s[block] += pend.s[c];
-  st.t[block] += pend.t[c];
-  asm volatile("" : "+v"(st.s[block]), "+v"(st.t[block]));
+// The lane's number, made anew (what hangs on it would otherwise be kept in registers through the contraction).
+__device__ __forceinline__ int fresh_lane() {
+  int lane = threadIdx.x;
+  asm volatile("" : "+v"(lane));
+  return lane & 63;
 }
-// The factored form (y as in sweep_group).
-template <int KS>
-__device__ __forceinline__ void sweep_group_factored(const float (&y)[4][4], SweepState<KS, false>& st, const SweepTable& tab,
-                                                     unsigned first, const GemmArgs& p) {
-  SweepPending pend;
-  // references
-  float most[4];
+
+// An argument, likewise (for comparisons with it).
+__device__ __forceinline__ int fresh_scalar(int x) {
+  asm volatile("" : "+s"(x));
+  return x;
+}
+
+// (no instructions: without it the compiler copies the accumulators' elements out of a loop, into registers it does not have)
+__device__ __forceinline__ void keep_in_accumulators(f32x4 (&acc)[16][4]) {
 #pragma unroll
-  for (int j = 0; j < 4; ++j) most[j] = fmaxf(fmaxf(y[j][0], y[j][1]), fmaxf(y[j][2], y[j][3]));
-  bool move = false;
+  for (int q = 0; q < 16; ++q)
 #pragma unroll
-  for (int j = 0; j < 4; ++j) move = move || most[j] > st.ref[j] + SWEEP_SHIFT;
-  if (__builtin_amdgcn_ballot_w64(move) != 0) {
+    for (int j = 0; j < 4; ++j) asm volatile("" : "+a"(acc[q][j]));
+}
+
+// Group i of the tile: y[j][r] is id 4 (l / 16) + r of the group for row 16 j + l % 16.
+__device__ __forceinline__ void sweep_read_group(f32x4 (&acc)[16][4], int i, float (&y)[4][4]) {
+  keep_in_accumulators(acc);
+  switch (i) {
+#define LL_CASE(I)                                                                                        \
+  case I:                                                                                                 \
+    _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                         \
+        _Pragma("unroll") for (int r = 0; r < 4; ++r) y[j][r] = acc_read(acc[I][j][r]);                   \
+    break;
+    LL_CASE(0) LL_CASE(1) LL_CASE(2) LL_CASE(3) LL_CASE(4) LL_CASE(5) LL_CASE(6) LL_CASE(7)
+    LL_CASE(8) LL_CASE(9) LL_CASE(10) LL_CASE(11) LL_CASE(12) LL_CASE(13) LL_CASE(14)
+    default:
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) y[j][r] = acc_read(acc[15][j][r]);
+#undef LL_CASE
+  }
+}
+
+// Pass 1.  Bit g of the result: some lane holds, of group g, a logit above lim[j] in row 16 j + l % 16.  top: the tile's largest
+// logits of those rows among the lane's ids.
+__device__ __forceinline__ unsigned sweep_scan(f32x4 (&acc)[16][4], const float (&lim)[4], float (&top)[4]) {
+  unsigned marked = 0;
+  keep_in_accumulators(acc);
+#pragma unroll
+  for (int j = 0; j < 4; ++j) top[j] = -INFINITY;
+  each16([&](auto g_) {
+    constexpr int g = decltype(g_)::value;
+    float most[4];
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
-      float full = fmaxf(most[j], __shfl_xor(most[j], 16, kWave));
-      full = fmaxf(full, __shfl_xor(full, 32, kWave));
-      const float ref = full > st.ref[j] + SWEEP_SHIFT ? full : st.ref[j];
-      const float sc = ref == st.ref[j] ? 1.0f : __builtin_amdgcn_exp2f((st.ref[j] - ref) * LOG2E);   // first group: exp2(-inf) = 0
-      st.ref[j] = ref;
-      st.s[j] *= sc;
-      st.t[j] *= sc;
+      const float y0 = acc_read(acc[g][j][0]), y1 = acc_read(acc[g][j][1]), y2 = acc_read(acc[g][j][2]), y3 = acc_read(acc[g][j][3]);
+      most[j] = max3(max3(y0, y1, y2), y3, y3);
+      top[j] = max3(top[j], most[j], most[j]);
     }
-  }
-  const float a0[4] = {tab.a0.x, tab.a0.y, tab.a0.z, tab.a0.w}, a1[4] = {tab.a1.x, tab.a1.y, tab.a1.z, tab.a1.w};
-  // Sums, row block by row block: the exponentials of the next one are made between the products of this one (a product
-  // occupies the matrix pipe for 32 cycles).
-  const bool second = p.n_alpha > SWEEP_SPLIT_ROWS;
-  float e[2][4], ez[2][4];
+    const bool any = (most[0] > lim[0]) | (most[1] > lim[1]) | (most[2] > lim[2]) | (most[3] > lim[3]);
+    if (__builtin_amdgcn_ballot_w64(any) != 0) marked |= 1u << g;
+    LL_SCHED_FENCE();
+  });
+  return marked;
+}
+
+// References: each the same for the four lanes that hold a row.
+template <int KS>
+__device__ __forceinline__ void sweep_move_references(SweepState<KS, false>& st, const float (&top)[4]) {
+  bool move = false;
 #pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    e[0][r] = __builtin_amdgcn_exp2f(fmaf(y[0][r], LOG2E, -st.ref[0] * LOG2E));
-    ez[0][r] = e[0][r] * y[0][r];
-  }
-  asm volatile("s_nop 1" : "+v"(e[0][0]), "+v"(e[0][1]), "+v"(e[0][2]), "+v"(e[0][3]), "+v"(ez[0][0]), "+v"(ez[0][1]), "+v"(ez[0][2]), "+v"(ez[0][3]));
+  for (int j = 0; j < 4; ++j) move = move || top[j] > st.ref[j] + SWEEP_SHIFT;
+  if (__builtin_amdgcn_ballot_w64(move) == 0) return;
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
-    const int c = j & 1, n = c ^ 1, jn = j < 3 ? j + 1 : 3;
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      LL_SCHED_FENCE();
-      if (r == 0) sweep_first_product(pend.s[c], a0[r], e[c][r]); else sweep_product(pend.s[c], a0[r], e[c][r]);
-      if (j < 3) {
-        e[n][r] = __builtin_amdgcn_exp2f(fmaf(y[jn][r], LOG2E, -st.ref[jn] * LOG2E));
-        asm volatile("" : "+v"(e[n][r]));   // (here, not where it is used)
-      }
-      LL_SCHED_FENCE();
-      if (r == 0) sweep_first_product(pend.t[c], a0[r], ez[c][r]); else sweep_product(pend.t[c], a0[r], ez[c][r]);
-      if (j < 3) {
-        ez[n][r] = e[n][r] * y[jn][r];
-        asm volatile("" : "+v"(ez[n][r]));
-      }
-    }
-    LL_SCHED_FENCE();
-    if (j > 0) sweep_fold(st, pend, j - 1);   // eight products since
-    LL_SCHED_FENCE();
-    if (second) {
-#pragma unroll
-      for (int r = 0; r < 4; ++r) sweep_product(pend.t[c], a1[r], e[c][r]);
-    }
-    if (j < 3) asm volatile("s_nop 1" : "+v"(e[n][3]), "+v"(ez[n][3]));   // (the last of them was written just now)
+    const auto larger = [](uint32_t a, uint32_t b) { return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b))); };
+    const float full = __uint_as_float(with_lane_xor<32>(with_lane_xor<16>(__float_as_uint(top[j]), larger), larger));
+    const float ref = full > st.ref[j] + SWEEP_SHIFT ? full : st.ref[j];
+    const float sc = ref == st.ref[j] ? 1.0f : __builtin_amdgcn_exp2f((st.ref[j] - ref) * LOG2E);   // first tile: exp2(-inf) = 0
+    st.ref[j] = ref;
+    st.st[j] *= sc;
+    st.more[j] *= sc;
   }
-  LL_SCHED_FENCE();
-  // Lists: the group's largest logit of the lane's own row against the least unshifted logit that any alpha might list (its
-  // list's last entry less the group's largest shift; with a margin for the rounding of both, 2^-22 of either.  The shift's is in
-  // the table, none where all shifts are zero: rows of equal logits, which strength 0 leaves equal, would otherwise walk every
-  // group: 1500 rows, d = 4096, V = 128256, every 64th row zero: 2183 us, 1541 without the margin).
-  float q0 = most[0], q1 = most[1], q2 = most[2], q3 = most[3];
-  transpose_blocks(q0, q1, q2, q3);
-  const float gmax = fmaxf(fmaxf(q0, q1), fmaxf(q2, q3));
-  float lim = INFINITY;   // (the lists of alphas that are not there end in infinity)
-  each_alpha([&](auto a_) {
-    constexpr int a = decltype(a_)::value;
-    if (a < SWEEP_FEW) lim = fminf(lim, minus_bcast16<a>(st.lv[a][KS - 1], tab.shift));
-  });
-  if (p.n_alpha > SWEEP_FEW)
+}
+
+// acc[alpha, row] += sum over lane blocks of a[alpha, id] b[id, row].  Written as an instruction: given the builtin the compiler
+// wants the results in AGPRs, which the contraction fills.  So the waits are ours: two states between a vector instruction
+// that writes an operand and the product that reads it, and 18 before a vector instruction reads a result.
+__device__ __forceinline__ void sweep_product(f32x4& acc, float a, float b) {
+  asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "v"(b));
+}
+__device__ __forceinline__ void sweep_first_product(f32x4& acc, float a, float b) {   // acc = 0 + ...
+  asm volatile("v_mfma_f32_16x16x4_f32 %0, %1, %2, 0" : "=&v"(acc) : "v"(a), "v"(b));
+}
+
+// The products of one group and row block start from zero and are added to the row's sums behind the next block's products:
+// the instruction does not round to nearest, and a chain of them over a split of 51 tiles left S too small by
+// 1.1e-5 of itself and the entropy by 1e-4 (6000 rows, V = 128256).  A group's products and one addition a group have
+// the error that a sum of exponentials in vector instructions has.
+__device__ __forceinline__ void sweep_fold(f32x4& sum, f32x4& pending) {
+  asm volatile("" : "+v"(pending));   // (here, not earlier)
+  sum += pending;
+  asm volatile("" : "+v"(sum));
+}
+
+// Pass 2.  Row block by row block: its eight products, then the exponentials that the next block's need, this block's plain sums
+// and the last block's additions.  fp32 products run on the vector ALU: eight of them take 258 cycles alone, 485 with four
+// vector instructions behind each, 449 with eight behind each pair, and 32 such instructions 200 (one wavefront, a bare loop).  So
+// nothing is to be had from interleaving them, and what counts is their number: with S in the upper eight rows of the result and
+// T in the lower ones, from the operand [E; alpha E u] times e and [0; E] times e z, a group takes 32.
+template <int KS>
+__device__ __forceinline__ void sweep_sums(f32x4 (&acc)[16][4], SweepState<KS, false>& st, int v0, const GemmArgs& p) {
+  const int lane = fresh_lane();
+  const bool nine = fresh_scalar(p.n_alpha) > SWEEP_SPLIT_ROWS, second = nine && p.zero_alpha < 0, plain = nine && !second;
+  const unsigned at = 4 * (lane & 15) + (lane >> 4);   // (row l % 16 of a group's table, ids 4 (l / 16) ..)
+  const float4* tab = reinterpret_cast<const float4*>(p.eu + (int64_t)v0 * SWEEP_ROWS);
+  const float4* const tab_end = tab + 15 * (SWEEP_GROUP * SWEEP_ROWS / 4);
+  const int64_t to_second = second ? (int64_t)p.tiles * BM * SWEEP_ROWS / 4 : 0;
+  float nref[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) nref[j] = -st.ref[j] * LOG2E;
+  float4 next1 = tab[at], next2 = tab[at + to_second];
+  float y[4][4], e[2][4], ez[2][4];
+  f32x4 pend[2], pend_more[2];
+  pend[1] = pend_more[1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  sweep_read_group(acc, 0, y);
+#pragma unroll
+  for (int r = 0; r < 4; ++r) {
+    e[0][r] = __builtin_amdgcn_exp2f(fmaf(y[0][r], LOG2E, nref[0]));
+    ez[0][r] = e[0][r] * y[0][r];
+  }
+#pragma unroll 1
+  for (int i = 0; i < 16; ++i) {
+    float a1[4] = {next1.x, next1.y, next1.z, next1.w}, a2[4] = {next2.x, next2.y, next2.z, next2.w};
+    if (tab != tab_end) tab += SWEEP_GROUP * SWEEP_ROWS / 4;
+    next1 = tab[at];
+    next2 = tab[at + to_second];
+    if (!second) {   // [0; E] from [E; alpha E u]
+#pragma unroll
+      for (int r = 0; r < 4; ++r) a2[r] = __uint_as_float(dpp<0x118>(__float_as_uint(a1[r])));   // row_shr:8, zeros moved in
+    }
+    asm volatile("s_nop 1" : "+v"(a1[0]), "+v"(a1[1]), "+v"(a1[2]), "+v"(a1[3]), "+v"(a2[0]), "+v"(a2[1]), "+v"(a2[2]), "+v"(a2[3]));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int c = j & 1, n = c ^ 1, jn = (j + 1) & 3, before = (j + 3) & 3;
+      LL_SCHED_FENCE();
+      sweep_first_product(pend[c], a1[0], e[c][0]);
+      sweep_product(pend[c], a1[1], e[c][1]);
+      sweep_product(pend[c], a1[2], e[c][2]);
+      sweep_product(pend[c], a1[3], e[c][3]);
+      sweep_product(pend[c], a2[0], ez[c][0]);
+      sweep_product(pend[c], a2[1], ez[c][1]);
+      sweep_product(pend[c], a2[2], ez[c][2]);
+      sweep_product(pend[c], a2[3], ez[c][3]);
+      if (second) {
+        sweep_first_product(pend_more[c], a2[0], e[c][0]);
+        sweep_product(pend_more[c], a2[1], e[c][1]);
+        sweep_product(pend_more[c], a2[2], e[c][2]);
+        sweep_product(pend_more[c], a2[3], e[c][3]);
+        sweep_fold(st.more[before], pend_more[n]);
+      }
+      if (j == 3) sweep_read_group(acc, min(i + 1, 15), y);   // (the block that comes next is the next group's first)
+      LL_SCHED_FENCE();
+#pragma unroll
+      for (int r = 0; r < 4; ++r) e[n][r] = __builtin_amdgcn_exp2f(fmaf(y[jn][r], LOG2E, nref[jn]));
+#pragma unroll
+      for (int r = 0; r < 4; ++r) ez[n][r] = e[n][r] * y[jn][r];
+      if (plain) {
+        st.more[j][0] += (e[c][0] + e[c][1]) + (e[c][2] + e[c][3]);
+        st.more[j][1] += (ez[c][0] + ez[c][1]) + (ez[c][2] + ez[c][3]);
+      }
+      asm volatile("" : "+v"(e[n][0]), "+v"(e[n][1]), "+v"(e[n][2]), "+v"(e[n][3]), "+v"(ez[n][0]), "+v"(ez[n][1]), "+v"(ez[n][2]), "+v"(ez[n][3]));
+      LL_SCHED_FENCE();
+      sweep_fold(st.st[before], pend[n]);   // eight products since its last one
+    }
+  }
+  asm volatile("s_nop 15\n\ts_nop 3" : "+v"(pend[1]), "+v"(pend_more[1]));
+  sweep_fold(st.st[3], pend[1]);
+  if (second) sweep_fold(st.more[3], pend_more[1]);
+}
+
+// A tile's 256 entries in four registers, entry 64 q + l in lane l: the register that holds group i's, and of these the lane's l % 16 th.
+__device__ __forceinline__ float sweep_group_register(const float (&x)[4], int i) {
+  const float lo = keep_select((i & 4) != 0, x[1], x[0]), hi = keep_select((i & 4) != 0, x[3], x[2]);
+  return keep_select((i & 8) != 0, hi, lo);
+}
+__device__ __forceinline__ float sweep_group_entry(const float (&x)[4], int i) {
+  const int lane = 16 * (i & 3) + (fresh_lane() & 15);
+  return __int_as_float(__builtin_amdgcn_ds_bpermute(4 * lane, __float_as_int(sweep_group_register(x, i))));
+}
+
+// The kernel's arguments that the factored form uses, likewise.
+__device__ __forceinline__ GemmArgs sweep_args() {
+  auto args = (const GemmArgs __attribute__((address_space(4)))*)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(args));
+  GemmArgs p = {};
+  p.u = args->u;
+  p.eu = args->eu;
+  p.shift_max = args->shift_max;
+  p.shift_min = args->shift_min;
+  p.shift_tile = args->shift_tile;
+  p.bound = args->bound;
+  p.rows = args->rows;
+  p.V = args->V;
+  p.k = args->k;
+  p.tiles = args->tiles;
+  p.n_alpha = args->n_alpha;
+  p.zero_alpha = args->zero_alpha;
+  return p;
+}
+
+// Lists, for every alpha, those of the group's logits above lim that beat its list's last entry, in id order.  All alphas
+// share one walk over the logits (their shifts are small: mostly the same ids), and all lanes stay on (a lane without a
+// candidate left takes part with one that ranks nowhere).
+template <int KS>
+__device__ __forceinline__ void sweep_collect_all(const float (&x)[16], float lim, SweepState<KS, false>& st, float u, unsigned first,
+                                                  const GemmArgs& p) {
+  const_f32_ptr alphas = sweep_alphas();
+  unsigned mask = above_mask16(x, lim);
+  while (__builtin_amdgcn_ballot_w64(mask != 0) != 0) {
+    const int o = mask != 0 ? __builtin_ctz(mask) : 0;
+    const float z = mask != 0 ? pick16(x, o) : -INFINITY;
+    const float uo = __int_as_float(__builtin_amdgcn_ds_bpermute(4 * o, __float_as_int(u)));   // (lanes 0 .. 15 hold the group's u)
+    const unsigned id = first + (unsigned)o;
+    mask &= mask - 1;
+#pragma unroll
+    for (int a = 0; a < SWEEP_MAX; ++a) {
+      if (a == SWEEP_FEW && p.n_alpha <= SWEEP_FEW) break;
+      sweep_insert<KS, false>(st, a, fmaf(alphas[a], uo, z), id);
+      LL_SCHED_FENCE();
+    }
+  }
+}
+
+// Pass 3, the marked groups.  The group's largest logit of the lane's own row against the least unshifted logit that any alpha might
+// list (its list's last entry less the group's largest shift; with a margin for the rounding of both, 2^-22 of either.  The
+// shift's is in the table, none where all shifts are zero: rows of equal logits, which strength 0 leaves equal, would otherwise
+// walk every group: 1500 rows, d = 4096, V = 128256, every 64th row zero: 2183 us, 1541 without the margin).
+template <int KS>
+__device__ __forceinline__ void sweep_lists(f32x4 (&acc)[16][4], SweepState<KS, false>& st, unsigned marked, const float (&u4)[4],
+                                            const float (&shift4)[4], int v0, const GemmArgs& p) {
+#pragma unroll 1
+  while (marked != 0) {
+    const int i = __builtin_ctz(marked);
+    marked &= marked - 1;
+    const int g0 = v0 + SWEEP_GROUP * i;
+    float y[4][4], x[16];
+    sweep_read_group(acc, i, y);
+    float u = sweep_group_entry(u4, i), shift = sweep_group_entry(shift4, i);
+    own_row(y, x);
+    const int tl = st.tgt - g0;
+    if (__builtin_amdgcn_ballot_w64((unsigned)tl < 16u) != 0) {
+#pragma unroll
+      for (int o = 0; o < 16; ++o)
+        st.z_tgt = keep_select(tl == o, x[o], st.z_tgt);
+    }
+    const float gmax = max16(x);
+    asm volatile("s_nop 1" : "+v"(shift), "+v"(u));   // (read by DPP instructions of ours from here on)
+    float lim = INFINITY;   // (the lists of alphas that are not there end in infinity)
     each_alpha([&](auto a_) {
       constexpr int a = decltype(a_)::value;
-      if (a >= SWEEP_FEW) lim = fminf(lim, minus_bcast16<a>(st.lv[a][KS - 1], tab.shift));
+      lim = fminf(lim, minus_bcast16<a>(st.lv[a][KS - 1], shift));
     });
-  lim = fmaxf(lim - fabsf(lim) * 0x1p-22f, NEG_BIG);   // (entries past the vocabulary are NEG_BIG)
-  asm volatile("s_nop 15\n\ts_nop 3" : "+v"(lim), "+v"(pend.s[1]), "+v"(pend.t[1]));   // (behind the limit's dozen instructions)
-  sweep_fold(st, pend, 3);
-  if (__builtin_amdgcn_ballot_w64(gmax > lim) != 0) {
-    float x[16];
-    own_row(y, x);
+    lim = fmaxf(lim - fabsf(lim) * 0x1p-22f, NEG_BIG);   // (entries past the vocabulary are NEG_BIG)
+    if (__builtin_amdgcn_ballot_w64(gmax > lim) == 0) continue;
     // Nor is a logit listed that KS others of the group beat whatever the shifts: those KS at least as large as `least`, less the
     // spread of the group's shifts (table entry 15), with the same margin.
     float least = gmax;
     if (KS > 1) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) least = fminf(least, fmaxf(fmaxf(x[4 * i], x[4 * i + 1]), fmaxf(x[4 * i + 2], x[4 * i + 3])));
+      for (int q = 0; q < 4; ++q) least = fminf(least, fmaxf(fmaxf(x[4 * q], x[4 * q + 1]), fmaxf(x[4 * q + 2], x[4 * q + 3])));
     }
-    least = minus_bcast16<15>(least, tab.shift);
+    least = minus_bcast16<15>(least, shift);
     lim = fmaxf(lim, least - (fabsf(least) + 4.0f * SWEEP_SHIFT) * 0x1p-22f);
-    sweep_collect_all<KS>(x, lim, st, tab.u, first, p);
+    sweep_collect_all<KS>(x, lim, st, u, (unsigned)(g0 - st.id0), p);
   }
 }
 
-// One group of 16 ids: y[j][r] is id 4 (l / 16) + r of the group for row 16 j + l % 16.
-template <int KS, bool GENERAL>
-__device__ __forceinline__ void sweep_group(const float (&y)[4][4], SweepState<KS, GENERAL>& st, const SweepTable& tab, int g0, const GemmArgs& p) {
-  const unsigned first = (unsigned)(g0 - st.id0);
-  const int tl = st.tgt - g0;
-  const bool has_target = __builtin_amdgcn_ballot_w64((unsigned)tl < 16u) != 0;
-  if (GENERAL || has_target) {
-    float x[16];
-    own_row(y, x);
-    if (has_target) {
-#pragma unroll
-      for (int o = 0; o < 16; ++o)
-        if (tl == o) st.z_tgt = x[o];
-    }
-    if constexpr (GENERAL) sweep_group_general<KS>(x, st, first, tab, p);
-  }
-  if constexpr (!GENERAL) sweep_group_factored<KS>(y, st, tab, first, p);
-}
-
-// As exchange_bound of the projection, per alpha: publishes the k-th best of this split's list and picks up the row's
-// best bound.  Entries below the bound cannot be in the row's top k: they give way to the largest float below it
+// What the splits of a row tell each other, per alpha.  The splits are dealt into k classes, and a class's entry is the best
+// shifted logit that any of its splits has seen: k different ids, each at least the least of the k entries, which therefore is a
+// bound on the row's k-th best (for k = 1 the best so far).  It ranks some k (1 + 1/2 + ... + 1/k) th of all ids seen; the best
+// k-th entry of any one split's list, of few ids each, ranks k + 1 to ten times lower: 500 rows, lists of three in 119 splits.
+// Entries that are not above the bound cannot be in the row's top k: they give way to the largest float below it
 // (below_bound: an equal logit with a smaller id still counts), which then is what a candidate has to beat.
 template <int KS>
-__device__ __forceinline__ void sweep_exchange(SweepState<KS, false>& st, const GemmArgs& p, int my_row) {
-  asm volatile("" : "+v"(my_row));   // (the addresses made anew for every tile rather than kept)
-  const int row = min(my_row, p.rows - 1);
-  auto at = [&](int a) { return reinterpret_cast<unsigned*>(reinterpret_cast<unsigned char*>(p.bound) + 4u * (unsigned)(a * p.rows + row)); };
-  unsigned fresh[SWEEP_MAX];
-  asm volatile("" ::: "memory");
+__device__ __forceinline__ unsigned* sweep_bound(const SweepState<KS, false>& st, const GemmArgs& p, int row, int cls, int a) {
+  return reinterpret_cast<unsigned*>(reinterpret_cast<unsigned char*>(p.bound) + 4u * (unsigned)((cls * p.n_alpha + a) * p.rows + row));
+}
+// Takes the bounds over into the lists; PUBLISH: and sends the lists' heads where they are news.  (The loads first: a wait for one of them is also a
+// wait for the atomics sent before it.)
+template <int KS, bool PUBLISH>
+__device__ __forceinline__ void sweep_take_bounds(SweepState<KS, false>& st, const GemmArgs& p, int my_row) {
+  asm volatile("" : "+v"(my_row)::"memory");   // (the addresses made anew for every tile rather than kept)
+  const int row = min(my_row, p.rows - 1), n_alpha = fresh_scalar(p.n_alpha), k = KS == 1 ? 1 : fresh_scalar(p.k), own = st.split % k;
+  unsigned least[SWEEP_MAX], known[SWEEP_MAX], fresh[KS][SWEEP_MAX];
 #pragma unroll
-  for (int a = 0; a < SWEEP_MAX; ++a)
-    fresh[a] = a < p.n_alpha ? __hip_atomic_load(at(a), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+  for (int cls = 0; cls < KS; ++cls)   // (all loads in flight together, and no branch among them: past the last class or alpha the last one's again)
+#pragma unroll
+    for (int a = 0; a < SWEEP_MAX; ++a)
+      fresh[cls][a] = __hip_atomic_load(sweep_bound(st, p, row, min(cls, k - 1), min(a, n_alpha - 1)), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 #pragma unroll
   for (int a = 0; a < SWEEP_MAX; ++a) {
-    if (a < p.n_alpha) {
-      float kth = st.lv[a][KS - 1];
+    least[a] = known[a] = fresh[0][a];
 #pragma unroll
-      for (int j = KS - 2; j >= 0; --j) kth = p.k - 1 == j ? st.lv[a][j] : kth;
-      const unsigned key = float_key(kth);
-      if (my_row < p.rows && key > fresh[a] && key > KEY_NEG_INF)
-        __hip_atomic_fetch_max(at(a), key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const float floor = below_bound(fresh[a]);
+    for (int cls = 1; cls < KS; ++cls) {
+      least[a] = min(least[a], fresh[cls][a]);
+      known[a] = cls == own ? fresh[cls][a] : known[a];
+    }
+  }
+#pragma unroll
+  for (int a = 0; a < SWEEP_MAX; ++a) {
+    if (a < n_alpha) {
+      if (PUBLISH) {   // the list's head (the one of a list that holds none is below the bound)
+        const unsigned key = float_key(st.lv[a][0]);
+        if (my_row < p.rows && key > known[a] && key > KEY_NEG_INF)
+          __hip_atomic_fetch_max(sweep_bound(st, p, my_row, own, a), key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+      const float floor = below_bound(least[a]);
 #pragma unroll
       for (int j = 0; j < KS; ++j) {
         const bool below = st.lv[a][j] <= floor;
@@ -472,6 +602,49 @@ __device__ __forceinline__ void sweep_exchange(SweepState<KS, false>& st, const 
       }
     }
   }
+  asm volatile("" ::: "memory");
+}
+// In a split's first tile, ahead of its lists: the best shifted logits, from below (a group's largest logit with its least shift, and
+// its least logit with its largest shift, which is the better one where a row's logits are nearly equal).
+template <int KS>
+__device__ __forceinline__ void sweep_announce(f32x4 (&acc)[16][4], SweepState<KS, false>& st, int v0, const GemmArgs& p, int my_row) {
+  float best[SWEEP_MAX], least4[4], most4[4];
+  const int lane = fresh_lane();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    least4[q] = p.shift_min[v0 + 64 * q + lane];
+    most4[q] = p.shift_max[v0 + 64 * q + lane];
+  }
+#pragma unroll
+  for (int a = 0; a < SWEEP_MAX; ++a) best[a] = -INFINITY;
+#pragma unroll 1
+  for (int i = 0; i < 16; ++i) {
+    float y[4][4], q[4], l[4];
+    sweep_read_group(acc, i, y);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      q[j] = max3(max3(y[j][0], y[j][1], y[j][2]), y[j][3], y[j][3]);
+      l[j] = min3(min3(y[j][0], y[j][1], y[j][2]), y[j][3], y[j][3]);
+    }
+    transpose_blocks(q[0], q[1], q[2], q[3]);
+    transpose_blocks(l[0], l[1], l[2], l[3]);
+    const float gmax = max3(max3(q[0], q[1], q[2]), q[3], q[3]), gmin = min3(min3(l[0], l[1], l[2]), l[3], l[3]);
+    const float least = sweep_group_entry(least4, i), most = sweep_group_entry(most4, i);
+    each_alpha([&](auto a_) {
+      constexpr int a = decltype(a_)::value;
+      best[a] = max3(best[a], gmax + bcast16<a>(least), gmin + bcast16<a>(most));
+    });
+  }
+#pragma unroll
+  for (int a = 0; a < SWEEP_MAX; ++a) {   // (less what rounding, and the margin of the largest shifts, may have added)
+    best[a] -= (fabsf(best[a]) + 4.0f * SWEEP_SHIFT) * 0x1p-22f;
+    if (!(best[a] > NEG_BIG * 0.5f)) best[a] = -INFINITY;
+  }
+  const int n_alpha = fresh_scalar(p.n_alpha), cls = st.split % fresh_scalar(p.k);
+#pragma unroll
+  for (int a = 0; a < SWEEP_MAX; ++a)
+    if (a < n_alpha && my_row < p.rows && best[a] > -INFINITY)
+      __hip_atomic_fetch_max(sweep_bound(st, p, my_row, cls, a), float_key(best[a]), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   asm volatile("" ::: "memory");
 }
 
@@ -485,11 +658,11 @@ struct SweepEpilogue {
     if (p.sweep_general == nullptr) return false;   // (the host launches one form only)
     return (*(const int __attribute__((address_space(4)))*)(uintptr_t)p.sweep_general != 0) != GENERAL;
   }
-  static __device__ __forceinline__ void init(State& st, const GemmArgs& p, int my_row) {
+  static __device__ __forceinline__ void init(State& st, const GemmArgs& p, int my_row, int split) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       st.ref[j] = -INFINITY;
-      st.s[j] = st.t[j] = f32x4{0.f, 0.f, 0.f, 0.f};
+      st.st[j] = st.more[j] = f32x4{0.f, 0.f, 0.f, 0.f};
     }
 #pragma unroll
     for (int a = 0; a < SWEEP_MAX; ++a) {
@@ -502,38 +675,95 @@ struct SweepEpilogue {
     st.tgt = (p.target != nullptr && my_row < p.rows) ? p.target[my_row] : -1;
     st.z_tgt = -INFINITY;
     st.id0 = -1;
+    st.split = split;
+    st.next_shift = 0.f;
   }
   static __device__ __forceinline__ void tile(f32x4 (&acc)[16][4], State& st, int v0, const GemmArgs& p, int my_row) {
-    if (st.id0 < 0) st.id0 = __builtin_amdgcn_readfirstlane(v0);   // (the split's first tile)
-    SweepTable ahead;
-    sweep_load_table<GENERAL>(ahead, __builtin_amdgcn_readfirstlane(v0), p);
+    if constexpr (GENERAL)
+      general_tile(acc, st, __builtin_amdgcn_readfirstlane(v0), p);
+    else
+      factored_tile(acc, st, __builtin_amdgcn_readfirstlane(v0), my_row);
+  }
+  static __device__ __forceinline__ void factored_tile(f32x4 (&acc)[16][4], State& st, int v0, int my_row) {
+    const int lane = fresh_lane();
+    const GemmArgs p = sweep_args();
+    const bool first = st.id0 < 0;
+    if (first) st.id0 = v0;   // (the split's first tile)
+    // of the sums' table (16 KB) one word a line, so that it is in this XCD's L2 by then
+    float warm = p.eu[(int64_t)v0 * SWEEP_ROWS + (64 * (threadIdx.x >> 6 & 1) + lane) * 32];
+    asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");   // as in epilogue_tile: let the last MFMA drain
+    if (v0 + BM > p.V) {   // only the last tile of the vocabulary: a real branch (the empty asm keeps it one)
+      asm volatile("");
+      const int id = v0 + 4 * (lane >> 4);
+      each16([&](auto g_) {
+        constexpr int g = decltype(g_)::value;
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+#pragma unroll
+          for (int j = 0; j < 4; ++j) {
+            float x = acc_read(acc[g][j][r]);
+            x = id + 16 * g + r >= p.V ? NEG_BIG : x;
+            asm volatile("v_accvgpr_write_b32 %0, %1" : "=a"(acc[g][j][r]) : "v"(x));
+          }
+        LL_SCHED_FENCE();
+      });
+      asm volatile("s_nop 3" ::: "memory");
+    }
+    unsigned marked;
+    float u4[4], shift4[4];
+#pragma unroll 1
+    for (bool again = false;; again = true) {
+      // the least unshifted logit that any alpha might list, as in sweep_lists but with the tile's largest shifts
+      float lim = INFINITY;
+#pragma unroll
+      for (int a = 0; a < SWEEP_MAX; ++a)
+        lim = fminf(lim, st.lv[a][KS - 1] - __int_as_float(__builtin_amdgcn_readlane(__float_as_int(st.next_shift), a)));
+      lim = fmaxf(lim - fabsf(lim) * 0x1p-22f, NEG_BIG);
+      float lims[4], top[4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) lims[j] = __int_as_float(__builtin_amdgcn_ds_bpermute(64 * j + 4 * (lane & 15), __float_as_int(lim)));
+      marked = sweep_scan(acc, lims, top);
+      if (again) break;
+      sweep_move_references<KS>(st, top);
+      if (first) {
+        st.next_shift = p.shift_tile[v0 / BM * 16 + (lane & 15)];
+        // (waited for here: at its use, which other tiles come to as well, the wait would be for the ring's loads too)
+        asm volatile("" : "+v"(st.next_shift));
+        sweep_announce<KS>(acc, st, v0, p, my_row);
+      }
+      asm volatile("" : "+v"(warm));
+      sweep_sums<KS>(acc, st, v0, p);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        u4[q] = p.u[v0 + 64 * q + lane];
+        shift4[q] = p.shift_max[v0 + 64 * q + lane];
+      }
+      if (!first) break;
+      sweep_take_bounds<KS, false>(st, p, my_row);   // and once more with what the others have announced meanwhile
+    }
+    const int tl = st.tgt - v0;
+    unsigned long long targets = __builtin_amdgcn_ballot_w64((unsigned)tl < (unsigned)BM);
+    while (targets != 0) {
+      marked |= 1u << (__builtin_amdgcn_readlane(tl, __builtin_ctzll(targets)) >> 4);
+      targets &= targets - 1;
+    }
+    sweep_lists<KS>(acc, st, marked, u4, shift4, v0, p);
+    const int ahead = min(v0 / BM + 1, p.tiles - 1);
+    st.next_shift = p.shift_tile[16 * ahead + (lane & 15)];
+    sweep_take_bounds<KS, true>(st, p, my_row);
+    asm volatile("" : "+v"(st.next_shift));   // (come back by now: as above)
+  }
+  static __device__ __forceinline__ void general_tile(f32x4 (&acc)[16][4], State& st, int v0, const GemmArgs& p) {
+    if (st.id0 < 0) st.id0 = v0;
+    float u_ahead = sweep_load_u(v0, p);
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");   // as in epilogue_tile: let the last MFMA drain
 #pragma unroll 1
     for (int i = 0; i < 16; ++i) {
-      // (no instructions: without it the compiler copies the accumulators' elements out of the loop, into registers it does not have)
-#pragma unroll
-      for (int q = 0; q < 16; ++q)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) asm volatile("" : "+a"(acc[q][j]));
-      const SweepTable tab = ahead;
-      sweep_load_table<GENERAL>(ahead, __builtin_amdgcn_readfirstlane(v0 + SWEEP_GROUP * min(i + 1, 15)), p);
+      const float u = u_ahead;
+      u_ahead = sweep_load_u(__builtin_amdgcn_readfirstlane(v0 + SWEEP_GROUP * min(i + 1, 15)), p);
       LL_SCHED_FENCE();
-      float y[4][4];
-      switch (i) {
-#define LL_CASE(I)                                                                                        \
-  case I:                                                                                                 \
-    _Pragma("unroll") for (int j = 0; j < 4; ++j)                                                         \
-        _Pragma("unroll") for (int r = 0; r < 4; ++r) y[j][r] = acc_read(acc[I][j][r]);                   \
-    break;
-        LL_CASE(0) LL_CASE(1) LL_CASE(2) LL_CASE(3) LL_CASE(4) LL_CASE(5) LL_CASE(6) LL_CASE(7)
-        LL_CASE(8) LL_CASE(9) LL_CASE(10) LL_CASE(11) LL_CASE(12) LL_CASE(13) LL_CASE(14)
-        default:
-#pragma unroll
-          for (int j = 0; j < 4; ++j)
-#pragma unroll
-            for (int r = 0; r < 4; ++r) y[j][r] = acc_read(acc[15][j][r]);
-#undef LL_CASE
-      }
+      float y[4][4], x[16];
+      sweep_read_group(acc, i, y);
       const int g0 = __builtin_amdgcn_readfirstlane(v0 + SWEEP_GROUP * i);
       if (g0 >= p.V) break;
       if (g0 + SWEEP_GROUP > p.V) {   // only the last group of the vocabulary: a real branch (the empty asm keeps it one)
@@ -543,24 +773,45 @@ struct SweepEpilogue {
         for (int r = 0; r < 4; ++r)
           if (id + r >= p.V) y[0][r] = y[1][r] = y[2][r] = y[3][r] = NEG_BIG;
       }
-      sweep_group<KS, GENERAL>(y, st, tab, g0, p);
+      own_row(y, x);
+      const int tl = st.tgt - g0;
+      if (__builtin_amdgcn_ballot_w64((unsigned)tl < 16u) != 0) {
+#pragma unroll
+        for (int o = 0; o < 16; ++o) {   // (lists: 477 us with selects that stay ones, 488 without; arg max 390 and 386)
+          if constexpr (KS > 1)
+            st.z_tgt = keep_select(tl == o, x[o], st.z_tgt);
+          else if (tl == o)
+            st.z_tgt = x[o];
+        }
+      }
+      sweep_group_general<KS>(x, st, (unsigned)(g0 - st.id0), u, p);
     }
-    if constexpr (!GENERAL) sweep_exchange<KS>(st, p, my_row);
   }
   static __device__ __forceinline__ void store(const GemmArgs& p, const State& st, int my_row, int split) {
-    if constexpr (!GENERAL) {   // statistics in accumulator layout: rows 16 j + l % 16 of the wavefront, alphas 4 (l / 16) + r
+    if constexpr (!GENERAL) {   // statistics in accumulator layout: rows 16 j + l % 16 of the wavefront, table rows 4 (l / 16) + r
       const int lane = threadIdx.x & 63;
-      const bool second = p.n_alpha > SWEEP_SPLIT_ROWS;
+      const bool second = p.n_alpha > SWEEP_SPLIT_ROWS && p.zero_alpha < 0;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int row = my_row - lane + 16 * j + (lane & 15);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
-          const float s = st.s[j][r], t = st.t[j][r];
-          const float t2 = __shfl_xor(s, 32, kWave);   // row 8 + a
-          const int a = 4 * (lane >> 4) + r;
-          if (row < p.rows && a < p.n_alpha)
-            p.sweep_stats[((int64_t)row * p.n_alpha + a) * p.splits + split] = make_float4(st.ref[j], s, second ? t : t + t2, 0.f);
+          const float other = __shfl_xor(st.st[j][r], 32, kWave);   // row 8 + a
+          int a = 4 * (lane >> 4) + r;
+          const bool there = row < p.rows && a < (p.n_alpha > SWEEP_SPLIT_ROWS && !second ? SWEEP_SPLIT_ROWS : p.n_alpha);
+          if (!second && p.n_alpha > SWEEP_SPLIT_ROWS && a >= p.zero_alpha) ++a;   // (the alphas but the one that is zero)
+          if (there)
+            p.sweep_stats[((int64_t)row * p.n_alpha + a) * p.splits + split] =
+                make_float4(st.ref[j], second ? st.more[j][r] : st.st[j][r], second ? st.st[j][r] : other, 0.f);
+        }
+        if (!second && p.n_alpha > SWEEP_SPLIT_ROWS) {
+          float s = st.more[j][0], t = st.more[j][1];
+          s += __shfl_xor(s, 16, kWave);
+          t += __shfl_xor(t, 16, kWave);
+          s += __shfl_xor(s, 32, kWave);
+          t += __shfl_xor(t, 32, kWave);
+          if (row < p.rows && lane < 16)
+            p.sweep_stats[((int64_t)row * p.n_alpha + p.zero_alpha) * p.splits + split] = make_float4(st.ref[j], s, t, 0.f);
         }
       }
     }

@@ -225,7 +225,7 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
 
   const int my_row = rb * BN + tid;
   typename EPI::State st;
-  EPI::init(st, p, my_row);
+  EPI::init(st, p, my_row, split);
 
   // prologue: W0 A0 W1 A1 and the first half of W2 in flight; stage 0 landed
   set_lds_dma_base(w_lds);

@@ -58,7 +58,7 @@ void ll_lens_gemm_kernel(const GemmArgs p) {
   // --- epilogue state: this lane owns lens row (rb*BN + tid).
   const int my_row = rb * BN + tid;
   typename EPI::State st;
-  EPI::init(st, p, my_row);
+  EPI::init(st, p, my_row, split);
 
   const int KT = (d + BK - 1) / BK;
 

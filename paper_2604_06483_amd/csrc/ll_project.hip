@@ -179,39 +179,65 @@ __global__ __launch_bounds__(256) void ll_unembed_direction_kernel(const uint16_
   }
 }
 
-// Step 2: what the sweep epilogue reads per group of 16 ids (see GemmArgs), the flag that says which form of the epilogue
-// runs, and the zeroed bounds.
+// Step 2: what the sweep epilogue reads per group of 16 ids and per tile (see GemmArgs), the flag that says which form of the
+// epilogue runs, and the zeroed bounds.  A block's turn is one tile.
 __global__ __launch_bounds__(256) void ll_sweep_table_kernel(const float* __restrict__ block_max, int n_blocks, int n_padded,
-                                                             AlphaList alphas, int n_alpha, const float* __restrict__ u,
+                                                             AlphaList alphas, int n_alpha, int zero_alpha, const float* __restrict__ u,
                                                              float* __restrict__ eu, float* __restrict__ shift_max,
+                                                             float* __restrict__ shift_min, float* __restrict__ shift_tile,
                                                              int* __restrict__ general, unsigned* __restrict__ bound, int n_bound) {
+  __shared__ float s_most[SWEEP_MAX][16];
+  static_assert(BM == 256, "a thread per id of a tile");
   for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_bound; i += gridDim.x * blockDim.x) bound[i] = 0u;
-  for (int id = blockIdx.x * blockDim.x + threadIdx.x; id < n_padded; id += gridDim.x * blockDim.x) {   // (whole groups: n_padded is a multiple of 256)
+  for (int id = blockIdx.x * blockDim.x + threadIdx.x; id < n_padded; id += gridDim.x * blockDim.x) {   // (whole tiles: n_padded is a multiple of 256)
     const float x = u[id];
-    float* const rows = eu + (int64_t)(id >> 4) * (SWEEP_ROWS * SWEEP_GROUP) + (id & 15);
-    const int second = n_alpha <= SWEEP_SPLIT_ROWS ? SWEEP_SPLIT_ROWS : SWEEP_GROUP;   // first row of the factors times u
+    const int group = (threadIdx.x >> 4) & 15, at = id & 15;
+    float* const rows = eu + (int64_t)(id >> 4) * (SWEEP_ROWS * SWEEP_GROUP) + at;
+    const bool leave_zero = n_alpha > SWEEP_SPLIT_ROWS && zero_alpha >= 0;
+    // (nine alphas none of which is zero: e^(alpha u) in a table of its own)
+    const bool two = n_alpha > SWEEP_SPLIT_ROWS && !leave_zero;
+    float* const factor = two ? rows + (int64_t)n_padded * SWEEP_ROWS : rows;
+    float* const factor_u = two ? rows : rows + SWEEP_SPLIT_ROWS * SWEEP_GROUP;
+    const int filled = two ? SWEEP_GROUP : SWEEP_SPLIT_ROWS;
     float spread = 0.f;
-    for (int a = 0; a < second; ++a) {
-      float e = 0.f, es = 0.f, most = 0.f, least = 0.f;
-      if (a < n_alpha) {
-        const float shift = alphas.a[a] * x;
-        e = expf(shift);
-        es = e * shift;
-        most = least = shift;
+    int row = 0;
+    for (int a = 0; a < n_alpha; ++a) {
+      const float shift = alphas.a[a] * x;
+      float most = shift, least = shift;
 #pragma unroll
-        for (int off = 8; off > 0; off >>= 1) {
-          most = fmaxf(most, __shfl_xor(most, off, kWave));
-          least = fminf(least, __shfl_xor(least, off, kWave));
-        }
-        spread = fmaxf(spread, most - least);
+      for (int off = 8; off > 0; off >>= 1) {
+        most = fmaxf(most, __shfl_xor(most, off, kWave));
+        least = fminf(least, __shfl_xor(least, off, kWave));
       }
-      rows[a * SWEEP_GROUP] = e;
-      rows[(second + a) * SWEEP_GROUP] = es;
-      // (alpha number a of the group: its first id + a; with the margin for its rounding, SWEEP_MARGIN, unless no logit is shifted at all)
-      if ((id & 15) == a && a < 15) shift_max[id] = most == 0.f && least == 0.f ? 0.f : most + SWEEP_MARGIN;
-      if (a == 0 && (id & 15) >= second && (id & 15) < 15) shift_max[id] = 0.f;
+      spread = fmaxf(spread, most - least);
+      // (with the margin for its rounding, SWEEP_MARGIN, unless no logit is shifted at all)
+      most = most == 0.f && least == 0.f ? 0.f : most + SWEEP_MARGIN;
+      if (at == a) {   // (alpha number a of the group: its first id + a)
+        shift_max[id] = most;
+        shift_min[id] = least;
+        s_most[a][group] = most;
+      }
+      if (leave_zero && a == zero_alpha) continue;
+      const float e = expf(shift);
+      factor[row * SWEEP_GROUP] = e;
+      factor_u[row * SWEEP_GROUP] = e * shift;
+      ++row;
     }
-    if ((id & 15) == 15) shift_max[id] = spread;
+    for (; row < filled; ++row) factor[row * SWEEP_GROUP] = factor_u[row * SWEEP_GROUP] = 0.f;
+    if (at >= n_alpha) {
+      shift_max[id] = at == 15 ? spread : 0.f;
+      shift_min[id] = 0.f;
+    }
+    __syncthreads();
+    if (threadIdx.x < 16) {
+      float most = 0.f;
+      if ((int)threadIdx.x < n_alpha) {
+        most = s_most[threadIdx.x][0];
+        for (int g = 1; g < 16; ++g) most = fmaxf(most, s_most[threadIdx.x][g]);
+      }
+      shift_tile[(id >> 8) * 16 + threadIdx.x] = most;
+    }
+    __syncthreads();
   }
   if (blockIdx.x != 0 || threadIdx.x >= 64) return;
   float largest = 0.f, alpha = 0.f;
@@ -422,8 +448,9 @@ __global__ __launch_bounds__(256) void ll_sweep_merge_kernel(const float4* __res
   const double lse = (double)M + log((double)S);
   zt = wave_max(zt);
   const int64_t o = (int64_t)a * out_stride + row;
+  // the projection kernel of this pass is done with the bounds, if it had any: clear them for the next pass
+  if (bound != nullptr && lane < k) bound[(lane * n_alpha + a) * rows + row] = 0u;
   if (lane == 0) {
-    bound[a * rows + row] = 0u;   // the projection kernel of this pass is done with it: clear it for the next pass
     out_entropy[o] = (float)(lse - (double)T / (double)S);
     if (target != nullptr) {
       const int t = target[row];
@@ -815,7 +842,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
 }
 
 struct SweepPlan {
-  size_t off_u, off_block_max, off_eu, off_shift, off_general, off_bound, off_stats, off_ztgt, off_top, off_panel, total;
+  size_t off_u, off_block_max, off_eu, off_shift, off_shift_min, off_shift_tile, off_general, off_bound, off_stats, off_ztgt, off_top, off_panel, total;
   size_t off_project, wanted;   // the projection's workspace where one alpha is left to it; wanted: what the call is fastest with
   int64_t lda;
   int n_padded;   // V in whole tiles
@@ -847,10 +874,12 @@ SweepPlan make_sweep_plan(const ll_shape* s, int n_alpha, int k = 1) {
   p.off_u = take((size_t)p.n_padded * sizeof(float));
   p.off_block_max = take(UD_BLOCKS * sizeof(float));
   p.off_project = off;
-  p.off_eu = take((size_t)p.n_padded * SWEEP_ROWS * sizeof(float));
+  p.off_eu = take((size_t)p.n_padded * 2 * SWEEP_ROWS * sizeof(float));
   p.off_shift = take((size_t)p.n_padded * sizeof(float));
+  p.off_shift_min = take((size_t)p.n_padded * sizeof(float));
+  p.off_shift_tile = take((size_t)tiles * 16 * sizeof(float));
   p.off_general = take(sizeof(int));
-  p.off_bound = take(rows * n_alpha * sizeof(unsigned));
+  p.off_bound = take(rows * n_alpha * k * sizeof(unsigned));
   p.off_stats = take(partials * n_alpha * sizeof(float4));
   p.off_ztgt = take(partials * sizeof(float));
   p.off_top = take(partials * n_alpha * (k > 1 ? SWEEP_KS : 1) * sizeof(uint2));
@@ -896,6 +925,8 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
   float* const u = reinterpret_cast<float*>(ws + plan.off_u);
   float* eu = reinterpret_cast<float*>(ws + plan.off_eu);
   float* shift_max = reinterpret_cast<float*>(ws + plan.off_shift);
+  float* shift_min = reinterpret_cast<float*>(ws + plan.off_shift_min);
+  float* shift_tile = reinterpret_cast<float*>(ws + plan.off_shift_tile);
   float* block_max = reinterpret_cast<float*>(ws + plan.off_block_max);
   int* general = reinterpret_cast<int*>(ws + plan.off_general);
   unsigned* bound = reinterpret_cast<unsigned*>(ws + plan.off_bound);
@@ -930,24 +961,28 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     return project_impl(shape, ws + plan.off_project, workspace_bytes - plan.off_project, hidden, gamma, W_U, u, 0u, eps, k, target_ids, out_ids,
                         out_p, out_logp, out_entropy, stream, nullptr);
   // Few alphas: the general form alone, without the tables and the launch that fills them.  Its cost grows with every alpha, the
-  // factored one's hardly does after a split's first tile, where it looks at more candidates: the line moves up with fewer tiles a
-  // split.  Whole calls, general | factored, us, d = 512 (N x V: tiles a split), arg max:
-  //   100 x 50257 (1)      A = 5  69 | 93       A = 6  75 | 95       A = 7  81 | 95
-  //   300 x 50257 (2)      A = 4  99 | 121      A = 5  110 | 127     A = 6  122 | 130    A = 7  134 | 133
-  //   700 x 50257 (3)      A = 4  133 | 150     A = 5  149 | 159     A = 6  167 | 162
-  //   1500 x 50257 (5)     A = 4  204 | 221     A = 5  231 | 231     A = 6  257 | 234
-  //   4000 x 128256 (32)   A = 4  1047 | 1081   A = 5  1181 | 1102
+  // factored one's hardly does: the line moves up where a split has few tiles and there are no lists.  Whole calls, general |
+  // factored, us, d = 512 (N x V: tiles a split), arg max:
+  //   60 x 20000 (1)       A = 6  67 | 77       A = 7  73 | 76       A = 8  78 | 76
+  //   1500 x 4096 (1)      A = 7  78 | 87       A = 8  84 | 88       A = 9  91 | 90
+  //   300 x 50257 (2)      A = 4  99 | 117      A = 5  109 | 119     A = 6  120 | 120    A = 7  131 | 116
+  //   700 x 50257 (3)      A = 3  117 | 145     A = 4  133 | 144     A = 5  149 | 147
+  //   1500 x 50257 (5)     A = 3  181 | 214     A = 4  206 | 217     A = 5  232 | 218
+  //   4000 x 128256 (32)   A = 3  923 | 963     A = 4  1055 | 968
   // and lists:
-  //   100 x 50257 (1)      A = 4  103 | 113     A = 5  117 | 134     A = 6  133 | 135    A = 7  147 | 137
-  //   700 x 50257 (3)      A = 3  161 | 190     A = 4  192 | 193     A = 5  222 | 228    A = 6  253 | 231
-  //   1500 x 50257 (5)     A = 3  236 | 275     A = 4  279 | 280     A = 5  324 | 319
-  //   4000 x 128256 (32)   A = 3  1089 | 1230   A = 4  1281 | 1245
-  const bool lists = k > 1, only_general = n_alpha <= (lists ? 3 : 4) + (each == 1 ? 2 : each <= 4 ? 1 : 0);
+  //   60 x 20000 (1)       A = 3  81 | 83       A = 4  94 | 84
+  //   300 x 50257 (2)      A = 3  125 | 132     A = 4  148 | 135
+  //   1500 x 50257 (5)     A = 3  240 | 250     A = 4  287 | 259
+  //   4000 x 128256 (32)   A = 3  1114 | 1120   A = 4  1306 | 1138
+  const bool lists = k > 1, only_general = n_alpha <= (lists || each > 8 ? 3 : each == 1 ? 7 : each == 2 ? 5 : 4);
+  int zero_alpha = -1;   // of nine alphas one that is zero needs no place in the tables
+  for (int a = 0; a < n_alpha; ++a)
+    if (n_alpha > SWEEP_SPLIT_ROWS && al.a[a] == 0.f) zero_alpha = a;
   if (!only_general) {
-    const int n_bound = (int)(N < CHUNK_ROWS ? N : CHUNK_ROWS) * n_alpha;
+    const int n_bound = (int)(N < CHUNK_ROWS ? N : CHUNK_ROWS) * n_alpha * k;
     hipLaunchKernelGGL(ll_sweep_table_kernel, dim3(plan.n_padded / 256 < 2048 ? plan.n_padded / 256 : 2048), dim3(256), 0, stream,
-                       (const float*)block_max, UD_BLOCKS, plan.n_padded, al, n_alpha, (const float*)u, eu, shift_max, general, bound,
-                       n_bound);
+                       (const float*)block_max, UD_BLOCKS, plan.n_padded, al, n_alpha, zero_alpha, (const float*)u, eu, shift_max,
+                       shift_min, shift_tile, general, bound, n_bound);
     LL_CHECK_S(hipGetLastError());
   }
   // (d is at most SWEEP_MAX_D: the direct-to-LDS kernel's 32-bit row offsets always suffice)
@@ -984,12 +1019,15 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     a.u = u;
     a.eu = eu;
     a.shift_max = shift_max;
+    a.shift_min = shift_min;
+    a.shift_tile = shift_tile;
     a.sweep_general = only_general ? nullptr : general;
     a.sweep_stats = stats;
     a.sweep_ztgt = ztgt;
     a.sweep_top = top;
     a.bound = bound;
     a.n_alpha = n_alpha;
+    a.zero_alpha = zero_alpha;
     for (int i = 0; i < SWEEP_MAX; ++i) a.alphas[i] = al.a[i];
     const int64_t blocks = ((int64_t)a.row_blocks * a.splits + NUM_XCD - 1) / NUM_XCD * NUM_XCD;
     for (const GemmKernel g : kern) {
@@ -1000,7 +1038,7 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     const auto merge = lists ? ll_sweep_merge_kernel<SWEEP_KS> : ll_sweep_merge_kernel<1>;
     hipLaunchKernelGGL(merge, dim3((unsigned)((rows * n_alpha + 3) / 4)), dim3(256), 0, stream, (const float4*)stats, (const uint2*)top,
                        (const float*)ztgt, (const float*)u, al, rows, a.splits, n_alpha, k, V, a.target, N, out_ids + r0 * k,
-                       out_p + r0 * k, out_logp ? out_logp + r0 : nullptr, out_entropy + r0, bound);
+                       out_p + r0 * k, out_logp ? out_logp + r0 : nullptr, out_entropy + r0, only_general ? nullptr : bound);
     LL_CHECK_S(hipGetLastError());
   }
 #undef LL_CHECK_S

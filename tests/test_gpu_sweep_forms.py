@@ -56,6 +56,20 @@ def test_splits(N, d, V, n_alpha, k):
     check(N, d, V, ALPHAS9[:n_alpha], k, 1.0, "splits")
 
 
+@pytest.mark.parametrize("k", [None, 3])
+@pytest.mark.parametrize("alphas", [
+    [-4.0, -3.0, -2.0, -1.0, 0.5, 1.0, 2.0, 3.0, 4.0],    # none is zero: a second table
+    [0.0, -3.0, -2.0, -1.0, 0.5, 1.0, 2.0, 3.0, 4.0],     # one is: its sums apart from the products; at either end, and beside another
+    [-4.0, -3.0, -2.0, -1.0, 0.5, 1.0, 2.0, 3.0, 0.0],
+    [-4.0, -3.0, 0.0, -1.0, 0.5, 1.0, -0.0, 3.0, 4.0],
+    [-4.0, -3.0, 0.0, -1.0, 0.5, 1.0, 2.0, 3.0],          # eight: as any other
+])
+def test_nine_strengths_with_and_without_zero(alphas, k):
+    say(f"sweep strengths {alphas} k={k}")
+    check(300, 128, 7000, alphas, k, 1.0, "strengths")
+    check(300, 72, 5003, alphas, k, 30.0, "strengths, ragged")
+
+
 @pytest.mark.parametrize("N,d,V,n_alpha,k", [
     (4200, 64, 100000, 9, 3),     # 17 row blocks, 15 splits of 27 tiles: 432 groups of 16 ids a sum
     (1500, 128, 50257, 8, None),  # 40 splits of five tiles

@@ -38,7 +38,10 @@ struct GemmArgs {
   int n_alpha, zero_alpha;  // zero_alpha: of nine, one that is zero, or -1
   float alphas[LL_SWEEP_MAX];
   // sharing top-k thresholds between the vocabulary splits of a row (nullptr: off)
-  unsigned* bound;          // [rows] (sweep: [k, n_alpha, rows]) lower bounds on each row's k-th best logit, as ordered keys; zero at launch
+  unsigned* bound;          // [rows] lower bounds on each row's k-th best logit, as ordered keys; zero at launch.  With classes: [classes, rows]
+                            // the best logits of the row that each class of splits has seen (sweep: [k, n_alpha, rows])
+  int classes;              // short calls: 0, or k, the classes that the splits are dealt into (see exchange_classes)
+  int half_tiles;           // short calls: 0, or V in half tiles where the splits are cut between those
 };
 
 using GemmKernel = void (*)(const GemmArgs);
@@ -47,6 +50,8 @@ using GemmKernel = void (*)(const GemmArgs);
 // list with a bias).
 GemmKernel tail_topk_kernel(int k, bool bias);
 GemmKernel tail_sweep_kernel(bool lists);
+// Those for calls of few tiles a workgroup, k <= 20 (ll_project_short.hip); ragged: d is not a multiple of 64.
+GemmKernel short_topk_kernel(int k, bool bias, bool ragged);
 // The general form of the steering sweep, for any d (see ll_epilogue_sweep.h).
 GemmKernel general_sweep_kernel(bool lists);
 
@@ -129,6 +134,8 @@ struct RowState {
   float z_tgt = -INFINITY;  // logit of the target id, once its tile has passed
   int tgt = -1;             // target id of the row (-1: none)
   float shared_bound = -INFINITY;   // nothing at or below this can reach the row's final top k (see exchange_bound)
+  int cls = -1;             // the split's class, if there are any
+  bool first = true;        // no tile has been seen
   float lv[KR];             // top logits
   int li[KR];               // their ids
   __device__ __forceinline__ void init() {
@@ -180,6 +187,13 @@ struct RowState {
     }
   }
 };
+
+// The largest of three, as one instruction (the compiler's fmaxf first makes every operand that it can't trace a quiet number).
+__device__ __forceinline__ float max3(float a, float b, float c) {
+  float r;
+  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
 
 // Reads one accumulator element where it lives (an AGPR) at the point of use, so that the
 // register allocator does not copy the whole 256-register tile into VGPRs ahead of the epilogue.
@@ -244,8 +258,8 @@ __device__ __forceinline__ void load_group(const f32x16 (&acc)[8][2], float (&x)
 // transpose, done by one round of v_permlane32_swap (blocks 2,3 of one register against blocks
 // 0,1 of another) and one of v_permlane16_swap (odd blocks against even blocks).  Afterwards lane
 // l owns lens row 64 w + l again, and register g holds vocabulary row 16 i + 4 g + r.
-template <int I>
-__device__ __forceinline__ void load_group(const f32x4 (&acc)[16][4], float (&x)[32]) {
+template <int I, int N>
+__device__ __forceinline__ void load_group(const f32x4 (&acc)[N][4], float (&x)[32]) {
 #pragma unroll
   for (int t = 0; t < 2; ++t) {
 #pragma unroll
@@ -353,10 +367,10 @@ __device__ __forceinline__ void epilogue_group(const ACC& acc, RowState<KR>& st,
   }
 }
 
-template <int KR, bool BIAS, class ACC>
-__device__ __forceinline__ void epilogue_tile(const ACC& acc, RowState<KR>& st, int v0, int V,
-                                              const float* __restrict__ bias) {
-  const bool partial = v0 + BM > V;
+// HALF: a tile of 128 entries (a short call's last tile).
+template <int KR, bool BIAS, bool HALF, class ACC>
+__device__ __forceinline__ void epilogue_tile(const ACC& acc, RowState<KR>& st, int v0, int V, const float* __restrict__ bias) {
+  const bool partial = v0 + (HALF ? BM / 2 : BM) > V;
   // The accumulators are read below through inline asm, which the compiler's MFMA hazard
   // bookkeeping does not see: let the last MFMA of the tile drain first.
   asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
@@ -364,10 +378,12 @@ __device__ __forceinline__ void epilogue_tile(const ACC& acc, RowState<KR>& st, 
   epilogue_group<1, KR, BIAS, ACC>(acc, st, v0, V, partial, bias);
   epilogue_group<2, KR, BIAS, ACC>(acc, st, v0, V, partial, bias);
   epilogue_group<3, KR, BIAS, ACC>(acc, st, v0, V, partial, bias);
-  epilogue_group<4, KR, BIAS, ACC>(acc, st, v0, V, partial, bias);
-  epilogue_group<5, KR, BIAS, ACC>(acc, st, v0, V, partial, bias);
-  epilogue_group<6, KR, BIAS, ACC>(acc, st, v0, V, partial, bias);
-  epilogue_group<7, KR, BIAS, ACC>(acc, st, v0, V, partial, bias);
+  if constexpr (!HALF) {
+    epilogue_group<4, KR, BIAS, ACC>(acc, st, v0, V, partial, bias);
+    epilogue_group<5, KR, BIAS, ACC>(acc, st, v0, V, partial, bias);
+    epilogue_group<6, KR, BIAS, ACC>(acc, st, v0, V, partial, bias);
+    epilogue_group<7, KR, BIAS, ACC>(acc, st, v0, V, partial, bias);
+  }
 }
 
 // The workgroups that sweep other parts of the vocabulary for the same rows tell each other how
@@ -406,6 +422,137 @@ __device__ __forceinline__ void exchange_bound(RowState<KR>& st, const GemmArgs&
   asm volatile("" ::: "memory");
 }
 
+// Short calls (ll_project_short.hip): where the splits are at least k, a better bound.  They are dealt into k classes, and a class's
+// entry is the best logit that any of its splits has seen: k different ids, each at least the least of the k entries, which is
+// the bound.  It ranks some k (1 + 1/2 + ... + 1/k) th of all ids seen by anyone, where the best k-th entry of one split of
+// few tiles ranks several hundredth.
+
+// The kernel's arguments that the exchange uses, read where it happens: kept in scalar registers through the epilogue they leave
+// none to load a bias ahead.
+typedef const GemmArgs __attribute__((address_space(4)))* const_args_ptr;
+__device__ __forceinline__ const_args_ptr args_again() {
+  auto args = (const_args_ptr)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(args));
+  return args;
+}
+
+template <int KR>
+__device__ __forceinline__ unsigned least_of_classes(const RowState<KR>& st, unsigned* bound, int classes, int rows, int my_row, unsigned& own) {
+  asm volatile("" : "+v"(my_row));   // (the address made anew each time rather than kept)
+  const unsigned at = 4u * (unsigned)min(my_row, rows - 1);
+  const unsigned char* b = reinterpret_cast<const unsigned char*>(bound);
+  unsigned fresh[KR], least = 0xffffffffu;
+#pragma unroll
+  for (int c = 0; c < KR; ++c) {   // (all in flight together: past the last class the last one's again)
+    fresh[c] = __hip_atomic_load(reinterpret_cast<const unsigned*>(b + at), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (c + 1 < classes) b += 4 * (int64_t)rows;
+  }
+  own = 0u;
+#pragma unroll
+  for (int c = 0; c < KR; ++c) {
+    least = min(least, fresh[c]);
+    own = c == st.cls ? fresh[c] : own;
+  }
+  return least;
+}
+
+// BIAS: and the next tile's biases, a word a line, into this XCD's L2, from where the epilogue's scalar loads come back in a third of
+// the time.
+template <int KR, bool BIAS>
+__device__ __forceinline__ void exchange_classes(RowState<KR>& st, int v0, int my_row) {
+  const const_args_ptr p = args_again();
+  unsigned* const bound = p->bound;
+  if (bound == nullptr) return;
+  const int rows = p->rows;
+  unsigned* b = bound + min(my_row, rows - 1);
+  asm volatile("" ::: "memory");
+  float warm = 0.f;
+  if (BIAS) warm = p->bias[min(v0 + BM + 4 * (int)(threadIdx.x & 63), p->V - 1)];
+  unsigned fresh;
+  float mine;
+  if (st.cls >= 0) {
+    st.shared_bound = below_bound(least_of_classes(st, bound, p->classes, rows, my_row, fresh));
+    b += (int64_t)st.cls * rows;
+    mine = st.lv[0];
+  } else {
+    const int k = p->k;
+    fresh = __hip_atomic_load(b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    st.shared_bound = below_bound(fresh);
+    // own bound: the k-th best of this split's list (k <= KR, KR - k < 12)
+    // (each entry goes through an empty asm statement: a plain chain of selects on k the optimiser
+    // folds into an indexed access and moves the whole list to scratch memory)
+    mine = st.lv[KR - 1];
+#pragma unroll
+    for (int j = KR - 2; j >= 0 && j >= KR - 12; --j) {
+      float entry = st.lv[j];
+      asm volatile("" : "+v"(entry));
+      mine = (k - 1 == j) ? entry : mine;
+    }
+  }
+  if (BIAS) asm volatile("" : "+v"(warm));
+  // (only what is news: the split whose bound it is, or any while all logits are equal, would send it after every tile)
+  const unsigned key = float_key(mine);
+  if (my_row < rows && key > fresh && key > KEY_NEG_INF) __hip_atomic_fetch_max(b, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  asm volatile("" ::: "memory");
+}
+
+// The largest of the tile's logits of the lane's own row.  (Vocabulary rows past the end are the last one's again, whose logit
+// they repeat; with a bias the caller sees to it that there are none.)
+template <bool BIAS, bool HALF, class ACC>
+__device__ __forceinline__ float tile_max(const ACC& acc, int v0, const float* __restrict__ bias) {
+  float q[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};
+#pragma unroll
+  for (int i = 0; i < (HALF ? 8 : 16); ++i) {
+    float4 b = make_float4(0.f, 0.f, 0.f, 0.f);
+    if (BIAS) b = *reinterpret_cast<const float4*>(bias + v0 + 16 * i + 4 * ((threadIdx.x & 63) >> 4));
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      float y0 = acc_read(acc[i][j][0]), y1 = acc_read(acc[i][j][1]), y2 = acc_read(acc[i][j][2]), y3 = acc_read(acc[i][j][3]);
+      if (BIAS) {
+        y0 += b.x;
+        y1 += b.y;
+        y2 += b.z;
+        y3 += b.w;
+      }
+      q[j] = max3(max3(q[j], y0, y1), y2, y3);
+    }
+    LL_SCHED_FENCE();
+  }
+  // row block j's maxima are spread over the lane blocks: each lane block's own row block (see load_group)
+  auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(q[0]), __float_as_uint(q[2]), false, false);
+  auto c = __builtin_amdgcn_permlane32_swap(__float_as_uint(q[1]), __float_as_uint(q[3]), false, false);
+  auto e = __builtin_amdgcn_permlane16_swap(a[0], c[0], false, false);
+  auto f = __builtin_amdgcn_permlane16_swap(a[1], c[1], false, false);
+  return max3(fmaxf(__uint_as_float(e[0]), __uint_as_float(e[1])), __uint_as_float(f[0]), __uint_as_float(f[1]));
+}
+
+// A split's first tile, whose list is empty: the splits tell each other their best logits before any of them builds its list.
+// They come here at nearly the same time; a lane looks for the others' a few times (less than the insertions that it saves) and goes
+// on with what there is.  Cycles of the epilogue of the first tile, without | with: 957 rows, d = 4096, V = 128256,
+// k = 10: 66 800 | 31 000 (and 27 600 falling to 19 900 | 21 600 falling to 16 500 after that); 777 rows, d = 1608, V = 50257, k = 3
+// with a bias: 39 900 | 31 400.
+constexpr int FIRST_LOOKS = 8;
+template <int KR, bool BIAS, bool HALF, class ACC>
+__device__ __forceinline__ void first_bound(const ACC& acc, RowState<KR>& st, int v0, int my_row) {
+  const const_args_ptr p = args_again();
+  if (BIAS && v0 + (HALF ? BM / 2 : BM) > p->V) return;
+  asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");   // as in epilogue_tile
+  const float most = tile_max<BIAS, HALF>(acc, v0, p->bias);
+  unsigned* const bound = p->bound;
+  const int rows = p->rows, classes = p->classes;
+  if (my_row < rows && most > -INFINITY)
+    __hip_atomic_fetch_max(bound + (int64_t)st.cls * rows + my_row, float_key(most), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll 1
+  for (int look = 0; look < FIRST_LOOKS; ++look) {
+    asm volatile("" ::: "memory");
+    unsigned own;
+    const unsigned least = least_of_classes(st, bound, classes, rows, my_row, own);
+    st.shared_bound = below_bound(least);
+    if (__builtin_amdgcn_ballot_w64(least == 0u) == 0) break;
+  }
+  asm volatile("" ::: "memory");
+}
+
 // Per-(row, split) partial results: (m, S, T, z_target) and the k best (logit bits, id) pairs.
 template <int KR>
 __device__ __forceinline__ void epilogue_store(const GemmArgs& p, const RowState<KR>& st, int my_row, int split) {
@@ -419,20 +566,30 @@ __device__ __forceinline__ void epilogue_store(const GemmArgs& p, const RowState
 
 // What a GEMM kernel does with a finished tile is a policy: the state of the lane's row, how a
 // tile updates it, and what goes to the workspace at the end of the sweep.
-template <int KR, bool BIAS = false>
+// SHORT: with the classes of splits, and a last tile of half the width.
+template <int KR, bool BIAS = false, bool SHORT = false>
 struct TopKEpilogue {   // a5..a7: softmax statistics, k best logits, target logit (BIAS: Eq. 1's b added to every logit first)
   using State = RowState<KR>;
   static constexpr bool RELOAD_FRAGMENTS = false;
   static __device__ __forceinline__ bool skip(const GemmArgs&) { return false; }
-  static __device__ __forceinline__ void init(State& st, const GemmArgs& p, int my_row, int) {
+  static __device__ __forceinline__ void init(State& st, const GemmArgs& p, int my_row, int split) {
     st.init();
+    if (SHORT && p.classes > 0) st.cls = split % p.classes;
     st.tgt = (p.target != nullptr && my_row < p.rows) ? p.target[my_row] : -1;
   }
+  static __device__ __forceinline__ void settle(State& st) { asm volatile("" : "+v"(st.tgt)); }   // its loads have come back
   template <class ACC>
   static __device__ __forceinline__ void tile(const ACC& acc, State& st, int v0, const GemmArgs& p, int my_row) {
-    epilogue_tile<KR, BIAS, ACC>(acc, st, v0, p.V, p.bias);
+    epilogue_tile<KR, BIAS, false, ACC>(acc, st, v0, p.V, p.bias);
     // (the longest list together with a bias leaves no register for the exchange: that one kernel goes without)
     if (!(KR == 32 && BIAS)) exchange_bound(st, p, my_row);
+  }
+  template <bool HALF, class ACC>
+  static __device__ __forceinline__ void short_tile(const ACC& acc, State& st, int v0, const GemmArgs& p, int my_row) {
+    if (st.first && st.cls >= 0) first_bound<KR, BIAS, HALF>(acc, st, v0, my_row);
+    st.first = false;
+    epilogue_tile<KR, BIAS, HALF>(acc, st, v0, p.V, p.bias);
+    exchange_classes<KR, BIAS>(st, v0, my_row);
   }
   static __device__ __forceinline__ void store(const GemmArgs& p, const State& st, int my_row, int split) {
     epilogue_store(p, st, my_row, split);

@@ -265,13 +265,7 @@ __device__ __forceinline__ void sweep_group_general(const float (&x)[16], SweepS
   }
 }
 
-// The largest and the least of three, as one instruction (the compiler's fmaxf first makes every operand that it can't trace a
-// quiet number).
-__device__ __forceinline__ float max3(float a, float b, float c) {
-  float r;
-  asm("v_max3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
-  return r;
-}
+// The least of three (see max3).
 __device__ __forceinline__ float min3(float a, float b, float c) {
   float r;
   asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));

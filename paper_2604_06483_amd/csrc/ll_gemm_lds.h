@@ -103,20 +103,43 @@ __device__ __forceinline__ f32x4 mfma16_from_zero(bf16x8 a, bf16x8 b) {
   return c;
 }
 
-template <class EPI, bool TAIL>
+//
+// SHORT (likewise): for calls of few tiles a workgroup.  A split's last tile may be half a tile wide, with stages of two slices,
+// behind which the same loads go out and the same wait and barrier stand (the vocabulary rows past the end are the last one's
+// again).  In code of its own: one body with branches around the slices that a half tile leaves out makes the register allocator
+// copy accumulators to memory.  A half tile takes 0.6 of a whole one's time (d = 1608: 49 000
+// cycles, and 82 000).  197 tiles over 64 splits are four a workgroup; 393
+// half tiles are seven.
+// ---------------------------------------------------------------------------------------
+template <class EPI, bool TAIL, bool SHORT = false>
 __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* const smem) {
 
   const int logical = xcd_logical_block();
   if (__builtin_expect(logical >= p.row_blocks * p.splits || EPI::skip(p), 0)) return;
   const int split = logical % p.splits;
   const int rb = logical / p.splits;
-  const int tile0 = (int)((int64_t)split * p.tiles / p.splits);
-  const int tile1 = (int)((int64_t)(split + 1) * p.tiles / p.splits);
+  // the split's tiles; SHORT: counted from its first vocabulary row, row0, up to row_end
+  int tile0 = (int)((int64_t)split * p.tiles / p.splits);
+  int tile1 = (int)((int64_t)(split + 1) * p.tiles / p.splits);
+  int row0 = 0, row_end = p.V;
+  bool ends_in_half = false;
+  if (SHORT) {
+    int half0 = 2 * tile0, half1 = 2 * tile1;
+    if (p.half_tiles > 0) {
+      half0 = (int)((int64_t)split * p.half_tiles / p.splits);
+      half1 = (int)((int64_t)(split + 1) * p.half_tiles / p.splits);
+    }
+    row0 = half0 * (BM / 2);
+    if (half1 * (BM / 2) < row_end) row_end = half1 * (BM / 2);
+    ends_in_half = ((half1 - half0) & 1) != 0;
+    tile0 = 0;
+    tile1 = (half1 - half0 + 1) / 2;
+  }
 
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int d = p.d, V = p.V;
+  const int d = p.d;
   const int lda = (int)p.lda;
   const int KT = lda / DK;
 
@@ -151,7 +174,7 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
     for (int s = 0; s < 8; ++s) w_off[s] -= (s & 1) ? odd : even;
   };
   auto set_w_rows = [&](int tile) {
-    const int w_last = V - 1 - tile * BM;
+    const int w_last = row_end - 1 - row0 - tile * BM;
     int l = lane;
     if (EPI::RELOAD_FRAGMENTS) asm volatile("" : "+v"(l));   // (made anew for every tile: 18 registers less to keep)
     const int row = 64 * wave + (l >> 3), koff0 = ((l & 7) ^ (l >> 4)) * 8;
@@ -174,7 +197,7 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
   const unsigned a_lds_flip = (2 * W_SLOTS + 1) * SLOT_BYTES + 2 * lds_mid;   // slot 3 <-> slot 4
   const unsigned char* const a_base0 = reinterpret_cast<const unsigned char*>(p.A + (int64_t)rb * BN * lda) - IMM_BIAS;
   auto w_tile_base = [&](int tile) {
-    return reinterpret_cast<const unsigned char*>(p.W + (int64_t)tile * BM * d) - IMM_BIAS;
+    return reinterpret_cast<const unsigned char*>(p.W + ((int64_t)tile * BM + row0) * d) - IMM_BIAS;
   };
   // (LL_PIN_S: the value is computed where the statement stands; without it the compiler gathers
   // the scalar updates of a whole stage into one lump, and the matrix pipe idles behind it.)
@@ -226,6 +249,7 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
   const int my_row = rb * BN + tid;
   typename EPI::State st;
   EPI::init(st, p, my_row, split);
+  if constexpr (SHORT) EPI::settle(st);
 
   // prologue: W0 A0 W1 A1 and the first half of W2 in flight; stage 0 landed
   set_lds_dma_base(w_lds);
@@ -374,14 +398,28 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
     nW = nnW;                                        \
   }
 
+#define LL_HOOK_HALF(P)   /* (all of W(g+2)'s second half and of A(g+2)) */ \
+  if (P == 1) set_lds_dma_base(w_lds);               \
+  if (P == 2) LL_DMA_W(4);                           \
+  if (P == 3) LL_DMA_W(5);                           \
+  if (P == 4) LL_DMA_W(6);                           \
+  if (P == 5) { LL_DMA_W(7); advance_w(); }          \
+  if (P == 6) set_lds_dma_base(a_lds);               \
+  if (P == 7) LL_DMA_A(0);                           \
+  if (P == 8) LL_DMA_A(1);                           \
+  if (P == 9) LL_DMA_A(2);                           \
+  if (P == 10) LL_DMA_A(3);                          \
+  if (P == 11) LL_DMA_A(4);                          \
+  if (P == 12) LL_DMA_A(5);                          \
+  if (P == 13) LL_DMA_A(6);                          \
+  if (P == 14) LL_DMA_A(7)
+
   // Consumer state: LDS byte offsets of the W tiles of this stage and of the next, and of the A
   // tile the next stage's fragments come from (it includes the wavefront's own 64 rows).
   int cW = 0, nW = SLOT_BYTES, nnW = 2 * SLOT_BYTES;
   int nA = (W_SLOTS + 1) * SLOT_BYTES + a_wave_off;
   const int a_flip = (2 * W_SLOTS + 1) * SLOT_BYTES + 2 * a_wave_off;   // slot 3 <-> slot 4
-  for (int tile = tile0; tile < tile1; ++tile) {
-    f32x4 acc[16][4];   // first written by the K half 0 MFMAs of stage 0, with C = 0
-    // One stage; MF0 is the MFMA form of K half 0: from zero in a tile's first stage, accumulating after.
+  // One stage; MF0 is the MFMA form of K half 0: from zero in a tile's first stage, accumulating after.
 #define LL_STAGE(MF0, KTILE)                                                                           \
     LL_SLICE(MF0, 0, 1, fw0, fw1, cW, 1, LL_A_NONE, LL_A_NONE, LL_HOOK_S0, LL_RD_SPREAD)               \
     LL_SLICE(MF0, 1, 0, fw1, fw0, cW, 2, LL_A_NONE, LL_A_NONE, LL_HOOK_S1, LL_RD_SPREAD)               \
@@ -391,16 +429,39 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
     if (TAIL && (KT == 1 || (KTILE) == KT - 2)) zero_tail(nW);   /* stage g+1 is a row's last */        \
     __syncthreads();                                                                                   \
     LL_SLICE(MF0, 3, 1, fw1, fw0, nW, 0, LL_AIN_S3, LL_AOUT_S3, LL_HOOK_S3, LL_RD_SPREAD)
+  // The same of half a tile: vocabulary rows 0 .. 127 of it.
+#define LL_HALF_STAGE(MF0, KTILE)                                                                      \
+    LL_SLICE(MF0, 0, 1, fw0, fw1, cW, 1, LL_A_NONE, LL_A_NONE, LL_HOOK_HALF, LL_RD_AHEAD)              \
+    __builtin_amdgcn_s_waitcnt(waitcnt_imm(2 * LOADS_PER_TILE, 0));                                    \
+    if (TAIL && (KT == 1 || (KTILE) == KT - 2)) zero_tail(nW);                                         \
+    __syncthreads();                                                                                   \
+    LL_SLICE(MF0, 1, 1, fw1, fw0, nW, 0, LL_AIN_S3, LL_AOUT_S3, LL_HOOK_S3, LL_RD_SPREAD)
+  for (int tile = tile0; tile < (SHORT && ends_in_half ? tile1 - 1 : tile1); ++tile) {
+    f32x4 acc[16][4];   // first written by the K half 0 MFMAs of stage 0, with C = 0
     LL_STAGE(LL_MFMA16_Z, 0)
     for (int kt = 1; kt < KT; ++kt) {
       LL_STAGE(LL_MFMA16, kt)
     }
-#undef LL_STAGE
-    EPI::tile(acc, st, tile * BM, p, my_row);
+    if constexpr (SHORT)
+      EPI::template short_tile<false>(acc, st, row0 + tile * BM, p, my_row);
+    else
+      EPI::tile(acc, st, tile * BM, p, my_row);
     // An epilogue that needs the 64 registers reads the next stage's first fragments again: both tiles stay in LDS until that
     // stage's own slices send the loads that replace them.
     if (EPI::RELOAD_FRAGMENTS) read_fragments(cW, a_flip - nA);
   }
+  if constexpr (SHORT) {
+    if (ends_in_half) {
+      f32x4 acc[8][4];
+      LL_HALF_STAGE(LL_MFMA16_Z, 0)
+      for (int kt = 1; kt < KT; ++kt) {
+        LL_HALF_STAGE(LL_MFMA16, kt)
+      }
+      EPI::template short_tile<true>(acc, st, row0 + (tile1 - 1) * BM, p, my_row);
+    }
+  }
+#undef LL_STAGE
+#undef LL_HALF_STAGE
 #undef LL_PAIR
 #undef LL_RD_SPREAD
 #undef LL_RD_AHEAD
@@ -416,6 +477,7 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
 #undef LL_LDS_FRAG
 #undef LL_DMA_TILE
 #undef LL_HOOK_S3
+#undef LL_HOOK_HALF
 #undef LL_PIN_S
 #undef LL_HOOK_S2
 #undef LL_HOOK_S1
@@ -438,6 +500,13 @@ __global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(1, 1))
 void ll_lens_gemm_dma_tail_kernel(const GemmArgs p) {
   extern __shared__ __align__(16) unsigned char smem[];
   lens_gemm_dma<EPI, true>(p, smem);
+}
+
+template <class EPI, bool TAIL>
+__global__ __launch_bounds__(NTHREADS) __attribute__((amdgpu_waves_per_eu(1, 1)))
+void ll_lens_gemm_short_kernel(const GemmArgs p) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  lens_gemm_dma<EPI, TAIL, true>(p, smem);
 }
 
 }  // namespace

@@ -44,11 +44,11 @@ __global__ __launch_bounds__(256) void ll_rms_stats_kernel(const uint16_t* __res
 template <int NITER>
 __global__ __launch_bounds__(256) void ll_norm_panel_kernel(const uint16_t* __restrict__ hidden,
                                                             const uint16_t* __restrict__ gamma, uint16_t* __restrict__ panel,
-                                                            int rows, int d, int64_t lda, float eps, unsigned* __restrict__ bound) {
+                                                            int rows, int d, int64_t lda, float eps, unsigned* __restrict__ bound, int bounds) {
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   if (row >= rows) return;
-  if (bound != nullptr && lane == 0) bound[row] = 0u;   // the row's shared top-k bound, before the pass that uses it
+  if (bound != nullptr && lane < bounds) bound[(int64_t)lane * rows + row] = 0u;   // the row's shared top-k bounds, before the pass that uses them
   const uint4* src = reinterpret_cast<const uint4*>(hidden + (int64_t)row * d);
   uint4* dst = reinterpret_cast<uint4*>(panel + (int64_t)row * lda);
   const uint4* g4 = reinterpret_cast<const uint4*>(gamma);
@@ -270,7 +270,7 @@ __global__ __launch_bounds__(256) void ll_merge_kernel(const float4* __restrict_
                                                        int rows, int splits, int k, int V, int topk_softmax,
                                                        const int32_t* __restrict__ target, int32_t* __restrict__ out_ids,
                                                        float* __restrict__ out_p, float* __restrict__ out_logp,
-                                                       float* __restrict__ out_entropy, unsigned* __restrict__ bound) {
+                                                       float* __restrict__ out_entropy, unsigned* __restrict__ bound, int bounds) {
   extern __shared__ __align__(8) uint2 lists[];
   const int wave = threadIdx.x >> 6;
   const int lane = threadIdx.x & 63;
@@ -310,8 +310,8 @@ __global__ __launch_bounds__(256) void ll_merge_kernel(const float4* __restrict_
   const float T = wave_sum(t_lane);
   const float zt = wave_max(zt_lane);
   const float logS = logf(S);
+  if (bound != nullptr && lane < bounds) bound[(int64_t)lane * rows + row] = 0u;   // the projection kernel of this pass is done with them: clear them for the next pass
   if (lane == 0) {
-    if (bound != nullptr) bound[row] = 0u;   // the projection kernel of this pass is done with it: clear it for the next pass
     out_entropy[row] = (M - T / S) + logS;
     if (target != nullptr) {
       const int t = target[row];
@@ -519,7 +519,7 @@ FewPlan make_few_plan(const ll_shape* s, int k) {
 
 struct Plan {
   size_t off_inv_rms, off_bound, off_bias, off_stats, off_top, off_panel, total;   // total: never less for more rows
-  int64_t lda;
+  int64_t lda, bounds;
   FewPlan few;
   size_t few_total, few_off_stats, few_off_cand, few_off_count, few_off_panel;
 };
@@ -533,13 +533,20 @@ bool shape_ok(const ll_shape* s, int k) {
   return true;
 }
 
+// Shared bounds of a pass of at most `rows` rows: one a row, or one a row and class (k of them) where the splits are at least k.
+int64_t bound_entries(int64_t rows, int k) {
+  const int64_t classes = rows * k < MAX_PARTIALS ? rows * k : MAX_PARTIALS;
+  return rows > classes ? rows : classes;
+}
+
 Plan make_plan(const ll_shape* s, int k, int chunk_rows = CHUNK_ROWS) {
   Plan p = {};
   size_t off = 0;
   p.off_inv_rms = off;
   off = align_up(off + (size_t)s->N * sizeof(float), 256);
   p.off_bound = off;  // per-row top-k bounds shared between the splits of a pass
-  off = align_up(off + (size_t)(s->N < chunk_rows ? s->N : chunk_rows) * sizeof(unsigned), 256);
+  p.bounds = bound_entries(s->N < chunk_rows ? s->N : chunk_rows, k);
+  off = align_up(off + (size_t)p.bounds * sizeof(unsigned), 256);
   p.off_bias = off;   // the bias padded to whole tiles (ll_project_ex)
   off = align_up(off + (size_t)((s->V + BM - 1) / BM) * BM * sizeof(float), 256);
   const size_t rows = (size_t)(s->N < chunk_rows ? s->N : chunk_rows);
@@ -604,6 +611,13 @@ int allow_dynamic_lds(const void* kern, size_t lds) {
   return LL_OK;
 }
 
+// Most tiles a workgroup for which the kernel of short calls is taken, with the classes of splits and without (half tiles only).
+// Whole calls, us, long | short (d, V, rows, k: tiles a workgroup).  With classes: 256, 4096, 1500, 10 (1, in halves): 50 | 30; 1608,
+// 50257, 777, 3 with a bias (4): 197 | 187; 1024, 50257, 1500, 20 (5): 229 | 189; 4096, 128256, 957, 10 (8): 847 | 830; 1024,
+// 128256, 4000, 10 (32): 949 | 920; 5120, 151936, 4160, 3 with a bias (40): no difference.  Without: 256, 4096, 4000, 20 (1): 78 | 77;
+// 1608, 50257, 4000, 20 (13): 653 | 648; 256, 50257, 4000, 20 (13): 275 | 281; 256, 128256, 4000, 20 (32): 537 | 555.
+constexpr int SHORT_TILES = 32, SHORT_TILES_WITHOUT = 8;
+
 // The fewest vocabulary splits that give no workgroup more tiles than `most` splits would: the call takes as long as its
 // busiest workgroup, and the others' lists cost the merge (197 tiles over 64 splits are four each at most; so they are over 50).
 int even_splits(int tiles, int most) {
@@ -615,17 +629,17 @@ int even_splits(int tiles, int most) {
 
 // (few rows: one wavefront per block, so that they spread over the compute units)
 void launch_norm_panel(const uint16_t* hidden, const uint16_t* gamma, uint16_t* panel, int rows, int d, int64_t lda, float eps,
-                       unsigned* bound, hipStream_t stream) {
+                       unsigned* bound, int bounds, hipStream_t stream) {
   const int per_block = rows <= 1024 ? 1 : 4;
   const dim3 grid((unsigned)((rows + per_block - 1) / per_block)), block(64 * per_block);
   if (d <= 64 * 8 * 4)
-    hipLaunchKernelGGL(ll_norm_panel_kernel<4>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps, bound);
+    hipLaunchKernelGGL(ll_norm_panel_kernel<4>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps, bound, bounds);
   else if (d <= 64 * 8 * 8)
-    hipLaunchKernelGGL(ll_norm_panel_kernel<8>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps, bound);
+    hipLaunchKernelGGL(ll_norm_panel_kernel<8>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps, bound, bounds);
   else if (d <= 64 * 8 * 16)
-    hipLaunchKernelGGL(ll_norm_panel_kernel<16>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps, bound);
+    hipLaunchKernelGGL(ll_norm_panel_kernel<16>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps, bound, bounds);
   else
-    hipLaunchKernelGGL(ll_norm_panel_kernel<0>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps, bound);
+    hipLaunchKernelGGL(ll_norm_panel_kernel<0>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps, bound, bounds);
 }
 
 int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, const void* hidden, const void* gamma,
@@ -685,6 +699,9 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     return bias ? ll_lens_gemm_kernel<TopKEpilogue<KR, true>> : ll_lens_gemm_kernel<TopKEpilogue<KR, false>>;
   });
   if (const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(kern), lds); rc != LL_OK) return rc;
+  const GemmKernel short_kern = dma ? short_topk_kernel(k, bias != nullptr, d % DK != 0) : nullptr;
+  if (short_kern != nullptr)
+    if (const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(short_kern), lds); rc != LL_OK) return rc;
   // The direct-to-LDS kernel reads hidden in place when the rows need neither scaling nor padding.
   const bool need_panel = dma && (has_gamma || plan.lda != d);
 
@@ -733,7 +750,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     LL_CHECK_F(mark());
     if (copy) {
       launch_norm_panel(static_cast<const uint16_t*>(hidden), static_cast<const uint16_t*>(gamma), few_panel, (int)N, d, plan.lda, eps,
-                        nullptr, stream);
+                        nullptr, 0, stream);
       LL_CHECK_F(hipGetLastError());
     }
     FewArgs a;
@@ -769,7 +786,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
   if (dma) {
     bound = reinterpret_cast<unsigned*>(ws + plan.off_bound);
     if (!need_panel) {
-      const int n_zero = (int)(N < chunk_rows ? N : chunk_rows);
+      const int n_zero = (int)plan.bounds;
       hipLaunchKernelGGL(ll_zero_u32_kernel, dim3((n_zero + 255) / 256), dim3(256), 0, stream, bound, n_zero);
       LL_CHECK_F(hipGetLastError());
     }
@@ -783,22 +800,34 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
   for (int64_t r0 = 0; r0 < N; r0 += chunk_rows) {
     const int rows = (int)((N - r0) < chunk_rows ? (N - r0) : chunk_rows);
     const uint16_t* h_rows = static_cast<const uint16_t*>(hidden) + r0 * d;
+    const int row_blocks = (rows + BN - 1) / BN;
+    // One workgroup per compute unit: a pass of few rows cuts the vocabulary finer (its cost is then the one read
+    // of W_U, spread over every compute unit's share of the memory system).
+    const int most = NUM_CU / row_blocks < MAX_PROJECT_SPLITS ? NUM_CU / row_blocks : MAX_PROJECT_SPLITS;
+    int splits = even_splits(tiles, most), half_tiles = 0, classes = 0;
+    const int each = (tiles + splits - 1) / splits;
+    // Few tiles a workgroup: the kernel that can end a split in half a tile, where that leaves the busiest workgroup half a tile less,
+    // and that deals at least k splits into k classes (see exchange_classes).
+    if (short_kern != nullptr && each <= SHORT_TILES) {
+      const int halves = (V + BM / 2 - 1) / (BM / 2), each_half = (halves + most - 1) / most;
+      const int half_splits = (halves + each_half - 1) / each_half;
+      if (each_half < 2 * each && (half_splits >= k || each <= SHORT_TILES_WITHOUT)) {
+        half_tiles = halves;
+        splits = half_splits;
+      }
+      if (splits >= k) classes = k;
+    }
+    const int bounds = classes > 0 ? classes : 1;
     // a2 (+ a3 when the panel is used)
     LL_CHECK_F(mark());
     if (need_panel) {
-      launch_norm_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, d, plan.lda, eps, bound, stream);
+      launch_norm_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, d, plan.lda, eps, bound, bounds, stream);
       LL_CHECK_F(hipGetLastError());
     } else if (!dma && has_gamma) {
       hipLaunchKernelGGL(ll_rms_stats_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, h_rows, (int64_t)rows, d,
                          eps, inv_rms + r0);
       LL_CHECK_F(hipGetLastError());
     }
-    const int row_blocks = (rows + BN - 1) / BN;
-    // One workgroup per compute unit: a pass of few rows cuts the vocabulary finer (its cost is then the one read
-    // of W_U, spread over every compute unit's share of the memory system).
-    int splits = NUM_CU / row_blocks;
-    if (splits > MAX_PROJECT_SPLITS) splits = MAX_PROJECT_SPLITS;
-    splits = even_splits(tiles, splits);
     GemmArgs a;
     a.A = need_panel ? panel : h_rows;
     a.lda = need_panel ? plan.lda : d;
@@ -817,9 +846,11 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     a.tiles = tiles;
     a.row_blocks = row_blocks;
     a.bound = bound;
+    a.classes = classes;
+    a.half_tiles = half_tiles;
     const int grid = (row_blocks * splits + NUM_XCD - 1) / NUM_XCD * NUM_XCD;
     LL_CHECK_F(mark());
-    hipLaunchKernelGGL(kern, dim3(grid), dim3(NTHREADS), lds, stream, a);
+    hipLaunchKernelGGL(half_tiles > 0 || classes > 0 ? short_kern : kern, dim3(grid), dim3(NTHREADS), lds, stream, a);
     LL_CHECK_F(hipGetLastError());
     LL_CHECK_F(mark());
     if (splits <= MAX_SPLITS)
@@ -827,13 +858,13 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
                          (const float4*)stats, (const uint2*)top,
                          rows, splits, k, V, (flags & LL_FLAG_TOPK_SOFTMAX) ? 1 : 0, a.target, out_topk_ids + r0 * k,
                          out_topk_p + r0 * k,
-                         out_target_logp ? out_target_logp + r0 : nullptr, out_entropy + r0, bound);
+                         out_target_logp ? out_target_logp + r0 : nullptr, out_entropy + r0, bound, bounds);
     else   // (only passes of at most three row blocks get here: one row per block keeps the lists within 64 KB of LDS)
       hipLaunchKernelGGL(ll_merge_kernel<MERGE_LPL>, dim3(rows), dim3(256), (size_t)splits * k * sizeof(uint2), stream,
                          (const float4*)stats, (const uint2*)top,
                          rows, splits, k, V, (flags & LL_FLAG_TOPK_SOFTMAX) ? 1 : 0, a.target, out_topk_ids + r0 * k,
                          out_topk_p + r0 * k,
-                         out_target_logp ? out_target_logp + r0 : nullptr, out_entropy + r0, bound);
+                         out_target_logp ? out_target_logp + r0 : nullptr, out_entropy + r0, bound, bounds);
     LL_CHECK_F(hipGetLastError());
     LL_CHECK_F(mark());
   }
@@ -1001,7 +1032,7 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     const uint16_t* h_rows = static_cast<const uint16_t*>(hidden) + r0 * d;
     const bool need_panel = gamma != nullptr || plan.lda != d;
     if (need_panel) {
-      launch_norm_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, d, plan.lda, eps, nullptr, stream);
+      launch_norm_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, d, plan.lda, eps, nullptr, 0, stream);
       LL_CHECK_S(hipGetLastError());
     }
     GemmArgs a = {};

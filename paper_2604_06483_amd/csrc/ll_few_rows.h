@@ -9,7 +9,7 @@ namespace {
 // ---------------------------------------------------------------------------------------
 // With at most FEW_ROWS lens rows the contraction needs a fraction of the matrix pipe and the call
 // is one read of W_U (2 V d bytes).  What counts is the load stream:
-//   * W goes global -> registers, 8 rows x 128 B per instruction (whole cache lines) with the
+//   * W goes global -> registers, 8 rows x 128 B per instruction (whole cache lines), for a large W_U with the
 //     non-temporal hint (every byte is used once, by one wavefront; the hint keeps the A panel in
 //     L2), two K = 64 stages ahead;
 //   * a wavefront owns its vocabulary rows outright (MU groups of 16), so nothing is waited for but
@@ -30,10 +30,7 @@ namespace {
 // 6.3 TB/s, against 473 us on the 256-row tiles of the direct-to-LDS kernel; 151936 x 2560, 37 rows: 129 us
 // = 6.0 TB/s against 212 us.  A loop that only loads W this way reaches 6.6 TB/s (without the
 // non-temporal hint 5.9; W_U of 2.1 GB); loads of 16 rows x 64 B, which need no exchange of halves, 6.1.
-// The hint is not chosen by size.  Whole calls repeated on one W_U, with it | without, us: 24 rows, d = 4096: 60 MB 50 | 46,
-// 240 MB 65 | 51, 400 MB 101 | 109; d = 1024: 60 MB 27 | 26, 240 MB 56 | 58, 400 MB 83 | 91; 16 rows, d = 4096, 1.05 GB:
-// 172 | 192.  It costs where the Infinity Cache could keep W_U, and where rows are not whole lines of 128 bytes and a
-// line serves two stages (16 rows, d = 4104, 1.05 GB: 286 | 215).  The 256-row tiles need 68 to 445 us for these.
+// STREAM: with the hint (the caller chooses by the size and the alignment of W_U's rows).
 // ---------------------------------------------------------------------------------------
 constexpr int FEW_WAVES = 8;
 constexpr int FEW_THREADS = 64 * FEW_WAVES;
@@ -81,7 +78,7 @@ struct FewSearch {
   int ties[FEW_WAVES][R];    // such entries of each wavefront
 };
 
-template <int NJ, int MU>
+template <int NJ, int MU, bool STREAM>
 __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs p) {
   constexpr int R = 16 * NJ;
   constexpr int A_CHUNKS = R * 8;                                              // 16-byte chunks of an A tile
@@ -155,8 +152,10 @@ __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs 
     const unsigned char* const base = w_base + (size_t)min(kt, KT - 1) * 128;
     const unsigned back = (past_end && kt == KT - 1) ? (unsigned)w_chunk * 16 : 0u;
 #pragma unroll
-    for (int h = 0; h < 2 * MU; ++h)
-      q[h] = __builtin_nontemporal_load(reinterpret_cast<const few_u32x4*>(base + ((w_off[h] - back) & keep)));
+    for (int h = 0; h < 2 * MU; ++h) {
+      const few_u32x4* const src = reinterpret_cast<const few_u32x4*>(base + ((w_off[h] - back) & keep));
+      q[h] = STREAM ? __builtin_nontemporal_load(src) : *src;
+    }
   };
   // One K stage out of buffers B = kt % 2 of both operands; the loads of stage kt + 2 go out as the registers fall free.
   auto stage = [&](auto b_, int kt) {

@@ -583,9 +583,10 @@ Plan make_plan(const ll_shape* s, int k, int chunk_rows = CHUNK_ROWS) {
 // What a call is fastest with: room for the few-rows kernel's layout where that applies.
 size_t wanted_bytes(const Plan& plan) { return plan.few.ok && plan.few_total > plan.total ? plan.few_total : plan.total; }
 
+template <bool STREAM>
 void (*few_kernel(int nj, int mu))(const FewArgs) {
 #define LL_FEW(NJ, MU) \
-  if (nj == NJ && mu <= MU) return ll_lens_few_kernel<NJ, MU>
+  if (nj == NJ && mu <= MU) return ll_lens_few_kernel<NJ, MU, STREAM>
   LL_FEW(1, 1); LL_FEW(1, 3); LL_FEW(1, 5);
   LL_FEW(2, 1); LL_FEW(2, 3); LL_FEW(2, 5);
   LL_FEW(3, 1); LL_FEW(3, 3); LL_FEW(3, 5);
@@ -769,7 +770,17 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     a.splits = few.splits;
     a.units = few.units;
     LL_CHECK_F(mark());
-    hipLaunchKernelGGL(few_kernel(few.nj, few.mu), dim3(few.splits), dim3(FEW_THREADS), 0, stream, a);
+    // Whether the loads of W_U go past the caches.  Rows that are not whole lines of 128 bytes share lines between two stages: never.
+    // Others: not where the Infinity Cache can keep W_U for the next call, with room for what else runs in between; of rows of less
+    // than 1 KB always (whichever way, within 4 %).  Whole calls, k = 10, past the caches | through them, us, repeated on one W_U, and
+    // on W_U that are not in the cache (d, MB, rows):
+    //   2048, 120, 16: 41.4 | 34.6, 40.8 | 43.5    4096, 120, 81: 72.0 | 67.6, 71.7 | 72.8    8192, 120, 16: 83.1 | 77.8, 83.1 | 84.7
+    //   4096, 240, 16: 65.4 | 52.6, 63.9 | 69.3 (two W_U in turn: 62.6 | 67.9)                  4096, 400, 16: 102 | 111, 98 | 105
+    //   1608, 60, 16: 32.3 | 26.3, 35.5 | 34.2     1608, 400, 81: 138 | 113, 137 | 112        4104, 1050, 16: 298 | 224, 300 | 226
+    //   256, 60, 16: 27.8 | 28.8, 27.8 | 29.2
+    const bool whole_lines = ((uintptr_t)W_U | (uintptr_t)d * 2) % 128 == 0;
+    const bool stream_W = whole_lines && (d < 512 || (int64_t)V * d * 2 > INFINITY_CACHE_BYTES / 2);
+    hipLaunchKernelGGL(stream_W ? few_kernel<true>(few.nj, few.mu) : few_kernel<false>(few.nj, few.mu), dim3(few.splits), dim3(FEW_THREADS), 0, stream, a);
     LL_CHECK_F(hipGetLastError());
     LL_CHECK_F(mark());
     hipLaunchKernelGGL(ll_few_merge_kernel, dim3((unsigned)N), dim3(FEW_MERGE_THREADS), 0, stream, (const float4*)a.stats, (const uint2*)a.cand,

@@ -25,6 +25,7 @@ struct GemmArgs {
   uint2* top;               // [rows, splits, k]  (logit bits, id), sorted
   int64_t lda;              // row stride of A in elements
   int rows, d, V, k, splits, tiles, row_blocks;
+  int last_row;             // of A, what is read for the rows past the end of a block: a row of zeros behind a panel, else the last row
   // steering sweep only (Sec. 3.4, Eq. 3 for several alpha in one pass):
   const float* u;           // [tiles * BM] fp32: W_U v, zero padded
   const float* eu;          // [2, tiles * BM / 16, 16, 16]: rows of e^(alpha u) and alpha u e^(alpha u) of 16 ids (see ll_epilogue_sweep.h)

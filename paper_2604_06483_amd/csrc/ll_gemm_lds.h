@@ -153,7 +153,7 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
   const int seg_row = 64 * wave + (lane >> 3);                        // + 8 s
   const int seg_koff0 = ((lane & 7) ^ (lane >> 4)) * 8;               // element offset, even segments
   const int seg_koff1 = seg_koff0 ^ 32;                               // odd segments
-  const int a_last = p.rows - 1 - rb * BN;                            // last valid row of this block
+  const int a_last = p.last_row - rb * BN;                            // what rows past the end are read from
   constexpr int IMM_BIAS = 3072;                                      // largest immediate, segment 7
 
   // Per-lane byte offsets of the 8 segments, fixed for the whole sweep (W: per vocabulary tile,

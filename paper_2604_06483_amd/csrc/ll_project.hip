@@ -47,13 +47,17 @@ __global__ __launch_bounds__(256) void ll_norm_panel_kernel(const uint16_t* __re
                                                             int rows, int d, int64_t lda, float eps, unsigned* __restrict__ bound, int bounds) {
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (row >= rows) return;
-  if (bound != nullptr && lane < bounds) bound[(int64_t)lane * rows + row] = 0u;   // the row's shared top-k bounds, before the pass that uses them
-  const uint4* src = reinterpret_cast<const uint4*>(hidden + (int64_t)row * d);
-  uint4* dst = reinterpret_cast<uint4*>(panel + (int64_t)row * lda);
-  const uint4* g4 = reinterpret_cast<const uint4*>(gamma);
+  if (row > rows) return;
   const int n16 = d >> 3;
   const int n16_pad = (int)(lda >> 3);
+  uint4* dst = reinterpret_cast<uint4*>(panel + (int64_t)row * lda);
+  if (row == rows) {   // one row of zeros behind them: what stands for the rows that are missing from a whole block
+    for (int c = lane; c < n16_pad; c += 64) dst[c] = make_uint4(0, 0, 0, 0);
+    return;
+  }
+  if (bound != nullptr && lane < bounds) bound[(int64_t)lane * rows + row] = 0u;   // the row's shared top-k bounds, before the pass that uses them
+  const uint4* src = reinterpret_cast<const uint4*>(hidden + (int64_t)row * d);
+  const uint4* g4 = reinterpret_cast<const uint4*>(gamma);
   float acc0 = 0.f, acc1 = 0.f;
   auto emit = [&](int c, const uint4 q, const uint4 g, float inv) {
     const uint32_t hw[4] = {q.x, q.y, q.z, q.w};
@@ -179,6 +183,12 @@ __global__ __launch_bounds__(256) void ll_unembed_direction_kernel(const uint16_
   }
 }
 
+// Over the lane's block of 16.
+__device__ __forceinline__ float largest_of_16(float x) {
+  const auto larger = [](uint32_t a, uint32_t b) { return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b))); };
+  return __uint_as_float(with_lane_xor<1>(with_lane_xor<2>(with_lane_xor<4>(with_lane_xor<8>(__float_as_uint(x), larger), larger), larger), larger));
+}
+
 // Step 2: what the sweep epilogue reads per group of 16 ids and per tile (see GemmArgs), the flag that says which form of the
 // epilogue runs, and the zeroed bounds.  A block's turn is one tile.
 __global__ __launch_bounds__(256) void ll_sweep_table_kernel(const float* __restrict__ block_max, int n_blocks, int n_padded,
@@ -204,11 +214,8 @@ __global__ __launch_bounds__(256) void ll_sweep_table_kernel(const float* __rest
     for (int a = 0; a < n_alpha; ++a) {
       const float shift = alphas.a[a] * x;
       float most = shift, least = shift;
-#pragma unroll
-      for (int off = 8; off > 0; off >>= 1) {
-        most = fmaxf(most, __shfl_xor(most, off, kWave));
-        least = fminf(least, __shfl_xor(least, off, kWave));
-      }
+      most = largest_of_16(most);
+      least = -largest_of_16(-least);
       spread = fmaxf(spread, most - least);
       // (with the margin for its rounding, SWEEP_MARGIN, unless no logit is shifted at all)
       most = most == 0.f && least == 0.f ? 0.f : most + SWEEP_MARGIN;
@@ -557,7 +564,7 @@ Plan make_plan(const ll_shape* s, int k, int chunk_rows = CHUNK_ROWS) {
   off = align_up(off + partials * (size_t)k * sizeof(uint2), 256);
   p.lda = (s->d + DK - 1) / DK * DK;
   p.off_panel = off;
-  off = align_up(off + rows * (size_t)p.lda * sizeof(uint16_t), 256);
+  off = align_up(off + (rows + 1) * (size_t)p.lda * sizeof(uint16_t), 256);
   p.total = off;
   // The few-rows kernel's own layout of the same workspace, larger than what many more rows need above: 64 entries a row and part.
   // It is taken only where it fits the workspace that the caller handed over (one sized for a longer call need not hold it), and
@@ -573,7 +580,7 @@ Plan make_plan(const ll_shape* s, int k, int chunk_rows = CHUNK_ROWS) {
     p.few_off_count = off;
     off = align_up(off + lists * sizeof(int), 256);
     p.few_off_panel = off;
-    off = align_up(off + rows * (size_t)p.lda * sizeof(uint16_t), 256);
+    off = align_up(off + (rows + 1) * (size_t)p.lda * sizeof(uint16_t), 256);
     p.few_total = off;
     p.few.ok = off <= (size_t)LL_STATIC_SCRATCH_BYTES;
   }
@@ -632,7 +639,7 @@ int even_splits(int tiles, int most) {
 void launch_norm_panel(const uint16_t* hidden, const uint16_t* gamma, uint16_t* panel, int rows, int d, int64_t lda, float eps,
                        unsigned* bound, int bounds, hipStream_t stream) {
   const int per_block = rows <= 1024 ? 1 : 4;
-  const dim3 grid((unsigned)((rows + per_block - 1) / per_block)), block(64 * per_block);
+  const dim3 grid((unsigned)((rows + per_block) / per_block)), block(64 * per_block);   // (and a row of zeros)
   if (d <= 64 * 8 * 4)
     hipLaunchKernelGGL(ll_norm_panel_kernel<4>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps, bound, bounds);
   else if (d <= 64 * 8 * 8)
@@ -850,6 +857,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     a.stats = stats;
     a.top = top;
     a.rows = rows;
+    a.last_row = need_panel ? rows : rows - 1;
     a.d = d;
     a.V = V;
     a.k = k;
@@ -926,7 +934,7 @@ SweepPlan make_sweep_plan(const ll_shape* s, int n_alpha, int k = 1) {
   p.off_ztgt = take(partials * sizeof(float));
   p.off_top = take(partials * n_alpha * (k > 1 ? SWEEP_KS : 1) * sizeof(uint2));
   p.lda = ((int64_t)s->d + DK - 1) / DK * DK;
-  p.off_panel = take(rows * (size_t)p.lda * sizeof(uint16_t));
+  p.off_panel = take((rows + 1) * (size_t)p.lda * sizeof(uint16_t));
   p.total = p.wanted = off;
   if (n_alpha == 1) {
     const Plan project = make_plan(s, k);
@@ -1052,6 +1060,7 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     a.W = static_cast<const uint16_t*>(W_U);
     a.target = target_ids ? target_ids + r0 : nullptr;
     a.rows = rows;
+    a.last_row = need_panel ? rows : rows - 1;
     a.d = d;
     a.V = V;
     a.k = k;

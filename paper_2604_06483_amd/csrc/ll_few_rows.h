@@ -486,6 +486,8 @@ __global__ __launch_bounds__(FEW_MERGE_THREADS) void ll_few_merge_kernel(
   __shared__ __align__(16) unsigned long long s_c[FEW_MERGE_MAX + 4];
   __shared__ float s_red[4][WAVES];
   __shared__ int2 s_list[LL_KMAX];   // (part, entries)
+  __shared__ int s_above[FEW_MERGE_THREADS / 2];
+  static_assert(LL_KMAX % WAVES == 0, "a list for each wavefront in every round");
   __shared__ float s_tau;
   __shared__ int s_n, s_count[2][WAVES];
   __shared__ float s_z[LL_KMAX];
@@ -526,18 +528,42 @@ __global__ __launch_bounds__(FEW_MERGE_THREADS) void ll_few_merge_kernel(
     s_red[2][wave] = s_wave;
     s_red[3][wave] = t_wave;
   }
+  // Ranks of the maxima.  Up to 256 parts: two threads a part, which count among half of them each (with that, and the loads of the
+  // lists below all in flight, 37 rows, d = 2560, V = 151936, k = 10, whole call: 141.5 us, 139.6 now).
+  const bool shared_count = splits > 64 && splits <= FEW_MERGE_THREADS / 2;   // (the same for all threads)
+  int rank = 0;
+  if (shared_count) {
+    const int part = tid & (FEW_MERGE_THREADS / 2 - 1), half = (((splits + 1) / 2) + 3) & ~3;
+    const bool upper = tid >= FEW_MERGE_THREADS / 2;   // (whole wavefronts)
+    const unsigned long long of = s_part[part];
+    rank = upper ? keys_above(s_part + half, ((splits + 3) & ~3) - half, of) : keys_above(s_part, half, of);
+    if (upper) s_above[part] = rank;
+  } else if (tid < splits) {
+    rank = keys_above(s_part, (splits + 3) & ~3, mine);
+  }
+  if (shared_count) {
+    __syncthreads();
+    if (tid < splits) rank += s_above[tid];
+  }
   if (tid < splits) {
-    const int rank = keys_above(s_part, (splits + 3) & ~3, mine);
     if (rank < k) s_list[rank] = make_int2(tid, entries);
     if (rank == k - 1) s_tau = q.x;
   }
   __syncthreads();
   const float tau = s_tau;
-  for (int l = wave; l < k; l += WAVES) {
-    const int2 list = s_list[l];
-    uint2 e = make_uint2(0u, 0u);
-    if (lane < list.y) e = cand[((int64_t)row * splits + list.x) * FEW_CAP + lane];
-    const bool pass = lane < list.y && __uint_as_float(e.x) >= tau;
+  constexpr int ROUNDS = (LL_KMAX + WAVES - 1) / WAVES;
+  uint2 found[ROUNDS];
+#pragma unroll
+  for (int i = 0; i < ROUNDS; ++i) {   // (lists past the k-th have no entries: s_list)
+    const int2 list = s_list[wave + WAVES * i];
+    found[i] = make_uint2(0u, 0u);
+    if (WAVES * i < k && lane < list.y) found[i] = cand[((int64_t)row * splits + list.x) * FEW_CAP + lane];
+  }
+#pragma unroll
+  for (int i = 0; i < ROUNDS; ++i) {
+    if (WAVES * i >= k) break;
+    const uint2 e = found[i];
+    const bool pass = lane < s_list[wave + WAVES * i].y && __uint_as_float(e.x) >= tau;
     const unsigned long long passing = __builtin_amdgcn_ballot_w64(pass);
     int at = 0;
     if (lane == 0 && passing != 0) at = atomicAdd(&s_n, __builtin_popcountll(passing));

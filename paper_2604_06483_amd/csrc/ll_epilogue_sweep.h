@@ -265,10 +265,10 @@ __device__ __forceinline__ void sweep_group_general(const float (&x)[16], SweepS
   }
 }
 
-// The least of three (see max3).
-__device__ __forceinline__ float min3(float a, float b, float c) {
+// The least of three (see max3), NaN once one of them is.
+__device__ __forceinline__ float sticky_min3(float a, float b, float c) {
   float r;
-  asm("v_min3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  asm("v_minimum3_f32 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
   return r;
 }
 
@@ -599,7 +599,8 @@ __device__ __forceinline__ void sweep_take_bounds(SweepState<KS, false>& st, con
   asm volatile("" ::: "memory");
 }
 // In a split's first tile, ahead of its lists: the best shifted logits, from below (a group's largest logit with its least shift, and
-// its least logit with its largest shift, which is the better one where a row's logits are nearly equal).
+// its least logit with its largest shift, which is the better one where a row's logits are nearly equal).  The second holds only while
+// every logit of the group is a number: the id with the largest shift might be the one that has none.
 template <int KS>
 __device__ __forceinline__ void sweep_announce(f32x4 (&acc)[16][4], SweepState<KS, false>& st, int v0, const GemmArgs& p, int my_row) {
   float best[SWEEP_MAX], least4[4], most4[4];
@@ -618,11 +619,11 @@ __device__ __forceinline__ void sweep_announce(f32x4 (&acc)[16][4], SweepState<K
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       q[j] = max3(max3(y[j][0], y[j][1], y[j][2]), y[j][3], y[j][3]);
-      l[j] = min3(min3(y[j][0], y[j][1], y[j][2]), y[j][3], y[j][3]);
+      l[j] = sticky_min3(sticky_min3(y[j][0], y[j][1], y[j][2]), y[j][3], y[j][3]);
     }
     transpose_blocks(q[0], q[1], q[2], q[3]);
     transpose_blocks(l[0], l[1], l[2], l[3]);
-    const float gmax = max3(max3(q[0], q[1], q[2]), q[3], q[3]), gmin = min3(min3(l[0], l[1], l[2]), l[3], l[3]);
+    const float gmax = max3(max3(q[0], q[1], q[2]), q[3], q[3]), gmin = sticky_min3(sticky_min3(l[0], l[1], l[2]), l[3], l[3]);
     const float least = sweep_group_entry(least4, i), most = sweep_group_entry(most4, i);
     each_alpha([&](auto a_) {
       constexpr int a = decltype(a_)::value;

@@ -174,3 +174,34 @@ def test_rows_of_zeros_cost_little_more_than_others(k, limit):
     some = call_time()
     say(f"sweep k={k}: {1e3 * without:.1f} us, with zero rows {1e3 * some:.1f} us")
     assert some < limit * without
+
+
+@pytest.mark.parametrize("k", [None, 3])
+def test_a_logit_that_is_no_number_leaves_the_others_listed(k):
+    """Token V / 2 overflows to +inf and back in rows 0, 2, ..: its logit there is NaN, and its shift is the largest of its group, far
+    above every shifted logit of the row.  The rows' lists are those of the other tokens; rows 1, 3, .. are sound."""
+    say(f"sweep, one NaN logit k={k}")
+    N, d, V, odd = 300, 64, 7000, 3500
+    g = torch.Generator(device=DEV).manual_seed(47)
+    W = (0.05 * torch.randn((V, d), generator=g, device=DEV)).to(torch.bfloat16)
+    h = torch.randn((N, d), generator=g, device=DEV).to(torch.bfloat16)
+    v = torch.zeros(d, device=DEV)
+    v[5] = 1.0
+    W[:, 5] *= 0.2
+    W[:, [0, 40]] = 0.0                              # columns of the two K halves
+    h[:, 5] = 0.0
+    h[::2, [0, 40]], h[1::2, [0, 40]] = 4.0, 1e-30
+    W[odd, 0], W[odd, 40], W[odd, 5] = 3e38, -3e38, 4.5
+    ids, p, logp, ent = LL.ll_steer_sweep(h, None, W, 1e-5, v, ALPHAS9, None, k=k)
+    n = 1 if k is None else k
+    ids, p = ids.reshape(len(ALPHAS9), N, n), p.reshape(len(ALPHAS9), N, n)
+    z = h.double() @ W.double().t()
+    z[::2, odd] = -float("inf")
+    for a, alpha in enumerate(ALPHAS9):
+        shifted = z + alpha * W[:, 5].double()
+        best = shifted.topk(n).values
+        assert 0 <= int(ids[a].min()) and int(ids[a].max()) < V
+        # fp32 sums of 64 products and one shift, all below 1
+        torch.testing.assert_close(shifted.gather(1, ids[a].long()), best, rtol=0, atol=64 * 2.0 ** -24)
+        assert torch.isfinite(p[a, 1::2]).all() and torch.isfinite(ent[a, 1::2]).all()
+        assert torch.isnan(ent[a, ::2]).all()

@@ -44,14 +44,15 @@ __global__ __launch_bounds__(256) void ll_rms_stats_kernel(const uint16_t* __res
 template <int NITER>
 __global__ __launch_bounds__(256) void ll_norm_panel_kernel(const uint16_t* __restrict__ hidden,
                                                             const uint16_t* __restrict__ gamma, uint16_t* __restrict__ panel,
-                                                            int rows, int d, int64_t lda, float eps, unsigned* __restrict__ bound, int bounds) {
+                                                            int rows, int zero_rows, int d, int64_t lda, float eps,
+                                                            unsigned* __restrict__ bound, int bounds) {
   const int lane = threadIdx.x & 63;
   const int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (row > rows) return;
+  if (row >= rows + zero_rows) return;
   const int n16 = d >> 3;
   const int n16_pad = (int)(lda >> 3);
   uint4* dst = reinterpret_cast<uint4*>(panel + (int64_t)row * lda);
-  if (row == rows) {   // one row of zeros behind them: what stands for the rows that are missing from a whole block
+  if (row == rows) {   // zero_rows = 1: one row of zeros behind them, what stands for the rows that are missing from a whole block
     for (int c = lane; c < n16_pad; c += 64) dst[c] = make_uint4(0, 0, 0, 0);
     return;
   }
@@ -525,8 +526,9 @@ FewPlan make_few_plan(const ll_shape* s, int k) {
 }
 
 struct Plan {
-  size_t off_inv_rms, off_bound, off_bias, off_stats, off_top, off_panel, total;   // total: never less for more rows
-  int64_t lda, bounds;
+  size_t off_inv_rms, off_bound, off_bias, off_stats, off_top, off_panel, total;   // total: the least that is accepted, never less for more rows
+  size_t roomy;   // with a row of zeros behind the panel and the bounds of the classes of splits (see classes_offset)
+  int64_t lda;
   FewPlan few;
   size_t few_total, few_off_stats, few_off_cand, few_off_count, few_off_panel;
 };
@@ -540,10 +542,18 @@ bool shape_ok(const ll_shape* s, int k) {
   return true;
 }
 
-// Shared bounds of a pass of at most `rows` rows: one a row, or one a row and class (k of them) where the splits are at least k.
-int64_t bound_entries(int64_t rows, int k) {
-  const int64_t classes = rows * k < MAX_PARTIALS ? rows * k : MAX_PARTIALS;
-  return rows > classes ? rows : classes;
+constexpr int SHORT_KMAX = 20;   // longest list of the kernel of short calls
+
+// Where the bounds of the classes of splits stand (one a row and class, k of them, in passes of at least k splits: rows x k never
+// exceeds MAX_PARTIALS), and how much room they may want: behind what of the panel the pass fills, so that only a workspace
+// that holds nothing beyond the largest pass's panel has none for them.  Such a call goes without classes, with the same results;
+// one that reserved them always would have smaller passes in the static buffer (d = 3328, V = 128256, k = 20: 7936 rows).
+size_t classes_offset(size_t off_panel, int64_t panel_rows, int64_t lda) {
+  return align_up(off_panel + (size_t)panel_rows * (size_t)lda * sizeof(uint16_t), 256);
+}
+size_t classes_bytes(size_t rows, int k) {
+  if (k > SHORT_KMAX) return 0;
+  return (rows * k < (size_t)MAX_PARTIALS ? rows * k : (size_t)MAX_PARTIALS) * sizeof(unsigned);
 }
 
 Plan make_plan(const ll_shape* s, int k, int chunk_rows = CHUNK_ROWS) {
@@ -551,12 +561,11 @@ Plan make_plan(const ll_shape* s, int k, int chunk_rows = CHUNK_ROWS) {
   size_t off = 0;
   p.off_inv_rms = off;
   off = align_up(off + (size_t)s->N * sizeof(float), 256);
+  const size_t rows = (size_t)(s->N < chunk_rows ? s->N : chunk_rows);
   p.off_bound = off;  // per-row top-k bounds shared between the splits of a pass
-  p.bounds = bound_entries(s->N < chunk_rows ? s->N : chunk_rows, k);
-  off = align_up(off + (size_t)p.bounds * sizeof(unsigned), 256);
+  off = align_up(off + rows * sizeof(unsigned), 256);
   p.off_bias = off;   // the bias padded to whole tiles (ll_project_ex)
   off = align_up(off + (size_t)((s->V + BM - 1) / BM) * BM * sizeof(float), 256);
-  const size_t rows = (size_t)(s->N < chunk_rows ? s->N : chunk_rows);
   p.off_stats = off;
   const size_t partials = rows * MAX_PROJECT_SPLITS < (size_t)MAX_PARTIALS ? rows * MAX_PROJECT_SPLITS : (size_t)MAX_PARTIALS;
   off = align_up(off + partials * sizeof(float4), 256);
@@ -564,8 +573,8 @@ Plan make_plan(const ll_shape* s, int k, int chunk_rows = CHUNK_ROWS) {
   off = align_up(off + partials * (size_t)k * sizeof(uint2), 256);
   p.lda = (s->d + DK - 1) / DK * DK;
   p.off_panel = off;
-  off = align_up(off + (rows + 1) * (size_t)p.lda * sizeof(uint16_t), 256);
-  p.total = off;
+  p.total = classes_offset(off, (int64_t)rows, p.lda);
+  p.roomy = align_up(classes_offset(off, (int64_t)rows + 1, p.lda) + classes_bytes(rows, k), 256);
   // The few-rows kernel's own layout of the same workspace, larger than what many more rows need above: 64 entries a row and part.
   // It is taken only where it fits the workspace that the caller handed over (one sized for a longer call need not hold it), and
   // where it also fits the library's static buffer, so that ll_project and ll_project_static run the same kernels.
@@ -580,7 +589,7 @@ Plan make_plan(const ll_shape* s, int k, int chunk_rows = CHUNK_ROWS) {
     p.few_off_count = off;
     off = align_up(off + lists * sizeof(int), 256);
     p.few_off_panel = off;
-    off = align_up(off + (rows + 1) * (size_t)p.lda * sizeof(uint16_t), 256);
+    off = align_up(off + rows * (size_t)p.lda * sizeof(uint16_t), 256);
     p.few_total = off;
     p.few.ok = off <= (size_t)LL_STATIC_SCRATCH_BYTES;
   }
@@ -588,7 +597,7 @@ Plan make_plan(const ll_shape* s, int k, int chunk_rows = CHUNK_ROWS) {
 }
 
 // What a call is fastest with: room for the few-rows kernel's layout where that applies.
-size_t wanted_bytes(const Plan& plan) { return plan.few.ok && plan.few_total > plan.total ? plan.few_total : plan.total; }
+size_t wanted_bytes(const Plan& plan) { return plan.few.ok && plan.few_total > plan.roomy ? plan.few_total : plan.roomy; }
 
 template <bool STREAM>
 void (*few_kernel(int nj, int mu))(const FewArgs) {
@@ -636,18 +645,18 @@ int even_splits(int tiles, int most) {
 }
 
 // (few rows: one wavefront per block, so that they spread over the compute units)
-void launch_norm_panel(const uint16_t* hidden, const uint16_t* gamma, uint16_t* panel, int rows, int d, int64_t lda, float eps,
-                       unsigned* bound, int bounds, hipStream_t stream) {
+void launch_norm_panel(const uint16_t* hidden, const uint16_t* gamma, uint16_t* panel, int rows, int zero_rows, int d, int64_t lda,
+                       float eps, unsigned* bound, int bounds, hipStream_t stream) {
   const int per_block = rows <= 1024 ? 1 : 4;
-  const dim3 grid((unsigned)((rows + per_block) / per_block)), block(64 * per_block);   // (and a row of zeros)
+  const dim3 grid((unsigned)((rows + zero_rows + per_block - 1) / per_block)), block(64 * per_block);
   if (d <= 64 * 8 * 4)
-    hipLaunchKernelGGL(ll_norm_panel_kernel<4>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps, bound, bounds);
+    hipLaunchKernelGGL(ll_norm_panel_kernel<4>, grid, block, 0, stream, hidden, gamma, panel, rows, zero_rows, d, lda, eps, bound, bounds);
   else if (d <= 64 * 8 * 8)
-    hipLaunchKernelGGL(ll_norm_panel_kernel<8>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps, bound, bounds);
+    hipLaunchKernelGGL(ll_norm_panel_kernel<8>, grid, block, 0, stream, hidden, gamma, panel, rows, zero_rows, d, lda, eps, bound, bounds);
   else if (d <= 64 * 8 * 16)
-    hipLaunchKernelGGL(ll_norm_panel_kernel<16>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps, bound, bounds);
+    hipLaunchKernelGGL(ll_norm_panel_kernel<16>, grid, block, 0, stream, hidden, gamma, panel, rows, zero_rows, d, lda, eps, bound, bounds);
   else
-    hipLaunchKernelGGL(ll_norm_panel_kernel<0>, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps, bound, bounds);
+    hipLaunchKernelGGL(ll_norm_panel_kernel<0>, grid, block, 0, stream, hidden, gamma, panel, rows, zero_rows, d, lda, eps, bound, bounds);
 }
 
 int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, const void* hidden, const void* gamma,
@@ -757,7 +766,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     const bool copy = has_gamma || plan.lda != d;
     LL_CHECK_F(mark());
     if (copy) {
-      launch_norm_panel(static_cast<const uint16_t*>(hidden), static_cast<const uint16_t*>(gamma), few_panel, (int)N, d, plan.lda, eps,
+      launch_norm_panel(static_cast<const uint16_t*>(hidden), static_cast<const uint16_t*>(gamma), few_panel, (int)N, 0, d, plan.lda, eps,
                         nullptr, 0, stream);
       LL_CHECK_F(hipGetLastError());
     }
@@ -798,14 +807,51 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     return finish(read_phases());
   }
 
+  // How a pass of `rows` rows deals the vocabulary, and where its shared bounds stand.
+  struct Deal {
+    int row_blocks, splits, half_tiles, classes;
+    size_t off_bound;
+    int bounds() const { return classes > 0 ? classes : 1; }
+  };
+  auto deal = [&](int rows) {
+    Deal l = {(rows + BN - 1) / BN, 0, 0, 0, plan.off_bound};
+    // One workgroup per compute unit: a pass of few rows cuts the vocabulary finer (its cost is then the one read
+    // of W_U, spread over every compute unit's share of the memory system).
+    const int most = NUM_CU / l.row_blocks < MAX_PROJECT_SPLITS ? NUM_CU / l.row_blocks : MAX_PROJECT_SPLITS;
+    l.splits = even_splits(tiles, most);
+    const int each = (tiles + l.splits - 1) / l.splits;
+    if (short_kern == nullptr || each > SHORT_TILES) return l;
+    // Few tiles a workgroup: the kernel that can end a split in half a tile, where that leaves the busiest workgroup half a tile less,
+    // and that deals at least k splits into k classes (see exchange_classes).
+    const int halves = (V + BM / 2 - 1) / (BM / 2), each_half = (halves + most - 1) / most;
+    const int half_splits = (halves + each_half - 1) / each_half;
+    if (each_half < 2 * each && (half_splits >= k || each <= SHORT_TILES_WITHOUT)) {
+      l.half_tiles = halves;
+      l.splits = half_splits;
+    }
+    const size_t at = classes_offset(plan.off_panel, need_panel ? rows + 1 : 0, plan.lda);
+    if (l.splits >= k && at + classes_bytes((size_t)rows, k) <= workspace_bytes) {
+      l.classes = k;
+      l.off_bound = at;
+    }
+    return l;
+  };
   // Top-k bounds shared between the vocabulary splits of a row (direct-to-LDS kernel): zero at the start of a pass.  The panel
-  // kernel clears them; where the rows are read in place a launch of its own does for the first pass, and the merge kernel of a pass for the next one.
-  unsigned* bound = nullptr;
-  if (dma) {
-    bound = reinterpret_cast<unsigned*>(ws + plan.off_bound);
-    if (!need_panel) {
-      const int n_zero = (int)plan.bounds;
-      hipLaunchKernelGGL(ll_zero_u32_kernel, dim3((n_zero + 255) / 256), dim3(256), 0, stream, bound, n_zero);
+  // kernel clears them; where the rows are read in place a launch of its own does for the first pass, and the merge kernel of a pass
+  // for the next one.  That launch clears what the passes use: all but the last are alike, and two kinds of them either share a place
+  // or have each its own.
+  if (dma && !need_panel) {
+    const int full = (int)(N < chunk_rows ? N : chunk_rows), last = (int)(N % chunk_rows);
+    Deal a = deal(full), b = last > 0 ? deal(last) : a;
+    int64_t n_a = (int64_t)full * a.bounds(), n_b = (int64_t)last * b.bounds();
+    if (a.off_bound == b.off_bound) {
+      n_a = n_a > n_b ? n_a : n_b;
+      n_b = 0;
+    }
+    hipLaunchKernelGGL(ll_zero_u32_kernel, dim3((unsigned)((n_a + 255) / 256)), dim3(256), 0, stream, reinterpret_cast<unsigned*>(ws + a.off_bound), (int)n_a);
+    LL_CHECK_F(hipGetLastError());
+    if (n_b > 0) {
+      hipLaunchKernelGGL(ll_zero_u32_kernel, dim3((unsigned)((n_b + 255) / 256)), dim3(256), 0, stream, reinterpret_cast<unsigned*>(ws + b.off_bound), (int)n_b);
       LL_CHECK_F(hipGetLastError());
     }
   }
@@ -818,28 +864,15 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
   for (int64_t r0 = 0; r0 < N; r0 += chunk_rows) {
     const int rows = (int)((N - r0) < chunk_rows ? (N - r0) : chunk_rows);
     const uint16_t* h_rows = static_cast<const uint16_t*>(hidden) + r0 * d;
-    const int row_blocks = (rows + BN - 1) / BN;
-    // One workgroup per compute unit: a pass of few rows cuts the vocabulary finer (its cost is then the one read
-    // of W_U, spread over every compute unit's share of the memory system).
-    const int most = NUM_CU / row_blocks < MAX_PROJECT_SPLITS ? NUM_CU / row_blocks : MAX_PROJECT_SPLITS;
-    int splits = even_splits(tiles, most), half_tiles = 0, classes = 0;
-    const int each = (tiles + splits - 1) / splits;
-    // Few tiles a workgroup: the kernel that can end a split in half a tile, where that leaves the busiest workgroup half a tile less,
-    // and that deals at least k splits into k classes (see exchange_classes).
-    if (short_kern != nullptr && each <= SHORT_TILES) {
-      const int halves = (V + BM / 2 - 1) / (BM / 2), each_half = (halves + most - 1) / most;
-      const int half_splits = (halves + each_half - 1) / each_half;
-      if (each_half < 2 * each && (half_splits >= k || each <= SHORT_TILES_WITHOUT)) {
-        half_tiles = halves;
-        splits = half_splits;
-      }
-      if (splits >= k) classes = k;
-    }
-    const int bounds = classes > 0 ? classes : 1;
+    const Deal l = deal(rows);
+    const int row_blocks = l.row_blocks, splits = l.splits, bounds = l.bounds();
+    unsigned* const bound = dma ? reinterpret_cast<unsigned*>(ws + l.off_bound) : nullptr;
+    // (a row of zeros for the rows that the last block lacks, where the workspace has room for one)
+    const int zero_rows = need_panel && rows % BN != 0 && plan.off_panel + (size_t)(rows + 1) * (size_t)plan.lda * sizeof(uint16_t) <= workspace_bytes ? 1 : 0;
     // a2 (+ a3 when the panel is used)
     LL_CHECK_F(mark());
     if (need_panel) {
-      launch_norm_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, d, plan.lda, eps, bound, bounds, stream);
+      launch_norm_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, zero_rows, d, plan.lda, eps, bound, bounds, stream);
       LL_CHECK_F(hipGetLastError());
     } else if (!dma && has_gamma) {
       hipLaunchKernelGGL(ll_rms_stats_kernel, dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, stream, h_rows, (int64_t)rows, d,
@@ -857,7 +890,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     a.stats = stats;
     a.top = top;
     a.rows = rows;
-    a.last_row = need_panel ? rows : rows - 1;
+    a.last_row = rows - 1 + zero_rows;
     a.d = d;
     a.V = V;
     a.k = k;
@@ -865,11 +898,11 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     a.tiles = tiles;
     a.row_blocks = row_blocks;
     a.bound = bound;
-    a.classes = classes;
-    a.half_tiles = half_tiles;
+    a.classes = l.classes;
+    a.half_tiles = l.half_tiles;
     const int grid = (row_blocks * splits + NUM_XCD - 1) / NUM_XCD * NUM_XCD;
     LL_CHECK_F(mark());
-    hipLaunchKernelGGL(half_tiles > 0 || classes > 0 ? short_kern : kern, dim3(grid), dim3(NTHREADS), lds, stream, a);
+    hipLaunchKernelGGL(l.half_tiles > 0 || l.classes > 0 ? short_kern : kern, dim3(grid), dim3(NTHREADS), lds, stream, a);
     LL_CHECK_F(hipGetLastError());
     LL_CHECK_F(mark());
     if (splits <= MAX_SPLITS)
@@ -1051,7 +1084,7 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     const uint16_t* h_rows = static_cast<const uint16_t*>(hidden) + r0 * d;
     const bool need_panel = gamma != nullptr || plan.lda != d;
     if (need_panel) {
-      launch_norm_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, d, plan.lda, eps, nullptr, 0, stream);
+      launch_norm_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, 1, d, plan.lda, eps, nullptr, 0, stream);
       LL_CHECK_S(hipGetLastError());
     }
     GemmArgs a = {};

@@ -154,6 +154,26 @@ def test_static_variant_sizes_its_passes_and_rejects_what_does_not_fit():
     assert b"static" in L.ll_error_string(LL.LL_ESCRATCH)
 
 
+@pytest.mark.parametrize("N,d,V,k,rows", [
+    (121500, 3328, 128256, 20, 8192), (121500, 2944, 128256, 32, 8192),    # whole passes, bit-identical to ll_project
+    (9000, 9664, 128256, 21, 2816), (121500, 8256, 128256, 11, 3584), (9000, 6848, 50257, 5, 4608),
+    (9000, 123432, 151936, 4, 256), (121500, 125760, 151936, 1, 256),      # one row block, which fills the buffer
+    (255, 100456, 300, 28, 8192),                                          # less than one, likewise
+])
+def test_static_passes_hold_the_rows_that_the_buffer_has_room_for(N, d, V, k, rows):
+    """What makes a call faster but not possible (bounds of the classes of splits, a row of zeros behind the panel) takes no room
+    from the rows of a pass: inv_rms, bounds, bias, partials, lists and panel of that many rows fit, and 256 more do not."""
+    up = lambda x: -(-x // 256) * 256
+    lda = -(-d // 64) * 64
+
+    def needs(chunk):
+        r = min(N, chunk)
+        partials = min(r * 256, 65536)
+        return up(4 * N) + up(4 * r) + up(4 * 256 * -(-V // 256)) + up(16 * partials) + up(8 * k * partials) + up(2 * lda * r)
+    assert needs(rows) <= LL.LL_STATIC_SCRATCH_BYTES and (rows == 8192 or needs(rows + 256) > LL.LL_STATIC_SCRATCH_BYTES)
+    assert LL.ll_project_static_pass_rows(N, d, V, k) == rows
+
+
 def test_project_ex_rejects_unknown_flags_and_misaligned_bias():
     L = LL.lib()
     f = _fake()

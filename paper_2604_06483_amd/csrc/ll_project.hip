@@ -118,7 +118,7 @@ struct AlphaList {
 
 constexpr int UD_ROWS = 8;   // vocabulary rows a wavefront takes at a time
 constexpr int UD_BLOCKS = NUM_CU * 4;
-constexpr int64_t INFINITY_CACHE_BYTES = 256ll << 20;
+constexpr int64_t INFINITY_CACHE_BYTES = 256ll << 20, L2_BYTES = 32ll << 20;   // (the L2s of the eight XCDs together)
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
@@ -663,7 +663,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
                  const void* W_U, const float* bias, unsigned flags, float eps, int k, const int32_t* target_ids,
                  int32_t* out_topk_ids, float* out_topk_p,
                  float* out_target_logp, float* out_entropy, hipStream_t stream, float* phase_ms,
-                 int chunk_rows = CHUNK_ROWS) {
+                 int chunk_rows = CHUNK_ROWS, bool W_in_cache = false) {
   if (!shape_ok(shape, k)) return LL_EINVAL;
   if (shape->N == 0) {
     if (phase_ms) phase_ms[0] = phase_ms[1] = phase_ms[2] = 0.f;
@@ -786,16 +786,18 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     a.splits = few.splits;
     a.units = few.units;
     LL_CHECK_F(mark());
-    // Whether the loads of W_U go past the caches.  Rows that are not whole lines of 128 bytes share lines between two stages: never.
-    // Others: not where the Infinity Cache can keep W_U for the next call, with room for what else runs in between; of rows of less
-    // than 1 KB always (whichever way, within 4 %).  Whole calls, k = 10, past the caches | through them, us, repeated on one W_U, and
-    // on W_U that are not in the cache (d, MB, rows):
-    //   2048, 120, 16: 41.4 | 34.6, 40.8 | 43.5    4096, 120, 81: 72.0 | 67.6, 71.7 | 72.8    8192, 120, 16: 83.1 | 77.8, 83.1 | 84.7
-    //   4096, 240, 16: 65.4 | 52.6, 63.9 | 69.3 (two W_U in turn: 62.6 | 67.9)                  4096, 400, 16: 102 | 111, 98 | 105
+    // Whether the loads of W_U go past the caches: where its rows are whole lines of 128 bytes (others share lines between two stages,
+    // and are faster through the caches whatever the size).  Through the caches a W_U that the Infinity Cache can keep is read faster by
+    // the next call on it, but by a call after which, or before which, something else has run, slower, and a lens behind a decoding step
+    // always is that one.  Whole calls, k = 10, past the caches | through them, us, repeated on one W_U, and on W_U that are not in
+    // the cache (d, MB, rows):
+    //   1024, 60, 81: 37.5 | 36.0, 36.7 | 37.4     2048, 120, 16: 38.8 | 32.0, 37.0 | 39.8     4096, 60, 81: 68.8 | 65.7, 69.5 | 69.9
+    //   4096, 120, 81: 70.7 | 66.5, 70.2 | 71.5    8192, 120, 16: 82.4 | 78.0, 82.2 | 83.5     4096, 240, 16: 63.3 | 50.4, 59.0 | 64.5
+    //   4096, 400, 16: 99.9 | 109, 93.8 | 101      2560, 778, 37: 144 | 159, 139 | 154         8192, 1050, 81: 194 | 213, 204 | 226
+    // and of rows that are not whole lines:
     //   1608, 60, 16: 32.3 | 26.3, 35.5 | 34.2     1608, 400, 81: 138 | 113, 137 | 112        4104, 1050, 16: 298 | 224, 300 | 226
-    //   256, 60, 16: 27.8 | 28.8, 27.8 | 29.2
-    const bool whole_lines = ((uintptr_t)W_U | (uintptr_t)d * 2) % 128 == 0;
-    const bool stream_W = whole_lines && (d < 512 || (int64_t)V * d * 2 > INFINITY_CACHE_BYTES / 2);
+    // (The scope bits of the loads, sc0 and sc1, make no difference either way.)
+    const bool stream_W = ((uintptr_t)W_U | (uintptr_t)d * 2) % 128 == 0 && !W_in_cache;
     hipLaunchKernelGGL(stream_W ? few_kernel<true>(few.nj, few.mu) : few_kernel<false>(few.nj, few.mu), dim3(few.splits), dim3(FEW_THREADS), 0, stream, a);
     LL_CHECK_F(hipGetLastError());
     LL_CHECK_F(mark());
@@ -1040,9 +1042,14 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
   hipLaunchKernelGGL(direction, dim3(UD_BLOCKS), dim3(256), v_bytes, stream, static_cast<const uint16_t*>(W_U), v, V, d,
                      as_projection ? al.a[0] : 1.0f, u, plan.n_padded, block_max);
   LL_CHECK_S(hipGetLastError());
+  // (The few-rows kernel then reads W_U through the caches where the direction kernel has just left it in the Infinity Cache, with room
+  // for what else is there; a W_U that the L2s hold together is left in them as that kernel has dealt it, for the next sweep's.  Whole
+  // calls, past the caches | through them, us, 8 rows (d, V, MB): 2560, 4096, 21: 42.1 | 45.1; 2560, 8192, 42: 50.8 | 46.2; 4096, 8192, 67:
+  // 72.7 | 68.8; 1024, 50257, 103: 54.2 | 49.3; 256, 128256, 66: no difference.)
+  const bool W_in_cache = d >= 512 && (int64_t)V * d * 2 > L2_BYTES && (int64_t)V * d * 2 <= INFINITY_CACHE_BYTES / 2;
   if (as_projection)
     return project_impl(shape, ws + plan.off_project, workspace_bytes - plan.off_project, hidden, gamma, W_U, u, 0u, eps, k, target_ids, out_ids,
-                        out_p, out_logp, out_entropy, stream, nullptr);
+                        out_p, out_logp, out_entropy, stream, nullptr, CHUNK_ROWS, W_in_cache);
   // Few alphas: the general form alone, without the tables and the launch that fills them.  Its cost grows with every alpha, the
   // factored one's hardly does: the line moves up where a split has few tiles and there are no lists.  Whole calls, general |
   // factored, us, d = 512 (N x V: tiles a split), arg max:

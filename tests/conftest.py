@@ -35,3 +35,14 @@ def say(msg):
             tr._tw.flush()
     else:
         print(line, file=sys.stderr, flush=True)
+
+
+def kernels_of(call):
+    """Names of this library's kernels that call() launches, in order: which path a shape takes is part of what some tests are about."""
+    import torch
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    found = [e for e in prof.events() if "::ll_" in e.name]
+    return [e.name.replace("(anonymous namespace)::", "").removeprefix("void ") for e in sorted(found, key=lambda e: e.time_range.start)]

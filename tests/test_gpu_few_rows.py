@@ -8,7 +8,7 @@ import oracle.lens_oracle as O
 from paper_2604_06483_amd import binding as LL
 from paper_2604_06483_amd import workloads as WL
 from tests import parity as P
-from tests.conftest import say
+from tests.conftest import kernels_of, say
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -175,3 +175,30 @@ def test_full_lists_cost_no_more_than_the_256_row_kernel(rows, V, k, what):
     few, many = call_time(w, rows, k), call_time(w, 129, k)
     say(f"few rows, time of {what}: {1e3 * few:.1f} us, 129 rows {1e3 * many:.1f} us")
     assert few < 1.5 * many
+
+
+@pytest.mark.parametrize("d,V,shift,past_the_caches", [
+    (2048, 30000, 0, True),    # 123 MB, which the Infinity Cache could hold: a call behind other work finds none of it there
+    (256, 5000, 0, True),
+    (2048, 30000, 8, False),   # the same rows, from 16 bytes into a line on
+    (1608, 20000, 0, False),   # rows that are not whole lines
+])
+def test_how_w_is_read_depends_on_its_lines_alone(d, V, shift, past_the_caches):
+    say(f"few rows, loads of W_U d={d} V={V} shift={shift}")
+    w = inputs(16, d, V)
+    W = torch.empty((V * d + shift,), dtype=torch.bfloat16, device=DEV)[shift:].view(V, d)
+    W.copy_(w.W_U)
+    names = kernels_of(lambda: LL.ll_project(w.hidden, w.gamma, W, w.cfg.eps, 5, w.target_ids))
+    assert len(names) == 3 and names[0].startswith("ll_norm_panel_kernel") and names[1].startswith("ll_lens_few_kernel")
+    assert names[1].split(">")[0].endswith("true" if past_the_caches else "false")
+
+
+@pytest.mark.parametrize("V,past_the_caches", [(3000, True), (20000, False), (60000, True)])
+def test_a_sweep_of_one_strength_reads_w_where_it_has_just_left_it(V, past_the_caches):
+    """12 MB stay in the L2s and 246 MB are more than the Infinity Cache keeps beside the rest; 82 MB are there."""
+    say(f"few rows, sweep of one strength V={V}")
+    w = inputs(16, 2048, V)
+    v = torch.randn((2048,), generator=torch.Generator(device=DEV).manual_seed(5), device=DEV)
+    names = kernels_of(lambda: LL.ll_steer_sweep(w.hidden.reshape(16, -1), w.gamma, w.W_U, w.cfg.eps, v / v.norm(), [2.0], w.target_ids))
+    assert names[0].startswith("ll_unembed_direction_kernel") and names[2].startswith("ll_lens_few_kernel")
+    assert names[2].split(">")[0].endswith("true" if past_the_caches else "false")

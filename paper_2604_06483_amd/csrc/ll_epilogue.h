@@ -139,10 +139,12 @@ struct RowState {
   bool first = true;        // no tile has been seen
   float lv[KR];             // top logits
   int li[KR];               // their ids
-  __device__ __forceinline__ void init() {
+  // present: the lane has a lens row.  Nothing ever beats the list of one past the last row, which stands for a row of zeros.
+  __device__ __forceinline__ void init(bool present) {
+    const float lowest = present ? -INFINITY : INFINITY;
 #pragma unroll
     for (int j = 0; j < KR; ++j) {
-      lv[j] = -INFINITY;
+      lv[j] = lowest;
       li[j] = INT_MAX;
     }
   }
@@ -574,7 +576,7 @@ struct TopKEpilogue {   // a5..a7: softmax statistics, k best logits, target log
   static constexpr bool RELOAD_FRAGMENTS = false;
   static __device__ __forceinline__ bool skip(const GemmArgs&) { return false; }
   static __device__ __forceinline__ void init(State& st, const GemmArgs& p, int my_row, int split) {
-    st.init();
+    st.init(my_row < p.rows);
     if (SHORT && p.classes > 0) st.cls = split % p.classes;
     st.tgt = (p.target != nullptr && my_row < p.rows) ? p.target[my_row] : -1;
   }

@@ -663,7 +663,9 @@ struct SweepEpilogue {
     for (int a = 0; a < SWEEP_MAX; ++a) {
       st.gs[a] = st.gt[a] = 0.f;
 #pragma unroll
-      for (int j = 0; j < KS; ++j) st.lv[a][j] = a < p.n_alpha ? -INFINITY : INFINITY;   // (nothing beats the lists of alphas that are not there)
+      // Nothing beats the lists of alphas that are not there, nor those of a lane past the last row: it holds the logits alpha u of a
+      // row of zeros, which for all anyone knows grow with the id.  (The latter finite: limits are derived from them.)
+      for (int j = 0; j < KS; ++j) st.lv[a][j] = a >= p.n_alpha ? INFINITY : my_row < p.rows ? -INFINITY : -NEG_BIG;
 #pragma unroll
       for (int j = 0; j < State::IDS; ++j) st.li[a][j] = 0xffffffffu;
     }

@@ -23,16 +23,20 @@ SOURCES = {
 pytestmark = pytest.mark.skipif(shutil.which("hipcc") is None, reason="hipcc not on PATH")
 
 
+def assembly(name, directory):
+    out = directory / (name + ".s")
+    cmd = ["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-S", "--cuda-device-only",
+           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument",
+           "-I", os.path.join(ROOT, "include"), "-I", CSRC, os.path.join(CSRC, name + ".hip"), "-o", str(out)]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    assert res.returncode == 0, res.stderr[-2000:]
+    return out.read_text()
+
+
 @pytest.fixture(scope="module", params=sorted(SOURCES))
 def source(request, tmp_path_factory):
     """(assembly, name of the direct-to-LDS kernels in it, their number)"""
-    out = tmp_path_factory.mktemp("isa") / (request.param + ".s")
-    cmd = ["hipcc", "--offload-arch=gfx950", "-O3", "-std=c++17", "-S", "--cuda-device-only",
-           "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops", "-Wno-unused-command-line-argument",
-           "-I", os.path.join(ROOT, "include"), "-I", CSRC, os.path.join(CSRC, request.param + ".hip"), "-o", str(out)]
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    assert res.returncode == 0, res.stderr[-2000:]
-    return (out.read_text(), *SOURCES[request.param])
+    return (assembly(request.param, tmp_path_factory.mktemp("isa")), *SOURCES[request.param])
 
 
 def kernel_bodies(asm_text, needle):
@@ -102,6 +106,23 @@ def test_no_valu_reads_an_sgpr_a_valu_wrote_within_two_instructions(source):
                     dests = ops[1].split(",")[:2]            # destination, and carry-out where there is one
                     assert all(sreg != dd.strip() for dd in dests), (name, prev, l)
     assert checked > 1000
+
+
+def test_list_insertions_are_eight_byte_instructions_on_their_boundaries(source):
+    """Four slots of a list are sixteen instructions of eight bytes, which take 3 to 4 % longer (whole calls of lists of 24) from four
+    bytes off: each such block starts at an alignment directive, and none holds another instruction."""
+    asm, kernel, _ = source
+    blocks = 0
+    for m in re.finditer(r"^(_Z\w*(?:" + kernel + r"|ll_lens_gemm_kernel)\w*TopKEpilogueILi\d+E\w*):[^\n]*\n(.*?)\n\s*s_endpgm", asm, re.S | re.M):
+        lines = [l.split(";")[0].strip() for l in m.group(2).splitlines()]
+        lines = [l for l in lines if l]
+        starts = [i for i, l in enumerate(lines) if l.split() == [".p2align", "3"]]
+        assert sum(l.startswith("v_med3_f32") for l in lines) == 4 * len(starts), m.group(1)
+        for i in starts:
+            body = lines[i + 1:i + 17]
+            assert all(re.match(r"v_(cmp_gt_f32_e64|med3_f32|cndmask_b32_e64) ", l) for l in body), (m.group(1), body)
+        blocks += len(starts)
+    assert blocks > 0
 
 
 def registers(operand):

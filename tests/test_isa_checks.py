@@ -125,6 +125,13 @@ def test_list_insertions_are_eight_byte_instructions_on_their_boundaries(source)
     assert blocks > 0
 
 
+def test_the_general_sweeps_groups_are_placed(source):
+    """Their code starts 20 bytes past a multiple of 32, whatever stands before it."""
+    asm, kernel, _ = source
+    for m in re.finditer(r"^(_Z\w*" + kernel + r"\w*SweepEpilogueILi\dELb1E\w*):[^\n]*\n(.*?)\n\s*s_endpgm", asm, re.S | re.M):
+        assert len(re.findall(r"\.p2align\s+5\s+(?:s_nop 0\s+){5};;#ASMEND", m.group(2))) == 1, m.group(1)
+
+
 def registers(operand):
     """The vector registers that an operand names."""
     m = re.fullmatch(r"v\[(\d+):(\d+)\]|v(\d+)", operand.strip())

@@ -430,6 +430,9 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
     __syncthreads();                                                                                   \
     LL_SLICE(MF0, 3, 1, fw1, fw0, nW, 0, LL_AIN_S3, LL_AOUT_S3, LL_HOOK_S3, LL_RD_SPREAD)
 #define LL_PLACE_LOOP ".p2align 6\n\ts_nop 0"
+  // Where the epilogues of short calls start: 4 bytes past a multiple of 32, the best of the eight places four bytes apart (whole calls
+  // of 13 shapes, lists of 4, 12 and 20, 23 to 800 us: up to 1.4 % in the mean of a kernel, 3.5 % in a call of 23 us).
+#define LL_PLACE_EPILOGUE ".p2align 5\n\ts_nop 0"
   // The same of half a tile: vocabulary rows 0 .. 127 of it.
 #define LL_HALF_STAGE(MF0, KTILE)                                                                      \
     LL_SLICE(MF0, 0, 1, fw0, fw1, cW, 1, LL_A_NONE, LL_A_NONE, LL_HOOK_HALF, LL_RD_AHEAD)              \
@@ -440,16 +443,20 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
   for (int tile = tile0; tile < (SHORT && ends_in_half ? tile1 - 1 : tile1); ++tile) {
     f32x4 acc[16][4];   // first written by the K half 0 MFMAs of stage 0, with C = 0
     LL_STAGE(LL_MFMA16_Z, 0)
-    // (The loop's place in the 64-byte instruction lines, which a change anywhere before it moves: with its first MFMA at byte 44 a
-    // pass of 8192 rows takes 0.7 % less at d = 2560 and 0.5 % less at d = 8192 than at bytes 52, 32 or 0.)
+    // (The loop's place in the 64-byte instruction lines, which a change anywhere before it would move.  In the projections of whole
+    // stages without a bias, which most long calls run, its first MFMA is at byte 44: a pass of 8192 rows takes 0.7 % less there at d = 2560
+    // and 0.5 % less at d = 8192 than at bytes 52, 32 or 0.  In the other kernels it is where the same directive leaves it, at bytes
+    // 24 to 48, and the loop of half tiles is not placed: not measured for them.)
     asm volatile(LL_PLACE_LOOP);
     for (int kt = 1; kt < KT; ++kt) {
       LL_STAGE(LL_MFMA16, kt)
     }
-    if constexpr (SHORT)
+    if constexpr (SHORT) {
+      asm volatile(LL_PLACE_EPILOGUE);
       EPI::template short_tile<false>(acc, st, row0 + tile * BM, p, my_row);
-    else
+    } else {
       EPI::tile(acc, st, tile * BM, p, my_row);
+    }
     // An epilogue that needs the 64 registers reads the next stage's first fragments again: both tiles stay in LDS until that
     // stage's own slices send the loads that replace them.
     if (EPI::RELOAD_FRAGMENTS) read_fragments(cW, a_flip - nA);
@@ -461,12 +468,14 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
       for (int kt = 1; kt < KT; ++kt) {
         LL_HALF_STAGE(LL_MFMA16, kt)
       }
+      asm volatile(LL_PLACE_EPILOGUE);
       EPI::template short_tile<true>(acc, st, row0 + (tile1 - 1) * BM, p, my_row);
     }
   }
 #undef LL_STAGE
 #undef LL_HALF_STAGE
 #undef LL_PLACE_LOOP
+#undef LL_PLACE_EPILOGUE
 #undef LL_PAIR
 #undef LL_RD_SPREAD
 #undef LL_RD_AHEAD

@@ -125,6 +125,24 @@ def test_list_insertions_are_eight_byte_instructions_on_their_boundaries(source)
     assert blocks > 0
 
 
+LLVM = "/opt/rocm/llvm/bin"
+
+
+@pytest.mark.skipif(not os.path.exists(os.path.join(LLVM, "llvm-mc")), reason="no assembler")
+def test_the_k_loop_of_projections_without_a_bias_starts_at_byte_44_of_a_line(tmp_path):
+    text = assembly("ll_project", tmp_path)
+    obj = tmp_path / "ll_project.o"
+    subprocess.run([os.path.join(LLVM, "llvm-mc"), "-triple=amdgcn-amd-amdhsa", "-mcpu=gfx950", "-filetype=obj", "-o", str(obj)],
+                   input=text, text=True, check=True)
+    found = {}
+    listing = subprocess.run([os.path.join(LLVM, "llvm-objdump"), "-d", "--mcpu=gfx950", str(obj)], capture_output=True, text=True, check=True).stdout
+    for m in re.finditer(r"^[0-9a-f]+ <(_Z\w*ll_lens_gemm_dma_kernel\w*TopKEpilogueILi(\d+)ELb0E\w*)>:\n(.*?)(?=\n\n)", listing + "\n\n", re.S | re.M):
+        at = [int(x, 16) for x in re.findall(r"v_mfma_f32_16x16x32_bf16[^\n]*//\s*([0-9A-F]+):", m.group(3))]
+        assert len(at) == 256                             # a tile's first stage and the loop's
+        found[int(m.group(2))] = at[128] % 64
+    assert found == {4: 44, 12: 44, 20: 44, 32: 44}
+
+
 def test_the_general_sweeps_groups_are_placed(source):
     """Their code starts 20 bytes past a multiple of 32, whatever stands before it."""
     asm, kernel, _ = source

@@ -502,6 +502,8 @@ struct FewPlan {
   int nj, mu, units, splits;   // nj: 16-row blocks of the kernel instance; mu: groups per wavefront; units: groups in all
 };
 
+constexpr int SHORT_KMAX = 20;   // longest list of the kernel of short calls
+
 FewPlan make_few_plan(const ll_shape* s, int k) {
   FewPlan f = {};
   if (s->N < 1 || s->N > FEW_ROWS) return f;
@@ -541,8 +543,6 @@ bool shape_ok(const ll_shape* s, int k) {
   if (k < 1 || k > LL_KMAX || k > s->V) return false;
   return true;
 }
-
-constexpr int SHORT_KMAX = 20;   // longest list of the kernel of short calls
 
 // Where the bounds of the classes of splits stand (one a row and class, k of them, in passes of at least k splits: rows x k never
 // exceeds MAX_PARTIALS), and how much room they may want: behind what of the panel the pass fills, so that only a workspace
@@ -644,6 +644,34 @@ int even_splits(int tiles, int most) {
   return (tiles + each - 1) / each;
 }
 
+// How a pass of `rows` rows deals the vocabulary.  One workgroup per compute unit: a pass of few rows cuts it finer (its cost is then the
+// one read of W_U, spread over every compute unit's share of the memory system).
+struct Deal {
+  int row_blocks, splits;
+  int half_tiles, classes;   // as in GemmArgs: of the kernel of short calls, where that is taken
+  int tiles_each;            // whole tiles of the busiest workgroup, were there no half ones
+};
+
+Deal deal_vocabulary(int rows, int V, int k, bool short_kernel) {
+  const int tiles = (V + BM - 1) / BM;
+  Deal l = {};
+  l.row_blocks = (rows + BN - 1) / BN;
+  const int most = NUM_CU / l.row_blocks < MAX_PROJECT_SPLITS ? NUM_CU / l.row_blocks : MAX_PROJECT_SPLITS;
+  l.splits = even_splits(tiles, most);
+  const int each = l.tiles_each = (tiles + l.splits - 1) / l.splits;
+  if (!short_kernel || each > SHORT_TILES) return l;
+  // Few tiles a workgroup: the kernel that can end a split in half a tile, where that leaves the busiest workgroup half a tile less,
+  // and that deals at least k splits into k classes (see exchange_classes).
+  const int halves = (V + BM / 2 - 1) / (BM / 2), each_half = (halves + most - 1) / most;
+  const int half_splits = (halves + each_half - 1) / each_half;
+  if (each_half < 2 * each && (half_splits >= k || each <= SHORT_TILES_WITHOUT)) {
+    l.half_tiles = halves;
+    l.splits = half_splits;
+  }
+  if (l.splits >= k) l.classes = k;
+  return l;
+}
+
 // (few rows: one wavefront per block, so that they spread over the compute units)
 void launch_norm_panel(const uint16_t* hidden, const uint16_t* gamma, uint16_t* panel, int rows, int zero_rows, int d, int64_t lda,
                        float eps, unsigned* bound, int bounds, hipStream_t stream) {
@@ -678,8 +706,6 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
   if (align_or & 15) return LL_EINVAL;
   const Plan plan = make_plan(shape, k, chunk_rows);
   if (workspace == nullptr || workspace_bytes < plan.total || ((uintptr_t)workspace & 255)) return LL_EWORKSPACE;
-  const bool few_rows = plan.few.ok && workspace_bytes >= plan.few_total && !(flags & LL_FLAG_REGISTER_STAGED);
-
   unsigned char* ws = static_cast<unsigned char*>(workspace);
   float* inv_rms = reinterpret_cast<float*>(ws + plan.off_inv_rms);
   float4* stats = reinterpret_cast<float4*>(ws + plan.off_stats);
@@ -689,21 +715,24 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
   const int64_t N = shape->N;
   const int d = shape->d, V = shape->V;
   const bool has_gamma = gamma != nullptr;
+  const bool few_rows = plan.few.ok && workspace_bytes >= plan.few_total && !(flags & LL_FLAG_REGISTER_STAGED);
   // The direct-to-LDS kernel addresses rows with 32-bit byte offsets from a per-tile base.  It takes every other shape, a d
   // that is not a multiple of 64 in an instantiation of its own, which the longest list with a bias does not have.
   // 777 rows, d = 1608, V = 50257, k = 3 with a bias: 201 us, on the register-staged kernel 369
-  // It needs the rows padded, which is a launch; calls whose busiest workgroup has little to do (fewer than ten stages of 64
-  // columns, with a norm fewer than six) are as fast or faster without.  Whole calls, direct-to-LDS over register-staged, 129 to
-  // 1500 rows, V = 5000 to 128256, by the stages and the tiles they are of; k = 1 and k = 10:
-  //   no norm:  4 of 1 tile 1.00-1.08, 0.97-1.03;  4 of 2 1.03-1.16, 1.05-1.13;  6 of 2 0.99-1.10, 1.03-1.11;  8 of 2 0.94-1.06,
-  //             0.99-1.07;  8 of 4 0.89-0.92, 0.98-1.05;  10 of 1 0.84-0.89, 0.87-0.93;  12 of 2 0.88-0.99, 0.95-1.01
-  //   a norm:   2 of 1 0.97-1.04, 0.95-1.01;  2 of 2 1.02-1.10, 1.03-1.12;  4 of 2 0.94-1.06, 1.00-1.08;  4 of 4 0.89-0.93, 0.98-1.05;
-  //             6 of 2 0.90-1.01, 0.96-1.05;  8 of 1 0.80-0.85, 0.82-0.86
+  // It needs the rows padded, which is a launch.  With classes of splits that always pays, unless there is a bias and no half tile; else
+  // calls whose busiest workgroup has little to do are as fast or faster without.  Whole calls, direct-to-LDS over register-staged, by the
+  // stages of 64 columns that the busiest workgroup has to do:
+  //   classes, no bias (150 to 8192 rows, V = 1000 to 128256, k = 1, 10, 20): 1 stage 0.54-0.93, 20 stages 0.53-0.74
+  //   k = 20 and 10 in fewer splits (2500 to 8192 rows): a norm  1 1.02-1.05, 2 0.99-1.02, 3 0.97-1.00;  none  1 1.05-1.08, 3 1.01-1.04, 5 0.99-1.02
+  //   a bias (k = 3, 10) and half tiles: 0.63-0.90;  whole ones: a norm  1 0.98-1.09, 2 at most 1.04, 3 1.02, 4 1.02;  none  1 1.01-1.13,
+  //     3 at most 1.07, 5 1.04, 7 1.03
+  //   no kernel of short calls (k = 24, 32; 16 with a bias): a norm  1 0.99-1.05, 4 0.97-1.0, 5 0.97-1.01;  none  1 1.02-1.09, 4 0.97-1.06
   const int tiles = (V + BM - 1) / BM;
-  const int first_blocks = (int)(((N < CHUNK_ROWS ? N : CHUNK_ROWS) + BN - 1) / BN);   // (whatever the scratch: the same kernel)
-  const int first_splits = even_splits(tiles, NUM_CU / first_blocks < MAX_PROJECT_SPLITS ? NUM_CU / first_blocks : MAX_PROJECT_SPLITS);
-  const int64_t stages = (int64_t)((tiles + first_splits - 1) / first_splits) * (plan.lda / DK);
-  const bool worth_padding = stages >= (has_gamma ? 6 : 10);
+  const bool has_short = short_topk_kernel(k, bias != nullptr, d % DK != 0) != nullptr;
+  const Deal first = deal_vocabulary((int)(N < CHUNK_ROWS ? N : CHUNK_ROWS), V, k, has_short);   // (whatever the scratch: the same kernel)
+  const int64_t stages = (int64_t)first.tiles_each * (plan.lda / DK);
+  const bool worth_padding = (first.classes > 0 && (bias == nullptr || first.half_tiles > 0)) ||
+                             stages >= (has_short ? (has_gamma ? 3 : 5) : (has_gamma ? 6 : 10));
   const GemmKernel tail_kern = d % DK != 0 && worth_padding ? tail_topk_kernel(k, bias != nullptr) : nullptr;
   const bool dma = !(flags & LL_FLAG_REGISTER_STAGED) && (d % DK == 0 || tail_kern != nullptr) &&
                    (int64_t)BM * plan.lda * 2 < (int64_t)1 << 31 && (int64_t)CHUNK_ROWS * plan.lda * 2 < (int64_t)1 << 31;
@@ -809,32 +838,19 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     return finish(read_phases());
   }
 
-  // How a pass of `rows` rows deals the vocabulary, and where its shared bounds stand.
-  struct Deal {
-    int row_blocks, splits, half_tiles, classes;
+  // A pass's deal, and where its shared bounds stand (off_bound; `bounds` of them a row).
+  struct Pass : Deal {
+    int bounds;
     size_t off_bound;
-    int bounds() const { return classes > 0 ? classes : 1; }
   };
-  auto deal = [&](int rows) {
-    Deal l = {(rows + BN - 1) / BN, 0, 0, 0, plan.off_bound};
-    // One workgroup per compute unit: a pass of few rows cuts the vocabulary finer (its cost is then the one read
-    // of W_U, spread over every compute unit's share of the memory system).
-    const int most = NUM_CU / l.row_blocks < MAX_PROJECT_SPLITS ? NUM_CU / l.row_blocks : MAX_PROJECT_SPLITS;
-    l.splits = even_splits(tiles, most);
-    const int each = (tiles + l.splits - 1) / l.splits;
-    if (short_kern == nullptr || each > SHORT_TILES) return l;
-    // Few tiles a workgroup: the kernel that can end a split in half a tile, where that leaves the busiest workgroup half a tile less,
-    // and that deals at least k splits into k classes (see exchange_classes).
-    const int halves = (V + BM / 2 - 1) / (BM / 2), each_half = (halves + most - 1) / most;
-    const int half_splits = (halves + each_half - 1) / each_half;
-    if (each_half < 2 * each && (half_splits >= k || each <= SHORT_TILES_WITHOUT)) {
-      l.half_tiles = halves;
-      l.splits = half_splits;
-    }
+  auto pass = [&](int rows) {
+    Pass l = {deal_vocabulary(rows, V, k, short_kern != nullptr), 1, plan.off_bound};
     const size_t at = classes_offset(plan.off_panel, need_panel ? rows + 1 : 0, plan.lda);
-    if (l.splits >= k && at + classes_bytes((size_t)rows, k) <= workspace_bytes) {
-      l.classes = k;
+    if (l.classes > 0 && at + classes_bytes((size_t)rows, k) <= workspace_bytes) {
+      l.bounds = k;
       l.off_bound = at;
+    } else {
+      l.classes = 0;
     }
     return l;
   };
@@ -844,8 +860,8 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
   // or have each its own.
   if (dma && !need_panel) {
     const int full = (int)(N < chunk_rows ? N : chunk_rows), last = (int)(N % chunk_rows);
-    Deal a = deal(full), b = last > 0 ? deal(last) : a;
-    int64_t n_a = (int64_t)full * a.bounds(), n_b = (int64_t)last * b.bounds();
+    const Pass a = pass(full), b = last > 0 ? pass(last) : a;
+    int64_t n_a = (int64_t)full * a.bounds, n_b = (int64_t)last * b.bounds;
     if (a.off_bound == b.off_bound) {
       n_a = n_a > n_b ? n_a : n_b;
       n_b = 0;
@@ -866,8 +882,8 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
   for (int64_t r0 = 0; r0 < N; r0 += chunk_rows) {
     const int rows = (int)((N - r0) < chunk_rows ? (N - r0) : chunk_rows);
     const uint16_t* h_rows = static_cast<const uint16_t*>(hidden) + r0 * d;
-    const Deal l = deal(rows);
-    const int row_blocks = l.row_blocks, splits = l.splits, bounds = l.bounds();
+    const Pass l = pass(rows);
+    const int row_blocks = l.row_blocks, splits = l.splits, bounds = l.bounds;
     unsigned* const bound = dma ? reinterpret_cast<unsigned*>(ws + l.off_bound) : nullptr;
     // (a row of zeros for the rows that the last block lacks, where the workspace has room for one)
     const int zero_rows = need_panel && rows % BN != 0 && plan.off_panel + (size_t)(rows + 1) * (size_t)plan.lda * sizeof(uint16_t) <= workspace_bytes ? 1 : 0;

@@ -1,0 +1,55 @@
+"""Which kernel a call takes, and its results against the CPU oracle there: shapes on either side of the lines of the dispatch, so that
+a line that moves cannot leave a kernel without a case of its own unnoticed."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2604_06483_amd import binding as LL
+from paper_2604_06483_amd import workloads as WL
+from tests import parity as P
+from tests.conftest import kernels_of, say
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+LONG, TAIL, SHORT = "ll_lens_gemm_dma_kernel", "ll_lens_gemm_dma_tail_kernel", "ll_lens_gemm_short_kernel"
+STAGED, FEW = "ll_lens_gemm_kernel", "ll_lens_few_kernel"
+
+
+def main_kernels(call):
+    return [n.split("(")[0] for n in kernels_of(call) if n.startswith(("ll_lens_", "ll_sweep_table"))]
+
+
+def projection(N, d, V, k, with_bias, gamma, expected, zero_rows=False):
+    """Runs the call, asserts its kernels (one name a pass) and compares up to 600 of its rows with the oracle."""
+    w = WL.make_workload(WL.LensConfig("route", L=1, T=N, d=d, V=V, k=k, n_outliers=2 if d > 100 else 0, outlier_scale=20.0), DEV, seed=67)
+    bias = 0.5 * torch.randn((V,), generator=torch.Generator(device=DEV).manual_seed(3), device=DEV) if with_bias else None
+    if zero_rows:
+        w.hidden.reshape(N, d)[::7] = 0
+        w.W_U[V // 2:] = w.W_U[:V - V // 2].clone()      # and two of every token
+    call = lambda: LL.ll_project(w.hidden, w.gamma if gamma else None, w.W_U, w.cfg.eps, k, w.target_ids, bias=bias)
+    got = P.to_numpy(call())
+    names = main_kernels(call)
+    assert [n.split("<")[0] for n in names] == expected, names
+    rows = np.arange(N) if N <= 600 else np.unique(np.r_[0:200, N // 2:N // 2 + 200, N - 200:N])
+    ref = P.oracle_rows(WL.bf16_bits(w.hidden.reshape(-1, d))[rows], WL.bf16_bits(w.gamma) if gamma else None, WL.bf16_bits(w.W_U),
+                        w.cfg.eps, k, w.target_ids.cpu().numpy()[rows], bias=None if bias is None else bias.cpu().numpy())
+    P.compare({n: x[rows] for n, x in got.items()}, ref, k, label="route")
+    return names
+
+
+@pytest.mark.parametrize("N,d,V,k,with_bias,gamma,expected", [
+    (300, 56, 10000, 4, False, True, [SHORT]),     # one stage: classes of splits always pay for the padded rows
+    (300, 72, 40000, 20, False, False, [SHORT]),   # no norm either
+    (1000, 56, 5000, 3, True, False, [SHORT]),     # a bias and half tiles
+    (700, 56, 15000, 3, True, True, [STAGED]),     # a bias, whole tiles: one stage
+    (700, 200, 15000, 3, True, True, [SHORT]),     # four
+    (700, 200, 15000, 3, True, False, [STAGED]),
+    (700, 264, 15000, 10, True, False, [SHORT]),   # five
+    (9000, 72, 2000, 20, False, True, [STAGED, STAGED]),   # fewer splits than k: two stages
+    (300, 200, 10000, 24, False, True, [STAGED]),  # the longest list: four stages, then six
+    (300, 328, 10000, 24, False, True, [TAIL]),
+])
+def test_ragged_hidden_sizes(N, d, V, k, with_bias, gamma, expected):
+    say(f"route N={N} d={d} V={V} k={k} bias={with_bias} gamma={gamma}")
+    projection(N, d, V, k, with_bias, gamma, expected)

@@ -498,11 +498,11 @@ __global__ __launch_bounds__(256) void ll_sweep_merge_kernel(const float4* __res
 // groups against all the rows, so the register file bounds MU by the number of 16-row blocks; a larger share of the
 // vocabulary goes in two or more rounds of workgroups.
 struct FewPlan {
-  bool ok;
+  bool ok, two_rounds;   // two_rounds: of more than 96 rows
   int nj, mu, units, splits;   // nj: 16-row blocks of the kernel instance; mu: groups per wavefront; units: groups in all
 };
 
-constexpr int SHORT_KMAX = 20;   // longest list of the kernel of short calls
+constexpr int SHORT_KMAX = 20, SHORT_KMAX_BIAS = 12;   // longest lists of the kernel of short calls
 
 FewPlan make_few_plan(const ll_shape* s, int k) {
   FewPlan f = {};
@@ -518,10 +518,14 @@ FewPlan make_few_plan(const ll_shape* s, int k) {
   f.splits = parts * rounds;
   if (f.splits > FEW_MAX_SPLITS) return f;   // V beyond some 200 000 to 330 000
   // More than 96 rows over more than one round (V past 98 000): a round's contraction and epilogue are no longer small beside
-  // its share of W_U, and what is saved is the 256-row kernel's insertions, few with its shortest list.  128 rows, here | 256-row
-  // kernel, us: V = 128256: d = 64: k = 1 54 | 45, k = 4 55 | 51, k = 5 55 | 66; d = 2560: k = 1 190 | 162, k = 4 185 | 167,
-  // k = 5 182 | 182, k = 10 184 | 188; d = 8192: k = 1 441 | 442, k = 4 441 | 437; V = 100000, d = 2560: k = 1 167 | 147, k = 5 167 | 166.
-  if (rounds > 1 && f.nj == 8 && k <= 4) return f;
+  // its share of W_U, and the 256-row tiles have few insertions left in a split's first tile (see exchange_classes), up to the
+  // longest list that has classes without a bias and with one (project_impl); with the shortest where rows are not whole stages, which
+  // those tiles pay more for (107 rows, d = 5096, V = 99168, k = 15: 280 | 305).  128 rows, here | 256-row kernels, us:
+  // V = 128256: d = 64: k = 1 54 | 34, k = 8 56 | 41, k = 20 59 | 55, k = 24 76 | 126; d = 2560: k = 1 186 | 167, k = 8 187 | 153, k = 20 187 | 167,
+  // k = 24 197 | 239; d = 8192: k = 1 432 | 427, k = 12 423 | 406, k = 20 421 | 416, k = 32 460 | 498; V = 151936, d = 1024: k = 1 113 | 100,
+  // k = 20 119 | 116.
+  f.two_rounds = rounds > 1 && f.nj == 8;
+  if (f.two_rounds && k <= (s->d % DK == 0 ? SHORT_KMAX_BIAS : 4)) return f;
   f.mu = ((f.units + f.splits - 1) / f.splits + FEW_WAVES - 1) / FEW_WAVES;
   f.ok = true;
   return f;
@@ -715,7 +719,8 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
   const int64_t N = shape->N;
   const int d = shape->d, V = shape->V;
   const bool has_gamma = gamma != nullptr;
-  const bool few_rows = plan.few.ok && workspace_bytes >= plan.few_total && !(flags & LL_FLAG_REGISTER_STAGED);
+  const bool few_rows = plan.few.ok && workspace_bytes >= plan.few_total && !(flags & LL_FLAG_REGISTER_STAGED) &&
+                        !(plan.few.two_rounds && d % DK == 0 && k <= SHORT_KMAX && bias == nullptr);
   // The direct-to-LDS kernel addresses rows with 32-bit byte offsets from a per-tile base.  It takes every other shape, a d
   // that is not a multiple of 64 in an instantiation of its own, which the longest list with a bias does not have.
   // 777 rows, d = 1608, V = 50257, k = 3 with a bias: 201 us, on the register-staged kernel 369

@@ -53,3 +53,14 @@ def projection(N, d, V, k, with_bias, gamma, expected, zero_rows=False):
 def test_ragged_hidden_sizes(N, d, V, k, with_bias, gamma, expected):
     say(f"route N={N} d={d} V={V} k={k} bias={with_bias} gamma={gamma}")
     projection(N, d, V, k, with_bias, gamma, expected)
+
+
+@pytest.mark.parametrize("N,d,V,k,with_bias,expected", [
+    (128, 64, 128256, 12, True, [SHORT]), (97, 64, 128256, 20, False, [SHORT]),
+    (128, 64, 128256, 13, True, [FEW]), (128, 64, 128256, 21, False, [FEW]),
+    (128, 72, 128256, 4, False, [SHORT]), (128, 72, 128256, 5, False, [FEW]),
+    (96, 64, 128256, 1, False, [FEW]), (128, 64, 98000, 1, False, [FEW]),      # one round of workgroups
+])
+def test_few_rows_in_two_rounds(N, d, V, k, with_bias, expected):
+    say(f"route N={N} d={d} V={V} k={k} bias={with_bias}")
+    projection(N, d, V, k, with_bias, True, expected)

@@ -1055,11 +1055,12 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     if (const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(direction), (size_t)SWEEP_MAX_D * sizeof(float)); rc != LL_OK) return rc;
   const int first_rows = (int)(N < CHUNK_ROWS ? N : CHUNK_ROWS), first_splits = sweep_splits(first_rows, tiles);
   const int each = (tiles + first_splits - 1) / first_splits;
-  // One strength is a projection whose bias is alpha u, which is the faster call for few rows and for many tiles a split (else
-  // its longer list and the copy of the bias cost more).  Whole calls, projection | the sweep's own kernel, us, d = 256 (N x V: tiles
-  // a split), arg max: 1500 x 4096 (1) 42 | 34, 4000 x 50257 (13) 193 | 218, 4000 x 128256 (32) 405 | 494; lists of two:
-  // 1500 x 128256 (12) 201 | 244, 4000 x 128256 (32) 417 | 545.
-  const bool as_projection = n_alpha == 1 && (N <= FEW_ROWS || each > 4);
+  // One strength is a projection whose bias is alpha u.  That is the faster call for lists, for few rows and for many tiles a split; the arg
+  // max alone over few tiles costs less than the copy of the bias and the longer list.  Whole calls, projection | the sweep's own
+  // kernel, us, d = 256 (N x V: tiles a split), arg max: 300 x 20000 (1) 39 | 34, 700 x 20000 (1) 43 | 34, 1500 x 4096 (1) 31 | 32, 300 x
+  // 50257 (2) 60 | 53, 700 x 50257 (3) 69 | 68, 4000 x 20000 (5) 91 | 98, 4000 x 50257 (13) 181 | 217; lists of two: 300 x 20000 40 | 43,
+  // 1500 x 4096 30 | 42, 300 x 50257 58 | 66, 700 x 50257 71 | 83, 4000 x 50257 185 | 254.
+  const bool as_projection = n_alpha == 1 && (N <= FEW_ROWS || k > 1 || each > 4);
   hipLaunchKernelGGL(direction, dim3(UD_BLOCKS), dim3(256), v_bytes, stream, static_cast<const uint16_t*>(W_U), v, V, d,
                      as_projection ? al.a[0] : 1.0f, u, plan.n_padded, block_max);
   LL_CHECK_S(hipGetLastError());

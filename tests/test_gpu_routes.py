@@ -8,6 +8,8 @@ from paper_2604_06483_amd import binding as LL
 from paper_2604_06483_amd import workloads as WL
 from tests import parity as P
 from tests.conftest import kernels_of, say
+from tests.test_gpu_sweep import ALPHAS9, direction
+from tests.test_gpu_sweep_forms import check
 
 pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
@@ -64,3 +66,17 @@ def test_ragged_hidden_sizes(N, d, V, k, with_bias, gamma, expected):
 def test_few_rows_in_two_rounds(N, d, V, k, with_bias, expected):
     say(f"route N={N} d={d} V={V} k={k} bias={with_bias}")
     projection(N, d, V, k, with_bias, True, expected)
+
+
+@pytest.mark.parametrize("N,d,V,A,k,expected", [
+    (300, 128, 20000, 1, 2, ["projection"]), (300, 72, 20000, 1, 4, ["projection"]), (300, 128, 20000, 1, None, ["general"]),
+    (1500, 64, 50257, 1, None, ["projection"]),
+])
+def test_sweeps(N, d, V, A, k, expected):
+    say(f"route sweep N={N} d={d} V={V} A={A} k={k}")
+    w = WL.make_workload(WL.LensConfig("route", L=1, T=N, d=d, V=V, k=1), DEV, seed=41)
+    names = main_kernels(lambda: LL.ll_steer_sweep(w.hidden.reshape(N, d), w.gamma, w.W_U, w.cfg.eps, direction(d), ALPHAS9[:A], w.target_ids, k=k))
+    kinds = ["table" if n.startswith("ll_sweep_table") else "projection" if "TopKEpilogue" in n else
+             "general" if "true> >" in n or "true>>" in n else "factored" for n in names]
+    assert kinds == expected, names
+    check(N, d, V, ALPHAS9[:A], k, 1.0, "route")

@@ -1073,20 +1073,24 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     return project_impl(shape, ws + plan.off_project, workspace_bytes - plan.off_project, hidden, gamma, W_U, u, 0u, eps, k, target_ids, out_ids,
                         out_p, out_logp, out_entropy, stream, nullptr, CHUNK_ROWS, W_in_cache);
   // Few alphas: the general form alone, without the tables and the launch that fills them.  Its cost grows with every alpha, the
-  // factored one's hardly does: the line moves up where a split has few tiles and there are no lists.  Whole calls, general |
-  // factored, us, d = 512 (N x V: tiles a split), arg max:
-  //   60 x 20000 (1)       A = 6  67 | 77       A = 7  73 | 76       A = 8  78 | 76
-  //   1500 x 4096 (1)      A = 7  78 | 87       A = 8  84 | 88       A = 9  91 | 90
-  //   300 x 50257 (2)      A = 4  99 | 117      A = 5  109 | 119     A = 6  120 | 120    A = 7  131 | 116
-  //   700 x 50257 (3)      A = 3  117 | 145     A = 4  133 | 144     A = 5  149 | 147
-  //   1500 x 50257 (5)     A = 3  181 | 214     A = 4  206 | 217     A = 5  232 | 218
-  //   4000 x 128256 (32)   A = 3  923 | 963     A = 4  1055 | 968
-  // and lists:
-  //   60 x 20000 (1)       A = 3  81 | 83       A = 4  94 | 84
-  //   300 x 50257 (2)      A = 3  125 | 132     A = 4  148 | 135
-  //   1500 x 50257 (5)     A = 3  240 | 250     A = 4  287 | 259
-  //   4000 x 128256 (32)   A = 3  1114 | 1120   A = 4  1306 | 1138
-  const bool lists = k > 1, only_general = n_alpha <= (lists || each > 8 ? 3 : each == 1 ? 7 : each == 2 ? 5 : 4);
+  // factored one's hardly does: the line moves up where a split has few tiles and there are no lists, and where the contraction is
+  // short (what the factored form adds to it is the same, and the smaller share of the call).  Whole calls, general | factored, us
+  // (N x V: tiles a split), arg max:
+  //   d = 512:   300 x 20000 (1)   A = 7  75 | 80      A = 8  80 | 81        1500 x 4096 (1)     A = 7  76 | 86     A = 8  83 | 87
+  //              300 x 50257 (2)   A = 5  107 | 120    A = 6  118 | 120      700 x 50257 (3)     A = 4  129 | 146   A = 5  146 | 149
+  //              1500 x 50257 (5)  A = 4  204 | 221    A = 5  231 | 221      1500 x 80000 (8)    A = 4  305 | 307   A = 5  345 | 311
+  //              1500 x 100000 (10)  A = 3  325 | 363  A = 4  374 | 367      4000 x 128256 (32)  A = 4  1043 | 977
+  //   d = 128:   300 x 50257 (2)   A = 6  103 | 119    A = 7  114 | 117      700 x 50257 (3)     A = 5  124 | 143   A = 6  141 | 144
+  //              1500 x 50257 (5)  A = 5  189 | 204    A = 6  215 | 204      1500 x 100000 (10)  A = 4  291 | 321   A = 5  341 | 329
+  //   d = 2048:  300 x 50257 (2)   A = 5  178 | 177    A = 6  189 | 180      1500 x 80000 (8)    A = 4  592 | 575
+  // and lists of three:
+  //   d = 512:   300 x 50257 (2)   A = 3  121 | 133    A = 4  143 | 134      4000 x 128256 (32)  A = 3  1098 | 1152   A = 4  1291 | 1162
+  //   d = 128:   300 x 50257 (2)   A = 4  128 | 129                          4000 x 128256 (32)  A = 3  865 | 1042    A = 4  1063 | 1053
+  //   d = 2048:  300 x 50257 (2)   A = 3  192 | 193                          4000 x 128256 (32)  A = 3  2058 | 2028
+  //   d = 64, A = 4, general over factored, lists of two and four: 60 x 20000 (1) 0.95, 0.90; 1500 x 50257 (5) 0.95, 0.90; 4000 x 50257 (13) 0.97, 0.91
+  const bool lists = k > 1;
+  const int most_general = lists ? (d <= 64 ? 4 : 3) : (each > 8 ? 3 : each > 2 ? 4 : each == 2 ? 5 : 7) + (d <= 256 ? 1 : 0);
+  const bool only_general = n_alpha <= most_general;
   int zero_alpha = -1;   // of nine alphas one that is zero needs no place in the tables
   for (int a = 0; a < n_alpha; ++a)
     if (n_alpha > SWEEP_SPLIT_ROWS && al.a[a] == 0.f) zero_alpha = a;

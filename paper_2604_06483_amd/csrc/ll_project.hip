@@ -656,14 +656,20 @@ struct Deal {
   int tiles_each;            // whole tiles of the busiest workgroup, were there no half ones
 };
 
-Deal deal_vocabulary(int rows, int V, int k, bool short_kernel) {
+// dear: the kernel of short calls costs more a tile than it saves in insertions, few in the shortest list (its bias comes late where
+// the last K stage is ragged; of eight stages and more: in shorter ones the insertions weigh more).  Taken up to SHORT_TILES_WITHOUT
+// tiles, for half a tile less up to twice those, for an arg max only for that.  Whole calls, long over short (N x V: tiles), k = 1 and 3 with a bias, d = 968: 300 x 128256
+// (4) 0.97, 1.04; 957 x 128256 (8) 0.96, 1.00; 2500 x 100000 (16) 0.95, 0.99; 4000 x 128256 (32) 0.96, 0.97; d = 1608: 300 x 128256 0.97, 1.00; 957
+// x 128256 0.99, 0.99; 1500 x 100000 (10, a half tile less) 1.01, 1.03;
+// 4000 x 128256 0.98, 1.00; d = 200: 4000 x 128256 1.04, 1.05.  k = 10: 1.03 to 1.18.
+Deal deal_vocabulary(int rows, int V, int k, bool short_kernel, bool dear) {
   const int tiles = (V + BM - 1) / BM;
   Deal l = {};
   l.row_blocks = (rows + BN - 1) / BN;
   const int most = NUM_CU / l.row_blocks < MAX_PROJECT_SPLITS ? NUM_CU / l.row_blocks : MAX_PROJECT_SPLITS;
   l.splits = even_splits(tiles, most);
   const int each = l.tiles_each = (tiles + l.splits - 1) / l.splits;
-  if (!short_kernel || each > SHORT_TILES) return l;
+  if (!short_kernel || each > (dear ? SHORT_TILES / 2 : SHORT_TILES)) return l;
   // Few tiles a workgroup: the kernel that can end a split in half a tile, where that leaves the busiest workgroup half a tile less,
   // and that deals at least k splits into k classes (see exchange_classes).
   const int halves = (V + BM / 2 - 1) / (BM / 2), each_half = (halves + most - 1) / most;
@@ -672,7 +678,7 @@ Deal deal_vocabulary(int rows, int V, int k, bool short_kernel) {
     l.half_tiles = halves;
     l.splits = half_splits;
   }
-  if (l.splits >= k) l.classes = k;
+  if (l.splits >= k && !(dear && l.half_tiles == 0 && (k == 1 || each > SHORT_TILES_WITHOUT))) l.classes = k;
   return l;
 }
 
@@ -734,7 +740,8 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
   //   no kernel of short calls (k = 24, 32; 16 with a bias): a norm  1 0.99-1.05, 4 0.97-1.0, 5 0.97-1.01;  none  1 1.02-1.09, 4 0.97-1.06
   const int tiles = (V + BM - 1) / BM;
   const bool has_short = short_topk_kernel(k, bias != nullptr, d % DK != 0) != nullptr;
-  const Deal first = deal_vocabulary((int)(N < CHUNK_ROWS ? N : CHUNK_ROWS), V, k, has_short);   // (whatever the scratch: the same kernel)
+  const bool dear = bias != nullptr && d % DK != 0 && k <= 4 && plan.lda >= 8 * DK;
+  const Deal first = deal_vocabulary((int)(N < CHUNK_ROWS ? N : CHUNK_ROWS), V, k, has_short, dear);   // (whatever the scratch: the same kernel)
   const int64_t stages = (int64_t)first.tiles_each * (plan.lda / DK);
   const bool worth_padding = (first.classes > 0 && (bias == nullptr || first.half_tiles > 0)) ||
                              stages >= (has_short ? (has_gamma ? 3 : 5) : (has_gamma ? 6 : 10));
@@ -849,7 +856,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     size_t off_bound;
   };
   auto pass = [&](int rows) {
-    Pass l = {deal_vocabulary(rows, V, k, short_kern != nullptr), 1, plan.off_bound};
+    Pass l = {deal_vocabulary(rows, V, k, short_kern != nullptr, dear), 1, plan.off_bound};
     const size_t at = classes_offset(plan.off_panel, need_panel ? rows + 1 : 0, plan.lda);
     if (l.classes > 0 && at + classes_bytes((size_t)rows, k) <= workspace_bytes) {
       l.bounds = k;

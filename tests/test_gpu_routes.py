@@ -49,6 +49,10 @@ def projection(N, d, V, k, with_bias, gamma, expected, zero_rows=False):
     (700, 200, 15000, 3, True, False, [STAGED]),
     (700, 264, 15000, 10, True, False, [SHORT]),   # five
     (9000, 72, 2000, 20, False, True, [STAGED, STAGED]),   # fewer splits than k: two stages
+    (300, 584, 128256, 1, True, True, [TAIL]), (300, 584, 128256, 3, True, True, [SHORT]),   # the shortest list with a bias: four tiles
+    (700, 584, 50257, 1, True, True, [SHORT]),     # half a tile less
+    (4000, 584, 60000, 3, True, True, [TAIL]), (4000, 584, 60000, 5, True, True, [SHORT]),   # fifteen
+    (4000, 200, 60000, 1, True, True, [SHORT]),    # fewer stages
     (300, 200, 10000, 24, False, True, [STAGED]),  # the longest list: four stages, then six
     (300, 328, 10000, 24, False, True, [TAIL]),
 ])

@@ -14,17 +14,18 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 
-def check(N, d, V, alphas, k, length, label):
+def check(N, d, V, alphas, k, length, label, rows=None):
     cfg = WL.LensConfig("form", L=1, T=N, d=d, V=V, k=1, n_outliers=2 if d > 100 else 0, outlier_scale=20.0)
     w = WL.make_workload(cfg, DEV, seed=41)
     v = direction(d) * length
     hidden = w.hidden.reshape(N, d)
     got = LL.ll_steer_sweep(hidden, w.gamma, w.W_U, cfg.eps, v, alphas, w.target_ids, k=k)
     torch.cuda.synchronize()
-    inputs = (WL.bf16_bits(hidden), WL.bf16_bits(w.gamma), WL.bf16_bits(w.W_U), cfg.eps, v.cpu().numpy(), alphas)
+    rows = np.arange(N) if rows is None else rows
+    inputs = (WL.bf16_bits(hidden)[rows], WL.bf16_bits(w.gamma), WL.bf16_bits(w.W_U), cfg.eps, v.cpu().numpy(), alphas)
     u = O.bf16_bits_to_f64(inputs[2]) @ inputs[4].astype(np.float64)
-    want = O.steer_sweep(*inputs, w.target_ids.cpu().numpy(), k=k or 1)
-    compare_sweep(got, want, np.arange(N), label, inputs)
+    want = O.steer_sweep(*inputs, w.target_ids.cpu().numpy()[rows], k=k or 1)
+    compare_sweep(got, want, rows, label, inputs)
     return max(abs(a) for a in alphas) * np.abs(u).max()
 
 
@@ -44,12 +45,12 @@ def test_both_forms(k, length, general, d):
     (300, 64, 66000, 9, 4),      # two row blocks, 86 splits of three tiles
     (1000, 64, 20000, 7, None),  # four row blocks
     (260, 192, 263, 9, 3),       # a last tile of seven ids
-    (70, 128, 5000, 4, None), (70, 128, 5000, 5, None),   # one tile a split: few enough for the form without tables
-    (70, 128, 5000, 3, 4), (70, 128, 5000, 4, 4), (70, 128, 5000, 1, 2),
-    (129, 72, 5000, 1, None), (300, 64, 140000, 1, 3), (300, 72, 140000, 1, None),   # one strength: the sweep's own kernel; a projection
-    (70, 128, 5000, 6, None), (70, 128, 5000, 7, None), (70, 128, 5000, 5, 4), (70, 128, 5000, 6, 4),   # either side of that number
+    (70, 128, 5000, 4, None), (70, 128, 5000, 5, None),   # one tile a split, the form without tables
+    (70, 128, 5000, 3, 4), (70, 128, 5000, 4, 4), (70, 128, 5000, 1, 2),   # the same; with tables; few rows of one strength: a projection
+    (129, 72, 5000, 1, None), (300, 64, 140000, 1, 3), (300, 72, 140000, 1, None),   # one strength: the sweep's own kernel; projections
+    (70, 128, 5000, 6, None), (70, 128, 5000, 7, None), (70, 128, 5000, 5, 4), (70, 128, 5000, 6, 4),   # without tables; with
     (10, 128, 70000, 5, None), (10, 128, 70000, 6, None), (10, 128, 70000, 4, 3), (10, 128, 70000, 5, 3),   # the same, two tiles
-    (260, 64, 140000, 3, 3), (260, 64, 140000, 4, 3),   # the same, five tiles
+    (260, 64, 140000, 3, 3), (260, 64, 140000, 4, 3),   # five tiles, without tables (test_gpu_routes.py has either side of each line)
 ])
 def test_splits(N, d, V, n_alpha, k):
     say(f"sweep splits N={N} d={d} V={V} A={n_alpha} k={k}")
@@ -205,3 +206,26 @@ def test_a_logit_that_is_no_number_leaves_the_others_listed(k):
         torch.testing.assert_close(shifted.gather(1, ids[a].long()), best, rtol=0, atol=64 * 2.0 ** -24)
         assert torch.isfinite(p[a, 1::2]).all() and torch.isfinite(ent[a, 1::2]).all()
         assert torch.isnan(ent[a, ::2]).all()
+
+
+@pytest.mark.parametrize("k", [None, 3])
+@pytest.mark.parametrize("n_alpha", [3, 9])
+@pytest.mark.parametrize("d", [64, 72])
+def test_rows_that_are_not_finite_leave_the_others_alone(d, n_alpha, k):
+    """A NaN and an infinity in two rows of a block, in both forms: the sound rows are the bits of a call that has the row of zeros there."""
+    say(f"sweep, rows that are not finite d={d} A={n_alpha} k={k}")
+    N, V = 300, 9000
+    cfg = WL.LensConfig("odd rows", L=1, T=N, d=d, V=V, k=1)
+    w = WL.make_workload(cfg, DEV, seed=41)
+    h, v = w.hidden.reshape(N, d), direction(d)
+    odd = [5, 70, 299]
+    h[odd] = 0
+    call = lambda: LL.ll_steer_sweep(h, w.gamma, w.W_U, cfg.eps, v, ALPHAS9[:n_alpha], w.target_ids, k=k)
+    want = [t.clone() for t in call()]
+    h[5, 3], h[70, 0], h[299, -1] = float("nan"), float("inf"), float("-inf")
+    sound = torch.ones(N, dtype=torch.bool, device=DEV)
+    sound[odd] = False
+    got = call()
+    for a, b in zip(got, want):
+        assert torch.equal(a[:, sound], b[:, sound])
+    assert torch.isnan(got[3][:, odd]).all()

@@ -1,5 +1,5 @@
-"""The direct-to-LDS kernel at hidden sizes that are not a multiple of 64 (more than 128 rows: fewer have a kernel of
-their own), against the CPU oracle and, where the oracle's fp64 says nothing (infinities), the register-staged kernel."""
+"""The direct-to-LDS kernels at hidden sizes that are not a multiple of 64 (more than 128 rows: fewer have a kernel of
+their own; the one of short calls in most cases, the long one where a case says so), against the CPU oracle and, where the oracle's fp64 says nothing (infinities), the register-staged kernel."""
 import numpy as np
 import pytest
 import torch
@@ -20,17 +20,17 @@ def inputs(N, d, V, k):
 
 @pytest.mark.parametrize("N,d,V,k,with_bias,gamma", [
     (129, 8, 700, 1, False, True),        # one stage, one chunk of it real
-    (300, 56, 257, 20, True, False),      # one stage, seven chunks; rows used as they are
-    (257, 72, 3000, 32, True, True),      # two stages, the second with one chunk; longest list with a bias
+    (300, 56, 257, 20, True, False),      # one stage, seven chunks, rows used as they are: register-staged
+    (257, 72, 3000, 32, True, True),      # the longest list with a bias: register-staged
     (520, 120, 5001, 12, False, True),    # two stages, seven chunks
     (777, 1608, 2050, 3, True, True),     # many stages
     (9000, 136, 600, 5, False, True),     # two row passes
     (8200, 8, 5001, 1, False, True),      # one stage, three tiles a workgroup
-    (8200, 56, 8000, 20, True, False),    # one stage, four tiles, rows only padded
-    (8200, 8, 12801, 1, False, True),     # one stage, seven tiles a workgroup (five and fewer are left to the register-staged kernel)
-    (8200, 56, 12801, 20, True, True),    # the same, seven chunks of the stage real
+    (8200, 56, 8000, 20, True, False),    # one stage, four tiles, a long list with a bias: register-staged
+    (8200, 8, 12801, 1, False, True),     # one stage, seven tiles a workgroup
+    (8200, 56, 12801, 20, True, True),    # the same, seven chunks of the stage real: the long kernel
     (1000, 72, 41000, 12, False, True),   # two stages, three tiles, the second stage with one chunk
-    (300, 328, 700, 32, False, True),     # six stages, one tile
+    (300, 328, 700, 32, False, True),     # six stages, one tile: the long kernel
     (300, 648, 700, 3, True, False),      # eleven stages, rows only padded
 ])
 def test_ragged_hidden_size(N, d, V, k, with_bias, gamma):
@@ -43,7 +43,7 @@ def test_ragged_hidden_size(N, d, V, k, with_bias, gamma):
     P.compare(got, ref, k, label="tail")
 
 
-@pytest.mark.parametrize("N,d", [(200, 200), (100, 200), (200, 392)])     # register-staged; the few-rows kernel; this kernel
+@pytest.mark.parametrize("N,d", [(200, 200), (100, 200), (200, 392)])     # the kernel of short calls, half tiles alone; the few-rows kernel
 def test_infinite_weights_stay_in_their_own_logit(N, d):
     say(f"tail, infinite weights N={N} d={d}")
     w = inputs(N, d, 1000, 6)

@@ -108,10 +108,14 @@ def _check(t, dtype, name, shape=None):
         raise ValueError(f"{name}: shape {tuple(t.shape)}, expected {tuple(shape)}")
 
 
+# torch.cuda.current_stream().cuda_stream without the object: torch's own, but not public, so only where they are there
+_raw_stream, _device = (getattr(torch._C, n, None) for n in ("_cuda_getCurrentRawStream", "_cuda_getDevice"))
+
+
 def _stream(stream):
-    if stream is not None:
-        return stream.cuda_stream
-    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())   # torch.cuda.current_stream().cuda_stream, without the object
+    if stream is None and _raw_stream is not None and _device is not None:
+        return _raw_stream(_device())
+    return (torch.cuda.current_stream() if stream is None else stream).cuda_stream
 
 
 def _rows(t, d):

@@ -281,3 +281,12 @@ def test_binding_refuses_cpu_tensors():
     h = torch.zeros(4, 64, dtype=torch.bfloat16)
     with pytest.raises(TypeError):
         LL.ll_project(h, h[0], torch.zeros(300, 64, dtype=torch.bfloat16), 1e-5, 3)
+
+
+def test_the_current_stream_without_torchs_private_functions(monkeypatch):
+    import types
+
+    import torch
+    monkeypatch.setattr(LL, "_raw_stream", None)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda: types.SimpleNamespace(cuda_stream=12345))
+    assert LL._stream(None) == 12345 and LL._stream(types.SimpleNamespace(cuda_stream=7)) == 7

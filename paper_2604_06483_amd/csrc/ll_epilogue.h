@@ -393,6 +393,21 @@ __device__ __forceinline__ void epilogue_tile(const ACC& acc, RowState<KR>& st, 
   }
 }
 
+// The k-th best of a split's list (k <= KR, KR - k < 12).
+// (Each entry goes through an empty asm statement: a plain chain of selects on k the optimiser
+// folds into an indexed access and moves the whole list to scratch memory.)
+template <int KR>
+__device__ __forceinline__ float kth_best(const RowState<KR>& st, int k) {
+  float best = st.lv[KR - 1];
+#pragma unroll
+  for (int j = KR - 2; j >= 0 && j >= KR - 12; --j) {
+    float entry = st.lv[j];
+    asm volatile("" : "+v"(entry));
+    best = (k - 1 == j) ? entry : best;
+  }
+  return best;
+}
+
 // The workgroups that sweep other parts of the vocabulary for the same rows tell each other how
 // good a logit has to be.  A split's k-th best logit so far is a lower bound on the row's k-th best
 // overall, and nothing below the largest such bound can be in the final top k; without it every
@@ -413,16 +428,7 @@ __device__ __forceinline__ void exchange_bound(RowState<KR>& st, const GemmArgs&
   asm volatile("" ::: "memory");
   const unsigned fresh = __hip_atomic_load(b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   st.shared_bound = below_bound(fresh);
-  // own bound: the k-th best of this split's list (k <= KR, KR - k < 12)
-  // (each entry goes through an empty asm statement: a plain chain of selects on k the optimiser
-  // folds into an indexed access and moves the whole list to scratch memory)
-  float mine = st.lv[KR - 1];
-#pragma unroll
-  for (int j = KR - 2; j >= 0 && j >= KR - 12; --j) {
-    float entry = st.lv[j];
-    asm volatile("" : "+v"(entry));
-    mine = (p.k - 1 == j) ? entry : mine;
-  }
+  const float mine = kth_best(st, p.k);
   // (only what is news: the split whose bound it is, or any while all logits are equal, would send it after every tile)
   const unsigned key = float_key(mine);
   if (my_row < p.rows && key > fresh && key > KEY_NEG_INF) __hip_atomic_fetch_max(b, key, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -485,16 +491,7 @@ __device__ __forceinline__ void exchange_classes(RowState<KR>& st, int v0, int m
     const int k = p->k;
     fresh = __hip_atomic_load(b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     st.shared_bound = below_bound(fresh);
-    // own bound: the k-th best of this split's list (k <= KR, KR - k < 12)
-    // (each entry goes through an empty asm statement: a plain chain of selects on k the optimiser
-    // folds into an indexed access and moves the whole list to scratch memory)
-    mine = st.lv[KR - 1];
-#pragma unroll
-    for (int j = KR - 2; j >= 0 && j >= KR - 12; --j) {
-      float entry = st.lv[j];
-      asm volatile("" : "+v"(entry));
-      mine = (k - 1 == j) ? entry : mine;
-    }
+    mine = kth_best(st, k);
   }
   if (BIAS) asm volatile("" : "+v"(warm));
   // (only what is news: the split whose bound it is, or any while all logits are equal, would send it after every tile)

@@ -19,8 +19,8 @@ namespace {
 //     e^(w - m) = e^(z - m) e^(alpha u),
 // one exponential per logit and a factor E = e^(alpha u) that is the same for every row, and the sums
 //     S = sum e E,   T1 = sum (e z) E,   T2 = sum e (alpha E u),        T = T1 + T2 = sum e^(w - m) w
-// become products of small matrices, [alphas, ids] times [ids, rows], which the matrix pipe does in fp32
-// (v_mfma_f32_16x16x4_f32: full precision, fp32 accumulation).  The accumulator layout of the contraction is the
+// become products of small matrices, [alphas, ids] times [ids, rows], in fp32
+// (v_mfma_f32_16x16x4_f32: full precision, fp32 accumulation; it runs on the vector ALU, but 1024 products an instruction).  The accumulator layout of the contraction is the
 // operand layout of that instruction: register r of a 16 x 16 tile is, for lane l, id 4 (l / 16) + r of lens row
 // l % 16, which is element (k = l / 16, n = l % 16) of the B operand, so the exponentials go in as they are, without the
 // transpose that the projection's epilogue needs.  The table comes in A operand layout, loaded a group ahead.

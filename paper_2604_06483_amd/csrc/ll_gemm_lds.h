@@ -55,6 +55,12 @@ namespace {
 // wavefront overwrites those chunks of its own 64 rows with zeros, before the barrier that hands the
 // tile to the others.  (A's padding is zero as well, but zero times an infinity of W would not be.)
 // Once per vocabulary tile: not measurable beside the padded share of the stage itself.
+//
+// SHORT (likewise): for calls of few tiles a workgroup.  A split's last tile may be half a tile wide, with stages of two slices,
+// behind which the same loads go out and the same wait and barrier stand (the vocabulary rows past the end are the last one's
+// again).  In code of its own: one body with branches around the slices that a half tile leaves out makes the register allocator
+// copy accumulators to memory.  A half tile takes 0.6 of a whole one's time (d = 1608: 49 000 cycles, and 82 000).  197 tiles over 64
+// splits are four a workgroup; 393 half tiles are seven.
 // ---------------------------------------------------------------------------------------
 constexpr int DK = 64;
 constexpr int W_SLOTS = 3, A_SLOTS = 2, SLOTS = W_SLOTS + A_SLOTS;
@@ -103,14 +109,6 @@ __device__ __forceinline__ f32x4 mfma16_from_zero(bf16x8 a, bf16x8 b) {
   return c;
 }
 
-//
-// SHORT (likewise): for calls of few tiles a workgroup.  A split's last tile may be half a tile wide, with stages of two slices,
-// behind which the same loads go out and the same wait and barrier stand (the vocabulary rows past the end are the last one's
-// again).  In code of its own: one body with branches around the slices that a half tile leaves out makes the register allocator
-// copy accumulators to memory.  A half tile takes 0.6 of a whole one's time (d = 1608: 49 000
-// cycles, and 82 000).  197 tiles over 64 splits are four a workgroup; 393
-// half tiles are seven.
-// ---------------------------------------------------------------------------------------
 template <class EPI, bool TAIL, bool SHORT = false>
 __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* const smem) {
 

@@ -532,8 +532,9 @@ FewPlan make_few_plan(const ll_shape* s, int k) {
 }
 
 struct Plan {
-  size_t off_inv_rms, off_bound, off_bias, off_stats, off_top, off_panel, total;   // total: the least that is accepted, never less for more rows
-  size_t roomy;   // with a row of zeros behind the panel and the bounds of the classes of splits (see classes_offset)
+  size_t off_inv_rms, off_bound, off_bias, off_stats, off_top, off_panel, total;   // total: what a call cannot do without
+  size_t roomy;   // with a row of zeros behind the panel and the bounds of the classes of splits (see classes_offset), never less for more rows:
+                  // the least that is accepted, but in the static buffer
   int64_t lda;
   FewPlan few;
   size_t few_total, few_off_stats, few_off_cand, few_off_count, few_off_panel;
@@ -549,9 +550,9 @@ bool shape_ok(const ll_shape* s, int k) {
 }
 
 // Where the bounds of the classes of splits stand (one a row and class, k of them, in passes of at least k splits: rows x k never
-// exceeds MAX_PARTIALS), and how much room they may want: behind what of the panel the pass fills, so that only a workspace
-// that holds nothing beyond the largest pass's panel has none for them.  Such a call goes without classes, with the same results;
-// one that reserved them always would have smaller passes in the static buffer (d = 3328, V = 128256, k = 20: 7936 rows).
+// exceeds MAX_PARTIALS), and how much room they may want: behind what of the panel the pass fills, so that only the largest pass in
+// the static buffer, where nothing is left behind its panel, has none for them.  Such a pass goes without classes, with the same results;
+// reserving them there always would make the passes smaller (d = 3328, V = 128256, k = 20: 7936 rows).
 size_t classes_offset(size_t off_panel, int64_t panel_rows, int64_t lda) {
   return align_up(off_panel + (size_t)panel_rows * (size_t)lda * sizeof(uint16_t), 256);
 }
@@ -701,7 +702,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
                  const void* W_U, const float* bias, unsigned flags, float eps, int k, const int32_t* target_ids,
                  int32_t* out_topk_ids, float* out_topk_p,
                  float* out_target_logp, float* out_entropy, hipStream_t stream, float* phase_ms,
-                 int chunk_rows = CHUNK_ROWS, bool W_in_cache = false) {
+                 int chunk_rows = CHUNK_ROWS, bool W_in_cache = false, bool static_buffer = false) {
   if (!shape_ok(shape, k)) return LL_EINVAL;
   if (shape->N == 0) {
     if (phase_ms) phase_ms[0] = phase_ms[1] = phase_ms[2] = 0.f;
@@ -715,7 +716,8 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
   const uintptr_t align_or = (uintptr_t)hidden | (uintptr_t)W_U | (uintptr_t)gamma;
   if (align_or & 15) return LL_EINVAL;
   const Plan plan = make_plan(shape, k, chunk_rows);
-  if (workspace == nullptr || workspace_bytes < plan.total || ((uintptr_t)workspace & 255)) return LL_EWORKSPACE;
+  if (workspace == nullptr || workspace_bytes < (static_buffer ? plan.total : plan.roomy) || ((uintptr_t)workspace & 255)) return LL_EWORKSPACE;
+
   unsigned char* ws = static_cast<unsigned char*>(workspace);
   float* inv_rms = reinterpret_cast<float*>(ws + plan.off_inv_rms);
   float4* stats = reinterpret_cast<float4*>(ws + plan.off_stats);
@@ -1001,7 +1003,7 @@ SweepPlan make_sweep_plan(const ll_shape* s, int n_alpha, int k = 1) {
   p.total = p.wanted = off;
   if (n_alpha == 1) {
     const Plan project = make_plan(s, k);
-    if (p.off_project + project.total > p.total) p.total = p.off_project + project.total;
+    if (p.off_project + project.roomy > p.total) p.total = p.off_project + project.roomy;
     p.wanted = p.off_project + wanted_bytes(project);
     if (p.wanted < p.total) p.wanted = p.total;
   }
@@ -1219,7 +1221,7 @@ int ll_project_static(const ll_shape* shape, const void* hidden, const void* gam
   void* ws = nullptr;
   if (const int rc = static_scratch_of_current_device(&ws); rc != LL_OK) return rc;
   return project_impl(shape, ws, (size_t)LL_STATIC_SCRATCH_BYTES, hidden, gamma, W_U, nullptr, 0u, eps, k, target_ids,
-                      out_topk_ids, out_topk_p, out_target_logp, out_entropy, static_cast<hipStream_t>(stream), nullptr, chunk);
+                      out_topk_ids, out_topk_p, out_target_logp, out_entropy, static_cast<hipStream_t>(stream), nullptr, chunk, false, true);
 }
 
 int64_t ll_project_static_pass_rows(const ll_shape* shape, int k) {

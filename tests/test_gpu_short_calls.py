@@ -75,29 +75,31 @@ def test_equal_logits_are_listed_by_id(N, d, V, k):
     torch.testing.assert_close(p, q, rtol=2e-5, atol=2e-5)
 
 
-@pytest.mark.parametrize("N,d,V,k,gamma", [(300, 128, 10000, 12, True), (1000, 200, 50257, 3, True), (8500, 64, 20000, 5, True),
-                                           (8500, 64, 20000, 5, False), (520, 64, 65000, 20, False)])
-def test_a_workspace_without_room_for_the_classes_gives_the_same_bits(N, d, V, k, gamma):
-    """The least workspace that is accepted holds neither the bounds of the classes nor the row of zeros behind the panel."""
-    say(f"short, least workspace N={N} d={d} V={V} k={k} gamma={gamma}")
+@pytest.mark.parametrize("N,d,V,k,static", [
+    (1422, 21376, 3000, 10, SHORT),                         # half tiles, without classes
+    (1700, 16320, 18000, 20, LONG),                         # whole ones
+    (1700, 16264, 18000, 20, "ll_lens_gemm_dma_tail_kernel"),
+])
+def test_a_pass_that_fills_the_static_buffer_gives_the_same_bits(N, d, V, k, static):
+    """Its panel ends where the buffer does: neither the bounds of the classes nor the row of zeros behind it have room."""
+    say(f"short, a pass that fills the static buffer N={N} d={d} V={V} k={k}")
     w = inputs(N, d, V, k)
-    g = w.gamma if gamma else None
-    want = LL.ll_project(w.hidden, g, w.W_U, w.cfg.eps, k, w.target_ids)
-    full = LL.ll_workspace_bytes(N, d, V, k)
-    ws = torch.empty((full,), dtype=torch.uint8, device=DEV)
-    lo, hi = 0, full // 256                                         # refused, accepted
-    while hi - lo > 1:
-        mid = (lo + hi) // 2
-        try:
-            LL.ll_project(w.hidden, g, w.W_U, w.cfg.eps, k, w.target_ids, workspace=ws[:256 * mid])
-            hi = mid
-        except LL.LLError as e:
-            assert e.code == LL.LL_EWORKSPACE
-            lo = mid
-    ws.fill_(0xA5)                                                  # stale contents of another call
-    got = LL.ll_project(w.hidden, g, w.W_U, w.cfg.eps, k, w.target_ids, workspace=ws[:256 * hi])
-    assert full - 256 * hi >= (4 * min(N, 3000) * k if gamma else 0) and (ws[256 * hi:] == 0xA5).all()
-    for a, b in zip(got, want):
+    workspace = lambda: LL.ll_project(w.hidden, w.gamma, w.W_U, w.cfg.eps, k, w.target_ids)
+    buffer = lambda: LL.ll_project_static(w.hidden, w.gamma, w.W_U, w.cfg.eps, k, w.target_ids)
+    runs(workspace, SHORT)
+    runs(buffer, static)
+    for a, b in zip(workspace(), buffer()):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("N,gamma", [(300, True), (9000, True), (9000, False)])
+def test_stale_contents_of_the_workspace(N, gamma):
+    say(f"short, stale workspace N={N} gamma={gamma}")
+    d, V, k = 64, 4000, 12
+    w = inputs(N, d, V, k)
+    ws = torch.full((LL.ll_workspace_bytes(N, d, V, k),), 0xA5, dtype=torch.uint8, device=DEV)
+    call = lambda **kw: LL.ll_project(w.hidden, w.gamma if gamma else None, w.W_U, w.cfg.eps, k, w.target_ids, **kw)
+    for a, b in zip(call(workspace=ws), call()):
         assert torch.equal(a, b)
 
 

@@ -637,7 +637,8 @@ int allow_dynamic_lds(const void* kern, size_t lds) {
 // Whole calls, us, long | short (d, V, rows, k: tiles a workgroup).  With classes: 256, 4096, 1500, 10 (1, in halves): 50 | 30; 1608,
 // 50257, 777, 3 with a bias (4): 197 | 187; 1024, 50257, 1500, 20 (5): 229 | 189; 4096, 128256, 957, 10 (8): 847 | 830; 1024,
 // 128256, 4000, 10 (32): 949 | 920; 5120, 151936, 4160, 3 with a bias (40): no difference.  Without: 256, 4096, 4000, 20 (1): 78 | 77;
-// 1608, 50257, 4000, 20 (13): 653 | 648; 256, 50257, 4000, 20 (13): 275 | 281; 256, 128256, 4000, 20 (32): 537 | 555.
+// 1608, 50257, 4000, 20 (13): 653 | 648; 256, 50257, 4000, 20 (13): 275 | 281; 256, 128256, 4000, 20 (32): 537 | 555; 4000 rows,
+// k = 20 at d = 1024 with 3, 4 and 13 tiles: 155 | 150, 185 | 180, 460 | 460, and at d = 64 with 13 and 17: 226 | 230, 271 | 275.
 constexpr int SHORT_TILES = 32, SHORT_TILES_WITHOUT = 8;
 
 // The fewest vocabulary splits that give no workgroup more tiles than `most` splits would: the call takes as long as its
@@ -659,10 +660,10 @@ struct Deal {
 
 // dear: the kernel of short calls costs more a tile than it saves in insertions, few in the shortest list (its bias comes late where
 // the last K stage is ragged; of eight stages and more: in shorter ones the insertions weigh more).  Taken up to SHORT_TILES_WITHOUT
-// tiles, for half a tile less up to twice those, for an arg max only for that.  Whole calls, long over short (N x V: tiles), k = 1 and 3 with a bias, d = 968: 300 x 128256
-// (4) 0.97, 1.04; 957 x 128256 (8) 0.96, 1.00; 2500 x 100000 (16) 0.95, 0.99; 4000 x 128256 (32) 0.96, 0.97; d = 1608: 300 x 128256 0.97, 1.00; 957
-// x 128256 0.99, 0.99; 1500 x 100000 (10, a half tile less) 1.01, 1.03;
-// 4000 x 128256 0.98, 1.00; d = 200: 4000 x 128256 1.04, 1.05.  k = 10: 1.03 to 1.18.
+// tiles, for half a tile less up to twice those, for an arg max only for that.  Whole calls, long over short (N x V: tiles), k = 1 and
+// 3 with a bias, d = 968: 300 x 128256 (4) 0.97, 1.04; 957 x 128256 (8) 0.96, 1.00; 2500 x 100000 (16) 0.95, 0.99; 4000 x 128256 (32)
+// 0.96, 0.97; d = 1608: 300 x 128256 0.97, 1.00; 957 x 128256 0.99, 0.99; 1500 x 100000 (10, a half tile less) 1.01, 1.03; 4000 x
+// 128256 0.98, 1.00; d = 200: 4000 x 128256 1.04, 1.05.  k = 10: 1.03 to 1.18.
 Deal deal_vocabulary(int rows, int V, int k, bool short_kernel, bool dear) {
   const int tiles = (V + BM - 1) / BM;
   Deal l = {};

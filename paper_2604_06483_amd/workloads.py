@@ -2,7 +2,7 @@
 
 This module draws random tensors and picks row indices; it holds none of the
 method's arithmetic (no normalisation, projection, softmax or steering maths)
-so that both the HIP library's callers and the CPU checker can take their
+so that both the HIP library's callers and the CPU oracle can take their
 inputs from it without sharing anything else.
 
 The shapes stand in for the paper's runs (Sec. 4: LLaMA-3.1 8B/70B and Qwen3

@@ -9,7 +9,7 @@ namespace {
 // ---------------------------------------------------------------------------------------
 // With at most FEW_ROWS lens rows the contraction needs a fraction of the matrix pipe and the call
 // is one read of W_U (2 V d bytes).  What counts is the load stream:
-//   * W goes global -> registers, 8 rows x 128 B per instruction (whole cache lines), with the
+//   * W goes global -> registers, 8 rows x 128 B per instruction (whole cache lines), for a large W_U with the
 //     non-temporal hint (every byte is used once, by one wavefront; the hint keeps the A panel in
 //     L2), two K = 64 stages ahead;
 //   * a wavefront owns its vocabulary rows outright (MU groups of 16), so nothing is waited for but
@@ -30,7 +30,7 @@ namespace {
 // 6.3 TB/s, against 473 us on the 256-row tiles of the direct-to-LDS kernel; 151936 x 2560, 37 rows: 129 us
 // = 6.0 TB/s against 212 us.  A loop that only loads W this way reaches 6.6 TB/s (without the
 // non-temporal hint 5.9; W_U of 2.1 GB); loads of 16 rows x 64 B, which need no exchange of halves, 6.1.
-// STREAM: with the hint (the caller chooses by whether W_U's rows are whole cache lines).
+// STREAM: with the hint (the caller chooses by W_U's size and by whether its rows are whole cache lines).
 // ---------------------------------------------------------------------------------------
 constexpr int FEW_WAVES = 8;
 constexpr int FEW_THREADS = 64 * FEW_WAVES;

@@ -703,7 +703,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
                  const void* W_U, const float* bias, unsigned flags, float eps, int k, const int32_t* target_ids,
                  int32_t* out_topk_ids, float* out_topk_p,
                  float* out_target_logp, float* out_entropy, hipStream_t stream, float* phase_ms,
-                 int chunk_rows = CHUNK_ROWS, bool W_in_cache = false, bool static_buffer = false) {
+                 int chunk_rows = CHUNK_ROWS, bool static_buffer = false, int W_in_cache = -1) {   // W_in_cache: -1 by its size
   if (!shape_ok(shape, k)) return LL_EINVAL;
   if (shape->N == 0) {
     if (phase_ms) phase_ms[0] = phase_ms[1] = phase_ms[2] = 0.f;
@@ -831,17 +831,22 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     a.units = few.units;
     LL_CHECK_F(mark());
     // Whether the loads of W_U go past the caches: where its rows are whole lines of 128 bytes (others share lines between two stages,
-    // and are faster through the caches whatever the size).  Through the caches a W_U that the Infinity Cache can keep is read faster by
-    // the next call on it, but by a call after which, or before which, something else has run, slower, and a lens behind a decoding step
-    // always is that one.  Whole calls, k = 10, past the caches | through them, us, repeated on one W_U, and on W_U that are not in
-    // the cache (d, MB, rows):
-    //   1024, 60, 81: 37.5 | 36.0, 36.7 | 37.4     2048, 120, 16: 38.8 | 32.0, 37.0 | 39.8     4096, 60, 81: 68.8 | 65.7, 69.5 | 69.9
-    //   4096, 120, 81: 70.7 | 66.5, 70.2 | 71.5    8192, 120, 16: 82.4 | 78.0, 82.2 | 83.5     4096, 240, 16: 63.3 | 50.4, 59.0 | 64.5
+    // and are faster through the caches whatever the size) and it is more than a third of the Infinity Cache.  Up to there it stays
+    // in that cache from one call to the next beside twice its bytes of other weights, and the next call finds it there; a larger one read
+    // that way only drives out what those would have found.  Whole calls, past the caches | through them, us: repeated on one
+    // W_U, behind a read of twice its bytes (the read included), and on W_U that are not in the cache (d, MB, rows; k = 10, at
+    // d = 576 16):
+    //   2048, 30, 37: 31.6 | 31.2, 54.2 | 51.8, 33.6 | 34.4     1024, 34, 37: 24.1 | 23.8, 47.3 | 45.5, 25.0 | 25.6
+    //   2560, 42, 37: 38.2 | 35.6, 63.2 | 59.2, 39.4 | 40.7     1024, 66, 37: 27.9 | 26.5, 58.9 | 57.4, 27.6 | 28.7
+    //   4096, 66, 37: 51.7 | 47.6, 83.8 | 78.6, 52.5 | 53.2      768, 77, 64: 35.0 | 32.8, 69.1 | 67.5, 34.6 | 36.1
+    //    576, 92, 36: 33.0 | 33.5, 72.8 | 83.1, 33.2 | 35.3     2048, 123, 37: 42.4 | 34.4, 92.2 | 118, 41.0 | 43.8
+    //   4096, 123, 37: 55.5 | 48.3, 106 | 129, 54.6 | 56.4      and repeated, not in the cache: 4096, 240, 16: 63.3 | 50.4, 59.0 | 64.5
     //   4096, 400, 16: 99.9 | 109, 93.8 | 101      2560, 778, 37: 144 | 159, 139 | 154         8192, 1050, 81: 194 | 213, 204 | 226
     // and of rows that are not whole lines:
     //   1608, 60, 16: 32.3 | 26.3, 35.5 | 34.2     1608, 400, 81: 138 | 113, 137 | 112        4104, 1050, 16: 298 | 224, 300 | 226
     // (The scope bits of the loads, sc0 and sc1, make no difference either way.)
-    const bool stream_W = ((uintptr_t)W_U | (uintptr_t)d * 2) % 128 == 0 && !W_in_cache;
+    const bool kept = W_in_cache < 0 ? (int64_t)V * d * 2 <= INFINITY_CACHE_BYTES / 3 : W_in_cache > 0;
+    const bool stream_W = ((uintptr_t)W_U | (uintptr_t)d * 2) % 128 == 0 && !kept;
     hipLaunchKernelGGL(stream_W ? few_kernel<true>(few.nj, few.mu) : few_kernel<false>(few.nj, few.mu), dim3(few.splits), dim3(FEW_THREADS), 0, stream, a);
     LL_CHECK_F(hipGetLastError());
     LL_CHECK_F(mark());
@@ -1081,7 +1086,7 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
   const bool W_in_cache = d >= 512 && (int64_t)V * d * 2 > L2_BYTES && (int64_t)V * d * 2 <= INFINITY_CACHE_BYTES / 2;
   if (as_projection)
     return project_impl(shape, ws + plan.off_project, workspace_bytes - plan.off_project, hidden, gamma, W_U, u, 0u, eps, k, target_ids, out_ids,
-                        out_p, out_logp, out_entropy, stream, nullptr, CHUNK_ROWS, W_in_cache);
+                        out_p, out_logp, out_entropy, stream, nullptr, CHUNK_ROWS, false, W_in_cache ? 1 : 0);
   // Few alphas: the general form alone, without the tables and the launch that fills them.  Its cost grows with every alpha, the
   // factored one's hardly does: the line moves up where a split has few tiles and there are no lists, and where the contraction is
   // short (what the factored form adds to it is the same, and the smaller share of the call).  Whole calls, general | factored, us
@@ -1222,7 +1227,7 @@ int ll_project_static(const ll_shape* shape, const void* hidden, const void* gam
   void* ws = nullptr;
   if (const int rc = static_scratch_of_current_device(&ws); rc != LL_OK) return rc;
   return project_impl(shape, ws, (size_t)LL_STATIC_SCRATCH_BYTES, hidden, gamma, W_U, nullptr, 0u, eps, k, target_ids,
-                      out_topk_ids, out_topk_p, out_target_logp, out_entropy, static_cast<hipStream_t>(stream), nullptr, chunk, false, true);
+                      out_topk_ids, out_topk_p, out_target_logp, out_entropy, static_cast<hipStream_t>(stream), nullptr, chunk, true);
 }
 
 int64_t ll_project_static_pass_rows(const ll_shape* shape, int k) {

@@ -178,12 +178,14 @@ def test_full_lists_cost_no_more_than_the_256_row_kernel(rows, V, k, what):
 
 
 @pytest.mark.parametrize("d,V,shift,past_the_caches", [
-    (2048, 30000, 0, True),    # 123 MB, which the Infinity Cache could hold: a call behind other work finds none of it there
-    (256, 5000, 0, True),
-    (2048, 30000, 8, False),   # the same rows, from 16 bytes into a line on
-    (1608, 20000, 0, False),   # rows that are not whole lines
+    (2048, 30000, 0, True),    # 123 MB, which the Infinity Cache could hold, but not beside twice its bytes
+    (2048, 21846, 0, True),    # 3 KB more than a third of the Infinity Cache
+    (2048, 21845, 0, False),
+    (256, 5000, 0, False),
+    (2048, 30000, 8, False),   # the first's rows, from 16 bytes into a line on
+    (1608, 30000, 0, False),   # rows that are not whole lines
 ])
-def test_how_w_is_read_depends_on_its_lines_alone(d, V, shift, past_the_caches):
+def test_how_w_is_read_depends_on_its_lines_and_size(d, V, shift, past_the_caches):
     say(f"few rows, loads of W_U d={d} V={V} shift={shift}")
     w = inputs(16, d, V)
     W = torch.empty((V * d + shift,), dtype=torch.bfloat16, device=DEV)[shift:].view(V, d)

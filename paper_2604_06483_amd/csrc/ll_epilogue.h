@@ -43,6 +43,7 @@ struct GemmArgs {
                             // the best logits of the row that each class of splits has seen (sweep: [k, n_alpha, rows])
   int classes;              // short calls: 0, or k, the classes that the splits are dealt into (see exchange_classes)
   int half_tiles;           // short calls: 0, or V in half tiles where the splits are cut between those
+  int group_rows;           // row blocks that an XCD's workgroups share W_U's tiles between (see place_of)
 };
 
 using GemmKernel = void (*)(const GemmArgs);
@@ -99,6 +100,25 @@ typedef const float __attribute__((address_space(4)))* const_f32_ptr;   // read 
 __device__ __forceinline__ int xcd_logical_block() {
   const int per_xcd = gridDim.x / NUM_XCD;
   return (blockIdx.x % NUM_XCD) * per_xcd + blockIdx.x / NUM_XCD;
+}
+
+// The row block and the vocabulary split of a workgroup.  The 32 workgroups of an XCD are to be a rectangle that is near a square, R row
+// blocks by 32 / R splits: per K stage R tiles of A and 32 / R of W come into its L2 from the fabric, 33 of 32 KB where they are of
+// one row block (6.9 TB/s at 957 rows, d = 4096) and 12 at 4 by 8.  So the row blocks go in groups of four (up to seven: one group), of a
+// group split after split, of a split block after block.  With at most eight splits an XCD has its four row blocks anyway.
+// Whole calls, one row block after the other | so: 957 rows, d = 4096, V = 128256 785 | 738 us; 777 rows, d = 1608, V = 50257 181 | 175; sweeps
+// of nine strengths, 1500 rows, d = 4096 1463 | 1418, lists, 500 rows, d = 2560 556 | 546; 4160 rows, d = 5120 4436 | 4415.
+struct Place {
+  int row_block, split;
+};
+inline int group_rows(int row_blocks, int splits) {   // row blocks of a group
+  const int groups = splits <= NUM_XCD ? row_blocks : row_blocks <= 7 ? 1 : (row_blocks + 3) / 4;
+  return (row_blocks + groups - 1) / groups;
+}
+__device__ __forceinline__ Place place_of(unsigned logical, const GemmArgs& p) {
+  const unsigned rows = p.group_rows, of_group = rows * p.splits, g = logical / of_group, first = g * rows;
+  const unsigned size = min(rows, p.row_blocks - first), at = logical - g * of_group, split = at / size;
+  return {(int)(first + at - split * size), (int)split};
 }
 
 // ---------------------------------------------------------------------------------------

@@ -114,8 +114,8 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
 
   const int logical = xcd_logical_block();
   if (__builtin_expect(logical >= p.row_blocks * p.splits || EPI::skip(p), 0)) return;
-  const int split = logical % p.splits;
-  const int rb = logical / p.splits;
+  const Place at = place_of(logical, p);
+  const int split = at.split, rb = at.row_block;
   // the split's tiles; SHORT: counted from its first vocabulary row, row0, up to row_end
   int tile0 = (int)((int64_t)split * p.tiles / p.splits);
   int tile1 = (int)((int64_t)(split + 1) * p.tiles / p.splits);

@@ -935,6 +935,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     a.splits = splits;
     a.tiles = tiles;
     a.row_blocks = row_blocks;
+    a.group_rows = group_rows(row_blocks, splits);
     a.bound = bound;
     a.classes = l.classes;
     a.half_tiles = l.half_tiles;
@@ -1148,6 +1149,7 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     a.tiles = tiles;
     a.row_blocks = (rows + BN - 1) / BN;
     a.splits = sweep_splits(rows, tiles);
+    a.group_rows = group_rows(a.row_blocks, a.splits);
     a.u = u;
     a.eu = eu;
     a.shift_max = shift_max;

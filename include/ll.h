@@ -249,14 +249,14 @@ int ll_capture_append(const ll_capture_shape* shape, void* store, const void* sl
  *   out_top1_p   [n_alpha, N] fp32    its full-softmax probability
  *   out_target_logp [n_alpha, N] fp32 NaN where the target id is outside [0, V)
  *   out_entropy  [n_alpha, N] fp32    nats
- * Requirements beyond ll_project's: d at most 40960 (the direction v is held in LDS while
- * u = W_U v is formed; LL_EINVAL beyond).  Workspace: ll_steer_sweep_workspace_bytes(shape,
+ * Requirements beyond ll_project's: d at most 40960 (the direction v is held in LDS where
+ * u = W_U v is formed by itself; LL_EINVAL beyond).  Workspace: ll_steer_sweep_workspace_bytes(shape,
  * n_alpha).  Same error, ownership, stream and N == 0 conventions as ll_project.
  *
  * ll_steer_sweep_topk: the same with the k most likely tokens per alpha and row instead of one
  * (1 <= k <= LL_SWEEP_KMAX; the paper's figures list k = 3), sorted as in ll_project:
  *   out_topk_ids [n_alpha, N, k] int32,  out_topk_p [n_alpha, N, k] fp32 (full-softmax probabilities)
- * With k == 1 it is ll_steer_sweep.  Any number of alphas takes one pass over W_U besides the one
+ * With k == 1 it is ll_steer_sweep.  Any number of alphas takes one pass over W_U, or one besides the one
  * that forms u (against nine for nine ll_steer_inject + ll_project pairs).  Workspace:
  * ll_steer_sweep_topk_workspace_bytes(shape, n_alpha, k).
  */

@@ -33,6 +33,12 @@ struct GemmArgs {
   const float* shift_min;   // [tiles * BM / 16, 16]: per alpha the least
   const float* shift_tile;  // [tiles, 16]: per alpha the largest of a tile, with the margin
   const int* sweep_general; // nonzero: some |alpha u| is too large for the factored form; nullptr: the general form in any case
+  float* u_out;             // where the kernel forms u itself (see SweepEpilogue): u, [tiles * BM]
+  int* exceeded;            // likewise: set once some |alpha u| turns out too large for the factored form
+  const float* sampled;     // likewise: the largest |alpha u| of some vocabulary rows, n_sampled of them; nullptr: the general form in any case
+  const float* block_max;   // and where that leaves open whether some are too large: the largest |u| of all, in n_block_max parts
+  int n_sampled, n_block_max;
+  float alpha_most;         // largest |alpha|
   float4* sweep_stats;      // [rows, n_alpha, splits]      (reference, S, T)
   float* sweep_ztgt;        // [rows, splits]               logit of the target id at alpha = 0
   uint2* sweep_top;         // [rows, n_alpha, splits, KS]  (logit bits, id), sorted
@@ -56,6 +62,8 @@ GemmKernel tail_sweep_kernel(bool lists);
 GemmKernel short_topk_kernel(int k, bool bias, bool ragged);
 // The general form of the steering sweep, for any d (see ll_epilogue_sweep.h).
 GemmKernel general_sweep_kernel(bool lists);
+// Both forms where the kernel forms u itself, any d (ll_project_sweep.hip).
+GemmKernel whole_sweep_kernel(bool lists, bool general, bool ragged);
 
 }  // namespace ll
 
@@ -594,7 +602,8 @@ __device__ __forceinline__ void epilogue_store(const GemmArgs& p, const RowState
 template <int KR, bool BIAS = false, bool SHORT = false>
 struct TopKEpilogue {   // a5..a7: softmax statistics, k best logits, target logit (BIAS: Eq. 1's b added to every logit first)
   using State = RowState<KR>;
-  static constexpr bool RELOAD_FRAGMENTS = false;
+  static constexpr bool RELOAD_FRAGMENTS = false, OWN_U = false;
+  static constexpr int ROWS = BN;
   static __device__ __forceinline__ bool skip(const GemmArgs&) { return false; }
   static __device__ __forceinline__ void init(State& st, const GemmArgs& p, int my_row, int split) {
     st.init(my_row < p.rows);

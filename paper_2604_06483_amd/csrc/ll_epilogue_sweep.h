@@ -45,10 +45,20 @@ namespace {
 // V = 128256, nine alphas: first tile 89 900 | 74 600, the others 62 000 | 50 100 falling to 44 000 (sums 33 800, scan 3500; the
 // contraction 145 000); lists of three, 500 rows, d = 2560, V = 151936: 184 700 | 96 400, then 103 000 falling to 78 900 | 69 700
 // falling to 55 600 (contraction 100 000).  Whole calls: 1505 | 1444 us and 647 | 557 us.
+//
+// Where u comes from.  A pass of its own over W_U (ll_unembed_direction_kernel, and a kernel that makes the tables from u) costs what reading
+// W_U costs, a tenth to a fifth of the calls above: 176 and 115 us.  The contraction reads the same W_U, and its blocks mostly have rows to
+// spare: with OWN_U three rows of every block are v in three bf16 parts (ll_sweep_panel_kernel), and behind a tile's K loop
+// the last wavefront's accumulators hold the tile's u.  The four wavefronts then make the tables in LDS, in the part of the ring that is free
+// between two tiles.  Which form runs is not known before u is: a sample of W_U's rows says so where it is clear, where it is not
+// the direction kernel does look at all of W_U, and should a shift past SWEEP_SHIFT still turn up, `exceeded` stops the
+// factored kernel at its workgroups' next tiles and the general one, launched behind it, runs.  Costs 2.6 us a tile (general form 0.4).
+// Whole calls, u before | within: 1386 | 1262 us and 549 | 449 us.
 // ---------------------------------------------------------------------------------------
 constexpr int SWEEP_MAX = LL_SWEEP_MAX;
 constexpr int SWEEP_KS = LL_SWEEP_KMAX;
 constexpr float SWEEP_SHIFT = 20.0f;
+constexpr float SWEEP_SHIFT_SURE = 0.7f * SWEEP_SHIFT;   // while a sample's largest shift is no more, the largest of all is taken to be below SWEEP_SHIFT
 constexpr float SWEEP_MARGIN = 2.0f * SWEEP_SHIFT * 0x1p-22f;   // more than the rounding of a shift up to SWEEP_SHIFT, and of a limit's own
 constexpr int SWEEP_GROUP = 16;
 constexpr unsigned SWEEP_NO_ID = 0xffffu;         // list entry that stands for "below the row's shared bound"
@@ -60,6 +70,7 @@ constexpr int SWEEP_MAX_TILES = 255;              // tiles per split: ids relati
 constexpr int SWEEP_ROWS = 16;
 constexpr int SWEEP_FEW = 4;          // code for all alphas is branched over past these
 constexpr int SWEEP_SPLIT_ROWS = 8;   // most alphas with both factors in one operand
+constexpr int SWEEP_PARTS = 3, SWEEP_OWN_ROWS = BN - SWEEP_PARTS;   // bf16 rows that are v, and the lens rows of a block that has them
 
 // u of id g0 + l % 16 (the general form reads no more of the tables).
 __device__ __forceinline__ float sweep_load_u(int g0, const GemmArgs& p) { return p.u[g0 + (threadIdx.x & 15)]; }
@@ -102,7 +113,7 @@ struct SweepState {
   // zero, more[j][0] and more[j][1] are the lane's share (ids 4 (l / 16) + r) of its S and T, the plain sums.
   float ref[4];
   f32x4 st[4], more[4];
-  float next_shift;                          // of the tile that comes next, largest alpha u of alpha number l % 16
+  float next_shift;                          // of the tile that comes next (OWN_U: of this one), largest alpha u of alpha number l % 16
   // General form, of the lane's own row.
   float gs[SWEEP_MAX], gt[SWEEP_MAX];
   // Of the lane's own row (64 w + l):
@@ -110,6 +121,7 @@ struct SweepState {
   unsigned li[SWEEP_MAX][IDS];
   float z_tgt;
   int tgt, id0, split;                       // id0: first id of the split
+  int given_up;                              // OWN_U: what `exceeded` was at the last tile's end
 };
 
 // Register j of lane block g <-> register g of lane block j (see load_group).
@@ -375,15 +387,30 @@ __device__ __forceinline__ void sweep_fold(f32x4& sum, f32x4& pending) {
   asm volatile("" : "+v"(sum));
 }
 
+// What a kernel that forms u itself keeps in LDS during a tile's epilogue: the upper half of each wavefront's 8 KB of the W slot whose
+// stage is done (halves SWEEP_CHUNK apart, from SWEEP_HALF on).  First the three parts of the tile's u, in halves 0, 1 and 2, and in half 3 a word
+// for all wavefronts; then the tables of four groups in each half.
+constexpr int SWEEP_CHUNK = 64 * 128, SWEEP_HALF = 4096, SWEEP_TABLE = SWEEP_ROWS * SWEEP_GROUP * 4;
+static_assert(4 * SWEEP_TABLE <= SWEEP_HALF && BM * 4 <= SWEEP_HALF, "a half");
+
+// alphas[at] (0 past the last).
+__device__ __forceinline__ float sweep_lane_alpha(int at) {
+  const_f32_ptr alphas = sweep_alphas();
+  float alpha = 0.f;
+#pragma unroll
+  for (int a = 0; a < SWEEP_MAX; ++a) alpha = at == a ? alphas[a] : alpha;
+  return alpha;
+}
+
 // Pass 2.  Row block by row block: its eight products, then the exponentials that the next block's need, this block's plain sums
 // and the last block's additions.  fp32 products run on the vector ALU: eight of them take 258 cycles alone, 485 with four
 // vector instructions behind each, 449 with eight behind each pair, and 32 such instructions 200 (one wavefront, a bare loop).  So
 // nothing is to be had from interleaving them, and what counts is their number: with S in the upper eight rows of the result and
 // T in the lower ones, from the operand [E; alpha E u] times e and [0; E] times e z, a group takes 32.
-template <int KS>
-__device__ __forceinline__ void sweep_sums(f32x4 (&acc)[16][4], SweepState<KS, false>& st, int v0, const GemmArgs& p) {
+template <int KS, bool OWN_U>
+__device__ __forceinline__ void sweep_sums(f32x4 (&acc)[16][4], SweepState<KS, false>& st, int v0, const GemmArgs& p, const unsigned char* lds) {
   const int lane = fresh_lane();
-  const bool nine = fresh_scalar(p.n_alpha) > SWEEP_SPLIT_ROWS, second = nine && p.zero_alpha < 0, plain = nine && !second;
+  const bool nine = fresh_scalar(p.n_alpha) > SWEEP_SPLIT_ROWS, second = !OWN_U && nine && p.zero_alpha < 0, plain = nine && !second;
   const unsigned at = 4 * (lane & 15) + (lane >> 4);   // (row l % 16 of a group's table, ids 4 (l / 16) ..)
   const float4* tab = reinterpret_cast<const float4*>(p.eu + (int64_t)v0 * SWEEP_ROWS);
   const float4* const tab_end = tab + 15 * (SWEEP_GROUP * SWEEP_ROWS / 4);
@@ -391,7 +418,15 @@ __device__ __forceinline__ void sweep_sums(f32x4 (&acc)[16][4], SweepState<KS, f
   float nref[4];
 #pragma unroll
   for (int j = 0; j < 4; ++j) nref[j] = -st.ref[j] * LOG2E;
-  float4 next1 = tab[at], next2 = tab[at + to_second];
+  // OWN_U: the table is in LDS, four groups in each wavefront's half
+  auto own = [&](int i) { return *reinterpret_cast<const float4*>(lds + SWEEP_HALF + SWEEP_CHUNK * (i >> 2) + SWEEP_TABLE * (i & 3) + 16 * at); };
+  float4 next1, next2;
+  if (OWN_U) {
+    next1 = next2 = own(0);
+  } else {
+    next1 = tab[at];
+    next2 = tab[at + to_second];
+  }
   float y[4][4], e[2][4], ez[2][4];
   f32x4 pend[2], pend_more[2];
   pend[1] = pend_more[1] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -404,9 +439,13 @@ __device__ __forceinline__ void sweep_sums(f32x4 (&acc)[16][4], SweepState<KS, f
 #pragma unroll 1
   for (int i = 0; i < 16; ++i) {
     float a1[4] = {next1.x, next1.y, next1.z, next1.w}, a2[4] = {next2.x, next2.y, next2.z, next2.w};
-    if (tab != tab_end) tab += SWEEP_GROUP * SWEEP_ROWS / 4;
-    next1 = tab[at];
-    next2 = tab[at + to_second];
+    if (OWN_U) {
+      next1 = next2 = own(min(i + 1, 15));
+    } else {
+      if (tab != tab_end) tab += SWEEP_GROUP * SWEEP_ROWS / 4;
+      next1 = tab[at];
+      next2 = tab[at + to_second];
+    }
     if (!second) {   // [0; E] from [E; alpha E u]
 #pragma unroll
       for (int r = 0; r < 4; ++r) a2[r] = __uint_as_float(dpp<0x118>(__float_as_uint(a1[r])));   // row_shr:8, zeros moved in
@@ -451,6 +490,12 @@ __device__ __forceinline__ void sweep_sums(f32x4 (&acc)[16][4], SweepState<KS, f
   if (second) sweep_fold(st.more[3], pend_more[1]);
 }
 
+// Over the lane's block of 16.
+__device__ __forceinline__ float largest_of_16(float x) {
+  const auto larger = [](uint32_t a, uint32_t b) { return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b))); };
+  return __uint_as_float(with_lane_xor<1>(with_lane_xor<2>(with_lane_xor<4>(with_lane_xor<8>(__float_as_uint(x), larger), larger), larger), larger));
+}
+
 // A tile's 256 entries in four registers, entry 64 q + l in lane l: the register that holds group i's, and of these the lane's l % 16 th.
 __device__ __forceinline__ float sweep_group_register(const float (&x)[4], int i) {
   const float lo = keep_select((i & 4) != 0, x[1], x[0]), hi = keep_select((i & 4) != 0, x[3], x[2]);
@@ -476,6 +521,9 @@ __device__ __forceinline__ GemmArgs sweep_args() {
   p.V = args->V;
   p.k = args->k;
   p.tiles = args->tiles;
+  p.u_out = args->u_out;
+  p.exceeded = args->exceeded;
+  p.alpha_most = args->alpha_most;
   p.n_alpha = args->n_alpha;
   p.zero_alpha = args->zero_alpha;
   return p;
@@ -602,14 +650,9 @@ __device__ __forceinline__ void sweep_take_bounds(SweepState<KS, false>& st, con
 // its least logit with its largest shift, which is the better one where a row's logits are nearly equal).  The second holds only while
 // every logit of the group is a number: the id with the largest shift might be the one that has none.
 template <int KS>
-__device__ __forceinline__ void sweep_announce(f32x4 (&acc)[16][4], SweepState<KS, false>& st, int v0, const GemmArgs& p, int my_row) {
-  float best[SWEEP_MAX], least4[4], most4[4];
-  const int lane = fresh_lane();
-#pragma unroll
-  for (int q = 0; q < 4; ++q) {
-    least4[q] = p.shift_min[v0 + 64 * q + lane];
-    most4[q] = p.shift_max[v0 + 64 * q + lane];
-  }
+__device__ __forceinline__ void sweep_announce(f32x4 (&acc)[16][4], SweepState<KS, false>& st, const float (&least4)[4], const float (&most4)[4],
+                                               const GemmArgs& p, int my_row) {
+  float best[SWEEP_MAX];
 #pragma unroll
   for (int a = 0; a < SWEEP_MAX; ++a) best[a] = -INFINITY;
 #pragma unroll 1
@@ -643,13 +686,106 @@ __device__ __forceinline__ void sweep_announce(f32x4 (&acc)[16][4], SweepState<K
   asm volatile("" ::: "memory");
 }
 
+// u of the tile, entry 64 q + l in lane l, from the three rows of the direction in the last wavefront's accumulators.  v is the
+// sum of three bf16 rows to the last bit (but for what is below the smallest normal number), so u = W v1 + W v2 + W v3 has the exact products that fp32 ones of W and v round.  An infinity of W
+// against a zero of v2 or v3 would be no number: where the first part is not finite it is u.  FACTORED: whether the factored form has to be given up,
+// in this tile or, for all that is known, elsewhere.
+template <bool FACTORED>
+__device__ __forceinline__ bool sweep_own_u(f32x4 (&acc)[16][4], int v0, const GemmArgs& p, int my_row, int given_up, unsigned char* lds,
+                                            float (&u4)[4]) {
+  const int lane = fresh_lane(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const unsigned char* const in = lds + SWEEP_HALF;
+  if (wave == 3) {
+    const int part = (lane & 15) - (16 - SWEEP_PARTS);
+    if (part >= 0) {
+      unsigned char* const out = lds + SWEEP_HALF + SWEEP_CHUNK * part + 16 * (lane >> 4);
+      each16([&](auto g_) {
+        constexpr int g = decltype(g_)::value;
+        *reinterpret_cast<float4*>(out + 4 * SWEEP_GROUP * g) =
+            make_float4(acc_read(acc[g][3][0]), acc_read(acc[g][3][1]), acc_read(acc[g][3][2]), acc_read(acc[g][3][3]));
+      });
+      if (FACTORED && lane == 63) *reinterpret_cast<int*>(lds + SWEEP_HALF + SWEEP_CHUNK * 3) = given_up;
+    }
+  }
+  __syncthreads();
+  bool large = false;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int id = 64 * q + lane;
+    const float a = *reinterpret_cast<const float*>(in + 4 * id), b = *reinterpret_cast<const float*>(in + SWEEP_CHUNK + 4 * id),
+                c = *reinterpret_cast<const float*>(in + 2 * SWEEP_CHUNK + 4 * id);
+    const float whole = fabsf(a) < INFINITY ? a + (b + c) : a;
+    u4[q] = v0 + id < p.V ? whole : 0.f;
+    large = large || !(p.alpha_most * fabsf(u4[q]) <= SWEEP_SHIFT);
+  }
+  if (__builtin_amdgcn_readfirstlane(my_row) == 64 * wave)   // the first row block's wavefronts: for the merge
+    p.u_out[v0 + 64 * wave + lane] = sweep_group_register(u4, 4 * wave);
+  if (!FACTORED) return false;
+  const bool here = __builtin_amdgcn_ballot_w64(large) != 0;   // (the same in all four wavefronts)
+  if (here && threadIdx.x == 0) __hip_atomic_store(p.exceeded, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return here || __builtin_amdgcn_readfirstlane(*reinterpret_cast<const int*>(in + SWEEP_CHUNK * 3)) != 0;
+}
+
+// The tables of the wavefront's own 64 ids, for all (at most eight alphas besides a zero one).
+__device__ __forceinline__ void sweep_put_tables(const float (&u4)[4], const GemmArgs& p, unsigned char* lds) {
+  const int lane = fresh_lane(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const float u = sweep_group_register(u4, 4 * wave);
+  float* const at = reinterpret_cast<float*>(lds + SWEEP_HALF + SWEEP_CHUNK * wave + SWEEP_TABLE * (lane >> 4) + 4 * (lane & 15));
+  const_f32_ptr alphas = sweep_alphas();
+  const int n_alpha = fresh_scalar(p.n_alpha), left_out = n_alpha > SWEEP_SPLIT_ROWS ? p.zero_alpha : SWEEP_MAX;
+  float alpha[SWEEP_MAX];
+#pragma unroll
+  for (int a = 0; a < SWEEP_MAX; ++a) alpha[a] = alphas[a];   // (all scalar loads at once)
+#pragma unroll
+  for (int r = 0; r < SWEEP_SPLIT_ROWS; ++r) {
+    const float shift = (r >= left_out ? alpha[r + 1] : alpha[r]) * u, e = r < n_alpha ? expf(shift) : 0.f;
+    at[SWEEP_GROUP * r] = e;
+    at[SWEEP_GROUP * (SWEEP_SPLIT_ROWS + r)] = e * shift;
+  }
+}
+
+// What GemmArgs' shift_tile holds, and its shift_max and shift_min of the tile's groups.  (Rounding keeps the order: the largest of alpha u
+// is that of the largest or of the least u.)
+__device__ __forceinline__ float sweep_tile_shift(const float (&u4)[4]) {
+  const auto larger = [](uint32_t a, uint32_t b) { return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b))); };
+  const auto of_all = [&](float x) {
+    return __uint_as_float(with_lane_xor<32>(with_lane_xor<16>(__float_as_uint(largest_of_16(x)), larger), larger));
+  };
+  const float above = of_all(fmaxf(fmaxf(u4[0], u4[1]), fmaxf(u4[2], u4[3]))), below = -of_all(-fminf(fminf(u4[0], u4[1]), fminf(u4[2], u4[3])));
+  const float alpha = sweep_lane_alpha(fresh_lane() & 15), most = fmaxf(alpha * above, alpha * below);
+  return above == 0.f && below == 0.f ? 0.f : most + SWEEP_MARGIN;
+}
+__device__ __forceinline__ void sweep_group_shifts(const float (&u4)[4], float (&most4)[4], float (&least4)[4]) {
+  const int at = fresh_lane() & 15;
+  const float alpha = sweep_lane_alpha(at);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float x = alpha * largest_of_16(u4[q]), y = alpha * -largest_of_16(-u4[q]);
+    const float most = fmaxf(x, y), least = fminf(x, y), spread = largest_of_16(most - least);
+    most4[q] = at == 15 ? spread : most == 0.f && least == 0.f ? 0.f : most + SWEEP_MARGIN;
+    least4[q] = least;
+  }
+}
+
 // Two kernels per list length, of which the one that the table's flag does not ask for returns at once: both forms in one
 // kernel do not fit the registers, and the host does not know the shifts.
-template <int KS, bool GENERAL>
-struct SweepEpilogue {
+template <int KS, bool GENERAL, bool OWN>
+struct AnySweepEpilogue {
   using State = SweepState<KS, GENERAL>;
-  static constexpr bool RELOAD_FRAGMENTS = true;
+  static constexpr bool RELOAD_FRAGMENTS = true, OWN_U = OWN;
+  static constexpr int ROWS = OWN_U ? SWEEP_OWN_ROWS : BN;
   static __device__ __forceinline__ bool skip(const GemmArgs& p) {
+    if (OWN_U) {
+      if (p.sampled == nullptr) return false;   // (the host launches the general form only)
+      bool large = GENERAL && *p.exceeded != 0, open = false;
+      for (int i = threadIdx.x & 63; i < p.n_sampled; i += 64) {
+        large = large || !(p.sampled[i] <= SWEEP_SHIFT);
+        open = open || p.sampled[i] > SWEEP_SHIFT_SURE;
+      }
+      if (__builtin_amdgcn_ballot_w64(large) == 0 && __builtin_amdgcn_ballot_w64(open) != 0)
+        for (int i = threadIdx.x & 63; i < p.n_block_max; i += 64) large = large || !(p.alpha_most * p.block_max[i] <= SWEEP_SHIFT);
+      return (__builtin_amdgcn_ballot_w64(large) != 0) != GENERAL;
+    }
     if (p.sweep_general == nullptr) return false;   // (the host launches one form only)
     return (*(const int __attribute__((address_space(4)))*)(uintptr_t)p.sweep_general != 0) != GENERAL;
   }
@@ -674,6 +810,7 @@ struct SweepEpilogue {
     st.id0 = -1;
     st.split = split;
     st.next_shift = 0.f;
+    st.given_up = 0;
   }
   static __device__ __forceinline__ void tile(f32x4 (&acc)[16][4], State& st, int v0, const GemmArgs& p, int my_row) {
     if constexpr (GENERAL)
@@ -681,14 +818,34 @@ struct SweepEpilogue {
     else
       factored_tile(acc, st, __builtin_amdgcn_readfirstlane(v0), my_row);
   }
-  static __device__ __forceinline__ void factored_tile(f32x4 (&acc)[16][4], State& st, int v0, int my_row) {
+  // OWN_U: false once the factored form does not apply to some tile of the call; all wavefronts alike.
+  static __device__ __forceinline__ bool own_tile(f32x4 (&acc)[16][4], State& st, int v0, const GemmArgs& p, int my_row,
+                                                  unsigned char* lds) {
+    v0 = __builtin_amdgcn_readfirstlane(v0);
+    if constexpr (GENERAL) {
+      general_tile(acc, st, v0, p, my_row, lds);
+      return true;
+    } else {
+      return factored_tile(acc, st, v0, my_row, lds);
+    }
+  }
+  static __device__ __forceinline__ bool factored_tile(f32x4 (&acc)[16][4], State& st, int v0, int my_row, unsigned char* lds = nullptr) {
     const int lane = fresh_lane();
     const GemmArgs p = sweep_args();
     const bool first = st.id0 < 0;
     if (first) st.id0 = v0;   // (the split's first tile)
     // of the sums' table (16 KB) one word a line, so that it is in this XCD's L2 by then
-    float warm = p.eu[(int64_t)v0 * SWEEP_ROWS + (64 * (threadIdx.x >> 6 & 1) + lane) * 32];
+    float warm = 0.f;
+    if (!OWN_U) warm = p.eu[(int64_t)v0 * SWEEP_ROWS + (64 * (threadIdx.x >> 6 & 1) + lane) * 32];
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");   // as in epilogue_tile: let the last MFMA drain
+    float u4[4], shift4[4];
+    bool given_up = false;
+    if constexpr (OWN_U) {
+      given_up = sweep_own_u<true>(acc, v0, p, my_row, st.given_up, lds, u4);   // (and on to the tile's end: a way out here costs 48 registers)
+      __syncthreads();   // (the parts are read)
+      sweep_put_tables(u4, p, lds);
+      st.next_shift = sweep_tile_shift(u4);
+    }
     if (v0 + BM > p.V) {   // only the last tile of the vocabulary: a real branch (the empty asm keeps it one)
       asm volatile("");
       const int id = v0 + 4 * (lane >> 4);
@@ -707,7 +864,7 @@ struct SweepEpilogue {
       asm volatile("s_nop 3" ::: "memory");
     }
     unsigned marked;
-    float u4[4], shift4[4];
+    if (OWN_U) __syncthreads();   // the tables of all four wavefronts
 #pragma unroll 1
     for (bool again = false;; again = true) {
       // the least unshifted logit that any alpha might list, as in sweep_lists but with the tile's largest shifts
@@ -723,17 +880,31 @@ struct SweepEpilogue {
       if (again) break;
       sweep_move_references<KS>(st, top);
       if (first) {
-        st.next_shift = p.shift_tile[v0 / BM * 16 + (lane & 15)];
-        // (waited for here: at its use, which other tiles come to as well, the wait would be for the ring's loads too)
-        asm volatile("" : "+v"(st.next_shift));
-        sweep_announce<KS>(acc, st, v0, p, my_row);
+        float least4[4];
+        if constexpr (OWN_U) {
+          sweep_group_shifts(u4, shift4, least4);
+        } else {
+          st.next_shift = p.shift_tile[v0 / BM * 16 + (lane & 15)];
+          // (waited for here: at its use, which other tiles come to as well, the wait would be for the ring's loads too)
+          asm volatile("" : "+v"(st.next_shift));
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            least4[q] = p.shift_min[v0 + 64 * q + lane];
+            shift4[q] = p.shift_max[v0 + 64 * q + lane];
+          }
+        }
+        sweep_announce<KS>(acc, st, least4, shift4, p, my_row);
       }
       asm volatile("" : "+v"(warm));
-      sweep_sums<KS>(acc, st, v0, p);
+      sweep_sums<KS, OWN_U>(acc, st, v0, p, lds);
+      if constexpr (OWN_U) {
+        __syncthreads();   // (the tables are read: the LDS is the ring's again)
+      } else {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        u4[q] = p.u[v0 + 64 * q + lane];
-        shift4[q] = p.shift_max[v0 + 64 * q + lane];
+        for (int q = 0; q < 4; ++q) {
+          u4[q] = p.u[v0 + 64 * q + lane];
+          shift4[q] = p.shift_max[v0 + 64 * q + lane];
+        }
       }
       if (!first) break;
       sweep_take_bounds<KS, false>(st, p, my_row);   // and once more with what the others have announced meanwhile
@@ -744,23 +915,47 @@ struct SweepEpilogue {
       marked |= 1u << (__builtin_amdgcn_readlane(tl, __builtin_ctzll(targets)) >> 4);
       targets &= targets - 1;
     }
+    if (OWN_U && marked != 0) {
+      float least4[4];
+      sweep_group_shifts(u4, shift4, least4);
+    }
     sweep_lists<KS>(acc, st, marked, u4, shift4, v0, p);
-    const int ahead = min(v0 / BM + 1, p.tiles - 1);
-    st.next_shift = p.shift_tile[16 * ahead + (lane & 15)];
+    int exceeded = 0;
+    if (OWN_U) {
+      exceeded = __hip_atomic_load(p.exceeded, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    } else {
+      const int ahead = min(v0 / BM + 1, p.tiles - 1);
+      st.next_shift = p.shift_tile[16 * ahead + (lane & 15)];
+    }
     sweep_take_bounds<KS, true>(st, p, my_row);
-    asm volatile("" : "+v"(st.next_shift));   // (come back by now: as above)
+    if (OWN_U)
+      st.given_up = __builtin_amdgcn_readfirstlane(exceeded);
+    else
+      asm volatile("" : "+v"(st.next_shift));   // (come back by now: as above)
+    return !given_up;
   }
-  static __device__ __forceinline__ void general_tile(f32x4 (&acc)[16][4], State& st, int v0, const GemmArgs& p) {
+  static __device__ __forceinline__ void general_tile(f32x4 (&acc)[16][4], State& st, int v0, const GemmArgs& p, int my_row = 0,
+                                                      unsigned char* lds = nullptr) {
     if (st.id0 < 0) st.id0 = v0;
-    float u_ahead = sweep_load_u(v0, p);
+    float u4[4], u_ahead = 0.f;
+    if constexpr (OWN_U) {
+      asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
+      sweep_own_u<false>(acc, v0, p, my_row, 0, lds, u4);
+      __syncthreads();   // the LDS is the ring's again
+    } else {
+      u_ahead = sweep_load_u(v0, p);
+    }
     // As in epilogue_tile: let the last MFMA drain.  And the code's place: with what follows 20 bytes past a multiple of 32 the whole call takes
     // 1.0 % (arg max) to 1.8 % (lists) less than where the placed K loop leaves it, and as long as before that was placed; the
     // worst of eight places, four bytes apart, is 0 (the mean of five shapes each, two to six strengths, 60 to 1500 rows).
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15\n\t.p2align 5\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0\n\ts_nop 0" ::: "memory");
 #pragma unroll 1
     for (int i = 0; i < 16; ++i) {
-      const float u = u_ahead;
-      u_ahead = sweep_load_u(__builtin_amdgcn_readfirstlane(v0 + SWEEP_GROUP * min(i + 1, 15)), p);
+      float u = u_ahead;
+      if constexpr (OWN_U)
+        u = sweep_group_entry(u4, i);
+      else
+        u_ahead = sweep_load_u(__builtin_amdgcn_readfirstlane(v0 + SWEEP_GROUP * min(i + 1, 15)), p);
       LL_SCHED_FENCE();
       float y[4][4], x[16];
       sweep_read_group(acc, i, y);
@@ -793,7 +988,8 @@ struct SweepEpilogue {
       const bool second = p.n_alpha > SWEEP_SPLIT_ROWS && p.zero_alpha < 0;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const int row = my_row - lane + 16 * j + (lane & 15);
+        const int row = OWN_U && (int)(threadIdx.x & ~63u) + 16 * j + (lane & 15) >= ROWS ? INT_MAX
+                                                                                          : __builtin_amdgcn_readfirstlane(my_row) + 16 * j + (lane & 15);
 #pragma unroll
         for (int r = 0; r < 4; ++r) {
           const float other = __shfl_xor(st.st[j][r], 32, kWave);   // row 8 + a
@@ -832,5 +1028,9 @@ struct SweepEpilogue {
       }
   }
 };
+template <int KS, bool GENERAL>
+struct SweepEpilogue : AnySweepEpilogue<KS, GENERAL, false> {};        // u and its tables from kernels before
+template <int KS, bool GENERAL>
+struct WholeSweepEpilogue : AnySweepEpilogue<KS, GENERAL, true> {};    // u formed by the contraction itself
 
 }  // namespace

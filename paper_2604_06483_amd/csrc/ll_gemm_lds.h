@@ -151,15 +151,19 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
   const int seg_row = 64 * wave + (lane >> 3);                        // + 8 s
   const int seg_koff0 = ((lane & 7) ^ (lane >> 4)) * 8;               // element offset, even segments
   const int seg_koff1 = seg_koff0 ^ 32;                               // odd segments
-  const int a_last = p.last_row - rb * BN;                            // what rows past the end are read from
+  constexpr int ROWS = EPI::ROWS;                                     // lens rows of a block
+  const int a_last = p.last_row - rb * ROWS;                          // what rows past the end are read from
   constexpr int IMM_BIAS = 3072;                                      // largest immediate, segment 7
 
   // Per-lane byte offsets of the 8 segments, fixed for the whole sweep (W: per vocabulary tile,
   // because the last tile clamps its rows to V-1): one load is one instruction.
   unsigned a_off[8], w_off[8];
 #pragma unroll
-  for (int s = 0; s < 8; ++s)
-    a_off[s] = (unsigned)(min(seg_row + 8 * s, a_last) * lda + ((s & 1) ? seg_koff1 : seg_koff0)) * 2u + (7168u - 1024u * s);
+  for (int s = 0; s < 8; ++s) {
+    int row = min(seg_row + 8 * s, a_last);
+    if (EPI::OWN_U && seg_row + 8 * s >= ROWS) row = a_last + 1 - ROWS + seg_row + 8 * s;   // the direction's, behind the row of zeros
+    a_off[s] = (unsigned)(row * lda + ((s & 1) ? seg_koff1 : seg_koff0)) * 2u + (7168u - 1024u * s);
+  }
   // TAIL: whole chunks of the last stage; lanes past them step back to the last one (made from the lane number each time, once
   // per vocabulary tile: the long lists leave no registers to keep the two distances in)
   const int tail_chunks = TAIL ? (d - (KT - 1) * DK) >> 3 : 8;
@@ -193,7 +197,7 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
   const unsigned lds_mid = (unsigned)(uintptr_t)(lptr_t)smem + wave * (64 * DK * 2) + 4096;
   const unsigned w_lds_wrap = lds_mid + W_SLOTS * SLOT_BYTES;
   const unsigned a_lds_flip = (2 * W_SLOTS + 1) * SLOT_BYTES + 2 * lds_mid;   // slot 3 <-> slot 4
-  const unsigned char* const a_base0 = reinterpret_cast<const unsigned char*>(p.A + (int64_t)rb * BN * lda) - IMM_BIAS;
+  const unsigned char* const a_base0 = reinterpret_cast<const unsigned char*>(p.A + (int64_t)rb * ROWS * lda) - IMM_BIAS;
   auto w_tile_base = [&](int tile) {
     return reinterpret_cast<const unsigned char*>(p.W + ((int64_t)tile * BM + row0) * d) - IMM_BIAS;
   };
@@ -244,7 +248,7 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
   for (int hk = 0; hk < 2; ++hk) f_off[hk] = f_row * (DK * 2) + (((4 * hk + f_grp) ^ f_swz) * 16);
   const int a_wave_off = (wave * 64) * (DK * 2);
 
-  const int my_row = rb * BN + tid;
+  const int my_row = tid < ROWS ? rb * ROWS + tid : INT_MAX;
   typename EPI::State st;
   EPI::init(st, p, my_row, split);
   if constexpr (SHORT) EPI::settle(st);
@@ -438,7 +442,8 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
     if (TAIL && (KT == 1 || (KTILE) == KT - 2)) zero_tail(nW);                                         \
     __syncthreads();                                                                                   \
     LL_SLICE(MF0, 1, 1, fw1, fw0, nW, 0, LL_AIN_S3, LL_AOUT_S3, LL_HOOK_S3, LL_RD_SPREAD)
-  for (int tile = tile0; tile < (SHORT && ends_in_half ? tile1 - 1 : tile1); ++tile) {
+  int end = SHORT && ends_in_half ? tile1 - 1 : tile1;
+  for (int tile = tile0; tile < end; ++tile) {
     f32x4 acc[16][4];   // first written by the K half 0 MFMAs of stage 0, with C = 0
     LL_STAGE(LL_MFMA16_Z, 0)
     // (The loop's place in the 64-byte instruction lines, which a change anywhere before it would move.  In the projections of whole
@@ -452,6 +457,9 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
     if constexpr (SHORT) {
       asm volatile(LL_PLACE_EPILOGUE);
       EPI::template short_tile<false>(acc, st, row0 + tile * BM, p, my_row);
+    } else if constexpr (EPI::OWN_U) {
+      // (the slot of the stage just done: the upper 4 KB of each wavefront's 8 are free until it sends the next stage's loads)
+      if (!EPI::own_tile(acc, st, tile * BM, p, my_row, smem + W_SLOTS * SLOT_BYTES - cW - nW)) end = 0;
     } else {
       EPI::tile(acc, st, tile * BM, p, my_row);
     }

@@ -36,23 +36,23 @@ __global__ __launch_bounds__(256) void ll_rms_stats_kernel(const uint16_t* __res
   if (lane == 0) inv_rms[row] = inv_rms_from_sumsq(ss, d, eps);
 }
 
+// The larger of two numbers, NaN once one of them is.
+__device__ __forceinline__ float sticky_max(float a, float b) { return (a != a || a >= b) ? a : b; }
+
 // ---------------------------------------------------------------------------------------
 // a2 + a3 materialised: panel[r, :] = bf16((h[r, :] * inv_rms[r]) * gamma), zero padded to the
 // panel's row stride; gamma == nullptr copies the rows unchanged.  One wavefront per row; the
 // row stays in registers between the statistic and the write when it fits.
 // ---------------------------------------------------------------------------------------
 template <int NITER>
-__global__ __launch_bounds__(256) void ll_norm_panel_kernel(const uint16_t* __restrict__ hidden,
-                                                            const uint16_t* __restrict__ gamma, uint16_t* __restrict__ panel,
-                                                            int rows, int zero_rows, int d, int64_t lda, float eps,
-                                                            unsigned* __restrict__ bound, int bounds) {
+__device__ __forceinline__ void norm_panel_row(const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ gamma,
+                                               uint16_t* __restrict__ panel, int row, int rows, int d, int64_t lda, float eps,
+                                               unsigned* __restrict__ bound, int bounds) {
   const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-  if (row >= rows + zero_rows) return;
   const int n16 = d >> 3;
   const int n16_pad = (int)(lda >> 3);
   uint4* dst = reinterpret_cast<uint4*>(panel + (int64_t)row * lda);
-  if (row == rows) {   // zero_rows = 1: one row of zeros behind them, what stands for the rows that are missing from a whole block
+  if (row == rows) {   // one row of zeros behind them, what stands for the rows that are missing from a whole block
     for (int c = lane; c < n16_pad; c += 64) dst[c] = make_uint4(0, 0, 0, 0);
     return;
   }
@@ -93,6 +93,78 @@ __global__ __launch_bounds__(256) void ll_norm_panel_kernel(const uint16_t* __re
   for (int c = n16 + lane; c < n16_pad; c += 64) dst[c] = make_uint4(0, 0, 0, 0);
 }
 
+template <int NITER>
+__global__ __launch_bounds__(256) void ll_norm_panel_kernel(const uint16_t* __restrict__ hidden,
+                                                            const uint16_t* __restrict__ gamma, uint16_t* __restrict__ panel,
+                                                            int rows, int zero_rows, int d, int64_t lda, float eps,
+                                                            unsigned* __restrict__ bound, int bounds) {
+  const int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  if (row >= rows + zero_rows) return;
+  norm_panel_row<NITER>(hidden, gamma, panel, row, rows, d, lda, eps, bound, bounds);
+}
+
+// The same for a sweep whose kernel forms u itself.  Behind the row of zeros three rows whose sum is v: what is cut off it at 8, 16 and 24
+// bits, so that nothing is lost (of an infinity or what is no number the first row has it, the others zero).  And the first
+// n_waves wavefronts look at `samples` rows of W_U, spread over the vocabulary: sampled[w] is the largest |alpha u| of wavefront w's, NaN once one is.
+template <int NITER>
+__global__ __launch_bounds__(256) void ll_sweep_panel_kernel(const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ gamma,
+                                                             uint16_t* __restrict__ panel, int rows, int d, int64_t lda, float eps,
+                                                             unsigned* __restrict__ bound, int bounds, const uint16_t* __restrict__ W, int V,
+                                                             const float* __restrict__ v, float alpha_most, int n_waves, int samples,
+                                                             float* __restrict__ sampled, int* __restrict__ exceeded) {
+  const int lane = threadIdx.x & 63, n16 = d >> 3;
+  int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+  const float4* const v4 = reinterpret_cast<const float4*>(v);
+  if (row < n_waves) {
+    float largest = 0.f;
+    for (int s = row; s < samples; s += n_waves) {
+      const uint4* const w = reinterpret_cast<const uint4*>(W + (int64_t)((int64_t)s * V / samples) * d);
+      float a = 0.f;
+#pragma unroll 4
+      for (int c = lane; c < n16; c += 64) {
+        const uint4 q = w[c];
+        const float4 v0 = v4[2 * c], v1 = v4[2 * c + 1];
+        a = fmaf(bf16_lo(q.x), v0.x, a);
+        a = fmaf(bf16_hi(q.x), v0.y, a);
+        a = fmaf(bf16_lo(q.y), v0.z, a);
+        a = fmaf(bf16_hi(q.y), v0.w, a);
+        a = fmaf(bf16_lo(q.z), v1.x, a);
+        a = fmaf(bf16_hi(q.z), v1.y, a);
+        a = fmaf(bf16_lo(q.w), v1.z, a);
+        a = fmaf(bf16_hi(q.w), v1.w, a);
+      }
+      largest = sticky_max(largest, fabsf(wave_sum(a)));
+    }
+    if (lane == 0) sampled[row] = alpha_most * largest;
+    return;
+  }
+  row -= n_waves;
+  if (row > rows + SWEEP_PARTS) return;
+  if (row <= rows) {
+    if (row == rows && lane == 0) *exceeded = 0;
+    norm_panel_row<NITER>(hidden, gamma, panel, row, rows, d, lda, eps, bound, bounds);
+    return;
+  }
+  const int part = row - rows - 1;
+  uint4* const dst = reinterpret_cast<uint4*>(panel + (int64_t)row * lda);
+  const auto cut = [&](float x) -> uint32_t {
+    const uint32_t first = __float_as_uint(x) & 0xffff0000u;
+    if (!(fabsf(x) < INFINITY)) return part != 0 ? 0u : x != x ? 0x7fc0u : first >> 16;
+    const float rest = x - __uint_as_float(first);
+    const uint32_t second = __float_as_uint(rest) & 0xffff0000u;
+    const uint32_t third = __float_as_uint(rest - __uint_as_float(second));
+    return (part == 0 ? first : part == 1 ? second : third) >> 16;
+  };
+  for (int c = lane; c < (int)(lda >> 3); c += 64) {
+    uint4 q = make_uint4(0, 0, 0, 0);
+    if (c < n16) {
+      const float4 a = v4[2 * c], b = v4[2 * c + 1];
+      q = make_uint4(cut(a.x) | cut(a.y) << 16, cut(a.z) | cut(a.w) << 16, cut(b.x) | cut(b.y) << 16, cut(b.z) | cut(b.w) << 16);
+    }
+    dst[c] = q;
+  }
+}
+
 // Copy of the bias of Eq. 1 padded with zeros to whole vocabulary tiles, so that the epilogue
 // reads 32 entries per group without looking at V.
 __global__ __launch_bounds__(256) void ll_pad_bias_kernel(const float* __restrict__ bias, int V, float* __restrict__ padded,
@@ -122,14 +194,20 @@ constexpr int64_t INFINITY_CACHE_BYTES = 256ll << 20, L2_BYTES = 32ll << 20;   /
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 
-// The larger of two numbers, NaN once one of them is.
-__device__ __forceinline__ float sticky_max(float a, float b) { return (a != a || a >= b) ? a : b; }
-
 template <bool STREAM>
 __global__ __launch_bounds__(256) void ll_unembed_direction_kernel(const uint16_t* __restrict__ W, const float* __restrict__ v,
                                                                    int V, int d, float scale, float* __restrict__ u, int n_padded,
-                                                                   float* __restrict__ block_max) {
+                                                                   float* __restrict__ block_max, const float* __restrict__ sampled,
+                                                                   int n_sampled) {
   extern __shared__ __align__(16) float sv[];
+  if (sampled != nullptr) {   // a look ahead of a kernel that forms u itself: only where the sample leaves open which form it is to be
+    bool open = false, large = false;
+    for (int i = threadIdx.x & 63; i < n_sampled; i += 64) {   // (every wavefront for itself: v may take all the LDS)
+      large = large || !(sampled[i] <= SWEEP_SHIFT);
+      open = open || sampled[i] > SWEEP_SHIFT_SURE;
+    }
+    if (__builtin_amdgcn_ballot_w64(large) != 0 || __builtin_amdgcn_ballot_w64(open) == 0) return;
+  }
   for (int j = threadIdx.x; j < d; j += blockDim.x) sv[j] = v[j];
   __syncthreads();
   const int lane = threadIdx.x & 63;
@@ -182,12 +260,6 @@ __global__ __launch_bounds__(256) void ll_unembed_direction_kernel(const uint16_
     for (int w = 1; w < 4; ++w) largest = sticky_max(largest, sv[w]);
     block_max[blockIdx.x] = largest;
   }
-}
-
-// Over the lane's block of 16.
-__device__ __forceinline__ float largest_of_16(float x) {
-  const auto larger = [](uint32_t a, uint32_t b) { return __float_as_uint(fmaxf(__uint_as_float(a), __uint_as_float(b))); };
-  return __uint_as_float(with_lane_xor<1>(with_lane_xor<2>(with_lane_xor<4>(with_lane_xor<8>(__float_as_uint(x), larger), larger), larger), larger));
 }
 
 // Step 2: what the sweep epilogue reads per group of 16 ids and per tile (see GemmArgs), the flag that says which form of the
@@ -699,6 +771,19 @@ void launch_norm_panel(const uint16_t* hidden, const uint16_t* gamma, uint16_t* 
     hipLaunchKernelGGL(ll_norm_panel_kernel<0>, grid, block, 0, stream, hidden, gamma, panel, rows, zero_rows, d, lda, eps, bound, bounds);
 }
 
+void launch_sweep_panel(const uint16_t* hidden, const uint16_t* gamma, uint16_t* panel, int rows, int d, int64_t lda, float eps,
+                        unsigned* bound, int bounds, const uint16_t* W, int V, const float* v, float alpha_most, int n_waves, int samples,
+                        float* sampled, int* exceeded, hipStream_t stream) {
+  const int per_block = rows <= 1024 ? 1 : 4;
+  const dim3 grid((unsigned)((n_waves + rows + 1 + SWEEP_PARTS + per_block - 1) / per_block)), block(64 * per_block);
+  const auto kernel = d <= 64 * 8 * 4    ? ll_sweep_panel_kernel<4>
+                      : d <= 64 * 8 * 8  ? ll_sweep_panel_kernel<8>
+                      : d <= 64 * 8 * 16 ? ll_sweep_panel_kernel<16>
+                                         : ll_sweep_panel_kernel<0>;
+  hipLaunchKernelGGL(kernel, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps, bound, bounds, W, V, v, alpha_most, n_waves, samples,
+                     sampled, exceeded);
+}
+
 int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, const void* hidden, const void* gamma,
                  const void* W_U, const float* bias, unsigned flags, float eps, int k, const int32_t* target_ids,
                  int32_t* out_topk_ids, float* out_topk_p,
@@ -964,21 +1049,22 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
 }
 
 struct SweepPlan {
-  size_t off_u, off_block_max, off_eu, off_shift, off_shift_min, off_shift_tile, off_general, off_bound, off_stats, off_ztgt, off_top, off_panel, total;
+  size_t off_u, off_block_max, off_sampled, off_eu, off_shift, off_shift_min, off_shift_tile, off_general, off_bound, off_stats, off_ztgt, off_top, off_panel, total;
   size_t off_project, wanted;   // the projection's workspace where one alpha is left to it; wanted: what the call is fastest with
   int64_t lda;
   int n_padded;   // V in whole tiles
 };
 
 // Vocabulary splits of a pass: one workgroup per compute unit, and ids within a split in 16 bits.
-int sweep_splits(int rows, int tiles) {
-  const int row_blocks = (rows + BN - 1) / BN;
+int sweep_splits(int rows, int tiles, int block_rows = BN) {
+  const int row_blocks = (rows + block_rows - 1) / block_rows;
   const int splits = even_splits(tiles, NUM_CU / row_blocks);
   const int least = (tiles + SWEEP_MAX_TILES - 1) / SWEEP_MAX_TILES;
   return splits > least ? splits : least;
 }
 
-SweepPlan make_sweep_plan(const ll_shape* s, int n_alpha, int k = 1) {
+// whole: of a call whose kernel forms u itself (no tables; the direction's rows behind the panel).  Callers bring the other's size.
+SweepPlan make_sweep_plan(const ll_shape* s, int n_alpha, int k = 1, bool whole = false) {
   SweepPlan p = {};
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -996,19 +1082,23 @@ SweepPlan make_sweep_plan(const ll_shape* s, int n_alpha, int k = 1) {
   p.off_u = take((size_t)p.n_padded * sizeof(float));
   p.off_block_max = take(UD_BLOCKS * sizeof(float));
   p.off_project = off;
-  p.off_eu = take((size_t)p.n_padded * 2 * SWEEP_ROWS * sizeof(float));
-  p.off_shift = take((size_t)p.n_padded * sizeof(float));
-  p.off_shift_min = take((size_t)p.n_padded * sizeof(float));
-  p.off_shift_tile = take((size_t)tiles * 16 * sizeof(float));
+  if (whole) {
+    p.off_sampled = take(UD_BLOCKS * sizeof(float));
+  } else {
+    p.off_eu = take((size_t)p.n_padded * 2 * SWEEP_ROWS * sizeof(float));
+    p.off_shift = take((size_t)p.n_padded * sizeof(float));
+    p.off_shift_min = take((size_t)p.n_padded * sizeof(float));
+    p.off_shift_tile = take((size_t)tiles * 16 * sizeof(float));
+  }
   p.off_general = take(sizeof(int));
   p.off_bound = take(rows * n_alpha * k * sizeof(unsigned));
   p.off_stats = take(partials * n_alpha * sizeof(float4));
   p.off_ztgt = take(partials * sizeof(float));
   p.off_top = take(partials * n_alpha * (k > 1 ? SWEEP_KS : 1) * sizeof(uint2));
   p.lda = ((int64_t)s->d + DK - 1) / DK * DK;
-  p.off_panel = take((rows + 1) * (size_t)p.lda * sizeof(uint16_t));
+  p.off_panel = take((rows + 1 + (whole ? SWEEP_PARTS : 0)) * (size_t)p.lda * sizeof(uint16_t));
   p.total = p.wanted = off;
-  if (n_alpha == 1) {
+  if (n_alpha == 1 && !whole) {
     const Plan project = make_plan(s, k);
     if (p.off_project + project.roomy > p.total) p.total = p.off_project + project.roomy;
     p.wanted = p.off_project + wanted_bytes(project);
@@ -1040,22 +1130,9 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     al.a[a] = a < n_alpha ? alphas[a] : 0.f;
     if (!(al.a[a] == al.a[a]) || al.a[a] - al.a[a] != 0.f) return LL_EINVAL;   // NaN or infinite
   }
-  const SweepPlan plan = make_sweep_plan(shape, n_alpha, k);
+  SweepPlan plan = make_sweep_plan(shape, n_alpha, k);
   if (workspace == nullptr || workspace_bytes < plan.total || ((uintptr_t)workspace & 255)) return LL_EWORKSPACE;
 
-  unsigned char* ws = static_cast<unsigned char*>(workspace);
-  float* const u = reinterpret_cast<float*>(ws + plan.off_u);
-  float* eu = reinterpret_cast<float*>(ws + plan.off_eu);
-  float* shift_max = reinterpret_cast<float*>(ws + plan.off_shift);
-  float* shift_min = reinterpret_cast<float*>(ws + plan.off_shift_min);
-  float* shift_tile = reinterpret_cast<float*>(ws + plan.off_shift_tile);
-  float* block_max = reinterpret_cast<float*>(ws + plan.off_block_max);
-  int* general = reinterpret_cast<int*>(ws + plan.off_general);
-  unsigned* bound = reinterpret_cast<unsigned*>(ws + plan.off_bound);
-  float4* stats = reinterpret_cast<float4*>(ws + plan.off_stats);
-  float* ztgt = reinterpret_cast<float*>(ws + plan.off_ztgt);
-  uint2* top = reinterpret_cast<uint2*>(ws + plan.off_top);
-  uint16_t* panel = reinterpret_cast<uint16_t*>(ws + plan.off_panel);
   const int64_t N = shape->N;
   const int d = shape->d, V = shape->V;
   const int tiles = (V + BM - 1) / BM;
@@ -1065,10 +1142,6 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     if (e__ != hipSuccess) return hip_failed(e__); \
   } while (0)
 
-  const auto direction = (int64_t)V * d * 2 >= INFINITY_CACHE_BYTES ? ll_unembed_direction_kernel<true> : ll_unembed_direction_kernel<false>;
-  const size_t v_bytes = (size_t)d * sizeof(float);
-  if (v_bytes > 64 * 1024)
-    if (const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(direction), (size_t)SWEEP_MAX_D * sizeof(float)); rc != LL_OK) return rc;
   const int first_rows = (int)(N < CHUNK_ROWS ? N : CHUNK_ROWS), first_splits = sweep_splits(first_rows, tiles);
   const int each = (tiles + first_splits - 1) / first_splits;
   // One strength is a projection whose bias is alpha u.  That is the faster call for lists, for few rows and for many tiles a split; the arg
@@ -1077,17 +1150,6 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
   // 50257 (2) 60 | 53, 700 x 50257 (3) 69 | 68, 4000 x 20000 (5) 91 | 98, 4000 x 50257 (13) 181 | 217; lists of two: 300 x 20000 40 | 43,
   // 1500 x 4096 30 | 42, 300 x 50257 58 | 66, 700 x 50257 71 | 83, 4000 x 50257 185 | 254.
   const bool as_projection = n_alpha == 1 && (N <= FEW_ROWS || k > 1 || each > 4);
-  hipLaunchKernelGGL(direction, dim3(UD_BLOCKS), dim3(256), v_bytes, stream, static_cast<const uint16_t*>(W_U), v, V, d,
-                     as_projection ? al.a[0] : 1.0f, u, plan.n_padded, block_max);
-  LL_CHECK_S(hipGetLastError());
-  // (The few-rows kernel then reads W_U through the caches where the direction kernel has just left it in the Infinity Cache, with room
-  // for what else is there; a W_U that the L2s hold together is left in them as that kernel has dealt it, for the next sweep's.  Whole
-  // calls, past the caches | through them, us, 8 rows (d, V, MB): 2560, 4096, 21: 42.1 | 45.1; 2560, 8192, 42: 50.8 | 46.2; 4096, 8192, 67:
-  // 72.7 | 68.8; 1024, 50257, 103: 54.2 | 49.3; 256, 128256, 66: no difference.)
-  const bool W_in_cache = d >= 512 && (int64_t)V * d * 2 > L2_BYTES && (int64_t)V * d * 2 <= INFINITY_CACHE_BYTES / 2;
-  if (as_projection)
-    return project_impl(shape, ws + plan.off_project, workspace_bytes - plan.off_project, hidden, gamma, W_U, u, 0u, eps, k, target_ids, out_ids,
-                        out_p, out_logp, out_entropy, stream, nullptr, CHUNK_ROWS, false, W_in_cache ? 1 : 0);
   // Few alphas: the general form alone, without the tables and the launch that fills them.  Its cost grows with every alpha, the
   // factored one's hardly does: the line moves up where a split has few tiles and there are no lists, and where the contraction is
   // short (what the factored form adds to it is the same, and the smaller share of the call).  Whole calls, general | factored, us
@@ -1110,29 +1172,97 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
   int zero_alpha = -1;   // of nine alphas one that is zero needs no place in the tables
   for (int a = 0; a < n_alpha; ++a)
     if (n_alpha > SWEEP_SPLIT_ROWS && al.a[a] == 0.f) zero_alpha = a;
-  if (!only_general) {
+  // Forming u in the contraction's own kernel saves the read of W_U before it (and the tables' kernel), takes three rows of every block, which
+  // mostly are to spare, and time in every tile: 0.4 us in the general form, 2.6 in the factored one, whose wavefronts exchange parts
+  // of u and tables and wait for each other four times.  So it is for calls of few tiles a workgroup on a large W_U; three rows that make a block more count as
+  // what the busiest workgroup then does more of.  Whole calls, u before | u within, us, nine strengths, arg max (N x d x V: tiles a workgroup): 250 x 2048 x
+  // 50257 (1) 133 | 107, 700 x 1024 x 50257 (3) 181 | 173, 1500 x 2048 x 50257 (5) 380 | 355, 1500 x 4096 x 128256 (12) 1386 | 1262, 4000 x 1024 x 50257 (13)
+  // 582 | 598, 8000 x 2560 x 151936 (75) 5370 | 5440; lists of three: 500 x 2560 x 151936 (5) 549 | 449, 4000 x 256 x 128256 (34) 1192 | 1260; three strengths:
+  // 1500 x 512 x 50257 (5) 169 | 160, 500 x 2560 x 151936 (5) 503 | 391.  A W_U of up to 64 MiB is read from the Infinity Cache
+  // in some 10 us; the factored form then gains little (300 x 512 x 50257 (2) 121 | 115, 1500 x 512 x 50257 (5) 229 | 230) and keeps the kernels before it.
+  bool whole = !as_projection && N <= CHUNK_ROWS && (only_general || ((n_alpha <= SWEEP_SPLIT_ROWS || zero_alpha >= 0) && (int64_t)V * d * 2 > (64 << 20)));
+  if (whole) {
+    const int own_splits = sweep_splits((int)N, tiles, SWEEP_OWN_ROWS);
+    const int own_each = (tiles + own_splits - 1) / own_splits;
+    const float tile_us = 1.15f * (float)((d + DK - 1) / DK) + (only_general ? 8.0f * n_alpha : 25.0f);
+    const float more_us = (float)(own_each - each) * tile_us + (float)own_each * (only_general ? 0.4f : 2.6f);
+    const SweepPlan own = make_sweep_plan(shape, n_alpha, k, true);
+    whole = more_us <= (float)V * (float)d * 2.0f / 6.0e6f + 5.0f && own.total <= plan.total;
+    if (whole) plan = own;
+  }
+
+  unsigned char* ws = static_cast<unsigned char*>(workspace);
+  float* const u = reinterpret_cast<float*>(ws + plan.off_u);
+  float* eu = reinterpret_cast<float*>(ws + plan.off_eu);
+  float* shift_max = reinterpret_cast<float*>(ws + plan.off_shift);
+  float* shift_min = reinterpret_cast<float*>(ws + plan.off_shift_min);
+  float* shift_tile = reinterpret_cast<float*>(ws + plan.off_shift_tile);
+  float* block_max = reinterpret_cast<float*>(ws + plan.off_block_max);
+  float* const sampled = reinterpret_cast<float*>(ws + plan.off_sampled);
+  int* general = reinterpret_cast<int*>(ws + plan.off_general);
+  unsigned* bound = reinterpret_cast<unsigned*>(ws + plan.off_bound);
+  float4* stats = reinterpret_cast<float4*>(ws + plan.off_stats);
+  float* ztgt = reinterpret_cast<float*>(ws + plan.off_ztgt);
+  uint2* top = reinterpret_cast<uint2*>(ws + plan.off_top);
+  uint16_t* panel = reinterpret_cast<uint16_t*>(ws + plan.off_panel);
+  const auto direction = (int64_t)V * d * 2 >= INFINITY_CACHE_BYTES ? ll_unembed_direction_kernel<true> : ll_unembed_direction_kernel<false>;
+  const size_t v_bytes = (size_t)d * sizeof(float);
+  if (v_bytes > 64 * 1024)
+    if (const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(direction), (size_t)SWEEP_MAX_D * sizeof(float)); rc != LL_OK) return rc;
+  if (!whole) {
+    hipLaunchKernelGGL(direction, dim3(UD_BLOCKS), dim3(256), v_bytes, stream, static_cast<const uint16_t*>(W_U), v, V, d,
+                       as_projection ? al.a[0] : 1.0f, u, plan.n_padded, block_max, (const float*)nullptr, 0);
+    LL_CHECK_S(hipGetLastError());
+  }
+  // (The few-rows kernel then reads W_U through the caches where the direction kernel has just left it in the Infinity Cache, with room
+  // for what else is there; a W_U that the L2s hold together is left in them as that kernel has dealt it, for the next sweep's.  Whole
+  // calls, past the caches | through them, us, 8 rows (d, V, MB): 2560, 4096, 21: 42.1 | 45.1; 2560, 8192, 42: 50.8 | 46.2; 4096, 8192, 67:
+  // 72.7 | 68.8; 1024, 50257, 103: 54.2 | 49.3; 256, 128256, 66: no difference.)
+  const bool W_in_cache = d >= 512 && (int64_t)V * d * 2 > L2_BYTES && (int64_t)V * d * 2 <= INFINITY_CACHE_BYTES / 2;
+  if (as_projection)
+    return project_impl(shape, ws + plan.off_project, workspace_bytes - plan.off_project, hidden, gamma, W_U, u, 0u, eps, k, target_ids, out_ids,
+                        out_p, out_logp, out_entropy, stream, nullptr, CHUNK_ROWS, false, W_in_cache ? 1 : 0);
+  if (!only_general && !whole) {
     const int n_bound = (int)(N < CHUNK_ROWS ? N : CHUNK_ROWS) * n_alpha * k;
     hipLaunchKernelGGL(ll_sweep_table_kernel, dim3(plan.n_padded / 256 < 2048 ? plan.n_padded / 256 : 2048), dim3(256), 0, stream,
                        (const float*)block_max, UD_BLOCKS, plan.n_padded, al, n_alpha, zero_alpha, (const float*)u, eu, shift_max,
                        shift_min, shift_tile, general, bound, n_bound);
     LL_CHECK_S(hipGetLastError());
   }
-  // (d is at most SWEEP_MAX_D: the direct-to-LDS kernel's 32-bit row offsets always suffice)
-  const GemmKernel kern[2] = {general_sweep_kernel(lists),   // of two, one returns at once
-                              only_general  ? nullptr
-                              : d % DK != 0 ? tail_sweep_kernel(lists)
-                              : lists       ? ll_lens_gemm_dma_kernel<SweepEpilogue<SWEEP_KS, false>>
-                                            : ll_lens_gemm_dma_kernel<SweepEpilogue<1, false>>};
+  // (d is at most SWEEP_MAX_D: the direct-to-LDS kernel's 32-bit row offsets always suffice)  Of two kernels one returns at once; where
+  // they form u themselves the general one comes last, for the shifts that only then turn out too large.
+  const GemmKernel general_kernel = whole ? whole_sweep_kernel(lists, true, true) : general_sweep_kernel(lists);
+  const GemmKernel factored_kernel = only_general  ? nullptr
+                                     : whole       ? whole_sweep_kernel(lists, false, d % DK != 0)
+                                     : d % DK != 0 ? tail_sweep_kernel(lists)
+                                     : lists       ? ll_lens_gemm_dma_kernel<SweepEpilogue<SWEEP_KS, false>>
+                                                   : ll_lens_gemm_dma_kernel<SweepEpilogue<1, false>>;
+  const GemmKernel kern[2] = {whole ? factored_kernel : general_kernel, whole ? general_kernel : factored_kernel};
   const size_t lds = (size_t)SLOTS * SLOT_BYTES;
   for (const GemmKernel g : kern)
     if (g != nullptr)
       if (const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(g), lds); rc != LL_OK) return rc;
 
+  // One vocabulary row in 32, at most two a wavefront: of Gaussian shifts the sample's largest is within a fifth of
+  // the largest.
+  const int samples = only_general ? 0 : V < 32 * 2 * UD_BLOCKS ? (V + 31) / 32 : 2 * UD_BLOCKS;
+  const int sample_waves = samples < UD_BLOCKS ? samples : UD_BLOCKS;
+  float alpha_most = 0.f;
+  for (int a = 0; a < n_alpha; ++a) alpha_most = fmaxf(alpha_most, fabsf(al.a[a]));
   for (int64_t r0 = 0; r0 < N; r0 += CHUNK_ROWS) {
     const int rows = (int)((N - r0 < CHUNK_ROWS) ? (N - r0) : CHUNK_ROWS);
     const uint16_t* h_rows = static_cast<const uint16_t*>(hidden) + r0 * d;
-    const bool need_panel = gamma != nullptr || plan.lda != d;
-    if (need_panel) {
+    const bool need_panel = gamma != nullptr || plan.lda != d || whole;
+    if (whole) {
+      launch_sweep_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, d, plan.lda, eps, bound, only_general ? 0 : n_alpha * k,
+                         static_cast<const uint16_t*>(W_U), V, v, alpha_most, sample_waves, samples, sampled, general, stream);
+      LL_CHECK_S(hipGetLastError());
+      if (!only_general) {
+        hipLaunchKernelGGL(direction, dim3(UD_BLOCKS), dim3(256), v_bytes, stream, static_cast<const uint16_t*>(W_U), v, V, d, 1.0f, u, plan.n_padded,
+                           block_max, (const float*)sampled, sample_waves);
+        LL_CHECK_S(hipGetLastError());
+      }
+    } else if (need_panel) {
       launch_norm_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, 1, d, plan.lda, eps, nullptr, 0, stream);
       LL_CHECK_S(hipGetLastError());
     }
@@ -1147,10 +1277,17 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     a.V = V;
     a.k = k;
     a.tiles = tiles;
-    a.row_blocks = (rows + BN - 1) / BN;
-    a.splits = sweep_splits(rows, tiles);
+    const int block_rows = whole ? SWEEP_OWN_ROWS : BN;
+    a.row_blocks = (rows + block_rows - 1) / block_rows;
+    a.splits = sweep_splits(rows, tiles, block_rows);
     a.group_rows = group_rows(a.row_blocks, a.splits);
-    a.u = u;
+    a.u = a.u_out = u;
+    a.exceeded = general;
+    a.sampled = only_general ? nullptr : sampled;
+    a.block_max = block_max;
+    a.n_block_max = UD_BLOCKS;
+    a.n_sampled = sample_waves;
+    a.alpha_most = alpha_most;
     a.eu = eu;
     a.shift_max = shift_max;
     a.shift_min = shift_min;

@@ -1,0 +1,115 @@
+"""Sweeps whose contraction forms u = W_U v itself, from three bf16 rows behind the lens rows of every block, in both forms: against
+the CPU oracle, and against the kernels that take u from a pass of its own."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2604_06483_amd import binding as LL
+from paper_2604_06483_amd import workloads as WL
+from tests.conftest import kernels_of, say
+from tests.test_gpu_sweep import ALPHAS9, direction
+from tests.test_gpu_sweep_forms import check
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def is_whole(call):
+    names = [n for n in kernels_of(call) if n.startswith("ll_lens_gemm")]
+    assert len({"WholeSweep" in n for n in names}) == 1, names
+    return "WholeSweep" in names[0]
+
+
+def workload(N, d, V, seed=61):
+    w = WL.make_workload(WL.LensConfig("whole", L=1, T=N, d=d, V=V, k=1), DEV, seed=seed)
+    return w, w.hidden.reshape(N, d)
+
+
+@pytest.mark.parametrize("N,d,V,n_alpha,k", [
+    (253, 64, 777, 3, None),      # a full block; one K stage, a vocabulary that ends within a tile
+    (507, 72, 20000, 2, 3),       # three blocks, the last of one row; a ragged hidden size
+    (1, 128, 300, 2, None),       # one row
+    (1500, 64, 50257, 1, None), (300, 128, 20000, 1, None),   # one strength: a projection; a sweep
+    (2000, 128, 33000, 3, 2),     # eight blocks
+])
+def test_general_form_matches_oracle(N, d, V, n_alpha, k):
+    say(f"whole sweep, general N={N} d={d} V={V} A={n_alpha} k={k}")
+    check(N, d, V, ALPHAS9[:n_alpha], k, 1.0, "whole, general", rows=np.unique(np.r_[0:min(N, 260), N - 1]))
+
+
+@pytest.mark.parametrize("k", [None, 3])
+@pytest.mark.parametrize("N,d,V,alphas,length", [
+    (253, 704, 50000, ALPHAS9, 1.0),              # one block, one tile a split
+    (300, 712, 50257, ALPHAS9[:8], 1.0),          # ragged hidden size; two blocks, two tiles; no zero strength of nine
+    (1012, 704, 50257, ALPHAS9, 20.0),            # four full blocks
+    (200, 704, 50257, [4.0, -3.0, -2.0, -1.0, 0.5, 1.0, 2.0, 3.0, 0.0], 50.0),   # shifts up to 17: the sample leaves it open
+    (200, 704, 50257, ALPHAS9, 120.0),            # shifts of 40: the sample has it
+])
+def test_factored_form_matches_oracle(N, d, V, alphas, length, k):
+    say(f"whole sweep N={N} d={d} V={V} A={len(alphas)} k={k} length={length}")
+    check(N, d, V, alphas, k, length, "whole", rows=np.unique(np.r_[0:8, N // 2:N // 2 + 8, min(N, 256) - 8:min(N, 256), N - 8:N]))
+    w, h = workload(N, d, V)
+    assert is_whole(lambda: LL.ll_steer_sweep(h, w.gamma, w.W_U, w.cfg.eps, direction(d), alphas, None, k=k))
+
+
+def both(h, gamma, W, v, alphas, target, k):
+    """Of the first 253 rows: from a call of just these (u within), and from one of 256 (a block more otherwise: u before)."""
+    one = lambda n: LL.ll_steer_sweep(h[:n].contiguous(), gamma, W, 1e-5, v, alphas, target[:n].contiguous(), k=k)
+    assert is_whole(lambda: one(253)) and not is_whole(lambda: one(256))
+    return one(253), tuple(t[:, :253] for t in one(256))
+
+
+@pytest.mark.parametrize("k", [None, 3])
+@pytest.mark.parametrize("what", ["plain", "one large shift", "large shifts", "infinite W", "NaN in W", "infinite v", "NaN in v", "no direction"])
+def test_as_with_u_from_a_pass_of_its_own(what, k):
+    """The forms agree to fp32 sums in another order, and to the places of what is no number.  "One large shift" is one token that the
+    sample does not meet: the factored form is given up while it runs."""
+    say(f"whole sweep, both ways: {what} k={k}")
+    d, V = 704, 50257
+    w, h = workload(256, d, V)
+    v, W = direction(d), w.W_U
+    if what == "one large shift":
+        W[-30] = (6.0 * v).to(torch.bfloat16)
+    if what == "large shifts":
+        v = v * 400.0
+    if what == "infinite W":
+        W[40000, 5] = float("inf")
+        v[5] = 0.25            # its second and third rows are zero
+    if what == "NaN in W":
+        W[40000, 5] = float("nan")
+    if what == "infinite v":
+        v[5] = -float("inf")
+    if what == "NaN in v":
+        v[5] = float("nan")
+    if what == "no direction":
+        v = torch.zeros_like(v)
+    a, b = both(h, w.gamma, W, v, ALPHAS9, w.target_ids, k)
+    finite = torch.isfinite(b[3]) & torch.isfinite(a[3])
+    assert torch.equal(torch.isnan(a[3]), torch.isnan(b[3])) and torch.equal(torch.isnan(a[2]), torch.isnan(b[2]))
+    if finite.any():
+        assert (a[0] != b[0])[finite].float().mean() < 1e-3        # near-ties
+        scale = float(b[3][finite].abs().max()) + 20.0             # sums of logits and shifts of this size round in the last place
+        for x, y in zip(a[1:], b[1:]):
+            torch.testing.assert_close(x[finite], y[finite], rtol=4e-5, atol=2e-6 * scale)
+    assert int(a[0].min()) >= 0 and torch.equal(a[0][~finite] < V, b[0][~finite] < V)
+
+
+def test_captured_and_replayed():
+    """One graph of it, replayed on other inputs in the same buffers: the results of a call."""
+    say("whole sweep, captured")
+    N, d, V = 300, 704, 50257
+    w, h = workload(N, d, V)
+    v, ws = direction(d), torch.empty(LL.ll_steer_sweep_workspace_bytes(N, d, V, 9, 1), dtype=torch.uint8, device=DEV)
+    call = lambda: LL.ll_steer_sweep(h, w.gamma, w.W_U, w.cfg.eps, v, ALPHAS9, w.target_ids, workspace=ws)
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = call()
+    for length in (1.0, 400.0, 30.0):     # the factored form, the general one, the factored one
+        v.copy_(direction(d) * length)
+        h.copy_(h.roll(1, 0))
+        want = [t.clone() for t in call()]
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(x, y) for x, y in zip(out, want))

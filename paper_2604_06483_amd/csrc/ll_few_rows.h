@@ -50,7 +50,8 @@ struct FewArgs {
   uint2* cand;              // [rows, splits, FEW_CAP]  (logit bits, id), unordered
   int* count;               // [rows, splits]           entries of the list
   int64_t lda;
-  int rows, d, V, k, splits, units;   // splits: workgroups, one vocabulary part each; units: groups of 16 vocabulary rows
+  int rows, d, V, k, splits, units;   // splits: vocabulary parts; units: groups of 16 vocabulary rows
+  int row_groups;           // workgroups of a part, 16 NJ rows each
 };
 
 typedef unsigned few_u32x4 __attribute__((ext_vector_type(4)));
@@ -79,8 +80,21 @@ struct FewSearch {
 };
 
 template <int NJ, int MU, bool STREAM>
-__global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs p) {
+__global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(FewArgs p) {
   constexpr int R = 16 * NJ;
+  int part = blockIdx.x;
+  if (p.row_groups > 1) {   // this workgroup's part, and its rows of it; those of one part side by side on one XCD, whose L2 they share W's lines in
+    const int logical = xcd_logical_block();
+    part = logical / p.row_groups;
+    if (part >= p.splits) return;
+    const int first = (logical - part * p.row_groups) * R;
+    p.rows = min(p.rows - first, R);
+    p.A += (int64_t)first * p.lda;
+    p.target = p.target != nullptr ? p.target + first : nullptr;
+    p.stats += (int64_t)first * p.splits;
+    p.cand += (int64_t)first * p.splits * FEW_CAP;
+    p.count += (int64_t)first * p.splits;
+  }
   constexpr int A_CHUNKS = R * 8;                                              // 16-byte chunks of an A tile
   constexpr int A_PER = (A_CHUNKS + FEW_THREADS - 1) / FEW_THREADS;
   __shared__ __align__(16) unsigned char sA[2][R * 128];
@@ -118,7 +132,6 @@ __global__ __launch_bounds__(FEW_THREADS) void ll_lens_few_kernel(const FewArgs 
 
   // (one part per workgroup and no loop over parts: the compiler would keep the epilogue's addresses in registers through the
   // next part's main loop)
-  const int part = blockIdx.x;
   const int ua = (int)((int64_t)part * p.units / p.splits);
   const int ub = (int)((int64_t)(part + 1) * p.units / p.splits);
   const int u0 = ua + (ub - ua) * wave / FEW_WAVES;                            // this wavefront's groups: u0 .. u0 + nu - 1

@@ -572,6 +572,7 @@ __global__ __launch_bounds__(256) void ll_sweep_merge_kernel(const float4* __res
 struct FewPlan {
   bool ok, two_rounds;   // two_rounds: of more than 96 rows
   int nj, mu, units, splits;   // nj: 16-row blocks of the kernel instance; mu: groups per wavefront; units: groups in all
+  int row_groups;              // workgroups that share a part, of nj blocks each
 };
 
 constexpr int SHORT_KMAX = 20, SHORT_KMAX_BIAS = 12;   // longest lists of the kernel of short calls
@@ -599,6 +600,20 @@ FewPlan make_few_plan(const ll_shape* s, int k) {
   f.two_rounds = rounds > 1 && f.nj == 8;
   if (f.two_rounds && k <= (s->d % DK == 0 ? SHORT_KMAX_BIAS : 4)) return f;
   f.mu = ((f.units + f.splits - 1) / f.splits + FEW_WAVES - 1) / FEW_WAVES;
+  // A vocabulary of up to 16384 has no part for every second compute unit: the rows are then dealt to several workgroups a part, down to 16 each.
+  // What that shortens is a part's epilogue, and the A tiles; W's lines come from memory once all the same (xcd_logical_block).  Whole
+  // calls, one workgroup a part | several, us (rows, d, V, k): 64, 256, 4096, 5: 17.4 | 13.3; 128, 64, 4000, 5: 22.5 | 12.3; 81, 512, 8000, 10: 26.5 | 17.8;
+  // 81, 1608, 6000, 5: 37.4 | 23.0; 100, 1024, 12000, 20: 31.7 | 25.8; 64, 2048, 16000, 10: 34.3 | 31.1; 128, 8192, 10000, 10: 114.6 | 91.7;
+  // 20, 8192, 16000, 10: 94.9 | 89.1.
+  f.row_groups = 1;
+  for (int nj = 1; nj < f.nj; ++nj) {
+    const int groups = (blocks + nj - 1) / nj;
+    if (nj != 5 && nj != 7 && f.splits * groups <= NUM_CU) {
+      f.nj = nj;
+      f.row_groups = groups;
+      break;
+    }
+  }
   f.ok = true;
   return f;
 }
@@ -914,6 +929,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     a.k = k;
     a.splits = few.splits;
     a.units = few.units;
+    a.row_groups = few.row_groups;
     LL_CHECK_F(mark());
     // Whether the loads of W_U go past the caches: where its rows are whole lines of 128 bytes (others share lines between two stages,
     // and are faster through the caches whatever the size) and it is more than a third of the Infinity Cache.  Up to there it stays
@@ -932,7 +948,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
     // (The scope bits of the loads, sc0 and sc1, make no difference either way.)
     const bool kept = W_in_cache < 0 ? (int64_t)V * d * 2 <= INFINITY_CACHE_BYTES / 3 : W_in_cache > 0;
     const bool stream_W = ((uintptr_t)W_U | (uintptr_t)d * 2) % 128 == 0 && !kept;
-    hipLaunchKernelGGL(stream_W ? few_kernel<true>(few.nj, few.mu) : few_kernel<false>(few.nj, few.mu), dim3(few.splits), dim3(FEW_THREADS), 0, stream, a);
+    hipLaunchKernelGGL(stream_W ? few_kernel<true>(few.nj, few.mu) : few_kernel<false>(few.nj, few.mu), dim3(few.row_groups > 1 ? (few.splits * few.row_groups + NUM_XCD - 1) / NUM_XCD * NUM_XCD : few.splits), dim3(FEW_THREADS), 0, stream, a);
     LL_CHECK_F(hipGetLastError());
     LL_CHECK_F(mark());
     hipLaunchKernelGGL(ll_few_merge_kernel, dim3((unsigned)N), dim3(FEW_MERGE_THREADS), 0, stream, (const float4*)a.stats, (const uint2*)a.cand,

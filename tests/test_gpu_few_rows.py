@@ -204,3 +204,19 @@ def test_a_sweep_of_one_strength_reads_w_where_it_has_just_left_it(V, past_the_c
     names = kernels_of(lambda: LL.ll_steer_sweep(w.hidden.reshape(16, -1), w.gamma, w.W_U, w.cfg.eps, v / v.norm(), [2.0], w.target_ids))
     assert names[0].startswith("ll_unembed_direction_kernel") and names[2].startswith("ll_lens_few_kernel")
     assert names[2].split(">")[0].endswith("true" if past_the_caches else "false")
+
+
+@pytest.mark.parametrize("V", [777, 4096, 8000, 16384, 16400])
+@pytest.mark.parametrize("N", [17, 48, 81, 128])
+def test_rows_dealt_to_several_workgroups_are_those_of_calls_of_sixteen(N, V):
+    """A small vocabulary's parts go to several workgroups, some rows each: the same bits as from calls of 16 rows, which have one a part."""
+    say(f"few rows, dealt N={N} V={V}")
+    d, k = 328, 7
+    w = WL.make_workload(WL.LensConfig("dealt", L=1, T=N, d=d, V=V, k=k), DEV, seed=29)
+    bias = 0.5 * torch.randn((V,), generator=torch.Generator(device=DEV).manual_seed(8), device=DEV)
+    h = w.hidden.reshape(N, d)
+    whole = LL.ll_project(h, w.gamma, w.W_U, w.cfg.eps, k, w.target_ids, bias=bias)
+    for r in range(0, N, 16):
+        part = LL.ll_project(h[r:r + 16].contiguous(), w.gamma, w.W_U, w.cfg.eps, k, w.target_ids[r:r + 16].contiguous(), bias=bias)
+        for a, b in zip(whole, part):
+            assert torch.equal(a[r:r + 16], b)

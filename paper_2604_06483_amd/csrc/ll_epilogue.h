@@ -33,12 +33,6 @@ struct GemmArgs {
   const float* shift_min;   // [tiles * BM / 16, 16]: per alpha the least
   const float* shift_tile;  // [tiles, 16]: per alpha the largest of a tile, with the margin
   const int* sweep_general; // nonzero: some |alpha u| is too large for the factored form; nullptr: the general form in any case
-  float* u_out;             // where the kernel forms u itself (see SweepEpilogue): u, [tiles * BM]
-  int* exceeded;            // likewise: set once some |alpha u| turns out too large for the factored form
-  const float* sampled;     // likewise: the largest |alpha u| of some vocabulary rows, n_sampled of them; nullptr: the general form in any case
-  const float* block_max;   // and where that leaves open whether some are too large: the largest |u| of all, in n_block_max parts
-  int n_sampled, n_block_max;
-  float alpha_most;         // largest |alpha|
   float4* sweep_stats;      // [rows, n_alpha, splits]      (reference, S, T)
   float* sweep_ztgt;        // [rows, splits]               logit of the target id at alpha = 0
   uint2* sweep_top;         // [rows, n_alpha, splits, KS]  (logit bits, id), sorted
@@ -50,6 +44,12 @@ struct GemmArgs {
   int classes;              // short calls: 0, or k, the classes that the splits are dealt into (see exchange_classes)
   int half_tiles;           // short calls: 0, or V in half tiles where the splits are cut between those
   int group_rows;           // row blocks that an XCD's workgroups share W_U's tiles between (see place_of)
+  // sweeps that form u themselves (see ll_epilogue_sweep.h):
+  float* u_out;             // u for the merge, [tiles * BM]
+  int* exceeded;            // set once some |alpha u| turns out too large for the factored form
+  const float* sampled;     // the largest |alpha u| of some vocabulary rows in SWEEP_SAMPLED parts; nullptr: the general form in any case
+  const float* block_max;   // and where that leaves open whether some are too large: the largest |u| of all, in SWEEP_BLOCK_MAX parts
+  float alpha_most;         // largest |alpha|
 };
 
 using GemmKernel = void (*)(const GemmArgs);

@@ -53,12 +53,13 @@ namespace {
 // between two tiles.  Which form runs is not known before u is: a sample of W_U's rows says so where it is clear, where it is not
 // the direction kernel does look at all of W_U, and should a shift past SWEEP_SHIFT still turn up, `exceeded` stops the
 // factored kernel at its workgroups' next tiles and the general one, launched behind it, runs.  Costs 2.6 us a tile (general form 0.4).
-// Whole calls, u before | within: 1386 | 1262 us and 549 | 449 us.
+// Whole calls, u before | within: 1386 | 1233 us and 549 | 439 us.
 // ---------------------------------------------------------------------------------------
 constexpr int SWEEP_MAX = LL_SWEEP_MAX;
 constexpr int SWEEP_KS = LL_SWEEP_KMAX;
 constexpr float SWEEP_SHIFT = 20.0f;
 constexpr float SWEEP_SHIFT_SURE = 0.7f * SWEEP_SHIFT;   // while a sample's largest shift is no more, the largest of all is taken to be below SWEEP_SHIFT
+constexpr int SWEEP_SAMPLED = 256, SWEEP_BLOCK_MAX = NUM_CU * 4;   // parts of the sample, and of the largest |u|
 constexpr float SWEEP_MARGIN = 2.0f * SWEEP_SHIFT * 0x1p-22f;   // more than the rounding of a shift up to SWEEP_SHIFT, and of a limit's own
 constexpr int SWEEP_GROUP = 16;
 constexpr unsigned SWEEP_NO_ID = 0xffffu;         // list entry that stands for "below the row's shared bound"
@@ -436,6 +437,9 @@ __device__ __forceinline__ void sweep_sums(f32x4 (&acc)[16][4], SweepState<KS, f
     e[0][r] = __builtin_amdgcn_exp2f(fmaf(y[0][r], LOG2E, nref[0]));
     ez[0][r] = e[0][r] * y[0][r];
   }
+  // (The code's place: 500 to 4000 rows, lists and arg max, took up to 1.3 % longer where changes before it had moved it; of four places in
+  // 32 bytes this is the best in the mean.)
+  asm volatile(".p2align 5" ::: "memory");
 #pragma unroll 1
   for (int i = 0; i < 16; ++i) {
     float a1[4] = {next1.x, next1.y, next1.z, next1.w}, a2[4] = {next2.x, next2.y, next2.z, next2.w};
@@ -767,6 +771,17 @@ __device__ __forceinline__ void sweep_group_shifts(const float (&u4)[4], float (
   }
 }
 
+// What a sample of the shifts says of all (for a wavefront; one load a lane, so that a kernel that is not the one returns soon).
+enum { SWEEP_FITS, SWEEP_OPEN, SWEEP_TOO_LARGE };
+__device__ __forceinline__ int sweep_sample_says(const float* sampled) {
+  static_assert(SWEEP_SAMPLED == 256, "four a lane");
+  const float4 x = reinterpret_cast<const float4*>(sampled)[threadIdx.x & 63];
+  const bool large = !(x.x <= SWEEP_SHIFT && x.y <= SWEEP_SHIFT && x.z <= SWEEP_SHIFT && x.w <= SWEEP_SHIFT);
+  const bool open = x.x > SWEEP_SHIFT_SURE || x.y > SWEEP_SHIFT_SURE || x.z > SWEEP_SHIFT_SURE || x.w > SWEEP_SHIFT_SURE;
+  if (__builtin_amdgcn_ballot_w64(large) != 0) return SWEEP_TOO_LARGE;
+  return __builtin_amdgcn_ballot_w64(open) != 0 ? SWEEP_OPEN : SWEEP_FITS;
+}
+
 // Two kernels per list length, of which the one that the table's flag does not ask for returns at once: both forms in one
 // kernel do not fit the registers, and the host does not know the shifts.
 template <int KS, bool GENERAL, bool OWN>
@@ -777,14 +792,19 @@ struct AnySweepEpilogue {
   static __device__ __forceinline__ bool skip(const GemmArgs& p) {
     if (OWN_U) {
       if (p.sampled == nullptr) return false;   // (the host launches the general form only)
-      bool large = GENERAL && *p.exceeded != 0, open = false;
-      for (int i = threadIdx.x & 63; i < p.n_sampled; i += 64) {
-        large = large || !(p.sampled[i] <= SWEEP_SHIFT);
-        open = open || p.sampled[i] > SWEEP_SHIFT_SURE;
+      const bool exceeded = GENERAL && *p.exceeded != 0;
+      int says = sweep_sample_says(p.sampled);
+      if (says == SWEEP_OPEN) {
+        bool large = false;
+#pragma unroll
+        for (int i = 0; i < SWEEP_BLOCK_MAX / 256; ++i) {
+          const float4 x = reinterpret_cast<const float4*>(p.block_max)[64 * i + (threadIdx.x & 63)];
+          large = large || !(p.alpha_most * x.x <= SWEEP_SHIFT && p.alpha_most * x.y <= SWEEP_SHIFT && p.alpha_most * x.z <= SWEEP_SHIFT &&
+                             p.alpha_most * x.w <= SWEEP_SHIFT);
+        }
+        says = __builtin_amdgcn_ballot_w64(large) != 0 ? SWEEP_TOO_LARGE : SWEEP_FITS;
       }
-      if (__builtin_amdgcn_ballot_w64(large) == 0 && __builtin_amdgcn_ballot_w64(open) != 0)
-        for (int i = threadIdx.x & 63; i < p.n_block_max; i += 64) large = large || !(p.alpha_most * p.block_max[i] <= SWEEP_SHIFT);
-      return (__builtin_amdgcn_ballot_w64(large) != 0) != GENERAL;
+      return (exceeded || says == SWEEP_TOO_LARGE) != GENERAL;
     }
     if (p.sweep_general == nullptr) return false;   // (the host launches one form only)
     return (*(const int __attribute__((address_space(4)))*)(uintptr_t)p.sweep_general != 0) != GENERAL;

@@ -248,7 +248,7 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
   for (int hk = 0; hk < 2; ++hk) f_off[hk] = f_row * (DK * 2) + (((4 * hk + f_grp) ^ f_swz) * 16);
   const int a_wave_off = (wave * 64) * (DK * 2);
 
-  const int my_row = tid < ROWS ? rb * ROWS + tid : INT_MAX;
+  const int my_row = ROWS == BN || tid < ROWS ? rb * ROWS + tid : INT_MAX;
   typename EPI::State st;
   EPI::init(st, p, my_row, split);
   if constexpr (SHORT) EPI::settle(st);

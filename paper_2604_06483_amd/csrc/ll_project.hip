@@ -105,7 +105,10 @@ __global__ __launch_bounds__(256) void ll_norm_panel_kernel(const uint16_t* __re
 
 // The same for a sweep whose kernel forms u itself.  Behind the row of zeros three rows whose sum is v: what is cut off it at 8, 16 and 24
 // bits, so that nothing is lost (of an infinity or what is no number the first row has it, the others zero).  And the first
-// n_waves wavefronts look at `samples` rows of W_U, spread over the vocabulary: sampled[w] is the largest |alpha u| of wavefront w's, NaN once one is.
+// n_waves wavefronts (SWEEP_SAMPLED, or none) look at `samples` rows of W_U, spread over the vocabulary, up to SAMPLE_ROWS each at once:
+// sampled[w] is the largest |alpha u| of wavefront w's, NaN once one is.
+constexpr int SAMPLE_ROWS = 8;
+
 template <int NITER>
 __global__ __launch_bounds__(256) void ll_sweep_panel_kernel(const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ gamma,
                                                              uint16_t* __restrict__ panel, int rows, int d, int64_t lda, float eps,
@@ -116,25 +119,33 @@ __global__ __launch_bounds__(256) void ll_sweep_panel_kernel(const uint16_t* __r
   int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   const float4* const v4 = reinterpret_cast<const float4*>(v);
   if (row < n_waves) {
-    float largest = 0.f;
-    for (int s = row; s < samples; s += n_waves) {
-      const uint4* const w = reinterpret_cast<const uint4*>(W + (int64_t)((int64_t)s * V / samples) * d);
-      float a = 0.f;
-#pragma unroll 4
-      for (int c = lane; c < n16; c += 64) {
-        const uint4 q = w[c];
-        const float4 v0 = v4[2 * c], v1 = v4[2 * c + 1];
-        a = fmaf(bf16_lo(q.x), v0.x, a);
-        a = fmaf(bf16_hi(q.x), v0.y, a);
-        a = fmaf(bf16_lo(q.y), v0.z, a);
-        a = fmaf(bf16_hi(q.y), v0.w, a);
-        a = fmaf(bf16_lo(q.z), v1.x, a);
-        a = fmaf(bf16_hi(q.z), v1.y, a);
-        a = fmaf(bf16_lo(q.w), v1.z, a);
-        a = fmaf(bf16_hi(q.w), v1.w, a);
-      }
-      largest = sticky_max(largest, fabsf(wave_sum(a)));
+    const uint4* w[SAMPLE_ROWS];
+    float a[SAMPLE_ROWS], largest = 0.f;
+#pragma unroll
+    for (int i = 0; i < SAMPLE_ROWS; ++i) {   // (past the last the last one again)
+      const int s = min(row + n_waves * i, samples - 1);
+      w[i] = reinterpret_cast<const uint4*>(W + (int64_t)((int64_t)s * V / samples) * d);
+      a[i] = 0.f;
     }
+    for (int c = lane; c < n16; c += 64) {
+      uint4 q[SAMPLE_ROWS];
+#pragma unroll
+      for (int i = 0; i < SAMPLE_ROWS; ++i) q[i] = w[i][c];
+      const float4 v0 = v4[2 * c], v1 = v4[2 * c + 1];
+#pragma unroll
+      for (int i = 0; i < SAMPLE_ROWS; ++i) {
+        a[i] = fmaf(bf16_lo(q[i].x), v0.x, a[i]);
+        a[i] = fmaf(bf16_hi(q[i].x), v0.y, a[i]);
+        a[i] = fmaf(bf16_lo(q[i].y), v0.z, a[i]);
+        a[i] = fmaf(bf16_hi(q[i].y), v0.w, a[i]);
+        a[i] = fmaf(bf16_lo(q[i].z), v1.x, a[i]);
+        a[i] = fmaf(bf16_hi(q[i].z), v1.y, a[i]);
+        a[i] = fmaf(bf16_lo(q[i].w), v1.z, a[i]);
+        a[i] = fmaf(bf16_hi(q[i].w), v1.w, a[i]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < SAMPLE_ROWS; ++i) largest = sticky_max(largest, fabsf(wave_sum(a[i])));
     if (lane == 0) sampled[row] = alpha_most * largest;
     return;
   }
@@ -189,7 +200,7 @@ struct AlphaList {
 };
 
 constexpr int UD_ROWS = 8;   // vocabulary rows a wavefront takes at a time
-constexpr int UD_BLOCKS = NUM_CU * 4;
+constexpr int UD_BLOCKS = SWEEP_BLOCK_MAX;
 constexpr int64_t INFINITY_CACHE_BYTES = 256ll << 20, L2_BYTES = 32ll << 20;   // (the L2s of the eight XCDs together)
 
 typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
@@ -197,16 +208,10 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 template <bool STREAM>
 __global__ __launch_bounds__(256) void ll_unembed_direction_kernel(const uint16_t* __restrict__ W, const float* __restrict__ v,
                                                                    int V, int d, float scale, float* __restrict__ u, int n_padded,
-                                                                   float* __restrict__ block_max, const float* __restrict__ sampled,
-                                                                   int n_sampled) {
+                                                                   float* __restrict__ block_max, const float* __restrict__ sampled) {
   extern __shared__ __align__(16) float sv[];
   if (sampled != nullptr) {   // a look ahead of a kernel that forms u itself: only where the sample leaves open which form it is to be
-    bool open = false, large = false;
-    for (int i = threadIdx.x & 63; i < n_sampled; i += 64) {   // (every wavefront for itself: v may take all the LDS)
-      large = large || !(sampled[i] <= SWEEP_SHIFT);
-      open = open || sampled[i] > SWEEP_SHIFT_SURE;
-    }
-    if (__builtin_amdgcn_ballot_w64(large) != 0 || __builtin_amdgcn_ballot_w64(open) == 0) return;
+    if (sweep_sample_says(sampled) != SWEEP_OPEN) return;   // (every wavefront for itself: v may take all the LDS)
   }
   for (int j = threadIdx.x; j < d; j += blockDim.x) sv[j] = v[j];
   __syncthreads();
@@ -1099,7 +1104,7 @@ SweepPlan make_sweep_plan(const ll_shape* s, int n_alpha, int k = 1, bool whole 
   p.off_block_max = take(UD_BLOCKS * sizeof(float));
   p.off_project = off;
   if (whole) {
-    p.off_sampled = take(UD_BLOCKS * sizeof(float));
+    p.off_sampled = take(SWEEP_SAMPLED * sizeof(float));
   } else {
     p.off_eu = take((size_t)p.n_padded * 2 * SWEEP_ROWS * sizeof(float));
     p.off_shift = take((size_t)p.n_padded * sizeof(float));
@@ -1192,8 +1197,8 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
   // mostly are to spare, and time in every tile: 0.4 us in the general form, 2.6 in the factored one, whose wavefronts exchange parts
   // of u and tables and wait for each other four times.  So it is for calls of few tiles a workgroup on a large W_U; three rows that make a block more count as
   // what the busiest workgroup then does more of.  Whole calls, u before | u within, us, nine strengths, arg max (N x d x V: tiles a workgroup): 250 x 2048 x
-  // 50257 (1) 133 | 107, 700 x 1024 x 50257 (3) 181 | 173, 1500 x 2048 x 50257 (5) 380 | 355, 1500 x 4096 x 128256 (12) 1386 | 1262, 4000 x 1024 x 50257 (13)
-  // 582 | 598, 8000 x 2560 x 151936 (75) 5370 | 5440; lists of three: 500 x 2560 x 151936 (5) 549 | 449, 4000 x 256 x 128256 (34) 1192 | 1260; three strengths:
+  // 50257 (1) 133 | 98, 700 x 1024 x 50257 (3) 181 | 163, 1500 x 2048 x 50257 (5) 380 | 343, 1500 x 4096 x 128256 (12) 1386 | 1233, 4000 x 1024 x 50257 (13)
+  // 602 | 614, 8000 x 2560 x 151936 (75) 5370 | 5440; lists of three: 500 x 2560 x 151936 (5) 549 | 439, 4000 x 512 x 128256 (34) 1267 | 1306; three strengths:
   // 1500 x 512 x 50257 (5) 169 | 160, 500 x 2560 x 151936 (5) 503 | 391.  A W_U of up to 64 MiB is read from the Infinity Cache
   // in some 10 us; the factored form then gains little (300 x 512 x 50257 (2) 121 | 115, 1500 x 512 x 50257 (5) 229 | 230) and keeps the kernels before it.
   bool whole = !as_projection && N <= CHUNK_ROWS && (only_general || ((n_alpha <= SWEEP_SPLIT_ROWS || zero_alpha >= 0) && (int64_t)V * d * 2 > (64 << 20)));
@@ -1227,7 +1232,7 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     if (const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(direction), (size_t)SWEEP_MAX_D * sizeof(float)); rc != LL_OK) return rc;
   if (!whole) {
     hipLaunchKernelGGL(direction, dim3(UD_BLOCKS), dim3(256), v_bytes, stream, static_cast<const uint16_t*>(W_U), v, V, d,
-                       as_projection ? al.a[0] : 1.0f, u, plan.n_padded, block_max, (const float*)nullptr, 0);
+                       as_projection ? al.a[0] : 1.0f, u, plan.n_padded, block_max, (const float*)nullptr);
     LL_CHECK_S(hipGetLastError());
   }
   // (The few-rows kernel then reads W_U through the caches where the direction kernel has just left it in the Infinity Cache, with room
@@ -1259,10 +1264,9 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     if (g != nullptr)
       if (const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(g), lds); rc != LL_OK) return rc;
 
-  // One vocabulary row in 32, at most two a wavefront: of Gaussian shifts the sample's largest is within a fifth of
-  // the largest.
-  const int samples = only_general ? 0 : V < 32 * 2 * UD_BLOCKS ? (V + 31) / 32 : 2 * UD_BLOCKS;
-  const int sample_waves = samples < UD_BLOCKS ? samples : UD_BLOCKS;
+  // One vocabulary row in 32, up to 2048: of Gaussian shifts the sample's largest is then mostly within a quarter of the largest.
+  const int samples = V < 32 * SAMPLE_ROWS * SWEEP_SAMPLED ? (V + 31) / 32 : SAMPLE_ROWS * SWEEP_SAMPLED;
+  const int sample_waves = only_general ? 0 : SWEEP_SAMPLED;
   float alpha_most = 0.f;
   for (int a = 0; a < n_alpha; ++a) alpha_most = fmaxf(alpha_most, fabsf(al.a[a]));
   for (int64_t r0 = 0; r0 < N; r0 += CHUNK_ROWS) {
@@ -1275,7 +1279,7 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
       LL_CHECK_S(hipGetLastError());
       if (!only_general) {
         hipLaunchKernelGGL(direction, dim3(UD_BLOCKS), dim3(256), v_bytes, stream, static_cast<const uint16_t*>(W_U), v, V, d, 1.0f, u, plan.n_padded,
-                           block_max, (const float*)sampled, sample_waves);
+                           block_max, (const float*)sampled);
         LL_CHECK_S(hipGetLastError());
       }
     } else if (need_panel) {
@@ -1301,8 +1305,6 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     a.exceeded = general;
     a.sampled = only_general ? nullptr : sampled;
     a.block_max = block_max;
-    a.n_block_max = UD_BLOCKS;
-    a.n_sampled = sample_waves;
     a.alpha_most = alpha_most;
     a.eu = eu;
     a.shift_max = shift_max;

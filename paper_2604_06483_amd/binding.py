@@ -7,6 +7,7 @@ PyTorch supplies device memory and the stream.  If the library has not been buil
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 from ctypes import POINTER, Structure, c_char_p, c_float, c_int, c_int32, c_int64, c_size_t, c_void_p
 
@@ -96,13 +97,19 @@ def lib() -> ctypes.CDLL:
 
 # A call of a decoding step (steer one row, append one token's slices) is two short kernels, and this module's own Python was what
 # bounded it: 17.5 us for the pair with a c_void_p made for every pointer, a torch.cuda.Stream object for every call and reshapes
-# that change nothing; 11.3 us without them (and 21.9 | 16.6 us for a steering direction and its injection).
+# that change nothing; 11.3 us without them (and 21.9 | 16.6 us for a steering direction and its injection); 9.0 us (10.9 before, timed in turn) with the
+# argument structures of the last shapes kept, a tensor's shape asked for once and no calls for what an expression does.
+_Tensor, _BF16, _F32 = torch.Tensor, torch.bfloat16, torch.float32
+_shape = functools.lru_cache(maxsize=64)(ll_shape)                     # (the library only reads them)
+_capture_shape = functools.lru_cache(maxsize=64)(ll_capture_shape)
+
+
 def _ptr(t):
     return None if t is None else t.data_ptr()
 
 
 def _check(t, dtype, name, shape=None):
-    if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous()):
+    if not (isinstance(t, _Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous()):
         raise TypeError(f"{name}: need a contiguous {dtype} tensor on the GPU")
     if shape is not None and t.shape != shape:
         raise ValueError(f"{name}: shape {tuple(t.shape)}, expected {tuple(shape)}")
@@ -120,7 +127,8 @@ def _stream(stream):
 
 def _rows(t, d):
     """t as [rows, d]; a matrix of that width as it is (a reshape of it would be the same tensor in another object)."""
-    return t if t.dim() == 2 and t.shape[1] == d else t.reshape(-1, d)
+    size = t.shape
+    return t if len(size) == 2 and size[1] == d else t.reshape(-1, d)
 
 
 def _scratch(nbytes, device, stream):
@@ -232,15 +240,16 @@ def ll_project_static(hidden, gamma, W_U, eps, k, target_ids=None, *, stream=Non
 
 def ll_steer_vector(base, target, normalize=True, *, workspace=None, stream=None, out=None):
     """base [Nb, d], target [Nt, d] bf16 -> v [d] fp32 (paper Eq. 2)."""
-    _check(base, torch.bfloat16, "base")
-    _check(target, torch.bfloat16, "target")
-    d = base.shape[-1]
-    if target.shape[-1] != d or base.dim() != 2 or target.dim() != 2:
+    _check(base, _BF16, "base")
+    _check(target, _BF16, "target")
+    b_size, t_size = base.shape, target.shape
+    d = b_size[-1]
+    if t_size[-1] != d or len(b_size) != 2 or len(t_size) != 2:
         raise ValueError("base and target must be [rows, d] with the same d")
     v = torch.empty((d,), dtype=torch.float32, device=base.device) if out is None else out
     wsb = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    rc = lib().ll_steer_vector(_ptr(base), base.shape[0], _ptr(target), target.shape[0], d, int(bool(normalize)),
-                               _ptr(v), _ptr(workspace), wsb, _stream(stream))
+    rc = (_lib or lib()).ll_steer_vector(base.data_ptr(), b_size[0], target.data_ptr(), t_size[0], d, 1 if normalize else 0,
+                                         v.data_ptr(), _ptr(workspace), wsb, _stream(stream))
     if rc != LL_OK:
         raise LLError(rc, "ll_steer_vector")
     return v
@@ -248,17 +257,18 @@ def ll_steer_vector(base, target, normalize=True, *, workspace=None, stream=None
 
 def ll_steer_inject(hidden, gamma, eps, v, alpha, *, stream=None, out=None):
     """bf16(RMSNorm(hidden) + alpha v), same shape as hidden (paper Eq. 3, post-norm)."""
-    d = hidden.shape[-1]
-    h2 = _rows(hidden, d)
-    _check(h2, torch.bfloat16, "hidden")
-    _check(gamma, torch.bfloat16, "gamma", (d,))
-    _check(v, torch.float32, "v", (d,))
+    size = hidden.shape
+    d = size[-1]
+    h2 = hidden if len(size) == 2 else hidden.reshape(-1, d)
+    _check(h2, _BF16, "hidden")
+    _check(gamma, _BF16, "gamma", (d,))
+    _check(v, _F32, "v", (d,))
     o = torch.empty_like(h2) if out is None else _rows(out, d)
-    rc = lib().ll_steer_inject(ll_shape(h2.shape[0], d, 0), _ptr(h2), _ptr(gamma), float(eps), _ptr(v), float(alpha),
-                               _ptr(o), _stream(stream))
+    rc = (_lib or lib()).ll_steer_inject(_shape(h2.shape[0], d, 0), h2.data_ptr(), gamma.data_ptr(), float(eps), v.data_ptr(), float(alpha),
+                                         o.data_ptr(), _stream(stream))
     if rc != LL_OK:
         raise LLError(rc, "ll_steer_inject")
-    return o if o.shape == hidden.shape else o.reshape(hidden.shape)
+    return o if o.shape == size else o.reshape(size)
 
 
 LL_SWEEP_MAX = 9
@@ -316,30 +326,32 @@ def ll_steer_sweep(hidden, gamma, W_U, eps, v, alphas, target_ids=None, *, k=Non
 def ll_steer_inject_raw(hidden, v, alpha, layer_scale=1.0, clip_ratio=0.0, *, stream=None, out=None):
     """bf16(hidden + beta v) with beta = alpha * layer_scale clipped to clip_ratio * ||row||_2 (paper Sec. 3.4,
     in-model injection with its two safeguards); same shape as hidden."""
-    d = hidden.shape[-1]
-    h2 = _rows(hidden, d)
-    _check(h2, torch.bfloat16, "hidden")
-    _check(v, torch.float32, "v", (d,))
+    size = hidden.shape
+    d = size[-1]
+    h2 = hidden if len(size) == 2 else hidden.reshape(-1, d)
+    _check(h2, _BF16, "hidden")
+    _check(v, _F32, "v", (d,))
     o = torch.empty_like(h2) if out is None else _rows(out, d)
-    rc = lib().ll_steer_inject_raw(ll_shape(h2.shape[0], d, 0), _ptr(h2), _ptr(v), float(alpha), float(layer_scale),
-                                   float(clip_ratio), _ptr(o), _stream(stream))
+    rc = (_lib or lib()).ll_steer_inject_raw(_shape(h2.shape[0], d, 0), h2.data_ptr(), v.data_ptr(), float(alpha), float(layer_scale),
+                                             float(clip_ratio), o.data_ptr(), _stream(stream))
     if rc != LL_OK:
         raise LLError(rc, "ll_steer_inject_raw")
-    return o if o.shape == hidden.shape else o.reshape(hidden.shape)
+    return o if o.shape == size else o.reshape(size)
 
 
 def ll_capture_append(store, slices, t0, *, stream=None):
     """store [L, C, T, d] bf16, slices [L*C, n_tok, d] bf16: writes tokens t0 .. t0+n_tok-1 of every trajectory
     (paper Sec. 3.1 Stage 2).  store.reshape(-1, d) is then what ll_project takes."""
-    _check(store, torch.bfloat16, "store")
-    if store.dim() != 4:
+    _check(store, _BF16, "store")
+    size = store.shape
+    if len(size) != 4:
         raise ValueError("store: need [L, C, T, d]")
-    L, C, T, d = store.shape
-    _check(slices, torch.bfloat16, "slices")
-    if slices.dim() != 3 or slices.shape[0] != L * C or slices.shape[2] != d:
-        raise ValueError(f"slices: shape {tuple(slices.shape)}, expected ({L * C}, n_tok, {d})")
-    rc = lib().ll_capture_append(ll_capture_shape(L, C, T, d), _ptr(store), _ptr(slices), int(t0), int(slices.shape[1]),
-                                 _stream(stream))
+    L, C, T, d = size
+    _check(slices, _BF16, "slices")
+    got = slices.shape
+    if len(got) != 3 or got[0] != L * C or got[2] != d:
+        raise ValueError(f"slices: shape {tuple(got)}, expected ({L * C}, n_tok, {d})")
+    rc = (_lib or lib()).ll_capture_append(_capture_shape(L, C, T, d), store.data_ptr(), slices.data_ptr(), int(t0), got[1], _stream(stream))
     if rc != LL_OK:
         raise LLError(rc, "ll_capture_append")
 

@@ -51,7 +51,7 @@ namespace {
 // spare: with OWN_U three rows of every block are v in three bf16 parts (ll_sweep_panel_kernel), and behind a tile's K loop
 // the last wavefront's accumulators hold the tile's u.  The four wavefronts then make the tables in LDS, in the part of the ring that is free
 // between two tiles.  Which form runs is not known before u is: a sample of W_U's rows says so where it is clear, where it is not
-// the direction kernel does look at all of W_U, and should a shift past SWEEP_SHIFT still turn up, `exceeded` stops the
+// (or where v is so long that the sums' rounding would show) the direction kernel does look at all of W_U, u is taken from there, and should a shift past SWEEP_SHIFT still turn up, `exceeded` stops the
 // factored kernel at its workgroups' next tiles and the general one, launched behind it, runs.  Costs 2.6 us a tile (general form 0.4).
 // Whole calls, u before | within: 1386 | 1233 us and 549 | 439 us.
 // ---------------------------------------------------------------------------------------
@@ -60,6 +60,7 @@ constexpr int SWEEP_KS = LL_SWEEP_KMAX;
 constexpr float SWEEP_SHIFT = 20.0f;
 constexpr float SWEEP_SHIFT_SURE = 0.7f * SWEEP_SHIFT;   // while a sample's largest shift is no more, the largest of all is taken to be below SWEEP_SHIFT
 constexpr int SWEEP_SAMPLED = 256, SWEEP_BLOCK_MAX = NUM_CU * 4;   // parts of the sample, and of the largest |u|
+constexpr float SWEEP_LONG = 0.2f;                         // longest alpha v, of the rows' length, whose u the contraction forms (see sweep_sample_says)
 constexpr float SWEEP_MARGIN = 2.0f * SWEEP_SHIFT * 0x1p-22f;   // more than the rounding of a shift up to SWEEP_SHIFT, and of a limit's own
 constexpr int SWEEP_GROUP = 16;
 constexpr unsigned SWEEP_NO_ID = 0xffffu;         // list entry that stands for "below the row's shared bound"
@@ -526,6 +527,7 @@ __device__ __forceinline__ GemmArgs sweep_args() {
   p.k = args->k;
   p.tiles = args->tiles;
   p.u_out = args->u_out;
+  p.given = args->given;
   p.exceeded = args->exceeded;
   p.alpha_most = args->alpha_most;
   p.n_alpha = args->n_alpha;
@@ -713,6 +715,7 @@ __device__ __forceinline__ bool sweep_own_u(f32x4 (&acc)[16][4], int v0, const G
   }
   __syncthreads();
   bool large = false;
+  const bool given = *(const int __attribute__((address_space(4)))*)(uintptr_t)p.given != 0;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int id = 64 * q + lane;
@@ -720,9 +723,14 @@ __device__ __forceinline__ bool sweep_own_u(f32x4 (&acc)[16][4], int v0, const G
                 c = *reinterpret_cast<const float*>(in + 2 * SWEEP_CHUNK + 4 * id);
     const float whole = fabsf(a) < INFINITY ? a + (b + c) : a;
     u4[q] = v0 + id < p.V ? whole : 0.f;
-    large = large || !(p.alpha_most * fabsf(u4[q]) <= SWEEP_SHIFT);
   }
-  if (__builtin_amdgcn_readfirstlane(my_row) == 64 * wave)   // the first row block's wavefronts: for the merge
+  if (given) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) u4[q] = p.u[v0 + 64 * q + lane];
+  }
+#pragma unroll
+  for (int q = 0; q < 4; ++q) large = large || !(p.alpha_most * fabsf(u4[q]) <= SWEEP_SHIFT);
+  if (!given && __builtin_amdgcn_readfirstlane(my_row) == 64 * wave)   // the first row block's wavefronts: for the merge
     p.u_out[v0 + 64 * wave + lane] = sweep_group_register(u4, 4 * wave);
   if (!FACTORED) return false;
   const bool here = __builtin_amdgcn_ballot_w64(large) != 0;   // (the same in all four wavefronts)
@@ -771,15 +779,21 @@ __device__ __forceinline__ void sweep_group_shifts(const float (&u4)[4], float (
   }
 }
 
-// What a sample of the shifts says of all (for a wavefront; one load a lane, so that a kernel that is not the one returns soon).
+// What a sample of the shifts says of all (for a wavefront; one load a lane, so that a kernel that is not the one returns soon).  Open is
+// also a direction that is long beside the rows (sampled[SWEEP_SAMPLED]: the square of its length over that of gamma, times the largest alpha's, over
+// SWEEP_LONG's square; not above 1, or not a number): u as the contraction's accumulators sum it is off by 6e-7 of its root mean square, as
+// their logits are of theirs, and the direction kernel's, of shorter sums, by a fifth of that.  Up to SWEEP_LONG that adds a fiftieth to the shifted
+// logits' error; where |alpha v| was twice the rows' length it doubled the target's log-probabilities' (250 rows, d = 4096: 7.3e-7 | 13.1e-7 rms).
 enum { SWEEP_FITS, SWEEP_OPEN, SWEEP_TOO_LARGE };
-__device__ __forceinline__ int sweep_sample_says(const float* sampled) {
+__device__ __forceinline__ int sweep_sample_says(const float* sampled, bool only_general) {
   static_assert(SWEEP_SAMPLED == 256, "four a lane");
+  const bool long_v = !(sampled[SWEEP_SAMPLED] <= 1.f);
+  if (only_general) return long_v ? SWEEP_OPEN : SWEEP_FITS;
   const float4 x = reinterpret_cast<const float4*>(sampled)[threadIdx.x & 63];
   const bool large = !(x.x <= SWEEP_SHIFT && x.y <= SWEEP_SHIFT && x.z <= SWEEP_SHIFT && x.w <= SWEEP_SHIFT);
   const bool open = x.x > SWEEP_SHIFT_SURE || x.y > SWEEP_SHIFT_SURE || x.z > SWEEP_SHIFT_SURE || x.w > SWEEP_SHIFT_SURE;
   if (__builtin_amdgcn_ballot_w64(large) != 0) return SWEEP_TOO_LARGE;
-  return __builtin_amdgcn_ballot_w64(open) != 0 ? SWEEP_OPEN : SWEEP_FITS;
+  return long_v || __builtin_amdgcn_ballot_w64(open) != 0 ? SWEEP_OPEN : SWEEP_FITS;
 }
 
 // Two kernels per list length, of which the one that the table's flag does not ask for returns at once: both forms in one
@@ -791,9 +805,9 @@ struct AnySweepEpilogue {
   static constexpr int ROWS = OWN_U ? SWEEP_OWN_ROWS : BN;
   static __device__ __forceinline__ bool skip(const GemmArgs& p) {
     if (OWN_U) {
-      if (p.sampled == nullptr) return false;   // (the host launches the general form only)
+      if (p.only_general) return false;   // (the host launches no other)
       const bool exceeded = GENERAL && *p.exceeded != 0;
-      int says = sweep_sample_says(p.sampled);
+      int says = sweep_sample_says(p.sampled, false);
       if (says == SWEEP_OPEN) {
         bool large = false;
 #pragma unroll

@@ -106,7 +106,7 @@ __global__ __launch_bounds__(256) void ll_norm_panel_kernel(const uint16_t* __re
 // The same for a sweep whose kernel forms u itself.  Behind the row of zeros three rows whose sum is v: what is cut off it at 8, 16 and 24
 // bits, so that nothing is lost (of an infinity or what is no number the first row has it, the others zero).  And the first
 // n_waves wavefronts (SWEEP_SAMPLED, or none) look at `samples` rows of W_U, spread over the vocabulary, up to SAMPLE_ROWS each at once:
-// sampled[w] is the largest |alpha u| of wavefront w's, NaN once one is.
+// sampled[w] is the largest |alpha u| of wavefront w's, NaN once one is.  (And sampled[SWEEP_SAMPLED], see sweep_sample_says.)
 constexpr int SAMPLE_ROWS = 8;
 
 template <int NITER>
@@ -157,6 +157,19 @@ __global__ __launch_bounds__(256) void ll_sweep_panel_kernel(const uint16_t* __r
     return;
   }
   const int part = row - rows - 1;
+  if (part == 0) {   // the direction's length beside gamma's, which is that of a normalised row
+    float vv = 0.f, gg = 0.f;
+    for (int c = lane; c < n16; c += 64) {
+      const float4 a = v4[2 * c], b = v4[2 * c + 1];
+      vv += (a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w) + (b.x * b.x + b.y * b.y + b.z * b.z + b.w * b.w);
+      float g0 = 0.f, g1 = 0.f;
+      if (gamma != nullptr) accum_sq(reinterpret_cast<const uint4*>(gamma)[c], g0, g1);
+      gg += gamma != nullptr ? g0 + g1 : 8.f;
+    }
+    vv = wave_sum(vv);
+    gg = wave_sum(gg);
+    if (lane == 0) sampled[SWEEP_SAMPLED] = alpha_most * alpha_most * vv / (SWEEP_LONG * SWEEP_LONG * gg);
+  }
   uint4* const dst = reinterpret_cast<uint4*>(panel + (int64_t)row * lda);
   const auto cut = [&](float x) -> uint32_t {
     const uint32_t first = __float_as_uint(x) & 0xffff0000u;
@@ -208,10 +221,13 @@ typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
 template <bool STREAM>
 __global__ __launch_bounds__(256) void ll_unembed_direction_kernel(const uint16_t* __restrict__ W, const float* __restrict__ v,
                                                                    int V, int d, float scale, float* __restrict__ u, int n_padded,
-                                                                   float* __restrict__ block_max, const float* __restrict__ sampled) {
+                                                                   float* __restrict__ block_max, const float* __restrict__ sampled,
+                                                                   bool only_general, int* __restrict__ given) {
   extern __shared__ __align__(16) float sv[];
-  if (sampled != nullptr) {   // a look ahead of a kernel that forms u itself: only where the sample leaves open which form it is to be
-    if (sweep_sample_says(sampled) != SWEEP_OPEN) return;   // (every wavefront for itself: v may take all the LDS)
+  if (sampled != nullptr) {   // a look ahead of a kernel that forms u itself: only where the sample asks for it
+    const bool wanted = sweep_sample_says(sampled, only_general) != SWEEP_FITS;   // (every wavefront for itself: v may take all the LDS)
+    if (blockIdx.x == 0 && threadIdx.x == 0) *given = wanted ? 1 : 0;
+    if (!wanted) return;
   }
   for (int j = threadIdx.x; j < d; j += blockDim.x) sv[j] = v[j];
   __syncthreads();
@@ -1104,14 +1120,14 @@ SweepPlan make_sweep_plan(const ll_shape* s, int n_alpha, int k = 1, bool whole 
   p.off_block_max = take(UD_BLOCKS * sizeof(float));
   p.off_project = off;
   if (whole) {
-    p.off_sampled = take(SWEEP_SAMPLED * sizeof(float));
+    p.off_sampled = take((SWEEP_SAMPLED + 1) * sizeof(float));
   } else {
     p.off_eu = take((size_t)p.n_padded * 2 * SWEEP_ROWS * sizeof(float));
     p.off_shift = take((size_t)p.n_padded * sizeof(float));
     p.off_shift_min = take((size_t)p.n_padded * sizeof(float));
     p.off_shift_tile = take((size_t)tiles * 16 * sizeof(float));
   }
-  p.off_general = take(sizeof(int));
+  p.off_general = take(2 * sizeof(int));   // (and whether u is given)
   p.off_bound = take(rows * n_alpha * k * sizeof(unsigned));
   p.off_stats = take(partials * n_alpha * sizeof(float4));
   p.off_ztgt = take(partials * sizeof(float));
@@ -1232,7 +1248,7 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     if (const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(direction), (size_t)SWEEP_MAX_D * sizeof(float)); rc != LL_OK) return rc;
   if (!whole) {
     hipLaunchKernelGGL(direction, dim3(UD_BLOCKS), dim3(256), v_bytes, stream, static_cast<const uint16_t*>(W_U), v, V, d,
-                       as_projection ? al.a[0] : 1.0f, u, plan.n_padded, block_max, (const float*)nullptr);
+                       as_projection ? al.a[0] : 1.0f, u, plan.n_padded, block_max, (const float*)nullptr, false, (int*)nullptr);
     LL_CHECK_S(hipGetLastError());
   }
   // (The few-rows kernel then reads W_U through the caches where the direction kernel has just left it in the Infinity Cache, with room
@@ -1277,11 +1293,9 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
       launch_sweep_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, d, plan.lda, eps, bound, only_general ? 0 : n_alpha * k,
                          static_cast<const uint16_t*>(W_U), V, v, alpha_most, sample_waves, samples, sampled, general, stream);
       LL_CHECK_S(hipGetLastError());
-      if (!only_general) {
-        hipLaunchKernelGGL(direction, dim3(UD_BLOCKS), dim3(256), v_bytes, stream, static_cast<const uint16_t*>(W_U), v, V, d, 1.0f, u, plan.n_padded,
-                           block_max, (const float*)sampled);
-        LL_CHECK_S(hipGetLastError());
-      }
+      hipLaunchKernelGGL(direction, dim3(UD_BLOCKS), dim3(256), v_bytes, stream, static_cast<const uint16_t*>(W_U), v, V, d, 1.0f, u, plan.n_padded,
+                         block_max, (const float*)sampled, only_general, general + 1);
+      LL_CHECK_S(hipGetLastError());
     } else if (need_panel) {
       launch_norm_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, 1, d, plan.lda, eps, nullptr, 0, stream);
       LL_CHECK_S(hipGetLastError());
@@ -1303,7 +1317,9 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     a.group_rows = group_rows(a.row_blocks, a.splits);
     a.u = a.u_out = u;
     a.exceeded = general;
-    a.sampled = only_general ? nullptr : sampled;
+    a.sampled = sampled;
+    a.given = general + 1;
+    a.only_general = only_general ? 1 : 0;
     a.block_max = block_max;
     a.alpha_most = alpha_most;
     a.eu = eu;

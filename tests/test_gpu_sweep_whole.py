@@ -113,3 +113,32 @@ def test_captured_and_replayed():
         graph.replay()
         torch.cuda.synchronize()
         assert all(torch.equal(x, y) for x, y in zip(out, want))
+
+
+@pytest.mark.parametrize("d,n_alpha,length", [
+    (4096, 3, 34.0),    # the general form, which takes u from the direction kernel here
+    (1024, 9, 17.0),    # the factored one
+    (1024, 9, 1.6),     # 0.2 of the rows' length: u of the contraction
+    (4096, 9, 1.0),
+])
+def test_a_long_direction_adds_no_error(d, n_alpha, length):
+    """Against 64 bits, rows given as bf16: the target's log-probability is no further off than with u from a pass of its own, but for
+    the fiftieth that sums of the contraction's kind add where |alpha v| is a fifth of the rows' length (and as much for chance)."""
+    say(f"whole sweep, error d={d} A={n_alpha} length={length}")
+    N, V = 256, 50257
+    g = torch.Generator(device=DEV).manual_seed(9)
+    h = torch.randn((N, d), generator=g, device=DEV).to(torch.bfloat16)
+    W = (0.02 * torch.randn((V, d), generator=g, device=DEV)).to(torch.bfloat16)
+    v = direction(d) * length
+    alphas = [4.0 * (2.0 * a / (n_alpha - 1) - 1.0) for a in range(n_alpha)]
+    target = torch.randint(0, V, (N,), generator=g, device=DEV, dtype=torch.int32)
+    within, before = both(h, None, W, v, alphas, target, None)
+    Wt = W.double().t().contiguous()
+    z, u = h[:253].double() @ Wt, v.double() @ Wt
+    off = [[], []]
+    for a, alpha in enumerate(alphas):
+        q = torch.log_softmax(z + alpha * u, -1).gather(1, target[:253].long()[:, None])[:, 0]
+        for o, got in zip(off, (within, before)):
+            o.append(got[2][a].double() - q)
+    rms = [float(torch.stack(o).square().mean().sqrt()) for o in off]
+    assert rms[0] <= 1.04 * rms[1], rms

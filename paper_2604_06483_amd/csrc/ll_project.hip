@@ -924,7 +924,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
 
   // Few rows: one read of W_U.  Whole call, us, here / on the 256-row tiles: d = 8192, V = 128256, k = 20: 1 row 331 / 480, 81 rows
   // 348 / 490, 97 to 128 rows (two rounds of workgroups) 460 / 495; d = 2560, V = 151936, k = 10: 37 rows 145 / 245, 128 rows 228 /
-  // 275; 64 rows of d = 256, V = 4096: 19 / 49.  Past 128 rows the accumulators do not fit and the 256-row tiles are the better split.
+  // 275; 64 rows of d = 256, V = 4096: 13 / 49.  Past 128 rows the accumulators do not fit and the 256-row tiles are the better split.
   if (few_rows) {
     const FewPlan& few = plan.few;
     uint16_t* few_panel = reinterpret_cast<uint16_t*>(ws + plan.few_off_panel);

@@ -530,6 +530,9 @@ __device__ __forceinline__ GemmArgs sweep_args() {
   p.given = args->given;
   p.exceeded = args->exceeded;
   p.alpha_most = args->alpha_most;
+  p.W = args->W;
+  p.direction = args->direction;
+  p.d = args->d;
   p.n_alpha = args->n_alpha;
   p.zero_alpha = args->zero_alpha;
   return p;
@@ -692,6 +695,55 @@ __device__ __forceinline__ void sweep_announce(f32x4 (&acc)[16][4], SweepState<K
   asm volatile("" ::: "memory");
 }
 
+// What the contraction's sums leave of u is exact enough beside the logits' own sums, but not for a token whose unembedding row lies along the
+// direction: its products have one sign, its u is many times the others', and every partial sum on the way rounds in that size (a token
+// shifted by 13, d = 4096, |alpha v| a sixteenth of the rows' length: its log-probability was off by 2.0e-6 rms where u from the direction kernel
+// leaves 1.1e-6, the entropy by 2.4e-6 | 1.2e-6).  So u of a token that has SWEEP_ODD times the mean |u| of its tile (six standard deviations of
+// Gaussian ones; of a tile at most 34) is summed as the direction kernel sums it, to the same bits: one wavefront a token, 1.5 us.
+constexpr float SWEEP_ODD = 7.5f;
+__device__ __forceinline__ void sweep_exact_u(float (&u4)[4], int v0, const GemmArgs& p, unsigned char* lds) {
+  const int lane = fresh_lane(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const float there = (float)min(BM, p.V - v0), limit = SWEEP_ODD * wave_sum((fabsf(u4[0]) + fabsf(u4[1])) + (fabsf(u4[2]) + fabsf(u4[3])));
+  const auto odd = [&](int q) { return there * fabsf(u4[q]) > limit; };   // (of an infinity, and in its tile, and of what is no number: never)
+  if (__builtin_amdgcn_ballot_w64(odd(0) || odd(1) || odd(2) || odd(3)) == 0) return;   // (the same in all four wavefronts)
+  __syncthreads();   // the parts are read
+  const float4* const v4 = reinterpret_cast<const float4*>(p.direction);
+  int n = 0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    unsigned long long left = __builtin_amdgcn_ballot_w64(odd(q));
+#pragma unroll 1
+    for (; left != 0; left &= left - 1) {
+      if ((n++ & 3) != wave) continue;
+      const int id = 64 * q + __builtin_ctzll(left);
+      const uint4* const row = reinterpret_cast<const uint4*>(p.W + (int64_t)(v0 + id) * p.d);
+      float a = 0.f;
+#pragma unroll 1
+      for (int c = lane; c < p.d >> 3; c += 64) {
+        const uint4 x = row[c];
+        const float4 v0 = v4[2 * c], v1 = v4[2 * c + 1];
+        a = fmaf(bf16_lo(x.x), v0.x, a);
+        a = fmaf(bf16_hi(x.x), v0.y, a);
+        a = fmaf(bf16_lo(x.y), v0.z, a);
+        a = fmaf(bf16_hi(x.y), v0.w, a);
+        a = fmaf(bf16_lo(x.z), v1.x, a);
+        a = fmaf(bf16_hi(x.z), v1.y, a);
+        a = fmaf(bf16_lo(x.w), v1.z, a);
+        a = fmaf(bf16_hi(x.w), v1.w, a);
+      }
+      a = wave_sum(a);
+      if (lane == 0) *reinterpret_cast<float*>(lds + SWEEP_HALF + 4 * id) = a;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q)
+    if (odd(q)) {
+      u4[q] = *reinterpret_cast<const float*>(lds + SWEEP_HALF + 4 * (64 * q + lane));
+      asm volatile("" : "+v"(u4[q]));   // (or the compiler makes this load and the caller's from memory one that can do both)
+    }
+}
+
 // u of the tile, entry 64 q + l in lane l, from the three rows of the direction in the last wavefront's accumulators.  v is the
 // sum of three bf16 rows to the last bit (but for what is below the smallest normal number), so u = W v1 + W v2 + W v3 has the exact products that fp32 ones of W and v round.  An infinity of W
 // against a zero of v2 or v3 would be no number: where the first part is not finite it is u.  FACTORED: whether the factored form has to be given up,
@@ -727,6 +779,8 @@ __device__ __forceinline__ bool sweep_own_u(f32x4 (&acc)[16][4], int v0, const G
   if (given) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) u4[q] = p.u[v0 + 64 * q + lane];
+  } else {
+    sweep_exact_u(u4, v0, p, lds);
   }
 #pragma unroll
   for (int q = 0; q < 4; ++q) large = large || !(p.alpha_most * fabsf(u4[q]) <= SWEEP_SHIFT);

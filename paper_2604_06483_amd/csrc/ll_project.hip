@@ -1316,6 +1316,7 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     a.splits = sweep_splits(rows, tiles, block_rows);
     a.group_rows = group_rows(a.row_blocks, a.splits);
     a.u = a.u_out = u;
+    a.direction = v;
     a.exceeded = general;
     a.sampled = sampled;
     a.given = general + 1;

@@ -142,3 +142,31 @@ def test_a_long_direction_adds_no_error(d, n_alpha, length):
             o.append(got[2][a].double() - q)
     rms = [float(torch.stack(o).square().mean().sqrt()) for o in off]
     assert rms[0] <= 1.04 * rms[1], rms
+
+
+@pytest.mark.parametrize("d,n_alpha,shift", [(2048, 9, 13.0), (2056, 9, 12.0), (4096, 9, 13.0), (4096, 3, 13.0)])
+def test_a_token_along_the_direction_adds_no_error(d, n_alpha, shift):
+    """Against 64 bits, eight tokens that the sample misses and whose unembedding rows lie along the direction, in a vocabulary whose u are
+    small: what is off in their log-probabilities and in the entropy is no more than with u from a pass of its own."""
+    say(f"whole sweep, along the direction d={d} A={n_alpha} shift={shift}")
+    N, V = 256, 50257
+    g = torch.Generator(device=DEV).manual_seed(19)
+    h = torch.randn((N, d), generator=g, device=DEV).to(torch.bfloat16)
+    W = (0.02 * torch.randn((V, d), generator=g, device=DEV)).to(torch.bfloat16)
+    v = direction(d) * (0.015 * d ** 0.5)
+    tokens = torch.arange(8, device=DEV) * 32 * 190 + 1000        # (the sample is one row in 32, from 0 on)
+    W[tokens] += (v * (shift / 4.0 / float(v.square().sum()))).to(torch.bfloat16)
+    alphas = [4.0 * (2.0 * a / (n_alpha - 1) - 1.0) for a in range(n_alpha)]
+    target = tokens[torch.arange(N, device=DEV) % 8].to(torch.int32)
+    within, before = both(h, None, W, v, alphas, target, None)
+    Wt = W.double().t().contiguous()
+    z, u = h[:253].double() @ Wt, v.double() @ Wt
+    off = [[], []]
+    for a, alpha in enumerate(alphas):
+        q = torch.log_softmax(z + alpha * u, -1)
+        entropy, q = -(q.exp() * q).sum(-1), q.gather(1, target[:253].long()[:, None])[:, 0]
+        for o, got in zip(off, (within, before)):
+            o.append(torch.stack([got[2][a].double() - q, got[3][a].double() - entropy]))
+    rms = [torch.stack(o, 1).square().mean((1, 2)).sqrt().tolist() for o in off]
+    # (two sums of the same logits in fp32, 253 rows and eight tokens: a tenth for chance)
+    assert all(x <= 1.1 * y for x, y in zip(*rms)), rms

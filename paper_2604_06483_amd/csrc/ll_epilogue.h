@@ -47,8 +47,8 @@ struct GemmArgs {
   // sweeps that form u themselves (see ll_epilogue_sweep.h):
   float* u_out;             // u for the merge, [tiles * BM]
   int* exceeded;            // set once some |alpha u| turns out too large for the factored form
-  const float* sampled;     // the largest |alpha u| of some vocabulary rows in SWEEP_SAMPLED parts; behind them how long the direction is (see sweep_sample_says)
-  const float* block_max;   // and where that leaves open whether some are too large: the largest |u| of all, in SWEEP_BLOCK_MAX parts
+  const float* sampled;     // the largest |alpha u| of some vocabulary rows in SWEEP_SAMPLED parts
+  const float* block_max;   // where u is given: the largest |u| of all, in SWEEP_BLOCK_MAX parts
   const float* direction;   // v
   const int* given;         // nonzero: u is there already (ll_unembed_direction_kernel), and is taken from there
   int only_general;         // the general form in any case

@@ -60,7 +60,7 @@ constexpr int SWEEP_KS = LL_SWEEP_KMAX;
 constexpr float SWEEP_SHIFT = 20.0f;
 constexpr float SWEEP_SHIFT_SURE = 0.7f * SWEEP_SHIFT;   // while a sample's largest shift is no more, the largest of all is taken to be below SWEEP_SHIFT
 constexpr int SWEEP_SAMPLED = 256, SWEEP_BLOCK_MAX = NUM_CU * 4;   // parts of the sample, and of the largest |u|
-constexpr float SWEEP_LONG = 0.2f;                         // longest alpha v, of the rows' length, whose u the contraction forms (see sweep_sample_says)
+constexpr float SWEEP_LONG = 0.1f;                         // longest alpha v, of the shortest row's length, whose u the contraction forms (see sweep_is_long)
 constexpr float SWEEP_MARGIN = 2.0f * SWEEP_SHIFT * 0x1p-22f;   // more than the rounding of a shift up to SWEEP_SHIFT, and of a limit's own
 constexpr int SWEEP_GROUP = 16;
 constexpr unsigned SWEEP_NO_ID = 0xffffu;         // list entry that stands for "below the row's shared bound"
@@ -833,21 +833,34 @@ __device__ __forceinline__ void sweep_group_shifts(const float (&u4)[4], float (
   }
 }
 
-// What a sample of the shifts says of all (for a wavefront; one load a lane, so that a kernel that is not the one returns soon).  Open is
-// also a direction that is long beside the rows (sampled[SWEEP_SAMPLED]: the square of its length over that of gamma, times the largest alpha's, over
-// SWEEP_LONG's square; not above 1, or not a number): u as the contraction's accumulators sum it is off by 6e-7 of its root mean square, as
-// their logits are of theirs, and the direction kernel's, of shorter sums, by a fifth of that.  Up to SWEEP_LONG that adds a fiftieth to the shifted
-// logits' error; where |alpha v| was twice the rows' length it doubled the target's log-probabilities' (250 rows, d = 4096: 7.3e-7 | 13.1e-7 rms).
+// What a sample of the shifts says of all (for a wavefront; one load a lane, so that a kernel that is not the one returns soon).
 enum { SWEEP_FITS, SWEEP_OPEN, SWEEP_TOO_LARGE };
-__device__ __forceinline__ int sweep_sample_says(const float* sampled, bool only_general) {
+__device__ __forceinline__ int sweep_sample_says(const float* sampled) {
   static_assert(SWEEP_SAMPLED == 256, "four a lane");
-  const bool long_v = !(sampled[SWEEP_SAMPLED] <= 1.f);
-  if (only_general) return long_v ? SWEEP_OPEN : SWEEP_FITS;
   const float4 x = reinterpret_cast<const float4*>(sampled)[threadIdx.x & 63];
   const bool large = !(x.x <= SWEEP_SHIFT && x.y <= SWEEP_SHIFT && x.z <= SWEEP_SHIFT && x.w <= SWEEP_SHIFT);
   const bool open = x.x > SWEEP_SHIFT_SURE || x.y > SWEEP_SHIFT_SURE || x.z > SWEEP_SHIFT_SURE || x.w > SWEEP_SHIFT_SURE;
   if (__builtin_amdgcn_ballot_w64(large) != 0) return SWEEP_TOO_LARGE;
-  return long_v || __builtin_amdgcn_ballot_w64(open) != 0 ? SWEEP_OPEN : SWEEP_FITS;
+  return __builtin_amdgcn_ballot_w64(open) != 0 ? SWEEP_OPEN : SWEEP_FITS;
+}
+// Whether the direction is long beside the shortest row (sampled[SWEEP_SAMPLED]: |alpha v|^2 of the largest alpha over SWEEP_LONG^2; row_sq: the rows'
+// squares).  u as the contraction's accumulators sum it is off by 6e-7 of its root mean square, as their logits are of theirs, and the direction
+// kernel's, of shorter sums, by a fifth of that.  Up to SWEEP_LONG the shifted logits are as exact as before, to what can be measured: rms errors of
+// log-probabilities and entropies against 64 bits 0.994 to 1.003 times those with the direction kernel's u (d = 1024 and 4096, lengths of 0.03 to
+// 0.1); at 0.19 up to 1.006, at twice the rows' length 1.8; rows of a twentieth of that length beside the same direction 1.015.
+__device__ __forceinline__ bool sweep_is_long(const float* sampled, const float* row_sq, int rows) {
+  const float length = sampled[SWEEP_SAMPLED];
+  const int fours = (rows + 3) / 4;   // (behind the last row infinities)
+  float shortest = INFINITY;          // (a row of what is no number has no say)
+  for (int i = threadIdx.x & 63; i < fours; i += 512) {
+    float4 x[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = reinterpret_cast<const float4*>(row_sq)[min(i + 64 * j, fours - 1)];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) shortest = fminf(fminf(fminf(shortest, x[j].x), fminf(x[j].y, x[j].z)), x[j].w);
+  }
+  shortest = -wave_max(-shortest);
+  return !(length <= shortest);
 }
 
 // Two kernels per list length, of which the one that the table's flag does not ask for returns at once: both forms in one
@@ -861,8 +874,8 @@ struct AnySweepEpilogue {
     if (OWN_U) {
       if (p.only_general) return false;   // (the host launches no other)
       const bool exceeded = GENERAL && *p.exceeded != 0;
-      int says = sweep_sample_says(p.sampled, false);
-      if (says == SWEEP_OPEN) {
+      int says = sweep_sample_says(p.sampled);
+      if (*(const int __attribute__((address_space(4)))*)(uintptr_t)p.given != 0) {   // the direction kernel has seen all
         bool large = false;
 #pragma unroll
         for (int i = 0; i < SWEEP_BLOCK_MAX / 256; ++i) {

@@ -44,10 +44,11 @@ __device__ __forceinline__ float sticky_max(float a, float b) { return (a != a |
 // panel's row stride; gamma == nullptr copies the rows unchanged.  One wavefront per row; the
 // row stays in registers between the statistic and the write when it fits.
 // ---------------------------------------------------------------------------------------
-template <int NITER>
+// SQUARES: and row_sq[row] the sum of the squares of what was written.
+template <int NITER, bool SQUARES = false>
 __device__ __forceinline__ void norm_panel_row(const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ gamma,
                                                uint16_t* __restrict__ panel, int row, int rows, int d, int64_t lda, float eps,
-                                               unsigned* __restrict__ bound, int bounds) {
+                                               unsigned* __restrict__ bound, int bounds, float* __restrict__ row_sq = nullptr) {
   const int lane = threadIdx.x & 63;
   const int n16 = d >> 3;
   const int n16_pad = (int)(lda >> 3);
@@ -59,7 +60,7 @@ __device__ __forceinline__ void norm_panel_row(const uint16_t* __restrict__ hidd
   if (bound != nullptr && lane < bounds) bound[(int64_t)lane * rows + row] = 0u;   // the row's shared top-k bounds, before the pass that uses them
   const uint4* src = reinterpret_cast<const uint4*>(hidden + (int64_t)row * d);
   const uint4* g4 = reinterpret_cast<const uint4*>(gamma);
-  float acc0 = 0.f, acc1 = 0.f;
+  float acc0 = 0.f, acc1 = 0.f, sq0 = 0.f, sq1 = 0.f;
   auto emit = [&](int c, const uint4 q, const uint4 g, float inv) {
     const uint32_t hw[4] = {q.x, q.y, q.z, q.w};
     const uint32_t gw[4] = {g.x, g.y, g.z, g.w};
@@ -67,10 +68,16 @@ __device__ __forceinline__ void norm_panel_row(const uint16_t* __restrict__ hidd
 #pragma unroll
     for (int i = 0; i < 4; ++i)
       ow[i] = pack_bf16(bf16_lo(hw[i]) * inv * bf16_lo(gw[i]), bf16_hi(hw[i]) * inv * bf16_hi(gw[i]));
-    dst[c] = make_uint4(ow[0], ow[1], ow[2], ow[3]);
+    const uint4 out = make_uint4(ow[0], ow[1], ow[2], ow[3]);
+    dst[c] = out;
+    if (SQUARES) accum_sq(out, sq0, sq1);
   };
   if (gamma == nullptr) {
-    for (int c = lane; c < n16; c += 64) dst[c] = src[c];
+    for (int c = lane; c < n16; c += 64) {
+      const uint4 q = src[c];
+      dst[c] = q;
+      if (SQUARES) accum_sq(q, sq0, sq1);
+    }
   } else if (NITER > 0) {
     // all loads of the row and of gamma before the first use, chunks past the end at the last one (their squares count as zero)
     uint4 cache[NITER > 0 ? NITER : 1], g[NITER > 0 ? NITER : 1];
@@ -91,6 +98,10 @@ __device__ __forceinline__ void norm_panel_row(const uint16_t* __restrict__ hidd
     for (int c = lane; c < n16; c += 64) emit(c, src[c], g4[c], inv);
   }
   for (int c = n16 + lane; c < n16_pad; c += 64) dst[c] = make_uint4(0, 0, 0, 0);
+  if (SQUARES) {
+    const float sq = wave_sum(sq0 + sq1);
+    if (lane == 0) row_sq[row] = sq;
+  }
 }
 
 template <int NITER>
@@ -106,7 +117,8 @@ __global__ __launch_bounds__(256) void ll_norm_panel_kernel(const uint16_t* __re
 // The same for a sweep whose kernel forms u itself.  Behind the row of zeros three rows whose sum is v: what is cut off it at 8, 16 and 24
 // bits, so that nothing is lost (of an infinity or what is no number the first row has it, the others zero).  And the first
 // n_waves wavefronts (SWEEP_SAMPLED, or none) look at `samples` rows of W_U, spread over the vocabulary, up to SAMPLE_ROWS each at once:
-// sampled[w] is the largest |alpha u| of wavefront w's, NaN once one is.  (And sampled[SWEEP_SAMPLED], see sweep_sample_says.)
+// sampled[w] is the largest |alpha u| of wavefront w's, NaN once one is.  What tells a long direction (see sweep_is_long): sampled[SWEEP_SAMPLED]
+// from the direction, row_sq from the rows.
 constexpr int SAMPLE_ROWS = 8;
 
 template <int NITER>
@@ -114,7 +126,8 @@ __global__ __launch_bounds__(256) void ll_sweep_panel_kernel(const uint16_t* __r
                                                              uint16_t* __restrict__ panel, int rows, int d, int64_t lda, float eps,
                                                              unsigned* __restrict__ bound, int bounds, const uint16_t* __restrict__ W, int V,
                                                              const float* __restrict__ v, float alpha_most, int n_waves, int samples,
-                                                             float* __restrict__ sampled, int* __restrict__ exceeded) {
+                                                             float* __restrict__ sampled, float* __restrict__ row_sq,
+                                                             int* __restrict__ exceeded) {
   const int lane = threadIdx.x & 63, n16 = d >> 3;
   int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   const float4* const v4 = reinterpret_cast<const float4*>(v);
@@ -150,25 +163,26 @@ __global__ __launch_bounds__(256) void ll_sweep_panel_kernel(const uint16_t* __r
     return;
   }
   row -= n_waves;
-  if (row > rows + SWEEP_PARTS) return;
+  if (row > rows + SWEEP_PARTS + 1) return;
   if (row <= rows) {
-    if (row == rows && lane == 0) *exceeded = 0;
-    norm_panel_row<NITER>(hidden, gamma, panel, row, rows, d, lda, eps, bound, bounds);
+    if (row == rows && lane == 0) {
+      *exceeded = 0;
+      for (int i = 0; i < 3; ++i) row_sq[rows + i] = INFINITY;
+    }
+    norm_panel_row<NITER, true>(hidden, gamma, panel, row, rows, d, lda, eps, bound, bounds, row_sq);
     return;
   }
   const int part = row - rows - 1;
-  if (part == 0) {   // the direction's length beside gamma's, which is that of a normalised row
-    float vv = 0.f, gg = 0.f;
-    for (int c = lane; c < n16; c += 64) {
-      const float4 a = v4[2 * c], b = v4[2 * c + 1];
-      vv += (a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w) + (b.x * b.x + b.y * b.y + b.z * b.z + b.w * b.w);
-      float g0 = 0.f, g1 = 0.f;
-      if (gamma != nullptr) accum_sq(reinterpret_cast<const uint4*>(gamma)[c], g0, g1);
-      gg += gamma != nullptr ? g0 + g1 : 8.f;
+  if (part == SWEEP_PARTS) {   // a wavefront of its own for the direction's length
+    float vv = 0.f;
+#pragma unroll 4
+    for (int c = lane; c < 2 * n16; c += 64) {
+      const float4 a = v4[c];
+      vv += a.x * a.x + a.y * a.y + a.z * a.z + a.w * a.w;
     }
     vv = wave_sum(vv);
-    gg = wave_sum(gg);
-    if (lane == 0) sampled[SWEEP_SAMPLED] = alpha_most * alpha_most * vv / (SWEEP_LONG * SWEEP_LONG * gg);
+    if (lane == 0) sampled[SWEEP_SAMPLED] = alpha_most * alpha_most * vv * (1.0f / (SWEEP_LONG * SWEEP_LONG));
+    return;
   }
   uint4* const dst = reinterpret_cast<uint4*>(panel + (int64_t)row * lda);
   const auto cut = [&](float x) -> uint32_t {
@@ -222,12 +236,18 @@ template <bool STREAM>
 __global__ __launch_bounds__(256) void ll_unembed_direction_kernel(const uint16_t* __restrict__ W, const float* __restrict__ v,
                                                                    int V, int d, float scale, float* __restrict__ u, int n_padded,
                                                                    float* __restrict__ block_max, const float* __restrict__ sampled,
-                                                                   bool only_general, int* __restrict__ given) {
+                                                                   const float* __restrict__ row_sq, int rows, bool only_general,
+                                                                   int* __restrict__ given) {
   extern __shared__ __align__(16) float sv[];
-  if (sampled != nullptr) {   // a look ahead of a kernel that forms u itself: only where the sample asks for it
-    const bool wanted = sweep_sample_says(sampled, only_general) != SWEEP_FITS;   // (every wavefront for itself: v may take all the LDS)
-    if (blockIdx.x == 0 && threadIdx.x == 0) *given = wanted ? 1 : 0;
-    if (!wanted) return;
+  if (sampled != nullptr) {   // a look ahead of a kernel that forms u itself: only where it is asked for
+    if (threadIdx.x < 64) {
+      const bool wanted = sweep_is_long(sampled, row_sq, rows) || (!only_general && sweep_sample_says(sampled) != SWEEP_FITS);
+      if (threadIdx.x == 0) sv[0] = wanted ? 1.f : 0.f;   // (v may take all the LDS)
+      if (blockIdx.x == 0 && threadIdx.x == 0) *given = wanted ? 1 : 0;
+    }
+    __syncthreads();
+    if (sv[0] == 0.f) return;
+    __syncthreads();
   }
   for (int j = threadIdx.x; j < d; j += blockDim.x) sv[j] = v[j];
   __syncthreads();
@@ -809,15 +829,15 @@ void launch_norm_panel(const uint16_t* hidden, const uint16_t* gamma, uint16_t* 
 
 void launch_sweep_panel(const uint16_t* hidden, const uint16_t* gamma, uint16_t* panel, int rows, int d, int64_t lda, float eps,
                         unsigned* bound, int bounds, const uint16_t* W, int V, const float* v, float alpha_most, int n_waves, int samples,
-                        float* sampled, int* exceeded, hipStream_t stream) {
+                        float* sampled, float* row_sq, int* exceeded, hipStream_t stream) {
   const int per_block = rows <= 1024 ? 1 : 4;
-  const dim3 grid((unsigned)((n_waves + rows + 1 + SWEEP_PARTS + per_block - 1) / per_block)), block(64 * per_block);
+  const dim3 grid((unsigned)((n_waves + rows + 1 + SWEEP_PARTS + 1 + per_block - 1) / per_block)), block(64 * per_block);
   const auto kernel = d <= 64 * 8 * 4    ? ll_sweep_panel_kernel<4>
                       : d <= 64 * 8 * 8  ? ll_sweep_panel_kernel<8>
                       : d <= 64 * 8 * 16 ? ll_sweep_panel_kernel<16>
                                          : ll_sweep_panel_kernel<0>;
   hipLaunchKernelGGL(kernel, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps, bound, bounds, W, V, v, alpha_most, n_waves, samples,
-                     sampled, exceeded);
+                     sampled, row_sq, exceeded);
 }
 
 int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, const void* hidden, const void* gamma,
@@ -1086,7 +1106,7 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
 }
 
 struct SweepPlan {
-  size_t off_u, off_block_max, off_sampled, off_eu, off_shift, off_shift_min, off_shift_tile, off_general, off_bound, off_stats, off_ztgt, off_top, off_panel, total;
+  size_t off_u, off_block_max, off_sampled, off_row_sq, off_eu, off_shift, off_shift_min, off_shift_tile, off_general, off_bound, off_stats, off_ztgt, off_top, off_panel, total;
   size_t off_project, wanted;   // the projection's workspace where one alpha is left to it; wanted: what the call is fastest with
   int64_t lda;
   int n_padded;   // V in whole tiles
@@ -1121,6 +1141,7 @@ SweepPlan make_sweep_plan(const ll_shape* s, int n_alpha, int k = 1, bool whole 
   p.off_project = off;
   if (whole) {
     p.off_sampled = take((SWEEP_SAMPLED + 1) * sizeof(float));
+    p.off_row_sq = take((rows + 3) * sizeof(float));
   } else {
     p.off_eu = take((size_t)p.n_padded * 2 * SWEEP_ROWS * sizeof(float));
     p.off_shift = take((size_t)p.n_padded * sizeof(float));
@@ -1236,6 +1257,7 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
   float* shift_tile = reinterpret_cast<float*>(ws + plan.off_shift_tile);
   float* block_max = reinterpret_cast<float*>(ws + plan.off_block_max);
   float* const sampled = reinterpret_cast<float*>(ws + plan.off_sampled);
+  float* const row_sq = reinterpret_cast<float*>(ws + plan.off_row_sq);
   int* general = reinterpret_cast<int*>(ws + plan.off_general);
   unsigned* bound = reinterpret_cast<unsigned*>(ws + plan.off_bound);
   float4* stats = reinterpret_cast<float4*>(ws + plan.off_stats);
@@ -1248,7 +1270,7 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     if (const int rc = allow_dynamic_lds(reinterpret_cast<const void*>(direction), (size_t)SWEEP_MAX_D * sizeof(float)); rc != LL_OK) return rc;
   if (!whole) {
     hipLaunchKernelGGL(direction, dim3(UD_BLOCKS), dim3(256), v_bytes, stream, static_cast<const uint16_t*>(W_U), v, V, d,
-                       as_projection ? al.a[0] : 1.0f, u, plan.n_padded, block_max, (const float*)nullptr, false, (int*)nullptr);
+                       as_projection ? al.a[0] : 1.0f, u, plan.n_padded, block_max, (const float*)nullptr, (const float*)nullptr, 0, false, (int*)nullptr);
     LL_CHECK_S(hipGetLastError());
   }
   // (The few-rows kernel then reads W_U through the caches where the direction kernel has just left it in the Infinity Cache, with room
@@ -1291,10 +1313,10 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     const bool need_panel = gamma != nullptr || plan.lda != d || whole;
     if (whole) {
       launch_sweep_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, d, plan.lda, eps, bound, only_general ? 0 : n_alpha * k,
-                         static_cast<const uint16_t*>(W_U), V, v, alpha_most, sample_waves, samples, sampled, general, stream);
+                         static_cast<const uint16_t*>(W_U), V, v, alpha_most, sample_waves, samples, sampled, row_sq, general, stream);
       LL_CHECK_S(hipGetLastError());
       hipLaunchKernelGGL(direction, dim3(UD_BLOCKS), dim3(256), v_bytes, stream, static_cast<const uint16_t*>(W_U), v, V, d, 1.0f, u, plan.n_padded,
-                         block_max, (const float*)sampled, only_general, general + 1);
+                         block_max, (const float*)sampled, (const float*)row_sq, rows, only_general, general + 1);
       LL_CHECK_S(hipGetLastError());
     } else if (need_panel) {
       launch_norm_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, 1, d, plan.lda, eps, nullptr, 0, stream);

@@ -35,6 +35,9 @@ def workload(N, d, V, seed=61):
 def test_general_form_matches_oracle(N, d, V, n_alpha, k):
     say(f"whole sweep, general N={N} d={d} V={V} A={n_alpha} k={k}")
     check(N, d, V, ALPHAS9[:n_alpha], k, 1.0, "whole, general", rows=np.unique(np.r_[0:min(N, 260), N - 1]))
+    if n_alpha > 1 or N == 300:
+        w, h = workload(N, d, V)
+        assert is_whole(lambda: LL.ll_steer_sweep(h, w.gamma, w.W_U, w.cfg.eps, direction(d), ALPHAS9[:n_alpha], None, k=k))
 
 
 @pytest.mark.parametrize("k", [None, 3])
@@ -50,6 +53,13 @@ def test_factored_form_matches_oracle(N, d, V, alphas, length, k):
     check(N, d, V, alphas, k, length, "whole", rows=np.unique(np.r_[0:8, N // 2:N // 2 + 8, min(N, 256) - 8:min(N, 256), N - 8:N]))
     w, h = workload(N, d, V)
     assert is_whole(lambda: LL.ll_steer_sweep(h, w.gamma, w.W_U, w.cfg.eps, direction(d), alphas, None, k=k))
+
+
+def u_of(n, h, gamma, W, v, alphas):
+    """The u that a call of n rows leaves at the start of its workspace, as bits."""
+    ws = torch.empty(LL.ll_steer_sweep_workspace_bytes(n, h.shape[1], W.shape[0], len(alphas), 1), dtype=torch.uint8, device=DEV)
+    LL.ll_steer_sweep(h[:n].contiguous(), gamma, W, 1e-5, v, alphas, None, workspace=ws)
+    return ws[:4 * W.shape[0]].view(torch.int32).clone()
 
 
 def both(h, gamma, W, v, alphas, target, k):
@@ -115,15 +125,15 @@ def test_captured_and_replayed():
         assert all(torch.equal(x, y) for x, y in zip(out, want))
 
 
-@pytest.mark.parametrize("d,n_alpha,length", [
-    (4096, 3, 34.0),    # the general form, which takes u from the direction kernel here
-    (1024, 9, 17.0),    # the factored one
-    (1024, 9, 1.6),     # 0.2 of the rows' length: u of the contraction
-    (4096, 9, 1.0),
+@pytest.mark.parametrize("d,n_alpha,length,own", [
+    (4096, 3, 34.0, False),   # the general form, u from the direction kernel
+    (1024, 9, 17.0, False),   # the factored one
+    (1024, 9, 0.72, True), (4096, 3, 1.4, True),   # 0.09 of the rows' length: u of the contraction, in both forms
+    (4096, 9, 1.0, True),
 ])
-def test_a_long_direction_adds_no_error(d, n_alpha, length):
-    """Against 64 bits, rows given as bf16: the target's log-probability is no further off than with u from a pass of its own, but for
-    the fiftieth that sums of the contraction's kind add where |alpha v| is a fifth of the rows' length (and as much for chance)."""
+def test_a_long_direction_adds_no_error(d, n_alpha, length, own):
+    """Against 64 bits, rows given as bf16: the target's log-probability is no further off than with u from a pass of its own but
+    for what the bound below allows for chance), whichever u it is."""
     say(f"whole sweep, error d={d} A={n_alpha} length={length}")
     N, V = 256, 50257
     g = torch.Generator(device=DEV).manual_seed(9)
@@ -133,6 +143,7 @@ def test_a_long_direction_adds_no_error(d, n_alpha, length):
     alphas = [4.0 * (2.0 * a / (n_alpha - 1) - 1.0) for a in range(n_alpha)]
     target = torch.randint(0, V, (N,), generator=g, device=DEV, dtype=torch.int32)
     within, before = both(h, None, W, v, alphas, target, None)
+    assert own != torch.equal(*(u_of(n, h, None, W, v, alphas) for n in (253, 256)))
     Wt = W.double().t().contiguous()
     z, u = h[:253].double() @ Wt, v.double() @ Wt
     off = [[], []]
@@ -141,7 +152,10 @@ def test_a_long_direction_adds_no_error(d, n_alpha, length):
         for o, got in zip(off, (within, before)):
             o.append(got[2][a].double() - q)
     rms = [float(torch.stack(o).square().mean().sqrt()) for o in off]
-    assert rms[0] <= 1.04 * rms[1], rms
+    # u of the contraction has an error of its own, as large beside the logits' as alpha v is beside the rows (r): it adds r^2 / 2, and by chance,
+    # over 253 rows with a token each, up to 3 r / sqrt(253).  A u that is the same: sums in another order.
+    r = 4.0 * length / d ** 0.5
+    assert rms[0] <= (1.0 + r * r / 2 + 3.0 * r / 253 ** 0.5 if own else 1.01) * rms[1], rms
 
 
 @pytest.mark.parametrize("d,n_alpha,shift", [(2048, 9, 13.0), (2056, 9, 12.0), (4096, 9, 13.0), (4096, 3, 13.0)])
@@ -170,3 +184,34 @@ def test_a_token_along_the_direction_adds_no_error(d, n_alpha, shift):
     rms = [torch.stack(o, 1).square().mean((1, 2)).sqrt().tolist() for o in off]
     # (two sums of the same logits in fp32, 253 rows and eight tokens: a tenth for chance)
     assert all(x <= 1.1 * y for x, y in zip(*rms)), rms
+
+
+@pytest.mark.parametrize("n_alpha", [3, 9])
+@pytest.mark.parametrize("length,rows,own", [
+    (0.09, "all", True), (0.11, "all", False),
+    (0.09, "one short", False), (0.09, "one zero", False), (0.09, "short", False), (0.0045, "short", True),
+    (0.09, "gamma", True), (0.18, "gamma", True), (0.22, "gamma", False), (0.09, "eps", False), (0.0, "one zero", True),
+])
+def test_where_u_comes_from(length, rows, own, n_alpha):
+    """The contraction's u only beside rows that are ten times as long as alpha v, by the rows themselves: else the direction kernel's, to the bit."""
+    say(f"whole sweep, source of u length={length} rows={rows} A={n_alpha}")
+    N, d, V = 256, 1024, 50257
+    g = torch.Generator(device=DEV).manual_seed(29)
+    h = torch.randn((N, d), generator=g, device=DEV)
+    h /= h.square().mean(-1, keepdim=True).sqrt()
+    gamma = None
+    if rows in ("gamma", "eps"):
+        gamma = torch.full((d,), 2.0, device=DEV, dtype=torch.bfloat16)
+    if rows == "eps":
+        h[17] *= 1e-4                     # beside eps = 1e-5 next to nothing after the norm too
+    if rows == "short":
+        h *= 0.05
+    if rows.startswith("one"):
+        h[252] *= 0.5 if rows == "one short" else 0.0
+    h = h.to(torch.bfloat16)
+    W = (0.02 * torch.randn((V, d), generator=g, device=DEV)).to(torch.bfloat16)
+    v = direction(d) * (length * d ** 0.5 / 4.0)
+    alphas = [4.0 * (2.0 * a / (n_alpha - 1) - 1.0) for a in range(n_alpha)]
+    both(h, gamma, W, v, alphas, torch.zeros((N,), device=DEV, dtype=torch.int32), None)     # (which is which)
+    within, before = (u_of(n, h, gamma, W, v, alphas) for n in (253, 256))
+    assert torch.equal(within, before) == (not own or length == 0.0)

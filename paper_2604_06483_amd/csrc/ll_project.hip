@@ -1232,8 +1232,9 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     if (n_alpha > SWEEP_SPLIT_ROWS && al.a[a] == 0.f) zero_alpha = a;
   // Forming u in the contraction's own kernel saves the read of W_U before it (and the tables' kernel), takes three rows of every block, which
   // mostly are to spare, and time in every tile: 0.4 us in the general form, 2.6 in the factored one, whose wavefronts exchange parts
-  // of u and tables and wait for each other four times.  So it is for calls of few tiles a workgroup on a large W_U; three rows that make a block more count as
-  // what the busiest workgroup then does more of.  Whole calls, u before | u within, us, nine strengths, arg max (N x d x V: tiles a workgroup): 250 x 2048 x
+  // of u and tables and wait for each other four times.  So it is for calls of few tiles a workgroup on a large W_U, and never where the three rows give the
+  // busiest workgroup a tile more: whether W_U is read all the same is only known on the device (see sweep_is_long; 256 rows, d = 5120, V = 148853, two
+  // strengths, five tiles instead of three, u before | within: 648 | 591 us beside a short direction, but 628 | 786 beside a long one).  Whole calls, u before | u within, us, nine strengths, arg max (N x d x V: tiles a workgroup): 250 x 2048 x
   // 50257 (1) 133 | 98, 700 x 1024 x 50257 (3) 181 | 163, 1500 x 2048 x 50257 (5) 380 | 343, 1500 x 4096 x 128256 (12) 1386 | 1233, 4000 x 1024 x 50257 (13)
   // 602 | 614, 8000 x 2560 x 151936 (75) 5370 | 5440; lists of three: 500 x 2560 x 151936 (5) 549 | 439, 4000 x 512 x 128256 (34) 1267 | 1306; three strengths:
   // 1500 x 512 x 50257 (5) 169 | 160, 500 x 2560 x 151936 (5) 503 | 391.  A W_U of up to 64 MiB is read from the Infinity Cache
@@ -1242,10 +1243,9 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
   if (whole) {
     const int own_splits = sweep_splits((int)N, tiles, SWEEP_OWN_ROWS);
     const int own_each = (tiles + own_splits - 1) / own_splits;
-    const float tile_us = 1.15f * (float)((d + DK - 1) / DK) + (only_general ? 8.0f * n_alpha : 25.0f);
-    const float more_us = (float)(own_each - each) * tile_us + (float)own_each * (only_general ? 0.4f : 2.6f);
+    const float more_us = (float)own_each * (only_general ? 0.4f : 2.6f);
     const SweepPlan own = make_sweep_plan(shape, n_alpha, k, true);
-    whole = more_us <= (float)V * (float)d * 2.0f / 6.0e6f + 5.0f && own.total <= plan.total;
+    whole = own_each <= each && more_us <= (float)V * (float)d * 2.0f / 6.0e6f + 5.0f && own.total <= plan.total;
     if (whole) plan = own;
   }
 

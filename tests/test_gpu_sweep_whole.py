@@ -215,3 +215,14 @@ def test_where_u_comes_from(length, rows, own, n_alpha):
     both(h, gamma, W, v, alphas, torch.zeros((N,), device=DEV, dtype=torch.int32), None)     # (which is which)
     within, before = (u_of(n, h, gamma, W, v, alphas) for n in (253, 256))
     assert torch.equal(within, before) == (not own or length == 0.0)
+
+
+@pytest.mark.parametrize("N,d,V,n_alpha,expected", [
+    (256, 4096, 131072, 2, False),    # a second block for three rows: four tiles a workgroup instead of two
+    (253, 4096, 131072, 2, True), (1000, 704, 50257, 9, True),
+    (256, 704, 20000, 2, True),       # a second block, and still one tile
+])
+def test_never_a_tile_more(N, d, V, n_alpha, expected):
+    say(f"whole sweep, which N={N} d={d} V={V} A={n_alpha}")
+    w, h = workload(N, d, V)
+    assert is_whole(lambda: LL.ll_steer_sweep(h, w.gamma, w.W_U, w.cfg.eps, direction(d), ALPHAS9[:n_alpha], None)) == expected

@@ -46,12 +46,17 @@ struct GemmArgs {
   int group_rows;           // row blocks that an XCD's workgroups share W_U's tiles between (see place_of)
   // sweeps that form u themselves (see ll_epilogue_sweep.h):
   float* u_out;             // u for the merge, [tiles * BM]
-  int* exceeded;            // set once some |alpha u| turns out too large for the factored form
+  int* exceeded;            // set once the factored form turns out not to do
+  int* left_any;            // set once it leaves out a token, because of its |alpha u|, that the merge adds:
+  float* left_z;            // [rows, splits, left_slots]: the logits of those tokens
+  int* left_id;             // [row_blocks, splits, left_slots]: their ids
+  int* left_n;              // [row_blocks, splits, 4]: how many (each wavefront's own count)
   const float* sampled;     // the largest |alpha u| of some vocabulary rows in SWEEP_SAMPLED parts
   const float* block_max;   // where u is given: the largest |u| of all, in SWEEP_BLOCK_MAX parts
   const float* direction;   // v
   const int* given;         // nonzero: u is there already (ll_unembed_direction_kernel), and is taken from there
   int only_general;         // the general form in any case
+  int left_slots;           // most tokens that are left out of a split
   float alpha_most;         // largest |alpha|
 };
 

@@ -50,9 +50,10 @@ namespace {
 // W_U costs, a tenth to a fifth of the calls above: 176 and 115 us.  The contraction reads the same W_U, and its blocks mostly have rows to
 // spare: with OWN_U three rows of every block are v in three bf16 parts (ll_sweep_panel_kernel), and behind a tile's K loop
 // the last wavefront's accumulators hold the tile's u.  The four wavefronts then make the tables in LDS, in the part of the ring that is free
-// between two tiles.  Which form runs is not known before u is: a sample of W_U's rows says so where it is clear, where it is not
-// (or where v is so long that the sums' rounding would show) the direction kernel does look at all of W_U, u is taken from there, and should a shift past SWEEP_SHIFT still turn up, `exceeded` stops the
-// factored kernel at its workgroups' next tiles and the general one, launched behind it, runs.  Costs 2.6 us a tile (general form 0.4).
+// between two tiles.  Which form runs is not known before u is: a sample of W_U's rows says so where it is clear; where it is not
+// (or where v is so long that the sums' rounding would show) the direction kernel does look at all of W_U, and u is taken from there.  A
+// token that the sample has missed and whose shift is past SWEEP_SHIFT is left out, and added by the merge (SweepLeaveOut); should they be too many, or one
+// be infinite, `exceeded` has the general form, launched behind the factored one, run over all.  Costs 2.6 us a tile (general form 0.4).
 // Whole calls, u before | within: 1386 | 1233 us and 549 | 439 us.
 // ---------------------------------------------------------------------------------------
 constexpr int SWEEP_MAX = LL_SWEEP_MAX;
@@ -123,7 +124,6 @@ struct SweepState {
   unsigned li[SWEEP_MAX][IDS];
   float z_tgt;
   int tgt, id0, split;                       // id0: first id of the split
-  int given_up;                              // OWN_U: what `exceeded` was at the last tile's end
 };
 
 // Register j of lane block g <-> register g of lane block j (see load_group).
@@ -390,8 +390,8 @@ __device__ __forceinline__ void sweep_fold(f32x4& sum, f32x4& pending) {
 }
 
 // What a kernel that forms u itself keeps in LDS during a tile's epilogue: the upper half of each wavefront's 8 KB of the W slot whose
-// stage is done (halves SWEEP_CHUNK apart, from SWEEP_HALF on).  First the three parts of the tile's u, in halves 0, 1 and 2, and in half 3 a word
-// for all wavefronts; then the tables of four groups in each half.
+// stage is done (halves SWEEP_CHUNK apart, from SWEEP_HALF on).  First the three parts of the tile's u, in halves 0, 1 and 2; then the tables
+// of four groups in each half.
 constexpr int SWEEP_CHUNK = 64 * 128, SWEEP_HALF = 4096, SWEEP_TABLE = SWEEP_ROWS * SWEEP_GROUP * 4;
 static_assert(4 * SWEEP_TABLE <= SWEEP_HALF && BM * 4 <= SWEEP_HALF, "a half");
 
@@ -529,6 +529,12 @@ __device__ __forceinline__ GemmArgs sweep_args() {
   p.u_out = args->u_out;
   p.given = args->given;
   p.exceeded = args->exceeded;
+  p.left_any = args->left_any;
+  p.left_z = args->left_z;
+  p.left_id = args->left_id;
+  p.left_n = args->left_n;
+  p.left_slots = args->left_slots;
+  p.splits = args->splits;
   p.alpha_most = args->alpha_most;
   p.W = args->W;
   p.direction = args->direction;
@@ -705,7 +711,7 @@ __device__ __forceinline__ void sweep_exact_u(float (&u4)[4], int v0, const Gemm
   const int lane = fresh_lane(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const float there = (float)min(BM, p.V - v0), limit = SWEEP_ODD * wave_sum((fabsf(u4[0]) + fabsf(u4[1])) + (fabsf(u4[2]) + fabsf(u4[3])));
   const auto odd = [&](int q) { return there * fabsf(u4[q]) > limit; };   // (of an infinity, and in its tile, and of what is no number: never)
-  if (__builtin_amdgcn_ballot_w64(odd(0) || odd(1) || odd(2) || odd(3)) == 0) return;   // (the same in all four wavefronts)
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd(0) || odd(1) || odd(2) || odd(3)) == 0, 1)) return;   // (the same in all four wavefronts)
   __syncthreads();   // the parts are read
   const float4* const v4 = reinterpret_cast<const float4*>(p.direction);
   int n = 0;
@@ -746,11 +752,8 @@ __device__ __forceinline__ void sweep_exact_u(float (&u4)[4], int v0, const Gemm
 
 // u of the tile, entry 64 q + l in lane l, from the three rows of the direction in the last wavefront's accumulators.  v is the
 // sum of three bf16 rows to the last bit (but for what is below the smallest normal number), so u = W v1 + W v2 + W v3 has the exact products that fp32 ones of W and v round.  An infinity of W
-// against a zero of v2 or v3 would be no number: where the first part is not finite it is u.  FACTORED: whether the factored form has to be given up,
-// in this tile or, for all that is known, elsewhere.
-template <bool FACTORED>
-__device__ __forceinline__ bool sweep_own_u(f32x4 (&acc)[16][4], int v0, const GemmArgs& p, int my_row, int given_up, unsigned char* lds,
-                                            float (&u4)[4]) {
+// against a zero of v2 or v3 would be no number: where the first part is not finite it is u.
+__device__ __forceinline__ void sweep_own_u(f32x4 (&acc)[16][4], int v0, const GemmArgs& p, int my_row, unsigned char* lds, float (&u4)[4]) {
   const int lane = fresh_lane(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const unsigned char* const in = lds + SWEEP_HALF;
   if (wave == 3) {
@@ -762,11 +765,9 @@ __device__ __forceinline__ bool sweep_own_u(f32x4 (&acc)[16][4], int v0, const G
         *reinterpret_cast<float4*>(out + 4 * SWEEP_GROUP * g) =
             make_float4(acc_read(acc[g][3][0]), acc_read(acc[g][3][1]), acc_read(acc[g][3][2]), acc_read(acc[g][3][3]));
       });
-      if (FACTORED && lane == 63) *reinterpret_cast<int*>(lds + SWEEP_HALF + SWEEP_CHUNK * 3) = given_up;
     }
   }
   __syncthreads();
-  bool large = false;
   const bool given = *(const int __attribute__((address_space(4)))*)(uintptr_t)p.given != 0;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
@@ -776,21 +777,88 @@ __device__ __forceinline__ bool sweep_own_u(f32x4 (&acc)[16][4], int v0, const G
     const float whole = fabsf(a) < INFINITY ? a + (b + c) : a;
     u4[q] = v0 + id < p.V ? whole : 0.f;
   }
-  if (given) {
+  if (__builtin_expect(given, 0)) {
 #pragma unroll
     for (int q = 0; q < 4; ++q) u4[q] = p.u[v0 + 64 * q + lane];
   } else {
     sweep_exact_u(u4, v0, p, lds);
   }
-#pragma unroll
-  for (int q = 0; q < 4; ++q) large = large || !(p.alpha_most * fabsf(u4[q]) <= SWEEP_SHIFT);
   if (!given && __builtin_amdgcn_readfirstlane(my_row) == 64 * wave)   // the first row block's wavefronts: for the merge
     p.u_out[v0 + 64 * wave + lane] = sweep_group_register(u4, 4 * wave);
-  if (!FACTORED) return false;
-  const bool here = __builtin_amdgcn_ballot_w64(large) != 0;   // (the same in all four wavefronts)
-  if (here && threadIdx.x == 0) __hip_atomic_store(p.exceeded, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return here || __builtin_amdgcn_readfirstlane(*reinterpret_cast<const int*>(in + SWEEP_CHUNK * 3)) != 0;
 }
+
+// The factored form leaves out tokens whose shift is too large for it, up to GemmArgs' left_slots a split: their logits (and u, for the others'
+// limits and the tables) give way to what stands for none, and go to memory, from where the merge adds them to the row's sums and lists.  The sample
+// mostly misses them where they are few: the token whose unembedding row the direction lies along, or some long rows.  Whole calls with such tokens, the
+// general form over all of the call behind the factored one | left out | u and the largest shift from a pass of their own, us: 1500 rows, d = 4096, V = 128256: one
+// 1790 to 2810 by its place | 1285 | 1770, sixty 1775 | 1283 | 1740, two hundred 1750 | 1331 | 1746; lists of three, 500 x 2560 x 151936: one 910 to 1145 | 462 | 830;
+// 250 x 2048 x 50257: one 200 | 104 | 151.
+template <int KS>
+struct SweepLeaveOut {
+  unsigned long long out[4];   // bit l of word q: entry 64 q + l is left out, or past the vocabulary
+  int n, to;                   // left out, and how many of the split were before
+  // u4 of what is left out becomes zero.  Too many, or one that is no number or infinite: `exceeded`, what the kernel makes of it is for nothing.
+  __device__ __forceinline__ void look(float (&u4)[4], const SweepState<KS, false>& st, int v0, const GemmArgs& p, int my_row) {
+    const int lane = fresh_lane();
+    bool endless = false;
+    n = to = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const float shift = p.alpha_most * fabsf(u4[q]);
+      const bool large = !(shift <= SWEEP_SHIFT);
+      endless = endless || !(shift < INFINITY);
+      out[q] = __builtin_amdgcn_ballot_w64(large);
+      n += __builtin_popcountll(out[q]);
+      u4[q] = large ? 0.f : u4[q];
+      out[q] |= __builtin_amdgcn_ballot_w64(v0 + 64 * q + lane >= p.V);
+    }
+    if (__builtin_expect(n == 0, 1)) return;
+    const GemmArgs more = sweep_args();   // (read here)
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), row0 = __builtin_amdgcn_readfirstlane(my_row);
+    // (the count so far is in memory, each wavefront's by itself: all of its lanes have written what they read here)
+    int* const count = more.left_n + 4 * ((row0 / SWEEP_OWN_ROWS) * more.splits + st.split) + wave;
+    to = __builtin_amdgcn_readfirstlane(__hip_atomic_load(count, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+    if (threadIdx.x == 0) *more.left_any = 1;
+    if (__builtin_amdgcn_ballot_w64(endless) == 0 && to + n <= more.left_slots) {   // (all wavefronts alike)
+      __hip_atomic_store(count, to + n, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      return;
+    }
+    if (threadIdx.x == 0) *more.exceeded = 1;
+    n = 0;
+  }
+  template <int G>
+  __device__ __forceinline__ unsigned of_group() const { return (unsigned)(out[G / 4] >> (16 * (G % 4))) & 0xffffu; }
+  __device__ __forceinline__ void save(f32x4 (&acc)[16][4], const SweepState<KS, false>& st, int v0, int my_row) const {
+    const GemmArgs p = sweep_args();
+    const int lane = fresh_lane(), row0 = __builtin_amdgcn_readfirstlane(my_row), of_block = (int)threadIdx.x & ~63;
+    int at = to;
+    each16([&](auto g_) {
+      constexpr int g = decltype(g_)::value;
+      unsigned bits = of_group<g>();
+      if (bits == 0) return;
+      float y[4][4];
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) y[j][r] = acc_read(acc[g][j][r]);
+#pragma unroll 1
+      for (; bits != 0; bits &= bits - 1) {
+        const int o = __builtin_ctz(bits), id = v0 + SWEEP_GROUP * g + o;
+        if (id >= p.V) break;
+        if (threadIdx.x == 0) p.left_id[((int64_t)(row0 / SWEEP_OWN_ROWS) * p.splits + st.split) * p.left_slots + at] = id;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          const int of_wave = 16 * j + (lane & 15), row = row0 + of_wave;
+          const float lo = keep_select((o & 1) != 0, y[j][1], y[j][0]), hi = keep_select((o & 1) != 0, y[j][3], y[j][2]);
+          const float z = keep_select((o & 2) != 0, hi, lo);
+          if (lane >> 4 == o >> 2 && of_block + of_wave < SWEEP_OWN_ROWS && row < p.rows)
+            p.left_z[((int64_t)row * p.splits + st.split) * p.left_slots + at] = z;
+        }
+        ++at;
+      }
+    });
+  }
+};
 
 // The tables of the wavefront's own 64 ids, for all (at most eight alphas besides a zero one).
 __device__ __forceinline__ void sweep_put_tables(const float (&u4)[4], const GemmArgs& p, unsigned char* lds) {
@@ -911,7 +979,6 @@ struct AnySweepEpilogue {
     st.id0 = -1;
     st.split = split;
     st.next_shift = 0.f;
-    st.given_up = 0;
   }
   static __device__ __forceinline__ void tile(f32x4 (&acc)[16][4], State& st, int v0, const GemmArgs& p, int my_row) {
     if constexpr (GENERAL)
@@ -919,18 +986,16 @@ struct AnySweepEpilogue {
     else
       factored_tile(acc, st, __builtin_amdgcn_readfirstlane(v0), my_row);
   }
-  // OWN_U: false once the factored form does not apply to some tile of the call; all wavefronts alike.
-  static __device__ __forceinline__ bool own_tile(f32x4 (&acc)[16][4], State& st, int v0, const GemmArgs& p, int my_row,
+  static __device__ __forceinline__ void own_tile(f32x4 (&acc)[16][4], State& st, int v0, const GemmArgs& p, int my_row,
                                                   unsigned char* lds) {
     v0 = __builtin_amdgcn_readfirstlane(v0);
     if constexpr (GENERAL) {
       general_tile(acc, st, v0, p, my_row, lds);
-      return true;
     } else {
-      return factored_tile(acc, st, v0, my_row, lds);
+      factored_tile(acc, st, v0, my_row, lds);
     }
   }
-  static __device__ __forceinline__ bool factored_tile(f32x4 (&acc)[16][4], State& st, int v0, int my_row, unsigned char* lds = nullptr) {
+  static __device__ __forceinline__ void factored_tile(f32x4 (&acc)[16][4], State& st, int v0, int my_row, unsigned char* lds = nullptr) {
     const int lane = fresh_lane();
     const GemmArgs p = sweep_args();
     const bool first = st.id0 < 0;
@@ -940,24 +1005,30 @@ struct AnySweepEpilogue {
     if (!OWN_U) warm = p.eu[(int64_t)v0 * SWEEP_ROWS + (64 * (threadIdx.x >> 6 & 1) + lane) * 32];
     asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");   // as in epilogue_tile: let the last MFMA drain
     float u4[4], shift4[4];
-    bool given_up = false;
+    SweepLeaveOut<KS> leave;
     if constexpr (OWN_U) {
-      given_up = sweep_own_u<true>(acc, v0, p, my_row, st.given_up, lds, u4);   // (and on to the tile's end: a way out here costs 48 registers)
+      sweep_own_u(acc, v0, p, my_row, lds, u4);
+      leave.look(u4, st, v0, p, my_row);
+      leave.n = fresh_scalar(__builtin_amdgcn_readfirstlane(leave.n));   // (or the paths of it are told apart and the accumulators copied)
+      leave.to = fresh_scalar(__builtin_amdgcn_readfirstlane(leave.to));
       __syncthreads();   // (the parts are read)
       sweep_put_tables(u4, p, lds);
       st.next_shift = sweep_tile_shift(u4);
     }
-    if (v0 + BM > p.V) {   // only the last tile of the vocabulary: a real branch (the empty asm keeps it one)
+    // (rarely: a real branch, which the empty asm keeps it)
+    if (OWN_U ? __builtin_expect((leave.out[0] | leave.out[1] | leave.out[2] | leave.out[3]) != 0, 0) : v0 + BM > p.V) {
       asm volatile("");
+      if (OWN_U && leave.n != 0) leave.save(acc, st, v0, my_row);
       const int id = v0 + 4 * (lane >> 4);
       each16([&](auto g_) {
         constexpr int g = decltype(g_)::value;
+        const unsigned mine = OWN_U ? leave.template of_group<g>() >> (4 * (lane >> 4)) : 0u;
 #pragma unroll
         for (int r = 0; r < 4; ++r)
 #pragma unroll
           for (int j = 0; j < 4; ++j) {
             float x = acc_read(acc[g][j][r]);
-            x = id + 16 * g + r >= p.V ? NEG_BIG : x;
+            x = (OWN_U ? (mine >> r & 1) != 0 : id + 16 * g + r >= p.V) ? NEG_BIG : x;
             asm volatile("v_accvgpr_write_b32 %0, %1" : "=a"(acc[g][j][r]) : "v"(x));
           }
         LL_SCHED_FENCE();
@@ -1021,19 +1092,12 @@ struct AnySweepEpilogue {
       sweep_group_shifts(u4, shift4, least4);
     }
     sweep_lists<KS>(acc, st, marked, u4, shift4, v0, p);
-    int exceeded = 0;
-    if (OWN_U) {
-      exceeded = __hip_atomic_load(p.exceeded, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    } else {
+    if (!OWN_U) {
       const int ahead = min(v0 / BM + 1, p.tiles - 1);
       st.next_shift = p.shift_tile[16 * ahead + (lane & 15)];
     }
     sweep_take_bounds<KS, true>(st, p, my_row);
-    if (OWN_U)
-      st.given_up = __builtin_amdgcn_readfirstlane(exceeded);
-    else
-      asm volatile("" : "+v"(st.next_shift));   // (come back by now: as above)
-    return !given_up;
+    if (!OWN_U) asm volatile("" : "+v"(st.next_shift));   // (come back by now: as above)
   }
   static __device__ __forceinline__ void general_tile(f32x4 (&acc)[16][4], State& st, int v0, const GemmArgs& p, int my_row = 0,
                                                       unsigned char* lds = nullptr) {
@@ -1041,7 +1105,7 @@ struct AnySweepEpilogue {
     float u4[4], u_ahead = 0.f;
     if constexpr (OWN_U) {
       asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
-      sweep_own_u<false>(acc, v0, p, my_row, 0, lds, u4);
+      sweep_own_u(acc, v0, p, my_row, lds, u4);
       __syncthreads();   // the LDS is the ring's again
     } else {
       u_ahead = sweep_load_u(v0, p);

@@ -442,7 +442,7 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
     if (TAIL && (KT == 1 || (KTILE) == KT - 2)) zero_tail(nW);                                         \
     __syncthreads();                                                                                   \
     LL_SLICE(MF0, 1, 1, fw1, fw0, nW, 0, LL_AIN_S3, LL_AOUT_S3, LL_HOOK_S3, LL_RD_SPREAD)
-  int end = SHORT && ends_in_half ? tile1 - 1 : tile1;
+  const int end = SHORT && ends_in_half ? tile1 - 1 : tile1;
   for (int tile = tile0; tile < end; ++tile) {
     f32x4 acc[16][4];   // first written by the K half 0 MFMAs of stage 0, with C = 0
     LL_STAGE(LL_MFMA16_Z, 0)
@@ -459,7 +459,7 @@ __device__ __forceinline__ void lens_gemm_dma(const GemmArgs& p, unsigned char* 
       EPI::template short_tile<false>(acc, st, row0 + tile * BM, p, my_row);
     } else if constexpr (EPI::OWN_U) {
       // (the slot of the stage just done: the upper 4 KB of each wavefront's 8 are free until it sends the next stage's loads)
-      if (!EPI::own_tile(acc, st, tile * BM, p, my_row, smem + W_SLOTS * SLOT_BYTES - cW - nW)) end = 0;
+      EPI::own_tile(acc, st, tile * BM, p, my_row, smem + W_SLOTS * SLOT_BYTES - cW - nW);
     } else {
       EPI::tile(acc, st, tile * BM, p, my_row);
     }

@@ -127,7 +127,7 @@ __global__ __launch_bounds__(256) void ll_sweep_panel_kernel(const uint16_t* __r
                                                              unsigned* __restrict__ bound, int bounds, const uint16_t* __restrict__ W, int V,
                                                              const float* __restrict__ v, float alpha_most, int n_waves, int samples,
                                                              float* __restrict__ sampled, float* __restrict__ row_sq,
-                                                             int* __restrict__ exceeded) {
+                                                             int* __restrict__ flags, int n_flags) {
   const int lane = threadIdx.x & 63, n16 = d >> 3;
   int row = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
   const float4* const v4 = reinterpret_cast<const float4*>(v);
@@ -165,9 +165,9 @@ __global__ __launch_bounds__(256) void ll_sweep_panel_kernel(const uint16_t* __r
   row -= n_waves;
   if (row > rows + SWEEP_PARTS + 1) return;
   if (row <= rows) {
-    if (row == rows && lane == 0) {
-      *exceeded = 0;
-      for (int i = 0; i < 3; ++i) row_sq[rows + i] = INFINITY;
+    if (row == rows) {
+      for (int i = lane; i < n_flags; i += 64) flags[i] = 0;
+      if (lane < 3) row_sq[rows + lane] = INFINITY;
     }
     norm_panel_row<NITER, true>(hidden, gamma, panel, row, rows, d, lda, eps, bound, bounds, row_sq);
     return;
@@ -241,7 +241,7 @@ __global__ __launch_bounds__(256) void ll_unembed_direction_kernel(const uint16_
   extern __shared__ __align__(16) float sv[];
   if (sampled != nullptr) {   // a look ahead of a kernel that forms u itself: only where it is asked for
     if (threadIdx.x < 64) {
-      const bool wanted = sweep_is_long(sampled, row_sq, rows) || (!only_general && sweep_sample_says(sampled) != SWEEP_FITS);
+      const bool wanted = sweep_is_long(sampled, row_sq, rows) || (!only_general && sweep_sample_says(sampled) == SWEEP_OPEN);
       if (threadIdx.x == 0) sv[0] = wanted ? 1.f : 0.f;   // (v may take all the LDS)
       if (blockIdx.x == 0 && threadIdx.x == 0) *given = wanted ? 1 : 0;
     }
@@ -515,6 +515,25 @@ __device__ __forceinline__ float exp_difference(float a, float b) {
 // l + 64, ... (increasing ids), keeps their KS best, and the wavefront takes the best of its lanes' heads k times.
 // The splits' references are any logits of the row, some of them far below its largest, so that M and log S are no small
 // numbers that nearly cancel: the last steps are in 64 bits.
+// LeftOut: of a sweep that forms u itself, the tokens that its factored form has left out (see ll_epilogue_sweep.h).
+enum { FLAG_EXCEEDED, FLAG_GIVEN, FLAG_LEFT, FLAGS };   // flags; behind them GemmArgs' left_n
+struct LeftOut {
+  const int* flags;   // nullptr: none
+  const float* z;
+  const int* id;
+  int slots;
+  // f(id, logit, shifted logit) of the row's tokens in this lane's splits
+  template <class F>
+  __device__ __forceinline__ void each(int row, int splits, float alpha, const float* u, F f) const {
+    const int block = row / SWEEP_OWN_ROWS * splits;
+    for (int s = threadIdx.x & 63; s < splits; s += 64)
+      for (int i = 0, n = flags[FLAGS + 4 * (block + s)]; i < n; ++i) {
+        const int t = id[(block + s) * slots + i];
+        const float x = z[((int64_t)row * splits + s) * slots + i];
+        f(t, x, fmaf(alpha, u[t], x));
+      }
+  }
+};
 template <int KS>
 __global__ __launch_bounds__(256) void ll_sweep_merge_kernel(const float4* __restrict__ stats, const uint2* __restrict__ top,
                                                              const float* __restrict__ ztgt, const float* __restrict__ u,
@@ -522,7 +541,7 @@ __global__ __launch_bounds__(256) void ll_sweep_merge_kernel(const float4* __res
                                                              const int32_t* __restrict__ target, int64_t out_stride,
                                                              int32_t* __restrict__ out_ids, float* __restrict__ out_p,
                                                              float* __restrict__ out_logp, float* __restrict__ out_entropy,
-                                                             unsigned* __restrict__ bound) {
+                                                             unsigned* __restrict__ bound, const LeftOut left) {
   const int item = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (item >= rows * n_alpha) return;
   const int lane = threadIdx.x & 63;
@@ -557,6 +576,22 @@ __global__ __launch_bounds__(256) void ll_sweep_merge_kernel(const float4* __res
       }
     }
   }
+  const bool some_left = left.flags != nullptr && left.flags[FLAG_LEFT] != 0 && left.flags[FLAG_EXCEEDED] == 0;
+  if (some_left)
+    left.each(row, splits, alphas.a[a], u, [&](int ie, float x, float ze) {
+      if (target != nullptr && ie == target[row]) zt = x;
+      m = fmaxf(m, ze);
+#pragma unroll
+      for (int j = 0; j < KS; ++j) {
+        const bool above = ze > z[j] || (ze == z[j] && ie < id[j]);
+        const float zo = z[j];
+        const int io = id[j];
+        z[j] = above ? ze : zo;
+        id[j] = above ? ie : io;
+        ze = above ? zo : ze;
+        ie = above ? io : ie;
+      }
+    });
   const float M = wave_max(m);
   float s_lane = 0.f, t_lane = 0.f;
   for (int s = lane; s < splits; s += 64) {
@@ -565,6 +600,12 @@ __global__ __launch_bounds__(256) void ll_sweep_merge_kernel(const float4* __res
     s_lane = fmaf(sc, x.y, s_lane);
     t_lane = fmaf(sc, x.z, t_lane);
   }
+  if (some_left)
+    left.each(row, splits, alphas.a[a], u, [&](int, float, float w) {
+      const float sc = exp_difference(w, M);
+      s_lane += sc;
+      t_lane = fmaf(sc, w, t_lane);
+    });
   const float S = wave_sum(s_lane), T = wave_sum(t_lane);
   const double lse = (double)M + log((double)S);
   zt = wave_max(zt);
@@ -829,7 +870,7 @@ void launch_norm_panel(const uint16_t* hidden, const uint16_t* gamma, uint16_t* 
 
 void launch_sweep_panel(const uint16_t* hidden, const uint16_t* gamma, uint16_t* panel, int rows, int d, int64_t lda, float eps,
                         unsigned* bound, int bounds, const uint16_t* W, int V, const float* v, float alpha_most, int n_waves, int samples,
-                        float* sampled, float* row_sq, int* exceeded, hipStream_t stream) {
+                        float* sampled, float* row_sq, int* flags, int n_flags, hipStream_t stream) {
   const int per_block = rows <= 1024 ? 1 : 4;
   const dim3 grid((unsigned)((n_waves + rows + 1 + SWEEP_PARTS + 1 + per_block - 1) / per_block)), block(64 * per_block);
   const auto kernel = d <= 64 * 8 * 4    ? ll_sweep_panel_kernel<4>
@@ -837,7 +878,7 @@ void launch_sweep_panel(const uint16_t* hidden, const uint16_t* gamma, uint16_t*
                       : d <= 64 * 8 * 16 ? ll_sweep_panel_kernel<16>
                                          : ll_sweep_panel_kernel<0>;
   hipLaunchKernelGGL(kernel, grid, block, 0, stream, hidden, gamma, panel, rows, d, lda, eps, bound, bounds, W, V, v, alpha_most, n_waves, samples,
-                     sampled, row_sq, exceeded);
+                     sampled, row_sq, flags, n_flags);
 }
 
 int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, const void* hidden, const void* gamma,
@@ -1106,10 +1147,11 @@ int project_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes,
 }
 
 struct SweepPlan {
-  size_t off_u, off_block_max, off_sampled, off_row_sq, off_eu, off_shift, off_shift_min, off_shift_tile, off_general, off_bound, off_stats, off_ztgt, off_top, off_panel, total;
+  size_t off_u, off_block_max, off_sampled, off_row_sq, off_eu, off_shift, off_shift_min, off_shift_tile, off_general, off_left_z, off_left_id, off_bound, off_stats, off_ztgt, off_top, off_panel, total;
   size_t off_project, wanted;   // the projection's workspace where one alpha is left to it; wanted: what the call is fastest with
   int64_t lda;
   int n_padded;   // V in whole tiles
+  int flags;      // whole: FLAGS, and the counts of what is left out
 };
 
 // Vocabulary splits of a pass: one workgroup per compute unit, and ids within a split in 16 bits.
@@ -1120,8 +1162,9 @@ int sweep_splits(int rows, int tiles, int block_rows = BN) {
   return splits > least ? splits : least;
 }
 
-// whole: of a call whose kernel forms u itself (no tables; the direction's rows behind the panel).  Callers bring the other's size.
-SweepPlan make_sweep_plan(const ll_shape* s, int n_alpha, int k = 1, bool whole = false) {
+// whole: of a call whose kernel forms u itself (no tables; the direction's rows behind the panel; left_slots as in GemmArgs).  Callers bring the
+// other's size.
+SweepPlan make_sweep_plan(const ll_shape* s, int n_alpha, int k = 1, bool whole = false, int left_slots = 0) {
   SweepPlan p = {};
   size_t off = 0;
   auto take = [&](size_t bytes) {
@@ -1136,19 +1179,24 @@ SweepPlan make_sweep_plan(const ll_shape* s, int n_alpha, int k = 1, bool whole 
   size_t partials = rows * NUM_CU < (size_t)MAX_PARTIALS ? rows * NUM_CU : (size_t)MAX_PARTIALS;
   const size_t least = rows * ((tiles + SWEEP_MAX_TILES - 1) / SWEEP_MAX_TILES);
   if (partials < least) partials = least;
+  if (whole) partials = rows * sweep_splits((int)rows, tiles, SWEEP_OWN_ROWS);   // (one pass)
   p.off_u = take((size_t)p.n_padded * sizeof(float));
   p.off_block_max = take(UD_BLOCKS * sizeof(float));
   p.off_project = off;
   if (whole) {
     p.off_sampled = take((SWEEP_SAMPLED + 1) * sizeof(float));
     p.off_row_sq = take((rows + 3) * sizeof(float));
+    const size_t blocks = (rows + SWEEP_OWN_ROWS - 1) / SWEEP_OWN_ROWS * (partials / rows);
+    p.flags = FLAGS + 4 * (int)blocks;
+    p.off_left_z = take(partials * left_slots * sizeof(float));
+    p.off_left_id = take(blocks * left_slots * sizeof(int));
   } else {
     p.off_eu = take((size_t)p.n_padded * 2 * SWEEP_ROWS * sizeof(float));
     p.off_shift = take((size_t)p.n_padded * sizeof(float));
     p.off_shift_min = take((size_t)p.n_padded * sizeof(float));
     p.off_shift_tile = take((size_t)tiles * 16 * sizeof(float));
   }
-  p.off_general = take(2 * sizeof(int));   // (and whether u is given)
+  p.off_general = take((whole ? p.flags : 1) * sizeof(int));
   p.off_bound = take(rows * n_alpha * k * sizeof(unsigned));
   p.off_stats = take(partials * n_alpha * sizeof(float4));
   p.off_ztgt = take(partials * sizeof(float));
@@ -1240,11 +1288,15 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
   // 1500 x 512 x 50257 (5) 169 | 160, 500 x 2560 x 151936 (5) 503 | 391.  A W_U of up to 64 MiB is read from the Infinity Cache
   // in some 10 us; the factored form then gains little (300 x 512 x 50257 (2) 121 | 115, 1500 x 512 x 50257 (5) 229 | 230) and keeps the kernels before it.
   bool whole = !as_projection && N <= CHUNK_ROWS && (only_general || ((n_alpha <= SWEEP_SPLIT_ROWS || zero_alpha >= 0) && (int64_t)V * d * 2 > (64 << 20)));
+  int left_slots = 0;
   if (whole) {
     const int own_splits = sweep_splits((int)N, tiles, SWEEP_OWN_ROWS);
     const int own_each = (tiles + own_splits - 1) / own_splits;
     const float more_us = (float)own_each * (only_general ? 0.4f : 2.6f);
-    const SweepPlan own = make_sweep_plan(shape, n_alpha, k, true);
+    // (the tables' place takes some 32 tokens a split and row; few where the vocabulary is small beside the rows)
+    left_slots = only_general ? 0 : 32;
+    SweepPlan own = make_sweep_plan(shape, n_alpha, k, true, left_slots);
+    for (; left_slots > 0 && own.total > plan.total; own = make_sweep_plan(shape, n_alpha, k, true, left_slots)) left_slots /= 2;
     whole = own_each <= each && more_us <= (float)V * (float)d * 2.0f / 6.0e6f + 5.0f && own.total <= plan.total;
     if (whole) plan = own;
   }
@@ -1259,6 +1311,8 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
   float* const sampled = reinterpret_cast<float*>(ws + plan.off_sampled);
   float* const row_sq = reinterpret_cast<float*>(ws + plan.off_row_sq);
   int* general = reinterpret_cast<int*>(ws + plan.off_general);
+  float* const left_z = reinterpret_cast<float*>(ws + plan.off_left_z);
+  int* const left_id = reinterpret_cast<int*>(ws + plan.off_left_id);
   unsigned* bound = reinterpret_cast<unsigned*>(ws + plan.off_bound);
   float4* stats = reinterpret_cast<float4*>(ws + plan.off_stats);
   float* ztgt = reinterpret_cast<float*>(ws + plan.off_ztgt);
@@ -1313,10 +1367,10 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     const bool need_panel = gamma != nullptr || plan.lda != d || whole;
     if (whole) {
       launch_sweep_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, d, plan.lda, eps, bound, only_general ? 0 : n_alpha * k,
-                         static_cast<const uint16_t*>(W_U), V, v, alpha_most, sample_waves, samples, sampled, row_sq, general, stream);
+                         static_cast<const uint16_t*>(W_U), V, v, alpha_most, sample_waves, samples, sampled, row_sq, general, plan.flags, stream);
       LL_CHECK_S(hipGetLastError());
       hipLaunchKernelGGL(direction, dim3(UD_BLOCKS), dim3(256), v_bytes, stream, static_cast<const uint16_t*>(W_U), v, V, d, 1.0f, u, plan.n_padded,
-                         block_max, (const float*)sampled, (const float*)row_sq, rows, only_general, general + 1);
+                         block_max, (const float*)sampled, (const float*)row_sq, rows, only_general, general + FLAG_GIVEN);
       LL_CHECK_S(hipGetLastError());
     } else if (need_panel) {
       launch_norm_panel(h_rows, static_cast<const uint16_t*>(gamma), panel, rows, 1, d, plan.lda, eps, nullptr, 0, stream);
@@ -1339,9 +1393,14 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     a.group_rows = group_rows(a.row_blocks, a.splits);
     a.u = a.u_out = u;
     a.direction = v;
-    a.exceeded = general;
+    a.exceeded = general + FLAG_EXCEEDED;
+    a.left_any = general + FLAG_LEFT;
+    a.left_n = general + FLAGS;
+    a.left_z = left_z;
+    a.left_id = left_id;
+    a.left_slots = left_slots;
     a.sampled = sampled;
-    a.given = general + 1;
+    a.given = general + FLAG_GIVEN;
     a.only_general = only_general ? 1 : 0;
     a.block_max = block_max;
     a.alpha_most = alpha_most;
@@ -1366,7 +1425,8 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
     const auto merge = lists ? ll_sweep_merge_kernel<SWEEP_KS> : ll_sweep_merge_kernel<1>;
     hipLaunchKernelGGL(merge, dim3((unsigned)((rows * n_alpha + 3) / 4)), dim3(256), 0, stream, (const float4*)stats, (const uint2*)top,
                        (const float*)ztgt, (const float*)u, al, rows, a.splits, n_alpha, k, V, a.target, N, out_ids + r0 * k,
-                       out_p + r0 * k, out_logp ? out_logp + r0 : nullptr, out_entropy + r0, only_general ? nullptr : bound);
+                       out_p + r0 * k, out_logp ? out_logp + r0 : nullptr, out_entropy + r0, only_general ? nullptr : bound,
+                       LeftOut{whole && !only_general ? general : nullptr, left_z, left_id, left_slots});
     LL_CHECK_S(hipGetLastError());
   }
 #undef LL_CHECK_S

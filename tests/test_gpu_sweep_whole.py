@@ -73,13 +73,14 @@ def both(h, gamma, W, v, alphas, target, k):
 @pytest.mark.parametrize("what", ["plain", "one large shift", "large shifts", "infinite W", "NaN in W", "infinite v", "NaN in v", "no direction"])
 def test_as_with_u_from_a_pass_of_its_own(what, k):
     """The forms agree to fp32 sums in another order, and to the places of what is no number.  "One large shift" is one token that the
-    sample does not meet: the factored form is given up while it runs."""
+    sample does not meet: the factored form leaves it out."""
     say(f"whole sweep, both ways: {what} k={k}")
     d, V = 704, 50257
     w, h = workload(256, d, V)
     v, W = direction(d), w.W_U
     if what == "one large shift":
-        W[-30] = (6.0 * v).to(torch.bfloat16)
+        v = v * 0.5                               # (short enough for u of the contraction)
+        W[-30] = (24.0 * v).to(torch.bfloat16)    # 6, times 4
     if what == "large shifts":
         v = v * 400.0
     if what == "infinite W":
@@ -158,7 +159,8 @@ def test_a_long_direction_adds_no_error(d, n_alpha, length, own):
     assert rms[0] <= (1.0 + r * r / 2 + 3.0 * r / 253 ** 0.5 if own else 1.01) * rms[1], rms
 
 
-@pytest.mark.parametrize("d,n_alpha,shift", [(2048, 9, 13.0), (2056, 9, 12.0), (4096, 9, 13.0), (4096, 3, 13.0)])
+@pytest.mark.parametrize("d,n_alpha,shift", [(2048, 9, 13.0), (2056, 9, 12.0), (4096, 9, 13.0), (4096, 3, 13.0),
+                                             (2048, 9, 21.0), (4096, 9, 30.0)])      # (left out of the factored form)
 def test_a_token_along_the_direction_adds_no_error(d, n_alpha, shift):
     """Against 64 bits, eight tokens that the sample misses and whose unembedding rows lie along the direction, in a vocabulary whose u are
     small: what is off in their log-probabilities and in the entropy is no more than with u from a pass of its own."""
@@ -226,3 +228,96 @@ def test_never_a_tile_more(N, d, V, n_alpha, expected):
     say(f"whole sweep, which N={N} d={d} V={V} A={n_alpha}")
     w, h = workload(N, d, V)
     assert is_whole(lambda: LL.ll_steer_sweep(h, w.gamma, w.W_U, w.cfg.eps, direction(d), ALPHAS9[:n_alpha], None)) == expected
+
+
+def unsampled(V, tile, at):
+    """An id of the tile that the sample (one row in 32) passes by, the one at `at` or just behind."""
+    sampled = {s * V // ((V + 31) // 32) for s in range((V + 31) // 32)}
+    i = tile * 256 + at
+    return i + 1 if i in sampled else i
+
+
+def with_large_shifts(N, d, V, tiles, seed=37):
+    """A sweep with a token of a large shift, unmet by the sample, in each of these tiles."""
+    w, h = workload(N, d, V, seed)
+    v, W = direction(d) * (0.015 * d ** 0.5), w.W_U
+    ids = [min(unsampled(V, t, 67 * i % 250), V - 1) for i, t in enumerate(tiles)]
+    assert len(set(ids)) == len(ids)
+    for i, t in enumerate(ids):
+        W[t] = (v * ((-8.0 if i % 3 == 1 else 6.5) / float(v.square().sum()))).to(torch.bfloat16)    # times 4: beyond 20
+    return w, h, v, ids
+
+
+EIGHT = [a for a in ALPHAS9 if a != 0.0]
+
+
+@pytest.mark.parametrize("k", [None, 1, 3, 4])
+@pytest.mark.parametrize("N,d,tiles,n_alpha", [
+    (1012, 704, [0], 8), (1012, 704, [3], 8), (1012, 712, [196], 8),      # a split's first tile, its last, the vocabulary's last (a part of one)
+    (1012, 704, [0, 2, 3, 40, 41, 77], 8), (1012, 704, [0, 2, 3, 40, 41, 77], 9),
+    (1012, 704, [0, 1, 2, 3] * 4, 9),                                     # as many as a split has place for
+    (1012, 704, [0, 1, 2, 3] * 5, 9),                                     # more: the general form for all
+    (253, 704, [5, 100, 196], 9), (300, 704, [0, 1, 195, 196], 6),        # one tile a split; a second block of few rows
+    (1012, 704, range(197), 9),                                           # one in every tile
+])
+def test_tokens_that_are_left_out(N, d, tiles, n_alpha, k):
+    """Tokens of large shifts that the sample misses: the factored form leaves them out, the merge adds them.  Against nine strengths none of which is
+    zero, which take u and its largest from a pass of its own and so the general form for all."""
+    say(f"whole sweep, left out N={N} d={d} tokens={len(tiles)} A={n_alpha} k={k}")
+    V = 50257
+    w, h, v, ids = with_large_shifts(N, d, V, tiles)
+    target = w.target_ids.clone()
+    target[::3] = torch.tensor(ids, device=DEV, dtype=torch.int32)[torch.arange(len(target[::3]), device=DEV) % len(ids)]
+    target[1::3] = torch.tensor([t // 256 * 256 + 7 for t in ids], device=DEV, dtype=torch.int32)[torch.arange(len(target[1::3]), device=DEV) % len(ids)]
+    target[4] = V
+    call = lambda alphas: LL.ll_steer_sweep(h, w.gamma, w.W_U, w.cfg.eps, v, alphas, target, k=k)
+    alphas = {6: EIGHT[2:], 8: EIGHT, 9: ALPHAS9}[n_alpha]
+    nonzero = [x for x in alphas if x != 0.0]
+    others = (nonzero + [0.125] * 9)[:9]
+    assert is_whole(lambda: call(alphas)) and not is_whole(lambda: call(others))
+    a, b = call(alphas), [t[:len(nonzero)] for t in call(others)]
+    if n_alpha == 9:   # strength 0: the projection
+        plain = LL.ll_project(h, w.gamma, w.W_U, w.cfg.eps, k or 1, target)
+        plain = [plain[0] if k else plain[0][:, 0], plain[1] if k else plain[1][:, 0], *plain[2:]]
+        b = [torch.cat([x[:4], y[None], x[4:]]) for x, y in zip(b, plain)]
+    assert (a[0] != b[0]).float().mean() < 1e-3        # near-ties
+    scale = float(b[3].abs().max()) + 20.0             # sums of logits and shifts of this size round in the last place
+    for x, y in zip(a[1:], b[1:]):
+        torch.testing.assert_close(x, y, rtol=4e-5, atol=2e-6 * scale, equal_nan=True)
+    assert torch.equal(torch.isnan(a[2]), torch.isnan(b[2])) and int(torch.isnan(a[2]).sum()) == n_alpha
+
+
+def test_equal_logits_of_tokens_left_out_keep_their_order():
+    """The same unembedding row several times, of a large shift, in one tile and in several splits: listed by id."""
+    say("whole sweep, equal logits of tokens left out")
+    N, d, V = 1012, 704, 50257
+    g = torch.Generator(device=DEV).manual_seed(3)
+    W = 0.02 * torch.randn((V, d), generator=g, device=DEV)
+    v = direction(d) * (0.015 * d ** 0.5)
+    same = [unsampled(V, 4, 9), unsampled(V, 5, 190), unsampled(V, 5, 252), unsampled(V, 70, 3)]
+    W[same] = 3.0 * torch.randn((d,), generator=g, device=DEV) / d ** 0.5 + v * (6.5 / float(v.square().sum()))
+    h = 20.0 * W[same[0]] + 0.1 * torch.randn((N, d), generator=g, device=DEV)
+    h = (h - (h @ v)[:, None] * v / v.square().sum()).to(torch.bfloat16)
+    W = W.to(torch.bfloat16)
+    ids4, p, _, _ = LL.ll_steer_sweep(h, None, W, 1e-5, v, EIGHT, None, k=4)
+    assert (ids4 == torch.tensor(same, device=DEV)).all() and torch.equal(p[..., 0], p[..., 3])
+
+
+def durations_of(call):
+    """Of this library's kernels that call() launches, in order: name and microseconds."""
+    from torch.profiler import ProfilerActivity, profile
+    with profile(activities=[ProfilerActivity.CUDA]) as prof:
+        call()
+        torch.cuda.synchronize()
+    return [(e.name, e.device_time) for e in sorted(prof.events(), key=lambda e: e.time_range.start) if "::ll_" in e.name]
+
+
+@pytest.mark.parametrize("k", [None, 3])
+def test_tokens_of_large_shifts_cost_no_second_pass(k):
+    """What is launched behind the factored form returns at once, though there are such tokens."""
+    say(f"whole sweep, the cost of tokens left out k={k}")
+    w, h, v, _ = with_large_shifts(1012, 704, 50257, [17, 130])
+    call = lambda: LL.ll_steer_sweep(h, w.gamma, w.W_U, w.cfg.eps, v, EIGHT, None, k=k)
+    call()
+    factored, general = (t for name, t in durations_of(call) if "ll_lens_gemm" in name)
+    assert general < 0.3 * factored, (factored, general)

@@ -110,6 +110,7 @@ constexpr float LOG2E = 1.4426950408889634f;
 #define LL_SCHED_FENCE() __builtin_amdgcn_sched_barrier(0)
 
 typedef const float __attribute__((address_space(4)))* const_f32_ptr;   // read through scalar loads when the address is wave-uniform
+typedef const int __attribute__((address_space(4)))* const_i32_ptr;
 
 // Workgroup ids are dealt round-robin over the 8 XCDs; remap so that one XCD (one L2) gets a
 // compact rectangle of (row blocks) x (all splits) and its CUs share A panels and W tiles.

@@ -124,6 +124,7 @@ struct SweepState {
   unsigned li[SWEEP_MAX][IDS];
   float z_tgt;
   int tgt, id0, split;                       // id0: first id of the split
+  int given;                                 // OWN_U, general form: GemmArgs' given
 };
 
 // Register j of lane block g <-> register g of lane block j (see load_group).
@@ -711,7 +712,8 @@ __device__ __forceinline__ void sweep_exact_u(float (&u4)[4], int v0, const Gemm
   const int lane = fresh_lane(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
   const float there = (float)min(BM, p.V - v0), limit = SWEEP_ODD * wave_sum((fabsf(u4[0]) + fabsf(u4[1])) + (fabsf(u4[2]) + fabsf(u4[3])));
   const auto odd = [&](int q) { return there * fabsf(u4[q]) > limit; };   // (of an infinity, and in its tile, and of what is no number: never)
-  if (__builtin_expect(__builtin_amdgcn_ballot_w64(odd(0) || odd(1) || odd(2) || odd(3)) == 0, 1)) return;   // (the same in all four wavefronts)
+  const float most = max3(max3(fabsf(u4[0]), fabsf(u4[1]), fabsf(u4[2])), fabsf(u4[3]), 0.f);
+  if (__builtin_expect(__builtin_amdgcn_ballot_w64(there * most > limit) == 0, 1)) return;   // (the same in all four wavefronts)
   __syncthreads();   // the parts are read
   const float4* const v4 = reinterpret_cast<const float4*>(p.direction);
   int n = 0;
@@ -752,9 +754,14 @@ __device__ __forceinline__ void sweep_exact_u(float (&u4)[4], int v0, const Gemm
 
 // u of the tile, entry 64 q + l in lane l, from the three rows of the direction in the last wavefront's accumulators.  v is the
 // sum of three bf16 rows to the last bit (but for what is below the smallest normal number), so u = W v1 + W v2 + W v3 has the exact products that fp32 ones of W and v round.  An infinity of W
-// against a zero of v2 or v3 would be no number: where the first part is not finite it is u.
-__device__ __forceinline__ void sweep_own_u(f32x4 (&acc)[16][4], int v0, const GemmArgs& p, int my_row, unsigned char* lds, float (&u4)[4]) {
+// against a zero of v2 or v3 would be no number: where the first part is not finite it is u.  given: u is there already.
+__device__ __forceinline__ void sweep_own_u(f32x4 (&acc)[16][4], int v0, const GemmArgs& p, int my_row, bool given, unsigned char* lds, float (&u4)[4]) {
   const int lane = fresh_lane(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  if (__builtin_expect(given, 0)) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) u4[q] = p.u[v0 + 64 * q + lane];
+    return;
+  }
   const unsigned char* const in = lds + SWEEP_HALF;
   if (wave == 3) {
     const int part = (lane & 15) - (16 - SWEEP_PARTS);
@@ -768,7 +775,6 @@ __device__ __forceinline__ void sweep_own_u(f32x4 (&acc)[16][4], int v0, const G
     }
   }
   __syncthreads();
-  const bool given = *(const int __attribute__((address_space(4)))*)(uintptr_t)p.given != 0;
 #pragma unroll
   for (int q = 0; q < 4; ++q) {
     const int id = 64 * q + lane;
@@ -777,13 +783,8 @@ __device__ __forceinline__ void sweep_own_u(f32x4 (&acc)[16][4], int v0, const G
     const float whole = fabsf(a) < INFINITY ? a + (b + c) : a;
     u4[q] = v0 + id < p.V ? whole : 0.f;
   }
-  if (__builtin_expect(given, 0)) {
-#pragma unroll
-    for (int q = 0; q < 4; ++q) u4[q] = p.u[v0 + 64 * q + lane];
-  } else {
-    sweep_exact_u(u4, v0, p, lds);
-  }
-  if (!given && __builtin_amdgcn_readfirstlane(my_row) == 64 * wave)   // the first row block's wavefronts: for the merge
+  sweep_exact_u(u4, v0, p, lds);
+  if (__builtin_amdgcn_readfirstlane(my_row) == 64 * wave)   // the first row block's wavefronts: for the merge
     p.u_out[v0 + 64 * wave + lane] = sweep_group_register(u4, 4 * wave);
 }
 
@@ -943,7 +944,7 @@ struct AnySweepEpilogue {
       if (p.only_general) return false;   // (the host launches no other)
       const bool exceeded = GENERAL && *p.exceeded != 0;
       int says = sweep_sample_says(p.sampled);
-      if (*(const int __attribute__((address_space(4)))*)(uintptr_t)p.given != 0) {   // the direction kernel has seen all
+      if (*(const_i32_ptr)(uintptr_t)p.given != 0) {   // the direction kernel has seen all
         bool large = false;
 #pragma unroll
         for (int i = 0; i < SWEEP_BLOCK_MAX / 256; ++i) {
@@ -979,6 +980,7 @@ struct AnySweepEpilogue {
     st.id0 = -1;
     st.split = split;
     st.next_shift = 0.f;
+    if (OWN_U && GENERAL) st.given = *(const_i32_ptr)(uintptr_t)p.given;   // (ahead of its use: calls of one tile would wait for it)
   }
   static __device__ __forceinline__ void tile(f32x4 (&acc)[16][4], State& st, int v0, const GemmArgs& p, int my_row) {
     if constexpr (GENERAL)
@@ -1007,7 +1009,7 @@ struct AnySweepEpilogue {
     float u4[4], shift4[4];
     SweepLeaveOut<KS> leave;
     if constexpr (OWN_U) {
-      sweep_own_u(acc, v0, p, my_row, lds, u4);
+      sweep_own_u(acc, v0, p, my_row, *(const_i32_ptr)(uintptr_t)p.given != 0, lds, u4);
       leave.look(u4, st, v0, p, my_row);
       leave.n = fresh_scalar(__builtin_amdgcn_readfirstlane(leave.n));   // (or the paths of it are told apart and the accumulators copied)
       leave.to = fresh_scalar(__builtin_amdgcn_readfirstlane(leave.to));
@@ -1105,7 +1107,7 @@ struct AnySweepEpilogue {
     float u4[4], u_ahead = 0.f;
     if constexpr (OWN_U) {
       asm volatile("s_nop 15\n\ts_nop 15\n\ts_nop 15" ::: "memory");
-      sweep_own_u(acc, v0, p, my_row, lds, u4);
+      sweep_own_u(acc, v0, p, my_row, st.given != 0, lds, u4);
       __syncthreads();   // the LDS is the ring's again
     } else {
       u_ahead = sweep_load_u(v0, p);

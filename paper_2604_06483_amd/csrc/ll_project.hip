@@ -120,6 +120,7 @@ __global__ __launch_bounds__(256) void ll_norm_panel_kernel(const uint16_t* __re
 // sampled[w] is the largest |alpha u| of wavefront w's, NaN once one is.  What tells a long direction (see sweep_is_long): sampled[SWEEP_SAMPLED]
 // from the direction, row_sq from the rows.
 constexpr int SAMPLE_ROWS = 8;
+__host__ __device__ inline int sweep_part_pieces(int64_t lda) { return (int)((lda / 8 + 63) / 64); }   // wavefronts of a part
 
 template <int NITER>
 __global__ __launch_bounds__(256) void ll_sweep_panel_kernel(const uint16_t* __restrict__ hidden, const uint16_t* __restrict__ gamma,
@@ -163,7 +164,6 @@ __global__ __launch_bounds__(256) void ll_sweep_panel_kernel(const uint16_t* __r
     return;
   }
   row -= n_waves;
-  if (row > rows + SWEEP_PARTS + 1) return;
   if (row <= rows) {
     if (row == rows) {
       for (int i = lane; i < n_flags; i += 64) flags[i] = 0;
@@ -172,8 +172,8 @@ __global__ __launch_bounds__(256) void ll_sweep_panel_kernel(const uint16_t* __r
     norm_panel_row<NITER, true>(hidden, gamma, panel, row, rows, d, lda, eps, bound, bounds, row_sq);
     return;
   }
-  const int part = row - rows - 1;
-  if (part == SWEEP_PARTS) {   // a wavefront of its own for the direction's length
+  row -= rows + 1;
+  if (row == 0) {   // a wavefront of its own for the direction's length
     float vv = 0.f;
 #pragma unroll 4
     for (int c = lane; c < 2 * n16; c += 64) {
@@ -184,7 +184,9 @@ __global__ __launch_bounds__(256) void ll_sweep_panel_kernel(const uint16_t* __r
     if (lane == 0) sampled[SWEEP_SAMPLED] = alpha_most * alpha_most * vv * (1.0f / (SWEEP_LONG * SWEEP_LONG));
     return;
   }
-  uint4* const dst = reinterpret_cast<uint4*>(panel + (int64_t)row * lda);
+  // and one for 64 chunks of each part
+  const int pieces = sweep_part_pieces(lda), part = (row - 1) / pieces, c = (row - 1 - part * pieces) * 64 + lane;
+  if (part >= SWEEP_PARTS || c >= (int)(lda >> 3)) return;
   const auto cut = [&](float x) -> uint32_t {
     const uint32_t first = __float_as_uint(x) & 0xffff0000u;
     if (!(fabsf(x) < INFINITY)) return part != 0 ? 0u : x != x ? 0x7fc0u : first >> 16;
@@ -193,14 +195,12 @@ __global__ __launch_bounds__(256) void ll_sweep_panel_kernel(const uint16_t* __r
     const uint32_t third = __float_as_uint(rest - __uint_as_float(second));
     return (part == 0 ? first : part == 1 ? second : third) >> 16;
   };
-  for (int c = lane; c < (int)(lda >> 3); c += 64) {
-    uint4 q = make_uint4(0, 0, 0, 0);
-    if (c < n16) {
-      const float4 a = v4[2 * c], b = v4[2 * c + 1];
-      q = make_uint4(cut(a.x) | cut(a.y) << 16, cut(a.z) | cut(a.w) << 16, cut(b.x) | cut(b.y) << 16, cut(b.z) | cut(b.w) << 16);
-    }
-    dst[c] = q;
+  uint4 q = make_uint4(0, 0, 0, 0);
+  if (c < n16) {
+    const float4 a = v4[2 * c], b = v4[2 * c + 1];
+    q = make_uint4(cut(a.x) | cut(a.y) << 16, cut(a.z) | cut(a.w) << 16, cut(b.x) | cut(b.y) << 16, cut(b.z) | cut(b.w) << 16);
   }
+  reinterpret_cast<uint4*>(panel + (int64_t)(rows + 1 + part) * lda)[c] = q;
 }
 
 // Copy of the bias of Eq. 1 padded with zeros to whole vocabulary tiles, so that the epilogue
@@ -872,7 +872,7 @@ void launch_sweep_panel(const uint16_t* hidden, const uint16_t* gamma, uint16_t*
                         unsigned* bound, int bounds, const uint16_t* W, int V, const float* v, float alpha_most, int n_waves, int samples,
                         float* sampled, float* row_sq, int* flags, int n_flags, hipStream_t stream) {
   const int per_block = rows <= 1024 ? 1 : 4;
-  const dim3 grid((unsigned)((n_waves + rows + 1 + SWEEP_PARTS + 1 + per_block - 1) / per_block)), block(64 * per_block);
+  const dim3 grid((unsigned)((n_waves + rows + 1 + 1 + SWEEP_PARTS * sweep_part_pieces(lda) + per_block - 1) / per_block)), block(64 * per_block);
   const auto kernel = d <= 64 * 8 * 4    ? ll_sweep_panel_kernel<4>
                       : d <= 64 * 8 * 8  ? ll_sweep_panel_kernel<8>
                       : d <= 64 * 8 * 16 ? ll_sweep_panel_kernel<16>
@@ -1287,6 +1287,9 @@ int sweep_impl(const ll_shape* shape, void* workspace, size_t workspace_bytes, c
   // 602 | 614, 8000 x 2560 x 151936 (75) 5370 | 5440; lists of three: 500 x 2560 x 151936 (5) 549 | 439, 4000 x 512 x 128256 (34) 1267 | 1306; three strengths:
   // 1500 x 512 x 50257 (5) 169 | 160, 500 x 2560 x 151936 (5) 503 | 391.  A W_U of up to 64 MiB is read from the Infinity Cache
   // in some 10 us; the factored form then gains little (300 x 512 x 50257 (2) 121 | 115, 1500 x 512 x 50257 (5) 229 | 230) and keeps the kernels before it.
+  // Beside a long direction, whose W_U the direction kernel reads all the same, u before | within (alpha v a quarter of the rows' length or more): nine strengths 1500 x 4096 x
+  // 128256 1499 | 1466, 500 x 2560 x 151936, lists, 604 | 605, 250 x 2048 x 50257, lists, 164 | 164, 700 x 1024 x 50257 196 | 198; three 1200 x 4096 x 100000 997 | 958; seven 137 x 1792 x
+  // 27710 101.8 | 103.0, 667 x 1792 x 9538 98.2 | 100.8 (short: 101.2 | 86.1 and 98.0 | 91.2); four 30 x 640 x 60000 66.2 | 67.6 (66.1 | 52.9).
   bool whole = !as_projection && N <= CHUNK_ROWS && (only_general || ((n_alpha <= SWEEP_SPLIT_ROWS || zero_alpha >= 0) && (int64_t)V * d * 2 > (64 << 20)));
   int left_slots = 0;
   if (whole) {

@@ -97,8 +97,9 @@ def lib() -> ctypes.CDLL:
 
 # A call of a decoding step (steer one row, append one token's slices) is two short kernels, and this module's own Python was what
 # bounded it: 17.5 us for the pair with a c_void_p made for every pointer, a torch.cuda.Stream object for every call and reshapes
-# that change nothing; 11.3 us without them (and 21.9 | 16.6 us for a steering direction and its injection); 9.0 us (10.9 before, timed in turn) with the
-# argument structures of the last shapes kept, a tensor's shape asked for once and no calls for what an expression does.
+# that change nothing; 11.3 us without them (and 21.9 | 16.6 us for a steering direction and its injection).  With the argument structures of the last shapes
+# kept, a tensor's shape asked for once and no calls for what an expression does, 10.4 | 9.4 us (host time, in turn; runs of one side differ by 0.1 to 1 us), and
+# 10.3 | 9.5 where 200 row counts come in turn, more than are kept.
 _Tensor, _BF16, _F32 = torch.Tensor, torch.bfloat16, torch.float32
 _shape = functools.lru_cache(maxsize=64)(ll_shape)                     # (the library only reads them)
 _capture_shape = functools.lru_cache(maxsize=64)(ll_capture_shape)

@@ -112,8 +112,9 @@ constexpr float LOG2E = 1.4426950408889634f;
 typedef const float __attribute__((address_space(4)))* const_f32_ptr;   // read through scalar loads when the address is wave-uniform
 typedef const int __attribute__((address_space(4)))* const_i32_ptr;
 
-// Workgroup ids are dealt round-robin over the 8 XCDs; remap so that one XCD (one L2) gets a
-// compact rectangle of (row blocks) x (all splits) and its CUs share A panels and W tiles.
+// Workgroup ids are dealt round-robin over the 8 XCDs; remap so that one XCD (one L2) gets an
+// eighth of the numbers in a row.  Which row blocks and splits these are is place_of's matter (few
+// rows: which parts), so that its CUs share A panels and W tiles.
 __device__ __forceinline__ int xcd_logical_block() {
   const int per_xcd = gridDim.x / NUM_XCD;
   return (blockIdx.x % NUM_XCD) * per_xcd + blockIdx.x / NUM_XCD;
@@ -123,8 +124,9 @@ __device__ __forceinline__ int xcd_logical_block() {
 // blocks by 32 / R splits: per K stage R tiles of A and 32 / R of W come into its L2 from the fabric, 33 of 32 KB where they are of
 // one row block (6.9 TB/s at 957 rows, d = 4096) and 12 at 4 by 8.  So the row blocks go in groups of four (up to seven: one group), of a
 // group split after split, of a split block after block.  With at most eight splits an XCD has its four row blocks anyway.
-// Whole calls, one row block after the other | so: 957 rows, d = 4096, V = 128256 785 | 738 us; 777 rows, d = 1608, V = 50257 181 | 175; sweeps
-// of nine strengths, 1500 rows, d = 4096 1463 | 1418, lists, 500 rows, d = 2560 556 | 546; 4160 rows, d = 5120 4436 | 4415.
+// Whole calls, one row block after the other | so, in turn on one card: 957 rows, d = 4096, V = 128256 786 | 746 us; 777 rows, d = 1608, V = 50257 172 | 161;
+// 4160 rows, d = 5120 4494 | 4471; sweeps of nine strengths whose u came from a pass of its own, 1500 rows, d = 4096 1454 | 1402, lists, 500 rows, d = 2560
+// 555 | 547.
 struct Place {
   int row_block, split;
 };

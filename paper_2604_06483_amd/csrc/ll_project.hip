@@ -647,8 +647,8 @@ __global__ __launch_bounds__(256) void ll_sweep_merge_kernel(const float4* __res
 // ---------------------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------------------
-// The few-rows kernel: how the vocabulary is dealt.  One part, of one workgroup, per compute unit, or fewer when there
-// are not eight groups of 16 vocabulary rows (one per wavefront) for each.  A wavefront holds the accumulators of MU
+// The few-rows kernel: how the vocabulary is dealt.  One part per compute unit, or fewer when there are not eight groups of
+// 16 vocabulary rows (one per wavefront) for each; a part has one workgroup, or several that share its rows (row_groups).  A wavefront holds the accumulators of MU
 // groups against all the rows, so the register file bounds MU by the number of 16-row blocks; a larger share of the
 // vocabulary goes in two or more rounds of workgroups.
 struct FewPlan {
@@ -686,7 +686,9 @@ FewPlan make_few_plan(const ll_shape* s, int k) {
   // What that shortens is a part's epilogue, and the A tiles; W's lines come from memory once all the same (xcd_logical_block).  Whole
   // calls, one workgroup a part | several, us (rows, d, V, k): 64, 256, 4096, 5: 17.4 | 13.3; 128, 64, 4000, 5: 22.5 | 12.3; 81, 512, 8000, 10: 26.5 | 17.8;
   // 81, 1608, 6000, 5: 37.4 | 23.0; 100, 1024, 12000, 20: 31.7 | 25.8; 64, 2048, 16000, 10: 34.3 | 31.1; 128, 8192, 10000, 10: 114.6 | 91.7;
-  // 20, 8192, 16000, 10: 94.9 | 89.1.
+  // 20, 8192, 16000, 10: 94.9 | 89.1.  With W_U out of the caches: 64, 256, 4096, 5: 24.1 | 18.9; 81, 1608, 6000, 5: 48.7 | 36.2; 33, 5120, 8192, 10: 79.2 | 71.2;
+  // 64, 2048, 16000, 10: 51.4 | 48.1; 128, 2560, 16000, 10: 75.1 | 59.9; 20, 8192, 16000, 10: 96.4 | 91.1.  The 256-row tiles take 0.98 to 1.4 times as long there (65, 96 and
+  // 128 rows, d = 256 to 8192, lists of five); from V = 16385 to 20000, with one workgroup a part, 0.79 to 1.0 times.
   f.row_groups = 1;
   for (int nj = 1; nj < f.nj; ++nj) {
     const int groups = (blocks + nj - 1) / nj;

@@ -84,20 +84,20 @@ def test_few_rows_in_two_rounds(N, d, V, k, with_bias, expected):
 
 
 @pytest.mark.parametrize("N,d,V,A,k,expected", [
-    (300, 128, 20000, 1, 2, ["projection"]), (300, 72, 20000, 1, 4, ["projection"]), (300, 128, 20000, 1, None, ["general"]),
+    (300, 128, 20000, 1, 2, ["projection"]), (300, 72, 20000, 1, 4, ["projection"]), (300, 128, 20000, 1, None, ["own general"]),
     (1500, 64, 50257, 1, None, ["projection"]),
-    (300, 128, 50257, 6, None, ["general"]), (300, 128, 50257, 7, None, ["table", "general", "factored"]),     # two tiles a split
-    (300, 512, 50257, 5, None, ["general"]), (300, 512, 50257, 6, None, ["table", "general", "factored"]),
-    (70, 128, 5000, 8, None, ["general"]), (70, 128, 5000, 9, None, ["table", "general", "factored"]),         # one
-    (2100, 64, 60000, 4, None, ["general"]), (2100, 320, 60000, 4, None, ["table", "general", "factored"]),    # nine
-    (70, 64, 5000, 4, 4, ["general"]), (70, 64, 5000, 5, 4, ["table", "general", "factored"]),                 # lists
-    (10, 128, 70000, 3, 3, ["general"]), (10, 128, 70000, 4, 3, ["table", "general", "factored"]),
+    (300, 128, 50257, 6, None, ["own general"]), (300, 128, 50257, 7, None, ["table", "general", "factored"]),     # two tiles a split
+    (300, 512, 50257, 5, None, ["own general"]), (300, 512, 50257, 6, None, ["table", "general", "factored"]),
+    (70, 128, 5000, 8, None, ["own general"]), (70, 128, 5000, 9, None, ["table", "general", "factored"]),         # one
+    (2100, 64, 60000, 4, None, ["own general"]), (2100, 320, 60000, 4, None, ["table", "general", "factored"]),    # nine
+    (70, 64, 5000, 4, 4, ["own general"]), (70, 64, 5000, 5, 4, ["table", "general", "factored"]),                 # lists
+    (10, 128, 70000, 3, 3, ["own general"]), (10, 128, 70000, 4, 3, ["table", "general", "factored"]),
 ])
 def test_sweeps(N, d, V, A, k, expected):
     say(f"route sweep N={N} d={d} V={V} A={A} k={k}")
     w = WL.make_workload(WL.LensConfig("route", L=1, T=N, d=d, V=V, k=1), DEV, seed=41)
     names = main_kernels(lambda: LL.ll_steer_sweep(w.hidden.reshape(N, d), w.gamma, w.W_U, w.cfg.eps, direction(d), ALPHAS9[:A], w.target_ids, k=k))
     kinds = ["table" if n.startswith("ll_sweep_table") else "projection" if "TopKEpilogue" in n else
-             "general" if "true> >" in n or "true>>" in n else "factored" for n in names]
+             ("own " if "WholeSweep" in n else "") + ("general" if "true> >" in n or "true>>" in n else "factored") for n in names]
     assert kinds == expected, names
     check(N, d, V, ALPHAS9[:A], k, 1.0, "route", rows=np.unique(np.r_[0:40, N // 2:N // 2 + 40, N - 40:N]) if N > 100 else None)
